@@ -67,6 +67,91 @@ constexpr bool gd_ok(uint32_t m, uint32_t g) {
     return (ipow(m, g) >> tw) < (1ull << 24);
 }
 constexpr uint32_t gd_of(uint32_t m) { uint32_t g = 1; while (gd_ok(m, g + 1)) g++; return g; }
+// label length of modulus m under the ceil rule: smallest lam with m^lam >= 2^128
+constexpr uint32_t lam_ceil(uint32_t m) { uint32_t l = 0; for (unsigned __int128 v = ~(unsigned __int128)0; v; v /= m) l++; return l; }
+
+// ---- constants of the base conversion (decompress), see there
+struct Big { uint32_t w[10]; };      // 320-bit number
+constexpr void big_mul(Big& b, uint32_t m) { uint64_t c = 0; for (int i = 0; i < 10; i++) { c += (uint64_t)b.w[i] * m; b.w[i] = (uint32_t)c; c >>= 32; } }
+constexpr bool big_ge(const Big& a, const Big& b) { for (int i = 9; i >= 0; i--) if (a.w[i] != b.w[i]) return a.w[i] > b.w[i]; return true; }
+constexpr void big_sub(Big& a, const Big& b) { uint64_t br = 0; for (int i = 0; i < 10; i++) { uint64_t t = (uint64_t)a.w[i] - b.w[i] - br; a.w[i] = (uint32_t)t; br = (t >> 32) & 1; } }
+constexpr void big_dbl(Big& a, uint32_t in) { for (int i = 9; i > 0; i--) a.w[i] = (a.w[i] << 1) | (a.w[i - 1] >> 31); a.w[0] = (a.w[0] << 1) | in; }
+constexpr Big big_recip(uint32_t s, const Big& D) {      // 2^s / D to the nearest integer
+    Big q{}, r{};
+    for (uint32_t i = 0; i <= s; i++) {
+        big_dbl(r, i == 0 ? 1u : 0u);
+        big_dbl(q, 0);
+        if (big_ge(r, D)) { big_sub(r, D); q.w[0] |= 1; }
+    }
+    big_dbl(r, 0);
+    if (big_ge(r, D)) for (int i = 0; i < 10; i++) if (++q.w[i]) break;
+    return q;
+}
+constexpr double big_double(const Big& b) { double d = 0; for (int i = 9; i >= 0; i--) d = d * 4294967296.0 + b.w[i]; return d; }
+constexpr double pow2(int e) { double d = 1; for (int i = 0; i < e; i++) d *= 2; for (int i = 0; i > e; i--) d *= 0.5; return d; }
+
+struct FracPlan {
+    uint32_t ns, top;        // super-digits of gc dwords, dwords of the (shorter) top one
+    Big R;                   // 2^256 / D, D = m^(digits below the top super-digit)
+    uint32_t c0;             // lowest 32-bit column of h R that is formed
+    uint32_t bcol, bword;    // start value: bword in column bcol, about R / 2
+    uint32_t w[16];          // words of the fraction before extraction k
+    double low, high;        // distance of the worst errors from the ends of the window that gives exact digits
+};
+constexpr FracPlan frac_plan(uint32_t m) {
+    FracPlan P{};
+    const uint32_t ndw = (lam_ceil(m) + 3) / 4, gc = gc_of(m);
+    P.ns = (ndw + gc - 1) / gc;
+    P.top = ndw - (P.ns - 1) * gc;
+    Big D{};
+    D.w[0] = 1;
+    for (uint32_t i = 0; i < (P.ns - 1) * gc * 4; i++) big_mul(D, m);
+    P.R = big_recip(256, D);
+    const double R = big_double(P.R), Q = (double)ipow(m, 4 * gc);
+    Big half = P.R;
+    for (int i = 0; i < 9; i++) half.w[i] = (half.w[i] >> 1) | (half.w[i + 1] << 31);
+    P.bcol = half.w[4] ? 4 : 3;
+    P.bword = half.w[P.bcol];
+    const double pos = P.bword * pow2(32 * (int)P.bcol) / R, rounding = 0.5 * pow2(128) / R;      // h times the rounding of R
+    double loss = rounding, drop = 0;
+    int rw = 0;
+    for (int i = 0; i < 10; i++) if (P.R.w[i]) rw = i + 1;
+    for (int c = 0; c < 4; c++) {
+        double n = 0;
+        for (int i = 0; i < 4; i++) if (c - i >= 0 && c - i < rw) n += 1;
+        const double d = n * pow2(64 + 32 * c) / R;
+        if (drop + d > 0.03) break;
+        drop += d;
+        P.c0 = (uint32_t)c + 1;
+    }
+    loss += drop;
+    double Dk = big_double(D);
+    for (uint32_t k = 0; k + 1 < P.ns; k++) {
+        uint32_t w = 1;
+        while (Dk * pow2(-32 * (int)w) > 0.05) w++;
+        const uint32_t have = k == 0 ? 8 - P.c0 : P.w[k - 1];
+        P.w[k] = w < have ? w : have;
+        if (w < have) loss += Dk * pow2(-32 * (int)w);
+        Dk /= Q;
+    }
+    P.low = pos - loss;
+    P.high = 1.0 - pos - rounding;
+    return P;
+}
+// smallest shift s for which floor(n / D) = mulhi(n, ceil(2^(32 + s) / D)) >> s for all n <= nmax; 32 if there is none
+constexpr uint32_t magic_shift(uint64_t nmax, uint64_t D) {
+    for (uint32_t s = 0; s < 32; s++) {
+        const unsigned __int128 t = (unsigned __int128)1 << (32 + s), M = (t + D - 1) / D;
+        if (M >> 32 == 0 && nmax * (M * D - t) < t) return s;
+    }
+    return 32;
+}
+constexpr uint32_t magic_mul(uint32_t s, uint64_t D) { return (uint32_t)((((unsigned __int128)1 << (32 + s)) + D - 1) / D); }
+// smallest shift s for which floor(x / m) = (x * ceil(2^s / m)) >> s for all x < m^2
+constexpr uint32_t small_shift(uint32_t m) {
+    for (uint32_t s = 1; s < 24; s++) if ((uint64_t)(m * m - 1) * ((((1ull << s) + m - 1) / m) * m - (1ull << s)) < (1ull << s)) return s;
+    return 24;
+}
 }  // namespace cm
 
 template <uint32_t MOD, uint32_t LAM>
@@ -75,12 +160,6 @@ struct CMod {
     static constexpr uint32_t mmagic = (uint32_t)(((1ull << 32) + MOD - 1) / MOD);
     static constexpr uint32_t m4 = MOD * 0x01010101u, c4 = MOD <= 128 ? (128 - MOD) * 0x01010101u : 0;
     static constexpr uint32_t gc = cm::gc_of(MOD), Qc = (uint32_t)cm::ipow(MOD, 4 * gc);
-    static constexpr uint32_t tw = cm::twos_of(MOD), mo = MOD >> tw;
-    static constexpr uint32_t omagic = (uint32_t)(((1ull << 32) + mo - 1) / mo);
-    static constexpr uint32_t gd = cm::gd_of(MOD), dsh = tw * gd, Qd = (uint32_t)cm::ipow(mo, gd);
-    static constexpr uint32_t Qdshift = Qd > 1 ? cm::ceil_log2(Qd) - 1 : 0;
-    static constexpr uint32_t Qdmagic = Qd > 1 ? (uint32_t)(((1ull << (32 + Qdshift)) + Qd - 1) / Qd) : 0;
-    static constexpr uint32_t Qdbits = dsh + cm::floor_log2(Qd);
     const uint32_t* dtab;
 };
 
@@ -128,51 +207,38 @@ template <class MI> DASH_HD uint32_t div_m(uint32_t n, const MI& M) { return mul
 template <class MI> DASH_HD uint32_t mod_m(uint32_t n, const MI& M) { return n - mul24(div_m(n, M), M.m); }  // n < 2^24
 DASH_HD uint32_t byte_of(uint32_t w, int b) { return (w >> (8 * b)) & 0xffu; }
 
-// 0xff in every byte of x whose top bit is set, 0x00 elsewhere (shifts and subtractions only: a
-// multiplication by 255 costs twice an addition)
-DASH_HD uint32_t ge_mask(uint32_t x) {
-    uint32_t hi = x & 0x80808080u;
-    return (hi - (hi >> 7)) | hi;
-}
-// Moduli above 128 (the accumulation moduli k d_j of the 12-prime digit set): a sum of two digits does not fit a
-// byte, so the digits go through 16-bit fields, two per word; "x >= m ? x - m : x" is min(x, x - m) on unsigned
-// 16-bit fields (the difference wraps to a large number when x < m): packed 16-bit subtract and minimum.
-DASH_HD uint32_t redmod2x16(uint32_t x, uint32_t m) {      // both fields below 2 m
+// Packed modular addition and subtraction on 4 digits.  The bytes that have to be corrected by m are found as a 0/1 flag per
+// byte, and flag * m is taken off (put on) the whole dword with ONE 32-bit multiplication: each byte of the result lies in
+// [0, m), so the carries and borrows between the bytes of the intermediate dwords cancel.  Six instructions; the byte mask that
+// served before (and, shift, subtract, or, and) took eight, on kernels that are bound by the number of vector instructions.
+constexpr uint32_t kOnes = 0x01010101u;
+// per byte (a + b + (r & 1)) >> 1, without carries between bytes
+DASH_HD uint32_t lerp4(uint32_t a, uint32_t b, uint32_t r) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-    const u16x2 v = __builtin_bit_cast(u16x2, x), mm = __builtin_bit_cast(u16x2, m * 0x00010001u);
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(v, (u16x2)(v - mm)));
+    return __builtin_amdgcn_lerp(a, b, r);
 #else
-    uint32_t lo = x & 0xffffu, hi = x >> 16;
-    lo = lo >= m ? lo - m : lo;
-    hi = hi >= m ? hi - m : hi;
-    return lo | (hi << 16);
+    uint32_t w = 0;
+    for (int i = 0; i < 32; i += 8) w |= ((((a >> i) & 0xffu) + ((b >> i) & 0xffu) + ((r >> i) & 1u)) >> 1) << i;
+    return w;
 #endif
 }
 // (a + b) mod m on 4 packed digits, a, b < m per byte.
 template <class MI>
 DASH_HD uint32_t addmod4(uint32_t a, uint32_t b, const MI& M) {
     if constexpr (cmod_m<MI>::value == 2) return a ^ b;          // digits are bits (one per byte)
-    if (M.m <= 128) {
-        uint32_t t = a + b;                                       // bytes <= 2m-2 <= 254
-        return t - (ge_mask(t + M.c4) & M.m4);
-    }
-    const uint32_t ev = redmod2x16((a & 0x00ff00ffu) + (b & 0x00ff00ffu), M.m);
-    const uint32_t od = redmod2x16(((a >> 8) & 0x00ff00ffu) + ((b >> 8) & 0x00ff00ffu), M.m);
-    return ev | (od << 8);
+    const uint32_t t = a + b;
+    if (M.m <= 128) return t - (((t + M.c4) >> 7) & kOnes) * M.m;                  // bytes of t + c4 reach 128 where t >= m
+    // moduli above 128: the sum does not fit a byte, its half does.  a + b >= m iff (a + b + (m odd)) / 2 >= ceil(m / 2).
+    const uint32_t h = lerp4(a, b, (M.m & 1u) * kOnes) + (128u - (M.m + 1u) / 2u) * kOnes;
+    return t - ((h >> 7) & kOnes) * M.m;
 }
 // (a - b) mod m on 4 packed digits.
 template <class MI>
 DASH_HD uint32_t submod4(uint32_t a, uint32_t b, const MI& M) {
     if constexpr (cmod_m<MI>::value == 2) return a ^ b;
-    if (M.m <= 128) {
-        uint32_t t = a + (M.m4 - b);                              // bytes in [1, 2m-1] <= 255
-        return t - (ge_mask(t + M.c4) & M.m4);
-    }
-    const uint32_t m2 = M.m * 0x00010001u;                        // fields a + m - b in [1, 2m-1]
-    const uint32_t ev = redmod2x16((a & 0x00ff00ffu) + (m2 - (b & 0x00ff00ffu)), M.m);
-    const uint32_t od = redmod2x16(((a >> 8) & 0x00ff00ffu) + (m2 - ((b >> 8) & 0x00ff00ffu)), M.m);
-    return ev | (od << 8);
+    const uint32_t t = a - b;
+    const uint32_t ge = M.m <= 128 ? t + 0x80808080u : lerp4(a, ~b, kOnes);        // top bit of a byte: a >= b
+    return t + (~(ge >> 7) & kOnes) * M.m;
 }
 // (a + c * b) mod m on 4 packed digits, c < m.
 template <class MI>
@@ -398,7 +464,7 @@ DASH_HD U128 prg_block(uint64_t elem, uint32_t slot, uint32_t layer, uint32_t do
 
 // ---------------------------------------------------------------------------------------------
 // decompress: digits floor(h / m^j) mod m, j = 0..lam-1, delivered as packed dwords emit(i, w)
-// for i = 0..ndw-1.  With m = 2^tw * mo, a super-digit of gd digits is taken off the 128-bit number by
+// for i = 0..ndw-1 (in any order).  Run-time description: with m = 2^tw * mo, a super-digit of gd digits is taken off the 128-bit number by
 // a shift (its low dsh bits) and a long division by Qd = mo^gd <= 2^15 over 16-bit half-words (every
 // partial dividend r * 2^16 + half is below 2^31, where the magic division is exact):
 //     h mod m^gd = ((h >> dsh) mod Qd) << dsh | (h & (2^dsh - 1)),   h div m^gd = (h >> dsh) div Qd.
@@ -434,95 +500,153 @@ DASH_HD uint32_t take_superdigit(U128& x, const MI& M, uint32_t bits) {
     return (r << M.dsh) | low;
 }
 
-// Compile-time descriptions: the gd digits of a super-digit S < m^G are split by halving, S = hi * m^G1 + lo,
-// so that all but the first division work on numbers below 2^15, where floor(n / D) = (n * M) >> s with a
-// 24-bit multiplication (M = ceil(2^s / D), s = bits(n) + ceil(log2 D): n * (M D - 2^s) < 2^s, so the result is
-// exact, and n * M < 2^32).  The halving also shortens the chain of dependent divisions from G to log2 G.
-template <class MI, int G>
-DASH_HD void split_digits(uint32_t S, uint32_t* d) {
-    if constexpr (G == 1) {
-        d[0] = S;
-    } else {
-        constexpr int G1 = G / 2, G2 = G - G1;
-        constexpr uint64_t mG = cm::ipow(MI::m, G), mG1 = cm::ipow(MI::m, G1), D = cm::ipow(MI::mo, G1);
-        constexpr uint32_t sh = MI::tw * G1;
-        constexpr uint64_t nmax = (mG - 1) >> sh;                 // S >> sh <= nmax
-        constexpr uint32_t a = cm::bits_of(nmax);
-        const uint32_t n = S >> sh;                               // floor(S / m^G1) = floor(n / D)
-        uint32_t hi;
-        if constexpr (D == 1) {
-            hi = n;
-        } else if constexpr (a <= 15) {
-            constexpr uint32_t sft = a + cm::ceil_log2(D);
-            constexpr uint32_t Mg = (uint32_t)(((1ull << sft) + D - 1) / D);
-            static_assert(nmax * Mg < (1ull << 32) && Mg < (1u << 24), "24-bit magic division out of range");
-            hi = mul24(n, Mg) >> sft;
-        } else {
-            static_assert(a + cm::ceil_log2(D) <= 32 && D < (1ull << 32), "multiply-high division out of range");
-            hi = mulhi(n, (uint32_t)(((1ull << 32) + D - 1) / D));
+// Compile-time descriptions.  The number is turned into a fraction once and the super-digits (gc dwords of 4 digits each, below
+// 2^32) come off its TOP end:  with D = m^(digits below the top super-digit) and R = 2^256 / D,  h R / 2^256 = h / D  has the top
+// super-digit as its integer part; multiplying the fraction by Q = m^(4 gc) gives the next one, and so on, on ever fewer words.
+// Exactness: any fraction in [x / D, (x + 1) / D) gives the digits of x.  The product starts at about R / 2, the middle of that
+// window, and what the rounding of R, the columns that are never formed and the words that are dropped can move it by is added
+// up at compile time (FracPlan) and must stay below half the window.
+// Against the long division over 16-bit half-words that the run-time description below uses, this is a 32 x 32 -> 64-bit
+// multiply-add per word instead of two steps of five instructions, with super-digits up to 2^32 instead of 2^15 times a power of
+// two: 89 vector instructions instead of 197 for m = 96 (20 digits), 110 instead of 283 for m = 204, 136 instead of 333 for m = 37.
+template <uint32_t MOD> struct Frac { static constexpr cm::FracPlan P = cm::frac_plan(MOD); };
+
+// products h.w[I..3] * R.w[C - I] of column C; an overflow of the 64-bit sum is watched for only where the constants allow one
+template <uint32_t MOD, int C, int I>
+DASH_HD void frac_column(const U128& h, uint64_t& acc, uint32_t& over) {
+    if constexpr (I < 4) {
+        constexpr int J = C - I;
+        if constexpr (J >= 0 && J < 10) {
+            constexpr uint32_t r = Frac<MOD>::P.R.w[J];
+            if constexpr (r != 0) {
+                constexpr auto bound = [] {
+                    unsigned __int128 b = (unsigned __int128)1 << 35;        // carry from the column before and the start value
+                    for (int i = 0; i <= I; i++) if (C - i >= 0 && C - i < 10) b += (unsigned __int128)0xffffffffu * Frac<MOD>::P.R.w[C - i];
+                    return b;
+                };
+                const uint64_t p = (uint64_t)h.w[I] * r;
+                acc += p;
+                if constexpr ((bound() >> 64) != 0) over += acc < p;
+            }
         }
-        static_assert(mG1 < (1ull << 24) && (mG - 1) / mG1 < (1ull << 24), "24-bit multiply out of range");
-        const uint32_t lo = S - mul24(hi, (uint32_t)mG1);
-        split_digits<MI, G1>(lo, d);
-        split_digits<MI, G2>(hi, d + G1);
+        frac_column<MOD, C, I + 1>(h, acc, over);
     }
 }
-// super-digit SD and all after it (compile-time descriptions under the ceil rule: m^lam >= 2^128, so the last
-// super-digit holds exactly the digits that are left)
-template <class MI, int SD, class Emit>
-DASH_HD void decompress_from(const MI& M, U128& x, uint32_t& w, Emit& emit) {
-    constexpr int first = SD * (int)MI::gd;
-    if constexpr (first < (int)MI::lam) {
-        constexpr int G = (int)MI::lam - first < (int)MI::gd ? (int)MI::lam - first : (int)MI::gd;
-        constexpr uint32_t bits = 128u > SD * MI::Qdbits ? 128u - SD * MI::Qdbits : 0u;
-        const uint32_t S = take_superdigit(x, M, bits);
-        uint32_t d[G];
-        split_digits<MI, G>(S, d);
+// columns C..8 of h R: columns 8 - w[0] .. 7 are the fraction, column 8 the top super-digit
+template <uint32_t MOD, int C>
+DASH_HD void frac_product(const U128& h, uint64_t acc, uint32_t* f, uint32_t& top) {
+    constexpr cm::FracPlan P = Frac<MOD>::P;
+    if constexpr (C == 8) {
+        top = (uint32_t)acc;
+    } else {
+        uint32_t over = 0;
+        if constexpr (C == (int)P.bcol) acc += P.bword;
+        frac_column<MOD, C, 0>(h, acc, over);
+        if constexpr (C >= 8 - (int)P.w[0]) f[C - (8 - (int)P.w[0])] = (uint32_t)acc;
+        frac_product<MOD, C + 1>(h, (acc >> 32) | ((uint64_t)over << 32), f, top);
+    }
+}
+// floor(v / m^E) for v <= VMAX
+template <uint32_t MOD, uint32_t E, uint64_t VMAX>
+DASH_HD uint32_t div_pow(uint32_t v) {
+    constexpr uint32_t tw = E * cm::twos_of(MOD);
+    constexpr uint64_t D = cm::ipow(MOD, E) >> tw;
+    if constexpr (D == 1) return v >> tw;
+    else {
+        constexpr uint32_t sh = cm::magic_shift(VMAX >> tw, D);
+        static_assert(sh < 32, "multiply-high division out of range");
+        return mulhi(v >> tw, cm::magic_mul(sh, D)) >> sh;
+    }
+}
+// the four digits of v < m^4, packed: v = lo + m^2 hi, then each half into its two digits.  The digits are put in place by adding
+// multiples of (256 - m) and (2^16 - m^2) to v: one multiply-add each, no shifts.
+template <uint32_t MOD>
+DASH_HD uint32_t split_dword(uint32_t v) {
+    constexpr uint32_t m2 = MOD * MOD;
+    const uint32_t hi = div_pow<MOD, 2, (uint64_t)m2 * m2 - 1>(v);
+    if constexpr (MOD <= 13) {       // both halves in 16-bit fields of one word: m^2 times the reciprocal fits a field
+        constexpr uint32_t s = cm::small_shift(MOD), M = ((1u << s) + MOD - 1) / MOD;
+        static_assert(s < 16 && (m2 - 1) * M < 65536u && ((m2 - 1) << 16) < (1u << 24), "16-bit fields out of range");
+        const uint32_t x = v + mul24(hi, 65536u - m2);
+        return x + mul24((mul24(x, M) >> s) & ((0xffffu >> s) * 0x00010001u), 256u - MOD);
+    } else {
+        const uint32_t lo = v - mul24(hi, m2);
+        const uint32_t t1 = div_pow<MOD, 1, m2 - 1>(hi), t0 = div_pow<MOD, 1, m2 - 1>(lo);
+        return v + mul24(hi, 65536u - m2) + mul24(t0, 256u - MOD) + mul24(t1, (256u - MOD) << 16);
+    }
+}
+// super-digit S < m^(4 N) into N dwords, the first at index i
+template <uint32_t MOD, int N, class Emit>
+DASH_HD void split_super(uint32_t S, int i, Emit& emit) {
+    if constexpr (N == 1) {
+        emit(i, split_dword<MOD>(S));
+    } else {
+        constexpr int N1 = N / 2;
+        const uint32_t hi = div_pow<MOD, 4 * N1, cm::ipow(MOD, 4 * N) - 1>(S);
+        split_super<MOD, N1>(S - hi * (uint32_t)cm::ipow(MOD, 4 * N1), i, emit);
+        split_super<MOD, N - N1>(hi, i + N1, emit);
+    }
+}
+// extraction K: super-digit ns - 2 - K off the top of the fraction f (w[K] words, least significant first)
+template <uint32_t MOD, int K, class Emit>
+DASH_HD void frac_extract(const uint32_t* f, Emit& emit) {
+    constexpr cm::FracPlan P = Frac<MOD>::P;
+    if constexpr (K + 1 < (int)P.ns) {
+        constexpr int w = (int)P.w[K], wn = K + 2 < (int)P.ns ? (int)P.w[K + 1] : 0, gc = (int)cm::gc_of(MOD);
+        constexpr uint32_t Q = (uint32_t)cm::ipow(MOD, 4 * gc);
+        uint32_t g[w], c = 0;
 #pragma unroll
-        for (int t = 0; t < G; t++) {
-            const int j = first + t;
-            w |= d[t] << (8 * (j & 3));
-            if ((j & 3) == 3) { emit(j >> 2, w); w = 0; }
+        for (int i = 0; i < w; i++) {
+            const uint64_t t = (uint64_t)f[i] * Q + c;
+            g[i] = (uint32_t)t; c = (uint32_t)(t >> 32);
         }
-        decompress_from<MI, SD + 1>(M, x, w, emit);
+        split_super<MOD, gc>(c, ((int)P.ns - 2 - K) * gc, emit);
+        frac_extract<MOD, K + 1>(g + (w - wn), emit);
     }
 }
 
 template <class MI, class Emit>
 DASH_HD void decompress(const MI& M, const U128& h, Emit emit) {
     if constexpr (cmod_m<MI>::value > 2) {
-        U128 x = h;
-        uint32_t w = 0;
-        decompress_from<MI, 0>(M, x, w, emit);
-        if (MI::lam & 3) emit((int)(MI::lam >> 2), w);
-        return;
-    }
-    if constexpr (cmod_m<MI>::value == 2) {   // digits are bits: spread 4 bits into 4 bytes
+        constexpr uint32_t m = cmod_m<MI>::value;
+        constexpr cm::FracPlan P = Frac<m>::P;
+        static_assert(P.low > 0 && P.high > 0, "errors leave the window of exact digits");
+        static_assert(MI::lam <= cm::lam_ceil(m), "digits past 2^128");
+        // shorter labels (the floor rule) are the same digits without the last ones
+        auto put = [&](int i, uint32_t w) {
+            if (MI::lam < cm::lam_ceil(m) && (MI::lam & 3) && i == (int)(MI::lam >> 2)) w &= (1u << (8 * (MI::lam & 3))) - 1u;
+            if (i < (int)MI::ndw) emit(i, w);
+        };
+        uint32_t f[8], top;
+        frac_product<m, (int)P.c0>(h, 0, f, top);
+        split_super<m, (int)P.top>(top, (int)((P.ns - 1) * cm::gc_of(m)), put);
+        frac_extract<m, 0>(f, put);
+    } else if constexpr (cmod_m<MI>::value == 2) {   // digits are bits: spread 4 bits into 4 bytes
 #pragma unroll
         for (int i = 0; i < (int)M.ndw; i++) {
             uint32_t nib = (h.w[i >> 3] >> (4 * (i & 7))) & 0xfu;
             emit(i, mul24(nib, 0x00204081u) & 0x01010101u);
         }
-        return;
-    }
-    U128 x = h;
-    uint32_t S = 0, have = 0;     // digits left in the current super-digit
-    uint32_t bits = 128;          // the number is below 2^bits
-    uint32_t w = 0;
+    } else {
+        U128 x = h;
+        uint32_t S = 0, have = 0;     // digits left in the current super-digit
+        uint32_t bits = 128;          // the number is below 2^bits
+        uint32_t w = 0;
 #pragma unroll
-    for (uint32_t j = 0; j < M.lam; j++) {
-        if (have == 0) {
-            S = take_superdigit(x, M, bits);
-            bits = bits > M.Qdbits ? bits - M.Qdbits : 0;
-            have = M.gd;
+        for (uint32_t j = 0; j < M.lam; j++) {
+            if (have == 0) {
+                S = take_superdigit(x, M, bits);
+                bits = bits > M.Qdbits ? bits - M.Qdbits : 0;
+                have = M.gd;
+            }
+            uint32_t q = M.omagic ? mulhi(S >> M.tw, M.omagic) : (S >> M.tw);   // S div m = (S >> tw) div mo; omagic = 0: mo = 1
+            uint32_t d = S - mul24(q, M.m);
+            S = q; have--;
+            w |= d << (8 * (j & 3));
+            if ((j & 3) == 3) { emit((int)(j >> 2), w); w = 0; }
         }
-        uint32_t q = M.omagic ? mulhi(S >> M.tw, M.omagic) : (S >> M.tw);   // S div m = (S >> tw) div mo; omagic = 0: mo = 1
-        uint32_t d = S - mul24(q, M.m);
-        S = q; have--;
-        w |= d << (8 * (j & 3));
-        if ((j & 3) == 3) { emit((int)(j >> 2), w); w = 0; }
+        if (M.lam & 3) emit((int)(M.lam >> 2), w);
     }
-    if (M.lam & 3) emit((int)(M.lam >> 2), w);
 }
 
 struct Limbs { uint32_t l[8]; };
