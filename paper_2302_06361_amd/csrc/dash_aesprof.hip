@@ -121,6 +121,7 @@ extern "C" int dash_profile_aes(dash_ctx* c, int variant, const uint8_t* key, co
     } else if (variant == 1) {
         uint64_t blocks = (n_blocks + kBigThreads - 1) / kBigThreads;
         if (blocks > 1024) blocks = 1024;
+        rotate_round_keys(K.rk);
         hipLaunchKernelGGL(k_aes_tab<true>, dim3((uint32_t)blocks), dim3(kBigThreads), 0, st, K, c->d_ttab, (const uint4*)in, (uint4*)out, n_blocks, repeat);
     } else {
         uint64_t blocks = (n_blocks + kThreads - 1) / kThreads;

@@ -30,8 +30,8 @@ DASH_HD void st_chunk(const LView& v, uint32_t e, int ch, const Dw4& d) { *(Dw4*
 // when that is the context's label length of modulus 2, the run-time record otherwise
 template <class LoadDw>
 DASH_HD U128 compress_mod2(const ModInfo* mods, LoadDw dw, uint32_t* colour) {
-    if (mods[2].lam == 128) return compress(CMod<2, 128>{nullptr}, dw, colour);
-    const ModInfo M2 = mods[2];
+    if (ld_mod(mods, 2).lam == 128) return compress(CMod<2, 128>{nullptr}, dw, colour);
+    const ModInfo M2 = ld_mod(mods, 2);
     return compress(M2, dw, colour);
 }
 
@@ -41,7 +41,7 @@ DASH_HD void draw_body(const DrawLaunch& L, uint32_t bx, uint32_t by, uint32_t t
     const DrawJob& J = L.jobs[by];
     uint32_t e = bx * kThreads + tx;
     if (e >= J.n_elem) return;
-    const ModInfo M = L.mods[J.m];
+    const ModInfo M = ld_mod(L.mods, J.m);
     U128 h = prg_block(J.elem_base + e, J.slot, L.layer, J.domain, J.m, L.key.rk, T);
     if (J.digit0_only) { J.out.p[e] = (uint8_t)mod_u128(h, M); return; }
     with_mod(M, [&](auto Q) {
@@ -55,7 +55,7 @@ DASH_HD void draw_body(const DrawLaunch& L, uint32_t bx, uint32_t by, uint32_t t
 // digits per 32-bit word in 16-bit fields; general coefficients go digit by digit.
 DASH_HD void affine_body(const AffineLaunch& L, uint32_t bx, uint32_t by, uint32_t tx) {
     const AffineJob& J = L.jobs[by];
-    const ModInfo M = L.mods[J.m];
+    const ModInfo M = ld_mod(L.mods, J.m);
     const uint64_t idx = (uint64_t)bx * kThreads + tx;
     if (idx >= (uint64_t)L.n_elem * M.nchunk) return;
     const uint32_t ch = (uint32_t)(idx / L.n_elem), e = (uint32_t)(idx - (uint64_t)ch * L.n_elem);
@@ -100,13 +100,12 @@ struct PerJobMod {};
 template <class QD, class Tab, class Sink>
 DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink) {
     const GateJob& J = L.jobs[by];
-    const ModInfo Mp = L.mods[J.p], Mq = L.mods[J.q];
-    // The block's first row is divided once (scalar unit); the lane's offset from it is small enough
-    // for the 24-bit magic division.
-    const uint64_t r0 = (uint64_t)bx * kThreads;
-    if (r0 >= (uint64_t)J.n_elem * Mp.m) return;
-    const uint32_t g0 = (uint32_t)(r0 / Mp.m);
-    const uint32_t off = (uint32_t)(r0 - (uint64_t)g0 * Mp.m) + tx;
+    const ModInfo Mp = ld_mod(L.mods, J.p), Mq = ld_mod(L.mods, J.q);
+    // The block's first row is divided once (scalar unit; rows of a job are below 2^32); the lane's offset from it is small
+    // enough for the 24-bit magic division.
+    const uint32_t r0 = bx * kThreads;
+    if ((uint64_t)bx * kThreads >= (uint64_t)J.n_elem * Mp.m) return;
+    const uint32_t g0 = div_any(r0, Mp), off = r0 - g0 * Mp.m + tx;
     const uint32_t dg = div_m(off, Mp);
     const uint32_t g = g0 + dg, a = off - dg * Mp.m;
     if (g >= J.n_elem) return;
@@ -167,7 +166,7 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
 template <class QD, class Tab>
 DASH_HD void eval_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T) {
     const GateJob& J = L.jobs[by];
-    const ModInfo Mp = L.mods[J.p], Mq = L.mods[J.q];
+    const ModInfo Mp = ld_mod(L.mods, J.p), Mq = ld_mod(L.mods, J.q);
     uint32_t g = bx * kThreads + tx;
     if (g >= J.n_elem) return;
     uint32_t colour = ld_dw(J.in, g, 0) & 0xffu;
@@ -294,21 +293,21 @@ DASH_HD void chain_eval_generic_body(const ChainLaunch& L, uint32_t bx, uint32_t
     if (e >= L.n_elem) return;
     const int n = (int)L.n;
     for (int j = n; j >= 1; j--) {
-        const ModInfo Mi = L.mods[L.m[j]];
+        const ModInfo Mi = ld_mod(L.mods, L.m[j]);
         const bool has_carry = j < n;
         auto in_dw = [&](int i) {
             uint32_t w = ld_dw(L.sum[j], e, i);
             return has_carry ? addmod4(w, ld_dw(L.carry[j], e, i), Mi) : w;
         };
         if (j >= 2) {
-            const ModInfo Mo = L.mods[L.m[j - 1]];
+            const ModInfo Mo = ld_mod(L.mods, L.m[j - 1]);
             chain_gate(L, Mi, Mo, e, j, in_dw, [&](int i, uint32_t w) { st_dw(L.carry[j - 1], e, i, w); }, T);
             for (int i = (int)Mo.ndw; i < (int)Mo.nchunk * 4; i++) st_dw(L.carry[j - 1], e, i, 0);
-        } else if (L.mods[2].lam == 128) {
+        } else if (ld_mod(L.mods, 2).lam == 128) {
             const CMod<2, 128> M2{nullptr};
             chain_gate(L, Mi, M2, e, 1, in_dw, [&](int i, uint32_t w) { chain_out(L, e, i, w); }, T);
         } else {                                // another label length of modulus 2: run-time constants
-            const ModInfo M2 = L.mods[2];
+            const ModInfo M2 = ld_mod(L.mods, 2);
             chain_gate(L, Mi, M2, e, 1, in_dw, [&](int i, uint32_t w) { chain_out(L, e, i, w); }, T);
             for (int i = (int)M2.ndw; i < (int)M2.nchunk * 4; i++) chain_out(L, e, i, 0);
         }
@@ -316,24 +315,39 @@ DASH_HD void chain_eval_generic_body(const ChainLaunch& L, uint32_t bx, uint32_t
 }
 
 // ---- evaluator, digit gates of the sign gadget -------------------------------------------------
-// gate (residue, digit j) of element e with the compressed input label K and its colour already known
-template <class MO, class Tab>
-DASH_HD void digit_gate(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& K, uint32_t colour, uint32_t e, int j, const Tab& T) {
+// The hashes of one label under the slots of its digit gates, one after the other: what they share (slot_hash_start) is
+// formed at the first and again only where the slots' upper 24 bits change (the same for all lanes).
+struct SlotHasher {
+    const U128 K; const uint64_t elem; const uint32_t layer;
+    SlotHash S; uint32_t hi = 0; bool started = false;
+    DASH_HD SlotHasher(const U128& K_, uint64_t elem_, uint32_t layer_) : K(K_), elem(elem_), layer(layer_) {}
+    template <class Tab> DASH_HD U128 get(uint32_t slot, const uint32_t* rk, const Tab& T) {
+        if (!started || (slot >> 8) != hi) { S = slot_hash_start(K, elem, slot, layer, rk, T); hi = slot >> 8; started = true; }
+        return slot_hash(S, slot, rk, T);
+    }
+};
+// gate (residue, digit j) of element e: hash(slot) gives the hash of its input label, colour is the label's colour (it names the
+// row, whose loads go out before the hash)
+template <class MO, class Hash>
+DASH_HD void digit_gate(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, uint32_t colour, uint32_t e, int j, Hash hash) {
     const uint8_t* seg = R.table + (size_t)L.n_elem * R.p * L.row_prefix[j];
     const uint32_t* row = (const uint32_t*)(seg + ((size_t)e * R.p + colour) * (Mo.ndw * 4));
-    uint32_t rw[cmod_ndw<MO>::value];
+    const LView out{R.out + L.out_prefix[j], L.out_cs, 16u};
+    const uint32_t slot = R.slot0 + (uint32_t)(j - 1);
     if constexpr (cmod_m<MO>::value != 0) {
+        uint32_t rw[MO::ndw];
 #pragma unroll
         for (int i = 0; i < (int)MO::ndw; i++) rw[i] = row[i];
-    }
-    const LView out{R.out + L.out_prefix[j], L.out_cs, 16u};
-    U128 h = hash_block(K, L.elem_base + e, R.slot0 + (uint32_t)(j - 1), L.layer, L.key.rk, T);
-    if constexpr (cmod_m<MO>::value != 0) {
-        decompress(Mo, h, [&](int i, uint32_t hd) { st_dw(out, e, i, submod4(rw[i], hd, Mo)); });
+        const U128 h = hash(slot);
+        Dw4 w[MO::nchunk] = {};
+        decompress(Mo, h, [&](int i, uint32_t hd) { w[i >> 2].w[i & 3] = submod4(rw[i], hd, Mo); });
+#pragma unroll
+        for (int ch = 0; ch < (int)MO::nchunk; ch++) st_chunk(out, e, ch, w[ch]);
     } else {
+        const U128 h = hash(slot);
         decompress(Mo, h, [&](int i, uint32_t hd) { st_dw(out, e, i, submod4(row[i], hd, Mo)); });
+        for (int i = (int)Mo.ndw; i < (int)Mo.nchunk * 4; i++) st_dw(out, e, i, 0);
     }
-    for (int i = (int)Mo.ndw; i < (int)Mo.nchunk * 4; i++) st_dw(out, e, i, 0);
 }
 // the same gate with its output label handed to put(dword index, packed digits) instead of stored (compile-time moduli)
 template <class MO, class Tab, class Put>
@@ -355,18 +369,19 @@ DASH_HD void digits_eval_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, u
     const DigitsRes& R = L.res[by];
     const uint32_t e = bx * kThreads + tx;
     if (e >= L.n_elem) return;
-    const ModInfo Mp = L.mods[R.p];
+    const ModInfo Mp = ld_mod(L.mods, R.p);
     uint32_t colour = 0;
     U128 K = {{0, 0, 0, 0}};
     with_mod(Mp, [&](auto P) { K = compress(P, [&](int i) { return ld_dw(R.in, e, i); }, &colour); });
+    SlotHasher H(K, L.elem_base + e, L.layer);
+    auto hash = [&](uint32_t slot) { return H.get(slot, L.key.rk, T); };
     if constexpr (cmod_m<MC>::value != 0) {
-        digit_gate(L, R, M1{nullptr}, K, colour, e, 1, T);
-        const MC Mc{nullptr};
-        for (int j = 2; j <= (int)L.n; j++) digit_gate(L, R, Mc, K, colour, e, j, T);
+        digit_gate(L, R, M1{nullptr}, colour, e, 1, hash);
+        for (int j = 2; j <= (int)L.n; j++) digit_gate(L, R, MC{nullptr}, colour, e, j, hash);
     } else {
         for (int j = 1; j <= (int)L.n; j++) {
-            const ModInfo Mo = L.mods[L.m[j]];      // a copy in registers: through the reference every use is a load
-            digit_gate(L, R, Mo, K, colour, e, j, T);
+            const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
+            digit_gate(L, R, Mo, colour, e, j, hash);
         }
     }
 }
@@ -378,31 +393,29 @@ DASH_HD void digits_eval_wide_body(const DigitsLaunch& L, uint32_t bx, uint32_t 
     const DigitsRes& R = L.res[by];
     const uint32_t e = bx * kThreads + tx;
     if (e >= L.n_elem || j < 1 || j > L.n) return;
-    const ModInfo Mp = L.mods[R.p];
+    const ModInfo Mp = ld_mod(L.mods, R.p);
     uint32_t colour = 0;
     U128 K = {{0, 0, 0, 0}};
     with_mod(Mp, [&](auto P) { K = compress(P, [&](int i) { return ld_dw(R.in, e, i); }, &colour); });
+    auto hash = [&](uint32_t slot) { return hash_block(K, L.elem_base + e, slot, L.layer, L.key.rk, T); };
     if constexpr (cmod_m<MC>::value != 0) {
-        if (j == 1) digit_gate(L, R, M1{nullptr}, K, colour, e, 1, T);
-        else digit_gate(L, R, MC{nullptr}, K, colour, e, (int)j, T);
+        if (j == 1) digit_gate(L, R, M1{nullptr}, colour, e, 1, hash);
+        else digit_gate(L, R, MC{nullptr}, colour, e, (int)j, hash);
     } else {
-        const ModInfo Mo = L.mods[L.m[j]];
-        digit_gate(L, R, Mo, K, colour, e, (int)j, T);
+        const ModInfo Mo = ld_mod(L.mods, L.m[j]);
+        digit_gate(L, R, Mo, colour, e, (int)j, hash);
     }
 }
 
 // ---- garbler, digit gates of the sign gadget ---------------------------------------------------
 // One lane per (element g, value a) of a residue: the label of a is formed and compressed once, then one
 // ciphertext row per digit: rows[colour] = out0 + phi_j(a) R_{m_j} + H_{m_j}(label, slot_j).
-template <class MO, class Tab>
-DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& K, uint32_t colour, uint32_t g, uint32_t a, int j,
-                       const Tab& T) {
+template <class MO>
+DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& h, uint32_t f, uint32_t colour, uint32_t g, int j) {
     uint8_t* seg = R.table + (size_t)L.n_elem * R.p * L.row_prefix[j];
     uint32_t* row = (uint32_t*)(seg + ((size_t)g * R.p + colour) * (Mo.ndw * 4));
     const LView out0{R.out + L.out_prefix[j], L.out_cs, 16u};
-    const uint32_t f = R.phi[(size_t)(j - 1) * R.p + a];
     const uint32_t* df = Mo.dtab + f * Mo.ndw;
-    U128 h = hash_block(K, L.elem_base + g, R.slot0 + (uint32_t)(j - 1), L.layer, L.key.rk, T);
     if constexpr (cmod_m<MO>::value != 0) {
         uint32_t pay[MO::ndw];
 #pragma unroll
@@ -417,11 +430,10 @@ DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, 
 template <class MC, class M1, class Tab>
 DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, uint32_t j0 = 0) {
     const DigitsRes& R = L.res[by];
-    const ModInfo Mp = L.mods[R.p];
-    const uint64_t r0 = (uint64_t)bx * kThreads;
-    if (r0 >= (uint64_t)L.n_elem * Mp.m) return;
-    const uint32_t g0 = (uint32_t)(r0 / Mp.m);
-    const uint32_t off = (uint32_t)(r0 - (uint64_t)g0 * Mp.m) + tx;
+    const ModInfo Mp = ld_mod(L.mods, R.p);
+    const uint32_t r0 = bx * kThreads;
+    if ((uint64_t)bx * kThreads >= (uint64_t)L.n_elem * Mp.m) return;
+    const uint32_t g0 = div_any(r0, Mp), off = r0 - g0 * Mp.m + tx;
     const uint32_t dg = div_m(off, Mp);
     const uint32_t g = g0 + dg, a = off - dg * Mp.m;
     if (g >= L.n_elem) return;
@@ -432,16 +444,16 @@ DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by,
         K = compress(P, [&](int i) { return addmod4(ld_dw(R.in, g, i), gload32(da + i), P); }, &colour);
     });
     const int jlo = j0 ? (int)j0 : 1, jhi = j0 ? (int)j0 : (int)L.n;
-    if constexpr (cmod_m<MC>::value != 0) {
-        if (jlo == 1) digit_row(L, R, M1{L.mods[L.m[1]].dtab}, K, colour, g, a, 1, T);
-        if (jhi >= 2) {
-            const MC Mc{L.mods[L.m[2]].dtab};
-            for (int j = jlo < 2 ? 2 : jlo; j <= jhi; j++) digit_row(L, R, Mc, K, colour, g, a, j, T);
-        }
-    } else {
-        for (int j = jlo; j <= jhi; j++) {
-            const ModInfo Mo = L.mods[L.m[j]];      // a copy in registers: through the reference every use is a load
-            digit_row(L, R, Mo, K, colour, g, a, j, T);
+    SlotHasher H(K, L.elem_base + g, L.layer);
+    for (int j = jlo; j <= jhi; j++) {
+        const uint32_t f = R.phi[(size_t)(j - 1) * R.p + a];
+        const U128 h = H.get(R.slot0 + (uint32_t)(j - 1), L.key.rk, T);
+        if constexpr (cmod_m<MC>::value != 0) {
+            if (j == 1) digit_row(L, R, M1{ld_mod(L.mods, L.m[1]).dtab}, h, f, colour, g, 1);
+            else digit_row(L, R, MC{ld_mod(L.mods, L.m[2]).dtab}, h, f, colour, g, j);
+        } else {
+            const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
+            digit_row(L, R, Mo, h, f, colour, g, j);
         }
     }
 }
@@ -490,7 +502,7 @@ DASH_HD void cast_halve_body(const CastLaunch& L, uint32_t bx, uint32_t by, uint
     const CastJob& J = L.jobs[by];
     const uint32_t e = bx * kThreads + tx;
     if (e >= L.n_elem) return;
-    const ModInfo Mp = L.mods[J.p];
+    const ModInfo Mp = ld_mod(L.mods, J.p);
     uint32_t colour = 0;
     U128 K = compress_mod2(L.mods, [&](int i) { return ld_dw(L.y, e, i); }, &colour);
     U128 h = hash_block(K, L.elem_base + e, J.slot, L.layer, L.key.rk, T);
@@ -524,7 +536,7 @@ DASH_HD void cast_digit_wide_body(const CastLaunch& C, const DigitsLaunch& L, ui
     const DigitsRes& R = L.res[by];
     const uint32_t e = bx * kThreads + tx;
     if (e >= L.n_elem || j < 1 || j > L.n) return;
-    const ModInfo Mp = C.mods[J.p];
+    const ModInfo Mp = ld_mod(C.mods, J.p);
     uint32_t colour = 0;
     U128 K2 = compress_mod2(C.mods, [&](int i) { return ld_dw(C.y, e, i); }, &colour);
     U128 h = hash_block(K2, C.elem_base + e, J.slot, C.layer, C.key.rk, T);
@@ -539,12 +551,13 @@ DASH_HD void cast_digit_wide_body(const CastLaunch& C, const DigitsLaunch& L, ui
             }
             uint32_t cb = 0;
             const U128 K = compress(P, [&](int i) { return xw[i >> 2].w[i & 3]; }, &cb);
+            auto hash = [&](uint32_t slot) { return hash_block(K, L.elem_base + e, slot, L.layer, L.key.rk, T); };
             if constexpr (cmod_m<MC>::value != 0) {
-                if (j == 1) digit_gate(L, R, M1{nullptr}, K, cb, e, 1, T);
-                else digit_gate(L, R, MC{nullptr}, K, cb, e, (int)j, T);
+                if (j == 1) digit_gate(L, R, M1{nullptr}, cb, e, 1, hash);
+                else digit_gate(L, R, MC{nullptr}, cb, e, (int)j, hash);
             } else {
-                const ModInfo Mo = L.mods[L.m[j]];
-                digit_gate(L, R, Mo, K, cb, e, (int)j, T);
+                const ModInfo Mo = ld_mod(L.mods, L.m[j]);
+                digit_gate(L, R, Mo, cb, e, (int)j, hash);
             }
         }
     });
@@ -573,7 +586,7 @@ DASH_HD void digits_sum_phase1(const CastT& C, const DigitsLaunch& L, uint32_t b
     const DigitsRes& R = L.res[by];
     const uint32_t e = bx * kSumElems + el;
     if (e >= L.n_elem || j < 1 || j > L.n) return;
-    const ModInfo Mp = L.mods[R.p];
+    const ModInfo Mp = ld_mod(L.mods, R.p);
     uint32_t colour = 0;
     U128 K = {{0, 0, 0, 0}};
     if constexpr (std::is_same<CastT, CastLaunch>::value) {        // scaling gadget: b of this residue first (stored by the lanes of digit 1)
@@ -636,7 +649,7 @@ DASH_HD void digits_sum_phase2(const DigitsLaunch& L, uint32_t bx, uint32_t j, u
 template <class Tab>
 DASH_HD void hg_finish_body(const HgLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T) {
     const HgJob& J = L.jobs[by];
-    const ModInfo Mp = L.mods[J.p];
+    const ModInfo Mp = ld_mod(L.mods, J.p);
     uint32_t e = bx * kThreads + tx;
     if (e >= L.n_elem) return;
     uint32_t colour = 0;
@@ -676,7 +689,7 @@ DASH_HD void hg_finish_body(const HgLaunch& L, uint32_t bx, uint32_t by, uint32_
 template <class Tab>
 DASH_HD void hg_eval_quad_body(const HgLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T) {
     const HgJob& J = L.jobs[by];
-    const ModInfo Mp = L.mods[J.p];
+    const ModInfo Mp = ld_mod(L.mods, J.p);
     const uint32_t lane = bx * kThreads + tx, e = lane >> 2, c = lane & 3u;
     if (e >= L.n_elem) return;
     with_mod(Mp, [&](auto P) {

@@ -203,8 +203,23 @@ DASH_HD uint32_t gload32(const uint32_t* p) {
     return *p;
 #endif
 }
+// record of a modulus: the table of moduli is never written while a kernel runs, so a wave-uniform index is a scalar load
+DASH_HD ModInfo ld_mod(const ModInfo* mods, uint32_t m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(sizeof(ModInfo) % 8 == 0, "copied in 8-byte words");
+    const auto* src = (const __attribute__((address_space(4))) uint64_t*)(mods + m);
+    union { uint64_t w[sizeof(ModInfo) / 8]; ModInfo M; } u;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(ModInfo) / 8); i++) u.w[i] = src[i];
+    return u.M;
+#else
+    return mods[m];
+#endif
+}
 template <class MI> DASH_HD uint32_t div_m(uint32_t n, const MI& M) { return mulhi(n, M.mmagic); }           // n < 2^24
 template <class MI> DASH_HD uint32_t mod_m(uint32_t n, const MI& M) { return n - mul24(div_m(n, M), M.m); }  // n < 2^24
+// floor(n / m) for any n < 2^32 (wave-uniform n: scalar unit): the rounded-up reciprocal is too large by at most one
+template <class MI> DASH_HD uint32_t div_any(uint32_t n, const MI& M) { const uint32_t q = mulhi(n, M.mmagic); return q - (q * M.m > n ? 1u : 0u); }
 DASH_HD uint32_t byte_of(uint32_t w, int b) { return (w >> (8 * b)) & 0xffu; }
 
 // Packed modular addition and subtraction on 4 digits.  The bytes that have to be corrected by m are found as a 0/1 flag per
@@ -357,38 +372,49 @@ template <class Tab, class = void> struct tab_two : std::false_type {};
 template <class Tab> struct tab_two<Tab, std::enable_if_t<Tab::two_tables>> : std::true_type {};
 DASH_HD uint32_t rot16(uint32_t v) { return (v << 16) | (v >> 16); }
 
+// (Tab::rotated_keys: the caller hands over the keys of rounds 1..9 rotated by 16 bits already, see rotate_round_keys.)
+template <class Tab, class = void> struct tab_rot : std::false_type {};
+template <class Tab> struct tab_rot<Tab, std::enable_if_t<Tab::rotated_keys>> : std::true_type {};
+DASH_HD void rotate_round_keys(uint32_t rk[44]) { for (int i = 4; i < 40; i++) rk[i] = rot16(rk[i]); }
+
+// one column of a round: bytes 0..3 of a0..a3 through T0..T3, and the round key.  With two tables the key goes in before the
+// rotation that T2 and T3 need, so that every step is a three-input exclusive-or: 7 instructions a column with the four addresses
+// instead of 8.
 template <class Tab>
-DASH_HD void aes128_encrypt(uint32_t s[4], const uint32_t* rk, const Tab& T) {
-    uint32_t a0 = s[0] ^ rk[0], a1 = s[1] ^ rk[1], a2 = s[2] ^ rk[2], a3 = s[3] ^ rk[3];
+DASH_HD uint32_t aes_column(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t rk, const Tab& T) {
     if constexpr (tab_two<Tab>::value) {
+        const uint32_t k = tab_rot<Tab>::value ? rk : rot16(rk);
+        return xor3(T.template at<0, 0>(a0), T.template at<1, 1>(a1), rot16(xor3(T.template at<0, 2>(a2), T.template at<1, 3>(a3), k)));
+    } else {
+        return xor3(xor3(T.template at<0, 0>(a0), T.template at<1, 1>(a1), T.template at<2, 2>(a2)), T.template at<3, 3>(a3), rk);
+    }
+}
+// rounds R0..10 on the state a
+template <int R0, class Tab>
+DASH_HD void aes_rounds(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t s[4], const uint32_t* rk, const Tab& T) {
 #pragma unroll
-        for (int r = 1; r < 10; r++) {
-            uint32_t b0 = xor3(T.template at<0, 0>(a0), T.template at<1, 1>(a1), rk[4 * r + 0]) ^ rot16(T.template at<0, 2>(a2) ^ T.template at<1, 3>(a3));
-            uint32_t b1 = xor3(T.template at<0, 0>(a1), T.template at<1, 1>(a2), rk[4 * r + 1]) ^ rot16(T.template at<0, 2>(a3) ^ T.template at<1, 3>(a0));
-            uint32_t b2 = xor3(T.template at<0, 0>(a2), T.template at<1, 1>(a3), rk[4 * r + 2]) ^ rot16(T.template at<0, 2>(a0) ^ T.template at<1, 3>(a1));
-            uint32_t b3 = xor3(T.template at<0, 0>(a3), T.template at<1, 1>(a0), rk[4 * r + 3]) ^ rot16(T.template at<0, 2>(a1) ^ T.template at<1, 3>(a2));
-            a0 = b0; a1 = b1; a2 = b2; a3 = b3;
-        }
+    for (int r = R0; r < 10; r++) {
+        const uint32_t b0 = aes_column(a0, a1, a2, a3, rk[4 * r + 0], T), b1 = aes_column(a1, a2, a3, a0, rk[4 * r + 1], T);
+        const uint32_t b2 = aes_column(a2, a3, a0, a1, rk[4 * r + 2], T), b3 = aes_column(a3, a0, a1, a2, rk[4 * r + 3], T);
+        a0 = b0; a1 = b1; a2 = b2; a3 = b3;
+    }
+    if constexpr (tab_two<Tab>::value) {
         // last round: S[x] sits in bytes 1 and 2 of T0 and in bytes 2 and 3 of T1
         s[0] = (((T.template at<0, 0>(a0) >> 8) & 0xffu) | (T.template at<0, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ rk[40];
         s[1] = (((T.template at<0, 0>(a1) >> 8) & 0xffu) | (T.template at<0, 1>(a2) & 0xff00u) | (T.template at<0, 2>(a3) & 0xff0000u) | (T.template at<1, 3>(a0) & 0xff000000u)) ^ rk[41];
         s[2] = (((T.template at<0, 0>(a2) >> 8) & 0xffu) | (T.template at<0, 1>(a3) & 0xff00u) | (T.template at<0, 2>(a0) & 0xff0000u) | (T.template at<1, 3>(a1) & 0xff000000u)) ^ rk[42];
         s[3] = (((T.template at<0, 0>(a3) >> 8) & 0xffu) | (T.template at<0, 1>(a0) & 0xff00u) | (T.template at<0, 2>(a1) & 0xff0000u) | (T.template at<1, 3>(a2) & 0xff000000u)) ^ rk[43];
     } else {
-#pragma unroll
-    for (int r = 1; r < 10; r++) {
-        uint32_t b0 = xor3(xor3(T.template at<0, 0>(a0), T.template at<1, 1>(a1), T.template at<2, 2>(a2)), T.template at<3, 3>(a3), rk[4 * r + 0]);
-        uint32_t b1 = xor3(xor3(T.template at<0, 0>(a1), T.template at<1, 1>(a2), T.template at<2, 2>(a3)), T.template at<3, 3>(a0), rk[4 * r + 1]);
-        uint32_t b2 = xor3(xor3(T.template at<0, 0>(a2), T.template at<1, 1>(a3), T.template at<2, 2>(a0)), T.template at<3, 3>(a1), rk[4 * r + 2]);
-        uint32_t b3 = xor3(xor3(T.template at<0, 0>(a3), T.template at<1, 1>(a0), T.template at<2, 2>(a1)), T.template at<3, 3>(a2), rk[4 * r + 3]);
-        a0 = b0; a1 = b1; a2 = b2; a3 = b3;
+        // last round: SubBytes + ShiftRows only.  S[x] sits in byte 0 of T2, byte 1 of T3, byte 2 of T0, byte 3 of T1.
+        s[0] = ((T.template at<2, 0>(a0) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ rk[40];
+        s[1] = ((T.template at<2, 0>(a1) & 0xffu) | (T.template at<3, 1>(a2) & 0xff00u) | (T.template at<0, 2>(a3) & 0xff0000u) | (T.template at<1, 3>(a0) & 0xff000000u)) ^ rk[41];
+        s[2] = ((T.template at<2, 0>(a2) & 0xffu) | (T.template at<3, 1>(a3) & 0xff00u) | (T.template at<0, 2>(a0) & 0xff0000u) | (T.template at<1, 3>(a1) & 0xff000000u)) ^ rk[42];
+        s[3] = ((T.template at<2, 0>(a3) & 0xffu) | (T.template at<3, 1>(a0) & 0xff00u) | (T.template at<0, 2>(a1) & 0xff0000u) | (T.template at<1, 3>(a2) & 0xff000000u)) ^ rk[43];
     }
-    // last round: SubBytes + ShiftRows only.  S[x] sits in byte 0 of T2, byte 1 of T3, byte 2 of T0, byte 3 of T1.
-    s[0] = ((T.template at<2, 0>(a0) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ rk[40];
-    s[1] = ((T.template at<2, 0>(a1) & 0xffu) | (T.template at<3, 1>(a2) & 0xff00u) | (T.template at<0, 2>(a3) & 0xff0000u) | (T.template at<1, 3>(a0) & 0xff000000u)) ^ rk[41];
-    s[2] = ((T.template at<2, 0>(a2) & 0xffu) | (T.template at<3, 1>(a3) & 0xff00u) | (T.template at<0, 2>(a0) & 0xff0000u) | (T.template at<1, 3>(a1) & 0xff000000u)) ^ rk[42];
-    s[3] = ((T.template at<2, 0>(a3) & 0xffu) | (T.template at<3, 1>(a0) & 0xff00u) | (T.template at<0, 2>(a1) & 0xff0000u) | (T.template at<1, 3>(a2) & 0xff000000u)) ^ rk[43];
-    }
+}
+template <class Tab>
+DASH_HD void aes128_encrypt(uint32_t s[4], const uint32_t* rk, const Tab& T) {
+    aes_rounds<1>(s[0] ^ rk[0], s[1] ^ rk[1], s[2] ^ rk[2], s[3] ^ rk[3], s, rk, T);
 }
 
 // AES-128 by the FOUR lanes of a quad (lanes 4i .. 4i + 3 of a wave) together: all four call with the same s, all four
@@ -442,6 +468,50 @@ DASH_HD U128 hash_block(const U128& K, uint64_t elem, uint32_t slot, uint32_t la
     uint32_t s[4] = {x[0], x[1], x[2], x[3]};
     aes128_encrypt(s, rk, T);
     U128 h = {{s[0] ^ x[0], s[1] ^ x[1], s[2] ^ x[2], s[3] ^ x[3]}};
+    return h;
+}
+// Several hashes of ONE label whose slots differ in the low byte only (the digit gates of a residue): that byte is one byte of
+// the state, it reaches one column in round 1 and one byte of every column in round 2.  Everything else of the two rounds is done
+// once: each further hash looks up 5 entries in them instead of 32.
+struct SlotHash { uint32_t x[4], b2, c[4]; };      // hash input; column 2 after round 1 and the columns after round 2, without what the slot's low byte contributes
+template <class Tab>
+DASH_HD SlotHash slot_hash_start(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const uint32_t* rk, const Tab& T) {
+    SlotHash S;
+    S.x[0] = K.w[0] ^ (uint32_t)elem; S.x[1] = K.w[1] ^ (uint32_t)(elem >> 32); S.x[2] = K.w[2] ^ (slot & ~0xffu); S.x[3] = K.w[3] ^ (layer & 0xffffu);
+    const uint32_t a0 = S.x[0] ^ rk[0], a1 = S.x[1] ^ rk[1], a2 = S.x[2] ^ rk[2], a3 = S.x[3] ^ rk[3];
+    const uint32_t b0 = aes_column(a0, a1, a2, a3, rk[4], T), b1 = aes_column(a1, a2, a3, a0, rk[5], T), b3 = aes_column(a3, a0, a1, a2, rk[7], T);
+    if constexpr (tab_two<Tab>::value) {
+        auto key = [&](int i) { return tab_rot<Tab>::value ? rk[i] : rot16(rk[i]); };
+        auto T0 = [&](auto B, uint32_t w) { return T.template at<0, decltype(B)::value>(w); };
+        auto T1 = [&](auto B, uint32_t w) { return T.template at<1, decltype(B)::value>(w); };
+        typedef std::integral_constant<int, 0> B0; typedef std::integral_constant<int, 1> B1; typedef std::integral_constant<int, 2> B2; typedef std::integral_constant<int, 3> B3;
+        S.b2 = T1(B1{}, a3) ^ rot16(xor3(T0(B2{}, a0), T1(B3{}, a1), key(6)));
+        S.c[0] = xor3(T0(B0{}, b0), T1(B1{}, b1), rot16(T1(B3{}, b3) ^ key(8)));
+        S.c[1] = T0(B0{}, b1) ^ rot16(xor3(T0(B2{}, b3), T1(B3{}, b0), key(9)));
+        S.c[2] = T1(B1{}, b3) ^ rot16(xor3(T0(B2{}, b0), T1(B3{}, b1), key(10)));
+        S.c[3] = xor3(T0(B0{}, b3), T1(B1{}, b0), rot16(T0(B2{}, b1) ^ key(11)));
+    } else {
+        S.b2 = xor3(T.template at<1, 1>(a3), T.template at<2, 2>(a0), T.template at<3, 3>(a1)) ^ rk[6];
+        S.c[0] = xor3(T.template at<0, 0>(b0), T.template at<1, 1>(b1), T.template at<3, 3>(b3)) ^ rk[8];
+        S.c[1] = xor3(T.template at<0, 0>(b1), T.template at<2, 2>(b3), T.template at<3, 3>(b0)) ^ rk[9];
+        S.c[2] = xor3(T.template at<1, 1>(b3), T.template at<2, 2>(b0), T.template at<3, 3>(b1)) ^ rk[10];
+        S.c[3] = xor3(T.template at<0, 0>(b3), T.template at<1, 1>(b0), T.template at<2, 2>(b1)) ^ rk[11];
+    }
+    return S;
+}
+// the hash for a slot with the same upper 24 bits
+template <class Tab>
+DASH_HD U128 slot_hash(const SlotHash& S, uint32_t slot, const uint32_t* rk, const Tab& T) {
+    const uint32_t x2 = S.x[2] ^ (slot & 0xffu);
+    const uint32_t b2 = S.b2 ^ T.template at<0, 0>(x2 ^ rk[2]);
+    uint32_t s[4];
+    if constexpr (tab_two<Tab>::value)
+        aes_rounds<3>(S.c[0] ^ rot16(T.template at<0, 2>(b2)), S.c[1] ^ T.template at<1, 1>(b2), S.c[2] ^ T.template at<0, 0>(b2),
+                      S.c[3] ^ rot16(T.template at<1, 3>(b2)), s, rk, T);
+    else
+        aes_rounds<3>(S.c[0] ^ T.template at<2, 2>(b2), S.c[1] ^ T.template at<1, 1>(b2), S.c[2] ^ T.template at<0, 0>(b2), S.c[3] ^ T.template at<3, 3>(b2),
+                      s, rk, T);
+    U128 h = {{s[0] ^ S.x[0], s[1] ^ S.x[1], s[2] ^ x2, s[3] ^ S.x[3]}};
     return h;
 }
 // the same by the four lanes of a quad together (aes128_encrypt_quad): same arguments and same result in all four
@@ -549,9 +619,10 @@ DASH_HD void frac_product(const U128& h, uint64_t acc, uint32_t* f, uint32_t& to
 // floor(v / m^E) for v <= VMAX
 template <uint32_t MOD, uint32_t E, uint64_t VMAX>
 DASH_HD uint32_t div_pow(uint32_t v) {
-    constexpr uint32_t tw = E * cm::twos_of(MOD);
+    constexpr uint32_t tw = E * cm::twos_of(MOD), plain = cm::magic_shift(VMAX, cm::ipow(MOD, E));
     constexpr uint64_t D = cm::ipow(MOD, E) >> tw;
     if constexpr (D == 1) return v >> tw;
+    else if constexpr (plain == 0) return mulhi(v, cm::magic_mul(0, cm::ipow(MOD, E)));      // no shift at all
     else {
         constexpr uint32_t sh = cm::magic_shift(VMAX >> tw, D);
         static_assert(sh < 32, "multiply-high division out of range");

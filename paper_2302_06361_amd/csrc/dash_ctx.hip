@@ -283,6 +283,8 @@ int dash_ctx_create(dash_ctx** out, const uint16_t* primes, int k, int lambda_ru
     for (int i = 0; i < 16; i++) fixed_key[i] = (uint8_t)i;
     expand_key(fixed_key, S, c->fixed.rk);
     expand_key(seed, S, c->seed.rk);
+    c->fixed_rot = c->fixed; rotate_round_keys(c->fixed_rot.rk);
+    c->seed_rot = c->seed; rotate_round_keys(c->seed_rot.rk);
 
     // moduli in use: 2, the primes, the accumulation moduli
     bool used[256] = {false};

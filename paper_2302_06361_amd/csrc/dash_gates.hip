@@ -23,7 +23,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads) void k_draw(const DrawLa
     __shared__ uint32_t tt[gate_tab<Banked>::words];
     const auto T = gate_tab<Banked>::load(tt, L.ttab);
     const uint32_t tiles = (L.jobs[blockIdx.y].n_elem + kThreads - 1) / kThreads;
-    const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+    const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) draw_body(L, tile, blockIdx.y, tx, T);
 }
 
@@ -38,8 +38,8 @@ int launch_draw(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s) {
         nmax = L.jobs[j].n_elem > nmax ? L.jobs[j].n_elem : nmax;
     }
     if (nmax == 0) return DASH_OK;
-    L.key = c->seed; L.ttab = c->d_ttab; L.mods = c->d_mods;
     const bool banked = lanes >= c->banked_min_lanes;
+    L.key = banked ? c->seed_rot : c->seed; L.ttab = c->d_ttab; L.mods = c->d_mods;
     dim3 grid(gate_grid_x_for((nmax + kThreads - 1) / kThreads, njobs, banked), njobs);
     if (banked) hipLaunchKernelGGL(k_draw<true>, grid, dim3(kBigThreads), 0, s, L);
     else hipLaunchKernelGGL(k_draw<false>, grid, dim3(kThreads), 0, s, L);
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         __shared__ uint32_t stage[kBigThreads * stride];
         __shared__ uint64_t sdst[kBigThreads];
         const BankTab T = load_banktab(tt, L.ttab);
-        const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+        const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
         const int lane = threadIdx.x & 63, w0 = threadIdx.x & ~63;       // this wave's rows: w0 .. w0 + 63
         auto tiles_of = [&](uint32_t j) { return (uint32_t)(((uint64_t)L.jobs[j].n_elem * L.jobs[j].p + kThreads - 1) / kThreads); };
         uint32_t total = 0;
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
             RegSink<ndw> sink;
             if (t < total) {
                 while (t >= next) { job++; base = next; next += tiles_of(job); }
-                garble_body<QD>(L, t - base, __builtin_amdgcn_readfirstlane(job), tx, T, sink);
+                garble_body<QD>(L, t - base, job, tx, T, sink);
             }
             sdst[threadIdx.x] = sink.addr;
 #pragma unroll
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
     } else {
         __shared__ uint32_t tt[gate_tab<Banked>::words];
         const auto T = gate_tab<Banked>::load(tt, L.ttab);
-        const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+        const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
         if constexpr (Banked) {
             // one-dimensional grid: the jobs differ in length (n_elem * p rows), so the blocks share the
             // concatenation of all jobs' tiles evenly.  job, base and next are the same in all lanes of a wave.
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
             for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
                 while (t >= next) { job++; base = next; next += tiles_of(job); }
                 DirectSink sink;
-                garble_body<QD>(L, t - base, __builtin_amdgcn_readfirstlane(job), tx, T, sink);
+                garble_body<QD>(L, t - base, job, tx, T, sink);
             }
         } else {
             for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) {
@@ -294,6 +294,7 @@ int launch_garble(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
     const int ki = q ? hot_mod_index(c->mods[q]) : 0;
     const bool staged = kGarbleStaged[ki];
     const bool banked = (uint64_t)units >= c->banked_min_lanes;
+    if (banked) L.key = c->fixed_rot;
     L.njobs = (uint32_t)njobs;
     dim3 grid(gate_grid_x_for(blocks, njobs, banked), njobs);
     if (banked) {       // one-dimensional: all jobs' tiles, 1024 lanes (4 tiles) per block at a time, two blocks per CU

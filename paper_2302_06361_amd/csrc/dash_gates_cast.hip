@@ -50,7 +50,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads) void k_cast_digits_eval(
     __shared__ uint32_t tt[gate_tab<Banked>::words];
     const auto T = gate_tab<Banked>::load(tt, L.ttab);
     const uint32_t tiles = (L.n_elem + kThreads - 1) / kThreads;
-    const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+    const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) {
         cast_halve_body(C, tile, blockIdx.y, tx, T);
         digits_eval_body<MC, M1>(L, tile, blockIdx.y, tx, T);
@@ -161,6 +161,7 @@ int launch_cast_digits_eval(const dash_ctx* c, CastLaunch& C, int njobs, DigitsL
         for (uint32_t j = 1; j <= L.n; j++) bytes += (double)L.n_elem * (c->mods[R.p].lam + 2.0 * c->mods[L.m[j]].lam);
     }
     const bool banked = (uint64_t)L.n_elem * L.nres >= c->banked_min_lanes;
+    if (banked) C.key = L.key = c->fixed_rot;
     dim3 grid(gate_grid_x_for((L.n_elem + kThreads - 1) / kThreads, (int)L.nres, banked), L.nres);
     const dim3 block(banked ? kBigThreads : kThreads);
     const int typed = typed_digits(c, L, uniform);

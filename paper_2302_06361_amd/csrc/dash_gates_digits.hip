@@ -19,14 +19,14 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_d
     constexpr int kGateTiles = gate_tab<Banked>::threads / kThreads;
     __shared__ uint32_t tt[gate_tab<Banked>::words];
     const auto T = gate_tab<Banked>::load(tt, L.ttab);
-    const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+    const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     auto tiles_of = [&](uint32_t i) { return (uint32_t)(((uint64_t)L.n_elem * L.res[i].p + kThreads - 1) / kThreads); };
     uint32_t total = 0;
     for (uint32_t i = 0; i < L.nres; i++) total += tiles_of(i);
     uint32_t res = 0, base = 0, next = tiles_of(0);
     for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
         while (t >= next) { res++; base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, __builtin_amdgcn_readfirstlane(res), tx, T);
+        digits_garble_body<MC, M1>(L, t - base, res, tx, T);
     }
 }
 
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kThreads) void k_digits_garble_wide(const DigitsLau
     uint32_t res = 0, base = 0, next = tiles_of(0);
     for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
         while (t >= next) { res++; base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, __builtin_amdgcn_readfirstlane(res), threadIdx.x, T, blockIdx.y + 1);
+        digits_garble_body<MC, M1>(L, t - base, res, threadIdx.x, T, blockIdx.y + 1);
     }
 }
 
@@ -79,6 +79,7 @@ int launch_digits_garble(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
         return DASH_OK;
     }
     const bool banked = (uint64_t)(units / L.n) >= c->digits_banked_min_lanes;
+    if (banked) L.key = c->fixed_rot;
     dim3 grid(gate_grid_x_for(tiles, 1, banked));
     const dim3 block(banked ? kBigThreads : kThreads);
     with_digit_set(typed, [&](auto ds) {

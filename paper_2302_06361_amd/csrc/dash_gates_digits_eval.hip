@@ -19,7 +19,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_d
     __shared__ uint32_t tt[gate_tab<Banked>::words];
     const auto T = gate_tab<Banked>::load(tt, L.ttab);
     const uint32_t tiles = (L.n_elem + kThreads - 1) / kThreads;
-    const uint32_t sub = threadIdx.x / kThreads, tx = threadIdx.x % kThreads;
+    const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles)
         digits_eval_body<MC, M1>(L, tile, blockIdx.y, tx, T);
 }
@@ -85,6 +85,7 @@ int launch_digits_eval(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
     }
     // (by lanes, not by hashes: with n hashes per lane the 64 KB tables were still measured slower below this size)
     const bool banked = (uint64_t)L.n_elem * L.nres >= c->banked_min_lanes;
+    if (banked) L.key = c->fixed_rot;
     dim3 grid(gate_grid_x_for((L.n_elem + kThreads - 1) / kThreads, (int)L.nres, banked), L.nres);
     const dim3 block(banked ? kBigThreads : kThreads);
     with_digit_set(typed, [&](auto ds) {

@@ -47,6 +47,7 @@ struct dash_ctx {
     uint64_t P;
     dash::ModInfo mods[256];         // host copy (dtab = device pointers)
     dash::AesKey fixed, seed;
+    dash::AesKey fixed_rot, seed_rot;   // the same for the kernels with the bank-replicated tables (rotate_round_keys)
     // device memory owned by the context
     dash::ModInfo* d_mods;
     uint32_t* d_ttab;

@@ -39,14 +39,15 @@ __device__ __forceinline__ LdsTab load_ttab(uint32_t* lds, const uint32_t* g) {
 }
 
 struct BankTab {
-    static constexpr bool two_tables = true;
+    static constexpr bool two_tables = true, rotated_keys = true;
     const uint8_t* t;
     uint32_t lane;       // byte 0: 4 * bank
     template <int R, int B> __device__ __forceinline__ uint32_t at(uint32_t w) const {
         static_assert(R < 2, "T0 and T1 only");
-        // v_perm_b32(hi = w, lo = lane): selector 0..3 bytes of lane, 4..7 bytes of w, 0x0c zero
+        // v_perm_b32(hi = w, lo = lane): selector 0..3 bytes of lane, 4..7 bytes of w, 0x0c zero.  (Byte 1 is in place already: an
+        // and-or, half the issue cost of a permute.)
         constexpr uint32_t sel = 0x0c0c0000u | ((4u + B) << 8);
-        const uint32_t a = __builtin_amdgcn_perm(w, lane, sel);
+        const uint32_t a = B == 1 ? (w & 0xff00u) | lane : __builtin_amdgcn_perm(w, lane, sel);
         return *(const uint32_t*)(t + a + R * 128);
     }
 };
