@@ -2,11 +2,16 @@
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 SO = os.path.join(HERE, "libdash.so")
-SOURCES = ["dash_ctx.hip", "dash_gates.hip", "dash_gates_digits.hip", "dash_gates_eval.hip", "dash_gates_digits_eval.hip", "dash_gates_cast.hip", "dash_layers.hip", "dash_linear.hip", "dash_gemm.hip", "dash_aesprof.hip"]
+GATE_SOURCES = ["dash_gates_cast.hip", "dash_gates.hip", "dash_gates_eval.hip", "dash_gates_digits_eval.hip", "dash_gates_digits.hip"]
+SOURCES = ["dash_ctx.hip", "dash_layers.hip", "dash_linear.hip", "dash_gemm.hip", "dash_aesprof.hip"]
+# (source, extra flags, object): the gate kernels once per label-length rule, the longest first
+UNITS = ([(s, [], s.replace(".hip", ".o")) for s in GATE_SOURCES] + [(s, ["-DDASH_RULE_FLOOR"], s.replace(".hip", "_floor.o")) for s in GATE_SOURCES] +
+         [(s, [], s.replace(".hip", ".o")) for s in SOURCES])
 HEADERS = ["dash_core.h", "dash_launch.h", "dash_bodies.h", "dash_hostconst.h", "dash_internal.h", "dash_tabs.h", "dash_aes_sliced.h", "dash_sbox_circuit.h", os.path.join("..", "..", "include", "dash.h"),
            os.path.join("..", "..", "include", "dash_profile.h")]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-Wno-pass-failed",
@@ -19,26 +24,28 @@ def build(force=True, verbose=False):
     or header is newer (or always with force)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     hdr_time = max(os.path.getmtime(os.path.join(CSRC, h)) for h in HEADERS)
-    objs, procs = [], []
-    for src in SOURCES:
-        s = os.path.join(CSRC, src)
-        o = os.path.join(CSRC, src.replace(".hip", ".o"))
+    objs, todo = [], []
+    for src, flags, obj in UNITS:
+        s, o = os.path.join(CSRC, src), os.path.join(CSRC, obj)
         objs.append(o)
         if force or not os.path.exists(o) or os.path.getmtime(o) < max(os.path.getmtime(s), hdr_time):
-            cmd = [hipcc] + FLAGS + ["-c", s, "-o", o]
-            if verbose:
-                print(" ".join(cmd))
-            procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+            todo.append((obj, [hipcc] + FLAGS + flags + ["-c", s, "-o", o]))
+
+    def compile_unit(item):
+        if verbose:
+            print(" ".join(item[1]))
+        return item[0], subprocess.run(item[1], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
     failed = False
-    for src, p in procs:
-        out, _ = p.communicate()
-        # the host pass does not know the packed-fp32 feature and says so: harmless
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
-        if out.strip():
-            print(out)
-        if p.returncode != 0:
-            failed = True
-            print("FAILED:", src)
+    with ThreadPoolExecutor(min(16, os.cpu_count() or 1)) as ex:
+        for obj, p in ex.map(compile_unit, todo):
+            # the host pass does not know the packed-fp32 feature and says so: harmless
+            out = "\n".join(l for l in p.stdout.splitlines() if "packed-fp32-ops" not in l)
+            if out.strip():
+                print(out)
+            if p.returncode != 0:
+                failed = True
+                print("FAILED:", obj)
     if failed:
         raise RuntimeError("hipcc failed")
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", SO] + objs)

@@ -7,6 +7,7 @@
 #include "dash_launch.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // dword i (digits 4i..4i+3) of element e of a label view
 // The chunk base is wave-uniform (scalar registers); the lane part is a 32-bit byte offset, so the
@@ -752,4 +753,5 @@ DASH_HD void hg_eval_quad_body(const HgLaunch& L, uint32_t bx, uint32_t by, uint
     });
 }
 
+}  // inline namespace
 }  // namespace dash

@@ -738,12 +738,25 @@ DASH_HD uint32_t mod_u128(const U128& h, const MI& M) {
     return r;
 }
 
-// The moduli with a compile-time description: the CRT primes up to 37 and the accumulation moduli of
-// the default digit sets, with their label lengths under the ceil rule.
+// The moduli with a compile-time description: the CRT primes up to 37 and the accumulation moduli of the default digit sets, with
+// their label lengths under one of the two rules.  The gate sources are compiled once per rule (DASH_RULE_FLOOR: the floor rule, else
+// the ceil rule), each in an inline namespace of its own; the launch functions carry the rule in their name (DASH_FN) and are picked
+// by the context's rule (dash_internal.h).
+#if defined(DASH_RULE_FLOOR)
+#define DASH_RULE_NS floor_rule
+#define DASH_FN(name) name##_floor
+#define DASH_HOT_MODS(X) \
+    X(2, 128) X(3, 80) X(5, 55) X(7, 45) X(11, 37) X(13, 34) X(17, 31) X(19, 30) X(23, 28) X(29, 26) X(31, 25) X(37, 24) \
+    X(26, 27) X(96, 19) X(46, 23) X(204, 16) X(10, 38) X(91, 19) X(22, 28) X(90, 19)
+#else
+#define DASH_RULE_NS ceil_rule
+#define DASH_FN(name) name##_ceil
 #define DASH_HOT_MODS(X) \
     X(2, 128) X(3, 81) X(5, 56) X(7, 46) X(11, 38) X(13, 35) X(17, 32) X(19, 31) X(23, 29) X(29, 27) X(31, 26) X(37, 25) \
     X(26, 28) X(96, 20) X(46, 24) X(204, 17) X(10, 39) X(91, 20) X(22, 29) X(90, 20)
+#endif
 
+inline namespace DASH_RULE_NS {
 // f(description of M): compile-time description for the hot moduli, run-time otherwise
 template <class F>
 DASH_HD void with_mod(const ModInfo& M, F&& f) {
@@ -771,8 +784,12 @@ DASH_HD int hot_mod_index(const ModInfo& M) {
 
 // Digit sets (d_1; d, .., d) of the sign gadget whose kernels exist with compile-time moduli, as (m_c, lambda, m_1, lambda):
 // m_1 = d_1 the accumulation modulus of digit 1, m_c = k d that of the others.  The default sets of the 8-, 12-, 7- and
-// 9-prime bases (the bases of the paper's models), under the ceil rule.
+// 9-prime bases (the bases of the paper's models).
+#if defined(DASH_RULE_FLOOR)
+#define DASH_DIGIT_SETS(X) X(96, 19, 26, 27) X(204, 16, 46, 23) X(91, 19, 10, 38) X(90, 19, 22, 28)
+#else
 #define DASH_DIGIT_SETS(X) X(96, 20, 26, 28) X(204, 17, 46, 24) X(91, 20, 10, 39) X(90, 20, 22, 29)
+#endif
 template <class MC_, class M1_> struct DigitSet { typedef MC_ MC; typedef M1_ M1; };
 // index (1..) of the set with these two moduli, 0 if none
 DASH_HD int digit_set_index(const ModInfo& Mc, const ModInfo& M1) {
@@ -792,4 +809,5 @@ void with_digit_set(int index, F&& f) {
     f(DigitSet<ModInfo, ModInfo>{});
 }
 
+}  // inline namespace
 }  // namespace dash

@@ -15,6 +15,7 @@
 #include "dash_tabs.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // ------------------------------------------------------------------------------------------ draw
 template <bool Banked>
@@ -27,7 +28,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads) void k_draw(const DrawLa
     for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) draw_body(L, tile, blockIdx.y, tx, T);
 }
 
-int launch_draw(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_draw)(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s) {
     static_assert(sizeof(DrawLaunch) <= 4096, "kernel argument block");
     if (njobs < 1 || njobs > kMaxDrawJobs) return DASH_EINVAL;
     uint64_t lanes = 0;
@@ -52,7 +53,7 @@ __global__ __launch_bounds__(kThreads) void k_affine(const AffineLaunch L) {
     affine_body(L, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
-int launch_affine(const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s) {
     static_assert(sizeof(AffineLaunch) <= 4096, "kernel argument block");
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
@@ -73,47 +74,134 @@ int launch_affine(const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s) 
 }
 
 // ------------------------------------------------------------------------------- packed table rows
-// one lane per row: working format [pitch_q bytes, one digit each] <-> 16-byte integer sum_j row[j] q^j
+// Working format [pitch_q bytes, one digit each] <-> 16-byte integer sum_j row[j] q^j.  The kernel is bound by the bytes it moves
+// (36 per 20-byte row), so a wave brings its 64 rows through LDS: the rows are contiguous in memory and every access to them is a
+// dword per lane, consecutive lanes consecutive dwords, whatever the pitch; the packed side is 16 bytes per lane.  Rows of bits (q = 2)
+// need no LDS: 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.  The segments of a
+// layer differ in length by a factor of 50, so the waves share the concatenation of their tiles, a contiguous range each.
+// (One lane per row, run-time constants and the same number of blocks for every segment took 6.0 ms for the 5.1 GB of tables of a
+// LeNet batch of 4; this form takes 2.2.)
 template <bool Pack>
 __global__ __launch_bounds__(kThreads) void k_rows_repack(const PackLaunch L) {
-    const PackSeg& S = L.seg[blockIdx.y];
-    const uint64_t rows = (uint64_t)L.n_elem * S.rows_per_gate;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    if (S.q == 0) {                     // one-digit rows; the packed segment is padded with zeros to a multiple of 16 bytes
-        const uint64_t padded = (rows + 15) & ~(uint64_t)15;
-        for (uint64_t r = (uint64_t)blockIdx.x * kThreads + threadIdx.x; r < padded; r += (uint64_t)gridDim.x * kThreads) {
-            if (Pack) S.packed[r] = r < rows ? S.rows[r * 4] : 0;
-            else if (r < rows) *(uint32_t*)(const_cast<uint8_t*>(S.rows) + r * 4) = S.packed[r];
+    constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
+    __shared__ uint32_t stage[kThreads / 64][64 * kMaxDw];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    uint32_t* st = stage[wave];
+    auto rows_of = [&](uint32_t i) { return (uint64_t)L.n_elem * L.seg[i].rows_per_gate; };
+    // one-digit rows: 1024 bytes of the packed segment per tile (padded with zeros to a multiple of 16 bytes)
+    auto tiles_of = [&](uint32_t i) { return L.seg[i].q ? (rows_of(i) + 63) / 64 : (rows_of(i) + 1023) / 1024; };
+    uint64_t total = 0;
+    for (uint32_t i = 0; i < L.nseg; i++) total += tiles_of(i);
+    const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64), per = (total + waves - 1) / waves;
+    uint64_t t = ((uint64_t)blockIdx.x * (kThreads / 64) + wave) * per;
+    const uint64_t t_end = t + per < total ? t + per : total;
+    if (t >= t_end) return;
+    uint32_t seg = 0;
+    uint64_t base = 0, next = tiles_of(0);
+    for (; t < t_end; t++) {
+        while (t >= next) { seg++; base = next; next += tiles_of(seg); }
+        const PackSeg& S = L.seg[seg];
+        const uint64_t rows = rows_of(seg);
+        if (S.q == 0) {
+            const uint64_t r0 = (t - base) * 1024 + lane * 16, padded = (rows + 15) & ~(uint64_t)15;
+            for (int k = 0; k < 16 && r0 + k < padded; k++) {
+                const uint64_t r = r0 + k;
+                if (Pack) S.packed[r] = r < rows ? S.rows[r * 4] : 0;
+                else if (r < rows) *(uint32_t*)(const_cast<uint8_t*>(S.rows) + r * 4) = S.packed[r];
+            }
+            continue;
         }
-        return;
-    }
-    for (uint64_t r = (uint64_t)blockIdx.x * kThreads + threadIdx.x; r < rows; r += (uint64_t)gridDim.x * kThreads) {
-        const ModInfo M = L.mods[S.q];
-        uint32_t* row = (uint32_t*)(const_cast<uint8_t*>(S.rows) + r * (M.ndw * 4));
-        if (Pack) {
-            uint32_t colour;
-            const U128 x = compress(M, [&](int i) { return row[i]; }, &colour);
-            *(u32x4*)(S.packed + r * 16) = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
-        } else {
-            const u32x4 v = *(const u32x4*)(S.packed + r * 16);
-            const U128 x = {{v.x, v.y, v.z, v.w}};
-            decompress(M, x, [&](int i, uint32_t w) { row[i] = w; });
-        }
+        const uint64_t r0 = (t - base) * 64;
+        const uint32_t n = rows - r0 < 64 ? (uint32_t)(rows - r0) : 64u;
+        u32x4* packed = (u32x4*)(S.packed + (r0 + lane) * 16);
+        with_mod(ld_mod(L.mods, S.q), [&](auto M) {
+            typedef decltype(M) MD;
+            if constexpr (cmod_m<MD>::value == 2) {
+                uint16_t* bits = (uint16_t*)(S.packed + r0 * 16);
+                u32x4* digits = (u32x4*)(const_cast<uint8_t*>(S.rows) + r0 * 128);
+                uint32_t v16[8];
+                u32x4 v[8];
+#pragma unroll
+                for (uint32_t i = 0; i < 8; i++) {                       // piece i * 64 + lane: row / 8, 16 digits of it
+                    const uint32_t d = i * 64 + lane < n * 8 ? i * 64 + lane : 0;
+                    if (Pack) v[i] = digits[d];
+                    else v16[i] = bits[d];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < 8; i++) {
+                    if (i * 64 + lane >= n * 8) continue;
+                    if (Pack) {
+                        uint32_t w = 0;
+#pragma unroll
+                        for (int q = 0; q < 4; q++) w |= dot4(v[i][q], 0x08040201u) << (4 * q);
+                        bits[i * 64 + lane] = (uint16_t)w;
+                    } else {
+                        u32x4 w;
+#pragma unroll
+                        for (int q = 0; q < 4; q++) w[q] = mul24((v16[i] >> (4 * q)) & 0xfu, 0x00204081u) & kOnes;
+                        digits[i * 64 + lane] = w;
+                    }
+                }
+            } else if constexpr (cmod_m<MD>::value != 0) {
+                constexpr uint32_t ndw = MD::ndw, stride = ndw | 1;      // (odd: a lane's own row without bank conflicts)
+                static_assert(stride <= kMaxDw, "stage");
+                uint32_t* rowbase = (uint32_t*)(const_cast<uint8_t*>(S.rows) + r0 * (ndw * 4));
+                if (Pack) {
+                    uint32_t v[ndw];                                     // all loads before the first wait
+#pragma unroll
+                    for (uint32_t i = 0; i < ndw; i++) v[i] = rowbase[i * 64 + lane < n * ndw ? i * 64 + lane : 0];
+#pragma unroll
+                    for (uint32_t i = 0; i < ndw; i++) {
+                        const uint32_t d = i * 64 + lane;
+                        st[(d / ndw) * stride + d % ndw] = v[i];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < n) {
+                        uint32_t colour;
+                        const U128 x = compress(M, [&](int i) { return st[lane * stride + i]; }, &colour);
+                        *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
+                    }
+                } else {
+                    if (lane < n) {
+                        const u32x4 v = *packed;
+                        decompress(M, U128{{v.x, v.y, v.z, v.w}}, [&](int i, uint32_t w) { st[lane * stride + i] = w; });
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (uint32_t i = 0; i < ndw; i++) {
+                        const uint32_t d = i * 64 + lane;
+                        if (d < n * ndw) rowbase[d] = st[(d / ndw) * stride + d % ndw];
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            } else if (lane < n) {                                       // any other modulus or length: run-time constants, a row per lane
+                uint32_t* row = (uint32_t*)(const_cast<uint8_t*>(S.rows) + (r0 + lane) * (M.ndw * 4));
+                if (Pack) {
+                    uint32_t colour;
+                    const U128 x = compress(M, [&](int i) { return row[i]; }, &colour);
+                    *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
+                } else {
+                    const u32x4 v = *packed;
+                    decompress(M, U128{{v.x, v.y, v.z, v.w}}, [&](int i, uint32_t w) { row[i] = w; });
+                }
+            }
+        });
     }
 }
 
-int launch_pack(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s) {
+int DASH_FN(launch_pack)(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s) {
     static_assert(sizeof(PackLaunch) <= 4096, "kernel argument block");
     if (L.nseg < 1 || L.nseg > (uint32_t)kMaxPackSegs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     L.mods = c->d_mods;
-    uint64_t rows = 0;
-    for (uint32_t i = 0; i < L.nseg; i++) {
-        const uint64_t r = (uint64_t)L.n_elem * L.seg[i].rows_per_gate + 15;      // (+ the padding of a one-digit segment)
-        rows = r > rows ? r : rows;
-    }
-    const uint64_t tiles = (rows + kThreads - 1) / kThreads;
-    dim3 grid(grid_x_for(tiles, (int)L.nseg), L.nseg);
+    uint64_t tiles = 0;
+    for (uint32_t i = 0; i < L.nseg; i++) tiles += ((uint64_t)L.n_elem * L.seg[i].rows_per_gate + 63) / 64;
+    const uint64_t blocks = (tiles + kThreads / 64 - 1) / (kThreads / 64);
+    dim3 grid((uint32_t)(blocks < 4096 ? blocks : 4096));              // seven blocks per CU fit at a time (LDS)
     if (pack) hipLaunchKernelGGL(k_rows_repack<true>, grid, dim3(kThreads), 0, s, L);
     else hipLaunchKernelGGL(k_rows_repack<false>, grid, dim3(kThreads), 0, s, L);
     DASH_HIP(hipGetLastError());
@@ -130,7 +218,7 @@ int launch_pack(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s) {
 template <class QD> struct stage_rows { static constexpr bool value = false; static constexpr int ndw = 1; };
 template <uint32_t MOD, uint32_t LAM> struct stage_rows<CMod<MOD, LAM>> {
     static constexpr int ndw = (LAM + 3) / 4;
-    static constexpr bool value = ndw >= 16 && ndw % 4 == 0;
+    static constexpr bool value = ndw >= 16 && ndw % 16 == 0;
 };
 struct StagedSink {
     uint32_t* st;        // this lane's row in LDS
@@ -266,7 +354,7 @@ static const bool kGarbleStaged[] = {false, DASH_HOT_MODS(DASH_GARBLE_S)};
 #undef DASH_GARBLE_S
 
 
-int launch_garble(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     L.key = c->fixed; L.ttab = c->d_ttab; L.mods = c->d_mods;
     uint64_t rows = 0, tiles_sum = 0;      // rows of the largest job; tiles of all jobs
@@ -310,4 +398,5 @@ int launch_garble(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
     return DASH_OK;
 }
 
+}  // inline namespace
 }  // namespace dash

@@ -7,6 +7,7 @@
 #include "dash_tabs.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // ----------------------------------------------------------------------------- scaling gadget, evaluator
 // cast of the mod-2 residue into every odd prime and the halving, one launch (a gate launch and a free-gate launch
@@ -19,7 +20,7 @@ __global__ __launch_bounds__(kThreads) void k_cast_halve(const CastLaunch L) {
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) cast_halve_body(L, tile, blockIdx.y, threadIdx.x, T);
 }
 
-int launch_cast_halve(const dash_ctx* c, CastLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_cast_halve)(const dash_ctx* c, CastLaunch& L, int njobs, hipStream_t s) {
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
@@ -97,7 +98,7 @@ static int check_cast(const dash_ctx* c, const CastLaunch& L, int njobs, double*
     return DASH_OK;
 }
 
-int launch_cast_digits_eval(const dash_ctx* c, CastLaunch& C, int njobs, DigitsLaunch& L, hipStream_t s) {
+int DASH_FN(launch_cast_digits_eval)(const dash_ctx* c, CastLaunch& C, int njobs, DigitsLaunch& L, hipStream_t s) {
     if (L.n < 1 || L.n > (uint32_t)kMaxChain || L.nres < 1 || L.nres > 16 || (int)L.nres != njobs) return DASH_EINVAL;
     if (C.n_elem != L.n_elem || C.layer != L.layer || C.elem_base != L.elem_base) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
@@ -175,4 +176,5 @@ int launch_cast_digits_eval(const dash_ctx* c, CastLaunch& C, int njobs, DigitsL
     return DASH_OK;
 }
 
+}  // inline namespace
 }  // namespace dash

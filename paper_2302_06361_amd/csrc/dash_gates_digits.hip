@@ -9,6 +9,7 @@
 #include "dash_tabs.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // --------------------------------------------------------------------- digit gates of the sign gadget, garbler
 // One launch for the k n digit gates of a sign gadget: lane = (element, value a) of a residue, which forms and
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(kThreads) void k_digits_garble_wide(const DigitsLau
     }
 }
 
-int launch_digits_garble(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
+int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
     if (L.n < 1 || L.n > (uint32_t)kMaxChain || L.nres < 1 || L.nres > 16) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
@@ -91,4 +92,5 @@ int launch_digits_garble(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
     return DASH_OK;
 }
 
+}  // inline namespace
 }  // namespace dash

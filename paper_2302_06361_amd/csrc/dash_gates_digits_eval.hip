@@ -9,6 +9,7 @@
 #include "dash_tabs.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // ------------------------------------------------------------------- digit gates of the sign gadget, evaluator
 // One launch for the k n digit gates of a sign gadget (four launches of k_proj_eval before), lane = (element,
@@ -50,12 +51,7 @@ __global__ __launch_bounds__(1024) void k_digits_sum_wide(const DigitsLaunch L) 
         if (wave == 0) digits_sum_phase2<MC, M1>(L, blockIdx.x, j, el, acc);
     }
 }
-// whether a wide launch can take that form
-bool digits_sum_wanted(const DigitsLaunch& L, int typed) {
-    return typed != 0 && L.n >= 2 && L.sum1 != nullptr && L.nres * kSumElems <= 1024;
-}
-
-int launch_digits_eval(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
+int DASH_FN(launch_digits_eval)(const dash_ctx* c, DigitsLaunch& L, hipStream_t s) {
     bool uniform = false;
     double bytes = 0;
     const int st = check_digits(c, L, &uniform, &bytes);
@@ -116,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_eval_generic(const ChainLaun
     for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) chain_eval_generic_body(L, tile, threadIdx.x, T);
 }
 
-int launch_chain_eval(const dash_ctx* c, ChainLaunch& L, hipStream_t s) {
+int DASH_FN(launch_chain_eval)(const dash_ctx* c, ChainLaunch& L, hipStream_t s) {
     if (L.n < 2 || L.n > (uint32_t)kMaxChain) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
@@ -145,4 +141,5 @@ int launch_chain_eval(const dash_ctx* c, ChainLaunch& L, hipStream_t s) {
     return DASH_OK;
 }
 
+}  // inline namespace
 }  // namespace dash

@@ -10,6 +10,7 @@
 #include "dash_tabs.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // ------------------------------------------------------------------------------------------ eval
 template <class QD, bool Banked>
@@ -28,7 +29,7 @@ static const GateKernel kEvalKernels[] = {k_proj_eval<ModInfo, false>, DASH_HOT_
 static const GateKernel kEvalKernelsBanked[] = {k_proj_eval<ModInfo, true>, DASH_HOT_MODS(DASH_EVAL_KB)};
 #undef DASH_EVAL_KB
 
-int launch_eval(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_eval)(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s) {
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     L.key = c->fixed; L.ttab = c->d_ttab; L.mods = c->d_mods;
     uint64_t lanes = 0;
@@ -74,13 +75,13 @@ __global__ __launch_bounds__(kThreads) void k_hg_eval_quad(const HgLaunch L) {
 }
 
 // whether launch_hg_eval_quad serves this layer: few elements, every prime with a compile-time description
-bool hg_eval_quad_wanted(const dash_ctx* c, uint32_t n_elem) {
+bool DASH_FN(hg_eval_quad_wanted)(const dash_ctx* c, uint32_t n_elem) {
     if ((uint64_t)n_elem * 4 * c->k > c->quad_max_lanes) return false;
     for (int i = 0; i < c->k; i++) if (!hot_mod_index(c->mods[c->prime[i]])) return false;
     return true;
 }
 
-int launch_hg_eval_quad(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_hg_eval_quad)(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s) {
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     if (L.n_elem > (1u << 26)) return DASH_ESIZE;
@@ -99,7 +100,7 @@ int launch_hg_eval_quad(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s
     return DASH_OK;
 }
 
-int launch_hg_finish(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s) {
+int DASH_FN(launch_hg_finish)(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s) {
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
@@ -110,4 +111,5 @@ int launch_hg_finish(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s) {
     return DASH_OK;
 }
 
+}  // inline namespace
 }  // namespace dash

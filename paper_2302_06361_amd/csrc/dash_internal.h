@@ -81,20 +81,29 @@ namespace dash {
 
 #define DASH_HIP(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) return DASH_EHIP; } while (0)
 
-// launch helpers (dash_gates.hip).  Each checks its own limits and returns a dash status.
-int launch_draw(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s);
-int launch_affine(const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s);
-int launch_garble(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s);
-int launch_eval(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s);
-int launch_chain_eval(const dash_ctx* c, ChainLaunch& L, hipStream_t s);
-int launch_digits_eval(const dash_ctx* c, DigitsLaunch& L, hipStream_t s);
-int launch_digits_garble(const dash_ctx* c, DigitsLaunch& L, hipStream_t s);
-int launch_cast_halve(const dash_ctx* c, CastLaunch& L, int njobs, hipStream_t s);
-int launch_cast_digits_eval(const dash_ctx* c, CastLaunch& C, int njobs, DigitsLaunch& L, hipStream_t s);
-int launch_hg_finish(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s);
-bool digits_sum_wanted(const DigitsLaunch& L, int typed);
-bool hg_eval_quad_wanted(const dash_ctx* c, uint32_t n_elem);
-int launch_hg_eval_quad(const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s);
+// launch helpers (dash_gates*.hip), compiled once per label-length rule; the context's rule picks the one whose moduli are known at
+// compile time.  Each checks its own limits and returns a dash status.
+#define DASH_BY_RULE(ret, name, params, args)                                     \
+    inline namespace ceil_rule { ret name##_ceil params; }                        \
+    inline namespace floor_rule { ret name##_floor params; }                      \
+    inline ret name params { return c->rule == DASH_LAMBDA_FLOOR ? name##_floor args : name##_ceil args; }
+DASH_BY_RULE(int, launch_draw, (const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_affine, (const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_garble, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_eval, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_chain_eval, (const dash_ctx* c, ChainLaunch& L, hipStream_t s), (c, L, s))
+DASH_BY_RULE(int, launch_digits_eval, (const dash_ctx* c, DigitsLaunch& L, hipStream_t s), (c, L, s))
+DASH_BY_RULE(int, launch_digits_garble, (const dash_ctx* c, DigitsLaunch& L, hipStream_t s), (c, L, s))
+DASH_BY_RULE(int, launch_cast_halve, (const dash_ctx* c, CastLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_cast_digits_eval, (const dash_ctx* c, CastLaunch& C, int njobs, DigitsLaunch& L, hipStream_t s), (c, C, njobs, L, s))
+DASH_BY_RULE(int, launch_hg_finish, (const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(bool, hg_eval_quad_wanted, (const dash_ctx* c, uint32_t n_elem), (c, n_elem))
+DASH_BY_RULE(int, launch_hg_eval_quad, (const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_pack, (const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s), (c, L, pack, s))
+// whether a wide launch of the evaluator's digit gates can add up their outputs itself
+inline bool digits_sum_wanted(const DigitsLaunch& L, int typed) {
+    return typed != 0 && L.n >= 2 && L.sum1 != nullptr && L.nres * 64 <= 1024;
+}
 
 // layer pipelines (dash_layers.hip)
 int layer_sizes(const dash_ctx* c, const dash_layer* L, int64_t* out_elems, size_t* table_bytes, size_t* scratch_bytes);
@@ -108,7 +117,6 @@ int proj_layers(dash_ctx* c, bool garble, int n, const dash_layer* Ls, const das
 // packed table format (dash_layers.hip)
 int tables_packed_bytes(const dash_ctx* c, const dash_layer* L, size_t* bytes);
 int tables_repack(dash_ctx* c, const dash_layer* L, bool pack, uint8_t* tables, uint8_t* packed, hipStream_t s);
-int launch_pack(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s);
 
 // linear layers (dash_linear.hip)
 int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels* in, dash_labels* out, hipStream_t s);

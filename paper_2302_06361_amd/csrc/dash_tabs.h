@@ -5,6 +5,7 @@
 #include "dash_internal.h"
 
 namespace dash {
+inline namespace DASH_RULE_NS {
 
 // AES tables in LDS, two layouts.
 //
@@ -125,4 +126,5 @@ inline int typed_digits(const dash_ctx* c, const DigitsLaunch& L, bool uniform) 
     return uniform ? digit_set_index(c->mods[L.m[L.n >= 2 ? 2 : 1]], c->mods[L.m[1]]) : 0;
 }
 
+}  // inline namespace
 }  // namespace dash
