@@ -9,9 +9,12 @@ CSRC = os.path.join(HERE, "csrc")
 SO = os.path.join(HERE, "libdash.so")
 GATE_SOURCES = ["dash_gates_cast.hip", "dash_gates.hip", "dash_gates_eval.hip", "dash_gates_digits_eval.hip", "dash_gates_digits.hip"]
 SOURCES = ["dash_ctx.hip", "dash_layers.hip", "dash_linear.hip", "dash_gemm.hip", "dash_aesprof.hip"]
-# (source, extra flags, object): the gate kernels once per label-length rule, the longest first
-UNITS = ([(s, [], s.replace(".hip", ".o")) for s in GATE_SOURCES] + [(s, ["-DDASH_RULE_FLOOR"], s.replace(".hip", "_floor.o")) for s in GATE_SOURCES] +
-         [(s, [], s.replace(".hip", ".o")) for s in SOURCES])
+# (source, extra flags, object): the gate kernels once per label-length rule, the evaluator's whole layers also once per digit set
+UNITS = []
+for _rule, _flags in (("", []), ("_floor", ["-DDASH_RULE_FLOOR"])):
+    UNITS += [(s, _flags, s.replace(".hip", _rule + ".o")) for s in GATE_SOURCES]
+    UNITS += [("dash_act_eval.hip", _flags + ["-DDASH_SET=%d" % k], "dash_act_eval_%d%s.o" % (k, _rule)) for k in (12, 9, 8, 7)]
+UNITS += [(s, [], s.replace(".hip", ".o")) for s in SOURCES]
 HEADERS = ["dash_core.h", "dash_launch.h", "dash_bodies.h", "dash_hostconst.h", "dash_internal.h", "dash_tabs.h", "dash_aes_sliced.h", "dash_sbox_circuit.h", os.path.join("..", "..", "include", "dash.h"),
            os.path.join("..", "..", "include", "dash_profile.h")]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-Wno-pass-failed",

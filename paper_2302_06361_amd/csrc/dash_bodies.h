@@ -200,7 +200,7 @@ DASH_HD void eval_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t t
 // goes dword by dword to out.
 // QUAD: the four lanes of a quad work on the same element and share the AES (hash_block_quad).
 template <bool QUAD = false, class MI, class MO, class Tab, class In, class Out>
-DASH_HD void chain_gate(const ChainLaunch& L, const MI& Mi, const MO& Mo, uint32_t e, int j, In in_dw, Out out, const Tab& T) {
+DASH_HD void chain_gate(const ChainLaunch& L, const MI& Mi, const MO& Mo, uint32_t e, int j, In in_dw, Out out, const Tab& T, const QuadKey& Q = QuadKey{}) {
     uint32_t colour = in_dw(0) & 0xffu;       // the row's loads go out before the hash
     const uint32_t* row = (const uint32_t*)(L.table[j] + ((size_t)e * Mi.m + colour) * (Mo.ndw * 4));
     uint32_t rw[cmod_ndw<MO>::value];
@@ -209,7 +209,7 @@ DASH_HD void chain_gate(const ChainLaunch& L, const MI& Mi, const MO& Mo, uint32
         for (int i = 0; i < (int)MO::ndw; i++) rw[i] = row[i];
     }
     U128 K = compress(Mi, in_dw, &colour);
-    U128 h = QUAD ? hash_block_quad(K, L.elem_base + e, L.slot[j], L.layer, L.key.rk, T)
+    U128 h = QUAD ? hash_block_quad(K, L.elem_base + e, L.slot[j], L.layer, Q, L.key.rk, T)
                   : hash_block(K, L.elem_base + e, L.slot[j], L.layer, L.key.rk, T);
     if constexpr (cmod_m<MO>::value != 0) {
         decompress(Mo, h, [&](int i, uint32_t hd) { out(i, submod4(rw[i], hd, Mo)); });
@@ -235,6 +235,7 @@ DASH_HD void chain_eval_body(const ChainLaunch& L, uint32_t bx, uint32_t tx, con
     const uint32_t e = QUAD ? lane >> 2 : lane;
     const bool writer = !QUAD || (lane & 3u) == 0;
     if (e >= L.n_elem) return;
+    const QuadKey Q = QUAD ? quad_key(L.key.rk, lane & 3u) : QuadKey{};
     const MC Mc{nullptr};
     const M1 Mf{nullptr};
     const CMod<2, 128> M2{nullptr};
@@ -253,7 +254,7 @@ DASH_HD void chain_eval_body(const ChainLaunch& L, uint32_t bx, uint32_t tx, con
         for (int i = 0; i < (int)MC::ndw; i++) in[i] = addmod4(sm[i], cw[i], Mc);   // cw = 0 at j = n
 #pragma unroll
         for (int i = 0; i < (int)MC::ndw; i++) sm[i] = ld_dw(L.sum[j - 1], e, i);
-        chain_gate<QUAD>(L, Mc, Mc, e, j, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { cw[i] = w; }, T);
+        chain_gate<QUAD>(L, Mc, Mc, e, j, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { cw[i] = w; }, T, Q);
     }
     {                                               // digit 2 -> carry into digit 1 (modulus of the first digit)
         uint32_t in[MC::ndw];
@@ -261,14 +262,14 @@ DASH_HD void chain_eval_body(const ChainLaunch& L, uint32_t bx, uint32_t tx, con
         for (int i = 0; i < (int)MC::ndw; i++) in[i] = addmod4(sm[i], cw[i], Mc);
 #pragma unroll
         for (int i = 0; i < (int)M1::ndw; i++) s1[i] = ld_dw(L.sum[1], e, i);
-        chain_gate<QUAD>(L, Mc, Mf, e, 2, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { c1[i] = w; }, T);
+        chain_gate<QUAD>(L, Mc, Mf, e, 2, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { c1[i] = w; }, T, Q);
     }
     {                                               // final gate: digit 1 -> the sign bit
         uint32_t in[M1::ndw];
 #pragma unroll
         for (int i = 0; i < (int)M1::ndw; i++) in[i] = addmod4(s1[i], c1[i], Mf);
         Dw4 bits[8];                                // the 128 digits of the output wire: stored 16 bytes at a time
-        chain_gate<QUAD>(L, Mf, M2, e, 1, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { bits[i >> 2].w[i & 3] = w; }, T);
+        chain_gate<QUAD>(L, Mf, M2, e, 1, [&](int i) { return in[i]; }, [&](int i, uint32_t w) { bits[i >> 2].w[i & 3] = w; }, T, Q);
         if (!writer) return;
 #pragma unroll
         for (int ch = 0; ch < 8; ch++) st_chunk(L.bit, e, ch, bits[ch]);

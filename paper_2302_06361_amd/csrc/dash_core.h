@@ -69,6 +69,8 @@ constexpr bool gd_ok(uint32_t m, uint32_t g) {
 constexpr uint32_t gd_of(uint32_t m) { uint32_t g = 1; while (gd_ok(m, g + 1)) g++; return g; }
 // label length of modulus m under the ceil rule: smallest lam with m^lam >= 2^128
 constexpr uint32_t lam_ceil(uint32_t m) { uint32_t l = 0; for (unsigned __int128 v = ~(unsigned __int128)0; v; v /= m) l++; return l; }
+// ... and under the floor rule (largest lam with m^lam <= 2^128)
+constexpr uint32_t lam_of(uint32_t m, bool floor_rule) { return lam_ceil(m) - (floor_rule && (m & (m - 1)) != 0 ? 1u : 0u); }
 
 // ---- constants of the base conversion (decompress), see there
 struct Big { uint32_t w[10]; };      // 320-bit number
@@ -422,26 +424,40 @@ DASH_HD void aes128_encrypt(uint32_t s[4], const uint32_t* rk, const Tab& T) {
 // quad permutes and does 4 look-ups instead of 16: a third of the instructions per lane, for kernels whose run time is
 // the chain of one lane (few elements).  The four lanes must be active together.  (Host build: each caller encrypts
 // on its own.)
+// Q: the lane's words of the key schedule, k[r] = rk[4 r + c] (rotated keys for tables that want them).  (Picking them per round with selects from the whole schedule
+// was turned into branches around scalar loads: 2.0 instead of 1.1 us per gate of a carry chain.)
+struct QuadKey { uint32_t k[11]; };
+DASH_HD QuadKey quad_key(const uint32_t* rk, uint32_t c) {
+    QuadKey Q;
+#pragma unroll
+    for (int r = 0; r < 11; r++) Q.k[r] = rk[4 * r + c];
+    return Q;
+}
+// bytes 0 and 1 of the last round's column, four tables (S[x] in byte 0 of T2 and byte 1 of T3)
 template <class Tab>
-DASH_HD void aes128_encrypt_quad(uint32_t s[4], const uint32_t* rk, const Tab& T) {
+DASH_HD uint32_t last_low(uint32_t a0, uint32_t a1, const Tab& T) {
+    if constexpr (!tab_two<Tab>::value) return (T.template at<2, 0>(a0) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u);
+    else return 0;
+}
+template <class Tab>
+DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t* rk, const Tab& T) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const uint32_t c = __lane_id() & 3u;
-    auto pick = [&](uint32_t k0, uint32_t k1, uint32_t k2, uint32_t k3) { return c == 0 ? k0 : c == 1 ? k1 : c == 2 ? k2 : k3; };
     // value of the lane 1, 2, 3 places up in the quad (cyclic), and of lane i of the quad
     auto up1 = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x39, 0xf, 0xf, true); };    // quad_perm:[1,2,3,0]
     auto up2 = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true); };    // quad_perm:[2,3,0,1]
     auto up3 = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x93, 0xf, 0xf, true); };    // quad_perm:[3,0,1,2]
-    uint32_t a = pick(s[0], s[1], s[2], s[3]) ^ pick(rk[0], rk[1], rk[2], rk[3]);
+    const uint32_t s01 = c & 1u ? s[1] : s[0], s23 = c & 1u ? s[3] : s[2];
+    uint32_t a = (c & 2u ? s23 : s01) ^ Q.k[0];
 #pragma unroll
     for (int r = 1; r < 10; r++) {
         const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
-        a = xor3(xor3(T.template at<0, 0>(a), T.template at<1, 1>(a1), T.template at<2, 2>(a2)), T.template at<3, 3>(a3),
-                 pick(rk[4 * r], rk[4 * r + 1], rk[4 * r + 2], rk[4 * r + 3]));
+        a = aes_column(a, a1, a2, a3, Q.k[r], T);
     }
     {
         const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
-        a = ((T.template at<2, 0>(a) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) |
-             (T.template at<1, 3>(a3) & 0xff000000u)) ^ pick(rk[40], rk[41], rk[42], rk[43]);
+        const uint32_t low = tab_two<Tab>::value ? (T.template at<0, 0>(a) >> 8 & 0xffu) | (T.template at<0, 1>(a1) & 0xff00u) : last_low(a, a1, T);
+        a = (low | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ Q.k[10];
     }
     s[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x00, 0xf, 0xf, true);      // quad_perm:[0,0,0,0]
     s[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x55, 0xf, 0xf, true);
@@ -516,10 +532,10 @@ DASH_HD U128 slot_hash(const SlotHash& S, uint32_t slot, const uint32_t* rk, con
 }
 // the same by the four lanes of a quad together (aes128_encrypt_quad): same arguments and same result in all four
 template <class Tab>
-DASH_HD U128 hash_block_quad(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const uint32_t* rk, const Tab& T) {
+DASH_HD U128 hash_block_quad(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const QuadKey& Q, const uint32_t* rk, const Tab& T) {
     uint32_t x[4] = {K.w[0] ^ (uint32_t)elem, K.w[1] ^ (uint32_t)(elem >> 32), K.w[2] ^ slot, K.w[3] ^ (layer & 0xffffu)};
     uint32_t s[4] = {x[0], x[1], x[2], x[3]};
-    aes128_encrypt_quad(s, rk, T);
+    aes128_encrypt_quad(s, Q, rk, T);
     U128 h = {{s[0] ^ x[0], s[1] ^ x[1], s[2] ^ x[2], s[3] ^ x[3]}};
     return h;
 }
@@ -742,21 +758,26 @@ DASH_HD uint32_t mod_u128(const U128& h, const MI& M) {
 // their label lengths under one of the two rules.  The gate sources are compiled once per rule (DASH_RULE_FLOOR: the floor rule, else
 // the ceil rule), each in an inline namespace of its own; the launch functions carry the rule in their name (DASH_FN) and are picked
 // by the context's rule (dash_internal.h).
+#define DASH_PASTE2(a, b) a##b
+#define DASH_PASTE(a, b) DASH_PASTE2(a, b)
 #if defined(DASH_RULE_FLOOR)
 #define DASH_RULE_NS floor_rule
-#define DASH_FN(name) name##_floor
+#define DASH_RULE_IS_FLOOR true
+#define DASH_FN(name) DASH_PASTE(name, _floor)
 #define DASH_HOT_MODS(X) \
     X(2, 128) X(3, 80) X(5, 55) X(7, 45) X(11, 37) X(13, 34) X(17, 31) X(19, 30) X(23, 28) X(29, 26) X(31, 25) X(37, 24) \
     X(26, 27) X(96, 19) X(46, 23) X(204, 16) X(10, 38) X(91, 19) X(22, 28) X(90, 19)
 #else
 #define DASH_RULE_NS ceil_rule
-#define DASH_FN(name) name##_ceil
+#define DASH_RULE_IS_FLOOR false
+#define DASH_FN(name) DASH_PASTE(name, _ceil)
 #define DASH_HOT_MODS(X) \
     X(2, 128) X(3, 81) X(5, 56) X(7, 46) X(11, 38) X(13, 35) X(17, 32) X(19, 31) X(23, 29) X(29, 27) X(31, 26) X(37, 25) \
     X(26, 28) X(96, 20) X(46, 24) X(204, 17) X(10, 39) X(91, 20) X(22, 29) X(90, 20)
 #endif
 
 inline namespace DASH_RULE_NS {
+constexpr bool kFloorRule = DASH_RULE_IS_FLOOR;
 // f(description of M): compile-time description for the hot moduli, run-time otherwise
 template <class F>
 DASH_HD void with_mod(const ModInfo& M, F&& f) {

@@ -239,6 +239,14 @@ int dash_ctx_create(dash_ctx** out, const uint16_t* primes, int k, int lambda_ru
     if (const char* e = getenv("DASH_WIDE_MAX_LANES")) c->wide_max_lanes = strtoull(e, nullptr, 10);                 // tuning and test hook
     c->sum_in_launch = 1;
     if (const char* e = getenv("DASH_SUM_IN_LAUNCH")) c->sum_in_launch = atoi(e) != 0;                               // tuning and test hook
+    // tuning and test hook; the variables of the step-by-step path select that path as well
+    c->act_eval = 1;
+    for (const char* v : {"DASH_FUSED_MIN_ELEMS_EVAL", "DASH_WIDE_MAX_LANES", "DASH_SUM_IN_LAUNCH", "DASH_QUAD_MAX_LANES"}) if (getenv(v)) c->act_eval = 0;
+    if (const char* e = getenv("DASH_ACT_EVAL")) c->act_eval = atoi(e) != 0;
+    c->act_deep_min_elems = 6144;
+    c->act_shallow_min_elems = ~0ull;      // (the size of a tiny launch decides)
+    if (const char* e = getenv("DASH_ACT_SHALLOW_MIN_ELEMS")) c->act_shallow_min_elems = strtoull(e, nullptr, 10);   // tuning and test hook
+    if (const char* e = getenv("DASH_ACT_DEEP_MIN_ELEMS")) c->act_deep_min_elems = strtoull(e, nullptr, 10);         // tuning and test hook
     c->quad_max_lanes = 1u << 18;
     if (const char* e = getenv("DASH_QUAD_MAX_LANES")) c->quad_max_lanes = strtoull(e, nullptr, 10);                 // tuning and test hook
     c->few_rows_max = 1u << 20;

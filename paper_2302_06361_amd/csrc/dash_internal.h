@@ -69,6 +69,8 @@ struct dash_ctx {
     uint64_t wide_max_lanes;         // evaluator: sign gadgets of at most this many digit gates run them one per lane
     int sum_in_launch;               // evaluator: digit gates of few elements add up their outputs in their own launch (1) or leave
                                      // it to a free-gate launch (0)
+    int act_eval;                    // evaluator: ReLU and scaling layers in one launch (dash_act_eval.hip) where it applies (1), or step by step (0)
+    uint64_t act_shallow_min_elems, act_deep_min_elems;     // ... smallest layers of its shallow and deep forms
     uint64_t quad_max_lanes;         // evaluator: carry chains of at most this many lanes (4 per element) run four lanes per element
     uint64_t few_rows_max;           // garbler: launches of at most this many rows take the forms for few rows (a lane per row of the
                                      // digit gates; gates of different output moduli in one launch)
@@ -100,6 +102,11 @@ DASH_BY_RULE(int, launch_hg_finish, (const dash_ctx* c, HgLaunch& L, int njobs, 
 DASH_BY_RULE(bool, hg_eval_quad_wanted, (const dash_ctx* c, uint32_t n_elem), (c, n_elem))
 DASH_BY_RULE(int, launch_hg_eval_quad, (const dash_ctx* c, HgLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 DASH_BY_RULE(int, launch_pack, (const dash_ctx* c, PackLaunch& L, bool pack, hipStream_t s), (c, L, pack, s))
+// whole activation layers (dash_act_eval.hip), by digit set (number of primes)
+DASH_BY_RULE(int, launch_act_eval_7, (const dash_ctx* c, ActLaunch& L, bool relu, hipStream_t s), (c, L, relu, s))
+DASH_BY_RULE(int, launch_act_eval_8, (const dash_ctx* c, ActLaunch& L, bool relu, hipStream_t s), (c, L, relu, s))
+DASH_BY_RULE(int, launch_act_eval_9, (const dash_ctx* c, ActLaunch& L, bool relu, hipStream_t s), (c, L, relu, s))
+DASH_BY_RULE(int, launch_act_eval_12, (const dash_ctx* c, ActLaunch& L, bool relu, hipStream_t s), (c, L, relu, s))
 // whether a wide launch of the evaluator's digit gates can add up their outputs itself
 inline bool digits_sum_wanted(const DigitsLaunch& L, int typed) {
     return typed != 0 && L.n >= 2 && L.sum1 != nullptr && L.nres * 64 <= 1024;

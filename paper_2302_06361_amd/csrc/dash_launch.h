@@ -195,5 +195,29 @@ struct DigitsLaunch {
     DigitsRes res[16];
 };
 
-}  // namespace dash
+enum { ACT_TINY, ACT_SHALLOW, ACT_DEEP };      // forms of k_act_eval
+// evaluator, a whole ReLU or scaling layer (dash_act_eval.hip).  Tables and slots are those of the first repetition; each further one
+// is rep_bytes and rep_slots on (a ReLU is one repetition).
+struct ActRes {
+    uint32_t p, digit_slot;       // residue; slot of the gate to digit 1
+    const uint8_t* digit_table;   // segment of that gate
+    LView in, out;
+    // ReLU: half gates with slots hg_slot, + 1, + 2.  Scaling: cast gate, and the ShiftDown constant as an active label
+    const uint8_t *g_table, *e_table, *s_table, *cast_table, *shift;
+    uint32_t hg_slot, cast_slot;
+};
+struct ActLaunch {
+    AesKey key, key_rot;                  // key_rot: for the bank-replicated tables (rotate_round_keys)
+    const uint32_t* ttab;
+    const ModInfo* mods;
+    uint64_t elem_base, rep_bytes;
+    uint32_t layer, n_elem, n, repeat, rep_slots;
+    uint32_t chain_slot;                  // slot of the carry gate out of digit 2; digit j: + j - 2; final gate: + n - 1
+    uint32_t up_coef, last_coef;          // scaling: whether the next repetition's mod-2 wire, the layer's output, is the bit + 1
+    const uint8_t* chain_table[kMaxChain + 1];
+    LView in2, out2;                      // scaling: the mod-2 residue
+    const uint8_t* one2;                  // scaling: active label of the constant-one wire of modulus 2
+    ActRes res[16];                       // ReLU: all residues; scaling: the odd ones
+};
 
+}  // namespace dash

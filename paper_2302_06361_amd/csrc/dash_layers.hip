@@ -347,6 +347,69 @@ int check_bundle(const dash_ctx* c, const dash_labels* t, int64_t n) {
     return DASH_OK;
 }
 
+// ---- evaluator: a whole ReLU or scaling layer in one launch --------------------------------------
+// The digit set whose kernel in dash_act_eval.hip serves the context (number of primes), 0 if none: one of the default digit sets
+// (or a shorter one with the same moduli), over the first primes, with the label lengths of the context's rule.
+int act_set(const dash_ctx* c) {
+    if (!c->act_eval || c->n < 2) return 0;
+    struct Set { int k, mc, m1; };
+    static const Set sets[] = {{7, 91, 10}, {8, 96, 26}, {9, 90, 22}, {12, 204, 46}};
+    static const int primes[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
+    auto by_rule = [&](int m) { return c->mods[m].lam == cm::lam_of((uint32_t)m, c->rule == DASH_LAMBDA_FLOOR); };
+    for (const Set& s : sets) {
+        if (c->k != s.k || c->mj[1] != s.m1) continue;
+        bool ok = by_rule(s.m1) && by_rule(s.mc);
+        for (int j = 2; j <= c->n; j++) ok = ok && c->mj[j] == s.mc;
+        for (int i = 0; i < c->k; i++) ok = ok && c->prime[i] == primes[i] && by_rule(primes[i]);
+        if (ok) return s.k;
+    }
+    return 0;
+}
+
+int launch_act_eval(const dash_ctx* c, int set, ActLaunch& L, bool relu, hipStream_t s) {
+    if (L.n_elem == 0) return DASH_OK;
+    if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
+    L.key = c->fixed; L.key_rot = c->fixed_rot; L.ttab = c->d_ttab; L.mods = c->d_mods;
+    double units = 0, bytes = 0;
+    const int res = relu ? c->k : c->k - 1;
+    for (int i = c->k - res; i < c->k; i++) {
+        const double lp = c->mods[c->prime[i]].lam;
+        bytes += relu ? 5 * lp + 260 : 128 + 2 * lp;
+        units += c->n + (relu ? 2 : 1);
+        for (int j = 1; j <= c->n; j++) bytes += lp + 2.0 * c->mods[c->mj[j]].lam;
+    }
+    for (int j = 1; j <= c->n; j++) bytes += c->mods[c->mj[j]].lam + (j >= 2 ? c->mods[c->mj[j - 1]].lam : 128);
+    units += c->n;
+    const double m = (double)L.n_elem * L.repeat;
+    ProfScope ps(c->prof, DASH_PROF_EVAL, s, m * units, m * bytes);
+    switch (set) {
+        case 7: return launch_act_eval_7(c, L, relu, s);
+        case 8: return launch_act_eval_8(c, L, relu, s);
+        case 9: return launch_act_eval_9(c, L, relu, s);
+        case 12: return launch_act_eval_12(c, L, relu, s);
+    }
+    return DASH_EUNSUPPORTED;
+}
+
+// the sign gadget's part of the launch: its digit and carry gates, the gadget's tables starting at seg
+void act_sign(const dash_ctx* c, ActLaunch& L, uint32_t E, uint8_t* seg, int first_res, uint32_t slot_base) {
+    const int k = c->k, n = c->n;
+    size_t cum = 0;
+    L.n = (uint32_t)n;
+    L.chain_slot = slot_base + (uint32_t)(k * n);
+    for (int sl = 0; sl < sign_nslots(c); sl++) {
+        uint8_t* at = seg + cum * E;
+        if (sl < k * n) {
+            if (sl % n == 0 && sl / n >= first_res) {
+                L.res[sl / n - first_res].digit_table = at;
+                L.res[sl / n - first_res].digit_slot = slot_base + (uint32_t)sl;
+            }
+        } else if (sl < k * n + n - 1) L.chain_table[sl - k * n + 2] = at;
+        else L.chain_table[1] = at;
+        cum += sign_slot_bytes(c, sl, first_res);
+    }
+}
+
 // ---- ReLU ------------------------------------------------------------------------------------
 struct ReluPlan { SignWires w; LView U[DASH_MAX_PRIMES], V[DASH_MAX_PRIMES]; uint8_t* r[DASH_MAX_PRIMES]; };
 void plan_relu(const dash_ctx* c, Arena& ar, int64_t E, ReluPlan& p) {
@@ -422,6 +485,18 @@ int relu_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels*
         product(ab);
         ab.flush();
         return ab.status;
+    }
+    if (const int set = act_set(c)) {
+        ActLaunch A;
+        memset(&A, 0, sizeof(A));
+        A.elem_base = eb; A.layer = layer; A.n_elem = E; A.repeat = 1;
+        for (int i = 0; i < k; i++) {
+            ActRes& R = A.res[i];
+            R.p = (uint32_t)c->prime[i]; R.in = x[i]; R.out = view_of(out, i);
+            R.g_table = G[i]; R.e_table = Eh[i]; R.s_table = S[i]; R.hg_slot = (uint32_t)(ns + 3 * i);
+        }
+        act_sign(c, A, E, tables, 0, 0);
+        return launch_act_eval(c, set, A, true, s);
     }
     int st = sign_core(c, false, E, layer, eb, x, 0, 1, 0, tables, pl.w, s);
     if (st) return st;
@@ -514,6 +589,23 @@ int scale_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels
         ab.add(2, pl.up, t, 2);
     };
     if (!garble) {
+        if (const int set = act_set(c)) {
+            ActLaunch A;
+            memset(&A, 0, sizeof(A));
+            A.elem_base = eb; A.layer = layer; A.n_elem = E; A.repeat = (uint32_t)L->repeat;
+            A.rep_bytes = (uint64_t)bpe * E; A.rep_slots = slots_per_rep;
+            A.in2 = x[0]; A.out2 = view_of(out, 0); A.one2 = c->d_one[0];
+            A.up_coef = (c0 + 1) % 2; A.last_coef = c0;
+            size_t cum = 0;
+            for (int i = 1; i < k; i++) {
+                ActRes& R = A.res[i - 1];
+                R.p = (uint32_t)c->prime[i]; R.in = x[i]; R.out = view_of(out, i);
+                R.cast_table = tables + cum * E; R.cast_slot = (uint32_t)(i - 1); R.shift = c->d_shift[i];
+                cum += 2 * pitch_of(c, c->prime[i]);
+            }
+            act_sign(c, A, E, tables + cum * E, 1, (uint32_t)(k - 1));
+            return launch_act_eval(c, set, A, false, s);
+        }
         AffineBatcher ab(c, E, s);
         shift_up(ab);
         ab.flush();
