@@ -107,7 +107,7 @@ typedef struct {
  * Draws the offset label R_m of every modulus in use (colour digit forced to 1) and the
  * constant-one wire of every prime.  Allocates a few hundred KB of device memory.  Tuning variables of
  * the environment (DASH_BANKED_MIN_LANES, DASH_DIGITS_BANKED_MIN_LANES, DASH_FUSED_MIN_ELEMS_GARBLE,
- * DASH_FUSED_MIN_ELEMS_EVAL, DASH_GEMM_TILE, DASH_ACT_EVAL, DASH_ACT_SHALLOW_MIN_ELEMS,
+ * DASH_FUSED_MIN_ELEMS_EVAL, DASH_GEMM_TILE, DASH_LINEAR_FORM, DASH_ACT_EVAL, DASH_ACT_SHALLOW_MIN_ELEMS,
  * DASH_ACT_DEEP_MIN_ELEMS) are read here, once per context, and nowhere else.
  * Errors: DASH_EINVAL (NULL, non-prime or repeated modulus, bad digits or lambda), DASH_ESIZE (product
  * of the primes too large), DASH_EUNSUPPORTED (no digit set found), DASH_EHIP. */

@@ -6,7 +6,8 @@
 // The garbler applies it to zero labels, the evaluator to active labels; the arithmetic is the same.
 //
 //   k_weights_prepare : int32 weights -> per-prime int8 residues in [0, p), rows padded to 64
-//   k_linear_direct   : any shape; one lane per (output value, 16-digit chunk)
+//   k_linear_tile     : any shape; one lane per (output pixel, 16-digit chunk) and CO output channels
+//   k_linear_split    : few outputs and a long reduction; one wave per (output pixel, 16-digit chunk) and CO output channels
 //   (dense layers that fill MFMA tiles go to k_dense_mfma in dash_gemm.hip)
 //   k_sumpool         : 2x2 sum, stride 2
 #include <string.h>
@@ -55,96 +56,168 @@ struct LinArgs {
     LinPrime pr[DASH_MAX_PRIMES];
 };
 
-// S lanes per (output value, chunk): 16 accumulators, one 16-byte label word per tap; blockIdx.y = prime.  S = 1 for
-// layers with enough outputs to fill the chip; S = 16 for layers with few (the last dense layers of a network at
-// batch 1): the reduction index is dealt out in groups of four to 16 neighbouring lanes, whose partial sums are
-// added up with lane shuffles, so that a lane's loop is 16 times shorter.
-template <int S>
-__global__ __launch_bounds__(kThreads) void k_linear_direct(const LinArgs AA) {
-    struct { uint32_t p; const int8_t* w; const int32_t* bias; const uint8_t* one; LView in, out; int64_t kpad;
-             int batch, in_h, in_w, in_c, out_c, kh, kw, stride, pad, out_h, out_w; } A;
-    {
-        const LinPrime& P = AA.pr[blockIdx.y];
-        A.p = P.p; A.w = P.w; A.bias = AA.bias; A.one = P.one; A.in = P.in; A.out = P.out; A.kpad = AA.kpad;
-        A.batch = AA.batch; A.in_h = AA.in_h; A.in_w = AA.in_w; A.in_c = AA.in_c; A.out_c = AA.out_c; A.kh = AA.kh; A.kw = AA.kw;
-        A.stride = AA.stride; A.pad = AA.pad; A.out_h = AA.out_h; A.out_w = AA.out_w;
+// Four consecutive entries k0 .. k0 + 3 of the reduction index against CO weight rows: the four 16-byte label words are turned around
+// with byte permutes, so that a dword holds one digit of the four taps, and one byte dot product takes the four weights of an output.
+// The permutes (32) and the loads are shared by the CO outputs, 16 dot products each.
+template <int CO>
+__device__ __forceinline__ void dot_group(const uint4* v, const uint32_t* w4, uint32_t acc[CO][16]) {
+    const uint32_t vq[4][4] = {{v[0].x, v[1].x, v[2].x, v[3].x}, {v[0].y, v[1].y, v[2].y, v[3].y}, {v[0].z, v[1].z, v[2].z, v[3].z}, {v[0].w, v[1].w, v[2].w, v[3].w}};
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        // v_perm_b32(hi, lo, sel): byte i of the result = byte sel.i of the 8 bytes {hi:lo}
+        const uint32_t ab02 = __builtin_amdgcn_perm(vq[q][1], vq[q][0], 0x06020400u), ab13 = __builtin_amdgcn_perm(vq[q][1], vq[q][0], 0x07030501u);
+        const uint32_t cd02 = __builtin_amdgcn_perm(vq[q][3], vq[q][2], 0x06020400u), cd13 = __builtin_amdgcn_perm(vq[q][3], vq[q][2], 0x07030501u);
+        const uint32_t d0 = __builtin_amdgcn_perm(cd02, ab02, 0x05040100u), d1 = __builtin_amdgcn_perm(cd13, ab13, 0x05040100u);
+        const uint32_t d2 = __builtin_amdgcn_perm(cd02, ab02, 0x07060302u), d3 = __builtin_amdgcn_perm(cd13, ab13, 0x07060302u);
+#pragma unroll
+        for (int c = 0; c < CO; c++) {
+            acc[c][4 * q + 0] = __builtin_amdgcn_udot4(d0, w4[c], acc[c][4 * q + 0], false);
+            acc[c][4 * q + 1] = __builtin_amdgcn_udot4(d1, w4[c], acc[c][4 * q + 1], false);
+            acc[c][4 * q + 2] = __builtin_amdgcn_udot4(d2, w4[c], acc[c][4 * q + 2], false);
+            acc[c][4 * q + 3] = __builtin_amdgcn_udot4(d3, w4[c], acc[c][4 * q + 3], false);
+        }
     }
-    const ModInfo M = AA.mods[A.p];
-    const int64_t n_out = (int64_t)A.batch * A.out_h * A.out_w * A.out_c;
-    const int64_t gl = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t idx = gl / S;
-    const int sl = (int)(gl % S);                       // this lane's share of the reduction index
-    if (idx >= n_out * M.nchunk) return;                // (the S lanes of an output leave together)
-    const uint32_t ch = (uint32_t)(idx / n_out);
-    const int64_t o = idx - (int64_t)ch * n_out;
-    int co = (int)(o % A.out_c);
-    int64_t t = o / A.out_c;
-    int ox = (int)(t % A.out_w); t /= A.out_w;
-    int oy = (int)(t % A.out_h);
-    int b = (int)(t / A.out_h);
-    uint32_t acc[16];
-    for (int d = 0; d < 16; d++) acc[d] = 0;
-    const int8_t* wrow = A.w + (int64_t)co * A.kpad;
-    const uint8_t* inc = A.in.p + (int64_t)ch * A.in.cs;
-    // The reduction index k = (ky * kw + kx) * in_c + ci runs in groups of four (the weight rows are padded with zeros to a
-    // multiple of 64): four 16-byte label words, their 4 x 4 byte blocks turned around with byte permutes so that a dword
-    // holds one digit of the four taps, then one byte dot product with the four weights per digit (48 instructions per
-    // four taps instead of 128 with a multiply-add per byte).
+}
+// an accumulator ((p-1)^2 K < 2^31 is checked on the host) mod p, in two steps so that the magic division applies (n < 2^24)
+__device__ __forceinline__ uint32_t reduce_acc(uint32_t a, const ModInfo& M) { return mod_m(mod_m(a >> 12, M) * (4096u % M.m) + (a & 4095u), M); }
+__device__ __forceinline__ uint32_t bias_of(const int32_t* bias, int co, const ModInfo& M) {
+    if (!bias) return 0;
+    const int32_t r = bias[co] % (int32_t)M.m;
+    return (uint32_t)(r < 0 ? r + (int32_t)M.m : r);
+}
+
+// One lane per (output pixel, chunk), CO output channels; blockIdx.y = prime, blockIdx.z = block of CO channels.  The taps are the same
+// for all lanes: their offsets, the weights and the loop run on the scalar unit.  Bound by vector issue: 32 permutes and 16 CO dot
+// products per four taps.  (One lane per output value repeated loads, permutes and 64-bit address arithmetic for every channel:
+// 6 -> 16 channels, 5 x 5, 14 x 14, batch 16, 8 primes: 131 us; CO = 8: 49 us.)
+template <int CO>
+__global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
+    const LinPrime& P = A.pr[blockIdx.y];
+    const ModInfo M = ld_mod(A.mods, P.p);
+    const uint32_t n_px = (uint32_t)A.batch * A.out_h * A.out_w;
+    const uint64_t idx = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (idx >= (uint64_t)n_px * M.nchunk) return;
+    const uint32_t ch = (uint32_t)(idx / n_px), px = (uint32_t)(idx - (uint64_t)ch * n_px);
+    const uint32_t row = px / (uint32_t)A.out_w, ox = px - row * A.out_w, b = row / (uint32_t)A.out_h, oy = row - b * A.out_h;
+    const int iy0 = (int)oy * A.stride - A.pad, ix0 = (int)ox * A.stride - A.pad;
+    const int base = (((int)b * A.in_h + iy0) * A.in_w + ix0) * A.in_c;      // (below 2^31; may be negative before the tap is added)
+    const uint8_t* inc = P.in.p + (int64_t)ch * P.in.cs;
+    const int co0 = blockIdx.z * CO;
+    const int8_t* wrow = P.w + (int64_t)co0 * A.kpad;                       // rows past out_c are there (padded to 32) and zero
+    typedef const __attribute__((address_space(4))) uint32_t* sptr;         // weights are wave-uniform and not written by the kernel: scalar loads
+    uint32_t acc[CO][16] = {};
     const int K = A.kh * A.kw * A.in_c;
     int ky = 0, kx = 0, ci = 0;
-    for (int k0 = 4 * sl; k0 < K; k0 += 4 * S) {
-        if constexpr (S > 1) {                          // not consecutive groups: the tap of k0 by division
-            const int tap = k0 / A.in_c;
-            ci = k0 - tap * A.in_c; ky = tap / A.kw; kx = tap - ky * A.kw;
+    struct Group { uint4 v[4]; uint32_t w4[CO]; };
+    auto load = [&](int k0, Group& g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CO; c++) g.w4[c] = *(sptr)(wrow + (int64_t)c * A.kpad + k0);
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            g.v[t] = make_uint4(0, 0, 0, 0);
+            if (k0 + t < K) {
+                const bool ok = A.pad == 0 || ((uint32_t)(iy0 + ky) < (uint32_t)A.in_h && (uint32_t)(ix0 + kx) < (uint32_t)A.in_w);
+                if (ok) g.v[t] = *(const uint4*)(inc + ((uint64_t)(uint32_t)(base + (ky * A.in_w + kx) * A.in_c + ci) << 4));
+                if (++ci == A.in_c) { ci = 0; if (++kx == A.kw) { kx = 0; ky++; } }
+            }
         }
-        const uint32_t w4 = *(const uint32_t*)(wrow + k0);
+    };
+    // the next group's loads go out before the current one is multiplied (few waves fit beside 16 CO accumulators)
+    Group ga, gb;
+    load(0, ga);
+    for (int k0 = 0; k0 < K; k0 += 8) {
+        if (k0 + 4 < K) load(k0 + 4, gb);
+        dot_group<CO>(ga.v, ga.w4, acc);
+        if (k0 + 4 >= K) break;
+        if (k0 + 8 < K) load(k0 + 8, ga);
+        dot_group<CO>(gb.v, gb.w4, acc);
+    }
+    uint32_t one[4] = {0, 0, 0, 0};
+    if (A.bias) { const uint4 o = *(const uint4*)(P.one + 16 * ch); one[0] = o.x; one[1] = o.y; one[2] = o.z; one[3] = o.w; }
+    uint8_t* dst = P.out.p + (int64_t)ch * P.out.cs + ((uint64_t)px * A.out_c + co0) * 16;
+#pragma unroll
+    for (int c = 0; c < CO; c++) {
+        if (co0 + c >= A.out_c) return;
+        const uint32_t bm = bias_of(A.bias, co0 + c, M);
+        uint32_t w[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            w[q] = 0;
+#pragma unroll
+            for (int d = 0; d < 4; d++) {
+                uint32_t r = reduce_acc(acc[c][4 * q + d], M);
+                if (bm) r = mod_m(r + mul24(bm, byte_of(one[q], d)), M);
+                w[q] |= r << (8 * d);
+            }
+        }
+        *(uint4*)(dst + 16 * c) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// One wave per (output pixel, chunk), 8 output channels; blockIdx.y = prime.  The lanes deal the reduction index out in groups of four;
+// the 128 sums are then added up over the wave so that lane l ends with the two of channel l / 8, digits 2 (l % 8) and + 1.  For layers
+// whose outputs do not fill the chip: the loop is 64 times shorter, at about 300 instructions for the addition.  (3 x 3 over 3 x 3 x 128 -> 128, 7 primes: 21 -> 11 us, the
+// rate of the host's calls; 4096 -> 256, 12 primes: 46 -> 33 us.)
+__global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
+    constexpr int CO = 8;
+    const LinPrime& P = A.pr[blockIdx.y];
+    const ModInfo M = ld_mod(A.mods, P.p);
+    const uint32_t lane = threadIdx.x & 63u, n_px = (uint32_t)A.batch * A.out_h * A.out_w, njb = ((uint32_t)A.out_c + CO - 1) / CO;
+    const uint32_t unit = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (unit >= n_px * njb * M.nchunk) return;                              // (n_px * njb * nchunk < 2^31 is checked on the host)
+    const uint32_t ch = unit / (n_px * njb), u = unit - ch * (n_px * njb), px = u / njb, co0 = (u - px * njb) * CO;
+    const uint32_t row = px / (uint32_t)A.out_w, ox = px - row * A.out_w, b = row / (uint32_t)A.out_h, oy = row - b * A.out_h;
+    const int iy0 = (int)oy * A.stride - A.pad, ix0 = (int)ox * A.stride - A.pad;
+    const int base = (((int)b * A.in_h + iy0) * A.in_w + ix0) * A.in_c;
+    const uint8_t* inc = P.in.p + (int64_t)ch * P.in.cs;
+    const int8_t* wrow = P.w + (int64_t)co0 * A.kpad;
+    uint32_t acc[CO][16] = {};
+    const uint32_t K = (uint32_t)A.kh * A.kw * A.in_c;
+    for (uint32_t k0 = 4 * lane; k0 < K; k0 += 256) {
+        uint32_t w4[CO];
+#pragma unroll
+        for (int c = 0; c < CO; c++) w4[c] = *(const uint32_t*)(wrow + (int64_t)c * A.kpad + k0);
+        uint32_t tap = A.kh * A.kw > 1 ? k0 / (uint32_t)A.in_c : 0u, ci = k0 - tap * A.in_c, ky = A.kw > 1 ? tap / (uint32_t)A.kw : tap, kx = tap - ky * A.kw;
         uint4 v[4];
 #pragma unroll
         for (int t = 0; t < 4; t++) {
-            const int iy = oy * A.stride + ky - A.pad, ix = ox * A.stride + kx - A.pad;
-            const bool ok = k0 + t < K && iy >= 0 && iy < A.in_h && ix >= 0 && ix < A.in_w;
+            const bool ok = k0 + t < K && (uint32_t)(iy0 + (int)ky) < (uint32_t)A.in_h && (uint32_t)(ix0 + (int)kx) < (uint32_t)A.in_w;
             v[t] = make_uint4(0, 0, 0, 0);
-            if (ok) v[t] = *(const uint4*)(inc + ((((int64_t)b * A.in_h + iy) * A.in_w + ix) * A.in_c + ci) * 16);
-            if (++ci == A.in_c) { ci = 0; if (++kx == A.kw) { kx = 0; ky++; } }
+            if (ok) v[t] = *(const uint4*)(inc + ((uint64_t)(uint32_t)(base + (int)((ky * A.in_w + kx) * A.in_c + ci)) << 4));
+            if (++ci == (uint32_t)A.in_c) { ci = 0; if (++kx == (uint32_t)A.kw) { kx = 0; ky++; } }
         }
-        const uint32_t vq[4][4] = {{v[0].x, v[1].x, v[2].x, v[3].x}, {v[0].y, v[1].y, v[2].y, v[3].y},
-                                   {v[0].z, v[1].z, v[2].z, v[3].z}, {v[0].w, v[1].w, v[2].w, v[3].w}};
+        dot_group<CO>(v, w4, acc);
+    }
+    // add up: halves of the wave, halves of 32 lanes (swaps), then within rows of 16 lanes (each lane keeps the half its bit names)
+    uint32_t* s = &acc[0][0];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            // v_perm_b32(hi, lo, sel): byte i of the result = byte sel.i of the 8 bytes {hi:lo}
-            const uint32_t ab02 = __builtin_amdgcn_perm(vq[q][1], vq[q][0], 0x06020400u), ab13 = __builtin_amdgcn_perm(vq[q][1], vq[q][0], 0x07030501u);
-            const uint32_t cd02 = __builtin_amdgcn_perm(vq[q][3], vq[q][2], 0x06020400u), cd13 = __builtin_amdgcn_perm(vq[q][3], vq[q][2], 0x07030501u);
-            const uint32_t d0 = __builtin_amdgcn_perm(cd02, ab02, 0x05040100u), d1 = __builtin_amdgcn_perm(cd13, ab13, 0x05040100u);
-            const uint32_t d2 = __builtin_amdgcn_perm(cd02, ab02, 0x07060302u), d3 = __builtin_amdgcn_perm(cd13, ab13, 0x07060302u);
-            acc[4 * q + 0] = __builtin_amdgcn_udot4(d0, w4, acc[4 * q + 0], false);
-            acc[4 * q + 1] = __builtin_amdgcn_udot4(d1, w4, acc[4 * q + 1], false);
-            acc[4 * q + 2] = __builtin_amdgcn_udot4(d2, w4, acc[4 * q + 2], false);
-            acc[4 * q + 3] = __builtin_amdgcn_udot4(d3, w4, acc[4 * q + 3], false);
+    for (int i = 0; i < 64; i++) { const auto r = __builtin_amdgcn_permlane32_swap(s[i], s[i + 64], false, false); s[i] = r[0] + r[1]; }
+#pragma unroll
+    for (int i = 0; i < 32; i++) { const auto r = __builtin_amdgcn_permlane16_swap(s[i], s[i + 32], false, false); s[i] = r[0] + r[1]; }
+#pragma unroll
+    for (int d = 8, n = 16; d >= 1; d >>= 1, n >>= 1) {
+        const bool up = (lane & d) != 0;
+#pragma unroll
+        for (int i = 0; i < n; i++) {
+            const uint32_t keep = up ? s[i + n] : s[i], send = up ? s[i] : s[i + n];
+            uint32_t got;
+            if (d == 8) got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x128, 0xf, 0xf, true);         // row_ror:8
+            else if (d == 4) got = (uint32_t)__builtin_amdgcn_ds_swizzle((int)send, (4 << 10) | 0x1f);           // lane ^ 4
+            else if (d == 2) got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x4E, 0xf, 0xf, true);     // quad_perm:[2,3,0,1]
+            else got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0xB1, 0xf, 0xf, true);                 // quad_perm:[1,0,3,2]
+            s[i] = keep + got;
         }
     }
-    if constexpr (S > 1) {
-        // the S partial sums of every accumulator (S consecutive lanes of one wave, all of them here): butterfly
-#pragma unroll
-        for (int off = S / 2; off >= 1; off >>= 1)
-#pragma unroll
-            for (int d = 0; d < 16; d++) acc[d] += (uint32_t)__shfl_xor((int)acc[d], off, 64);
-        if (sl != 0) return;
+    // sum index of s[0], s[1]: 64 (lane bit 5) + 32 (bit 4) + 16, 8, 4, 2 (bits 3..0): channel lane / 8, digits 2 (lane % 8), + 1
+    const int co = (int)(co0 + lane / 8), dg = 2 * (int)(lane % 8);
+    if (co >= A.out_c) return;
+    uint32_t r0 = reduce_acc(s[0], M), r1 = reduce_acc(s[1], M);
+    if (A.bias) {
+        const uint32_t bm = bias_of(A.bias, co, M);
+        r0 = mod_m(r0 + mul24(bm, P.one[16 * ch + dg]), M);
+        r1 = mod_m(r1 + mul24(bm, P.one[16 * ch + dg + 1]), M);
     }
-    // (p-1)^2 * K < 2^31 is checked on the host; reduce in two steps so the magic division applies (n < 2^24)
-    uint32_t bm = 0;
-    if (A.bias) { int32_t r = A.bias[co] % (int32_t)M.m; bm = (uint32_t)(r < 0 ? r + (int32_t)M.m : r); }
-    uint32_t outw[4];
-    for (int q = 0; q < 4; q++) {
-        uint32_t w = 0;
-        for (int bb = 0; bb < 4; bb++) {
-            uint32_t a = acc[4 * q + bb];
-            uint32_t r = mod_m(mod_m(a >> 12, M) * (4096u % M.m) + (a & 4095u), M);   // a = hi*4096 + lo
-            if (bm) r = mod_m(r + bm * A.one[ch * 16 + 4 * q + bb], M);
-            w |= r << (8 * bb);
-        }
-        outw[q] = w;
-    }
-    *(uint4*)(A.out.p + (int64_t)ch * A.out.cs + o * 16) = make_uint4(outw[0], outw[1], outw[2], outw[3]);
+    *(uint16_t*)(P.out.p + (int64_t)ch * P.out.cs + ((uint64_t)px * A.out_c + co) * 16 + dg) = (uint16_t)(r0 | (r1 << 8));
 }
 
 struct PoolPrime { uint32_t p; LView in, out; };
@@ -179,6 +252,26 @@ __global__ __launch_bounds__(kThreads) void k_sumpool(const PoolArgs AA) {
             w[2] = addmod4(w[2], v.z, M); w[3] = addmod4(w[3], v.w, M);
         }
     *(uint4*)(A.out.p + (int64_t)chunk * A.out.cs + o * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Which kernel takes a layer (times in us, from runs over the shapes of the benchmark's and the paper's networks at batches of 1 to 64).
+//   k_linear_split: about 3 + instructions of all its waves / 290 000: 190 per 256 of K, 360 for the addition over the wave
+//   k_dense_mfma:   about 6 + 0.6 per round and 64 of K, 8 more per further round of 256 tiles (where its tiles fit the layer at all)
+//   k_linear_tile:  0.6 per four of K (a chain of loads) while its waves are one round of the chip; eight channels per lane from 256
+//                   waves on (6x6 over 28x28x1 -> 16, 139 waves: 11.4 with four, 14 with eight; 2x2 over 28x28x32 -> 32, 355 waves:
+//                   50 and 33; 3x3 over 30x30x32 -> 32, 1420 waves: 226 and 114)
+enum LinearForm { LINEAR_TILE4 = 1, LINEAR_TILE8 = 2, LINEAR_SPLIT = 3, LINEAR_MFMA = 4 };
+static int linear_form(const dash_ctx* c, const dash_layer* L, int64_t batch, int64_t npx, int64_t chunks, int out_c, int K) {
+    if (c->linear_form) return c->linear_form;
+    const double split = 3 + (double)npx * ((out_c + 7) / 8) * chunks * ((K + 255) / 256 * 190 + 360) / 290e3;
+    if (dense_mfma_wanted(L, batch)) {
+        const int64_t tiles = (npx * chunks + 31) / 32 * ((out_c + 127) / 128), rounds = (tiles + 255) / 256;
+        return split < 6 + 0.6 * rounds * ((K + 63) / 64) + 8 * (rounds - 1) ? LINEAR_SPLIT : LINEAR_MFMA;
+    }
+    const int64_t waves8 = npx * chunks * ((out_c + 7) / 8) / 64;
+    const double tile = 4 + 0.6 * ((K + 3) / 4) * (1 + waves8 / 2048);
+    if (split < tile && npx * chunks * ((out_c + 7) / 8) < (1 << 24)) return LINEAR_SPLIT;
+    return waves8 < 256 ? LINEAR_TILE4 : LINEAR_TILE8;
 }
 
 int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels* in, dash_labels* out, hipStream_t s) {
@@ -219,14 +312,18 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
         uint64_t p1 = (uint64_t)(c->prime[i] - 1);
         if (p1 * p1 * (uint64_t)K >= (1ull << 31)) return DASH_ESIZE;      // int32 accumulators must not overflow
     }
-    if (dense_mfma_wanted(L, batch)) return dense_mfma(c, L, garble, in, out, s);
     const int out_h = (in_h + 2 * pad - kh) / stride + 1, out_w = (in_w + 2 * pad - kw) / stride + 1;
+    const int64_t npx = batch * out_h * out_w;
+    int64_t chunks = 0;
+    int nch = 1;                // chunks of all primes, of the prime with the most (the others' surplus blocks exit)
+    for (int i = 0; i < c->k; i++) { chunks += c->mods[c->prime[i]].nchunk; nch = (int)c->mods[c->prime[i]].nchunk > nch ? (int)c->mods[c->prime[i]].nchunk : nch; }
+    const int f = linear_form(c, L, batch, npx, chunks, out_c, K);
+    if (f == LINEAR_MFMA) return dense_mfma(c, L, garble, in, out, s);
     LinArgs A;
     memset(&A, 0, sizeof(A));
     A.mods = c->d_mods; A.bias = L->bias; A.kpad = Kp;
     A.batch = (int)batch; A.in_h = in_h; A.in_w = in_w; A.in_c = L->in_c; A.out_c = out_c;
     A.kh = kh; A.kw = kw; A.stride = stride; A.pad = pad; A.out_h = out_h; A.out_w = out_w;
-    int64_t lanes = 0;              // of the prime with the most chunks; the others' surplus blocks exit
     double macs = 0, bytes = 0;
     for (int i = 0; i < c->k; i++) {
         LinPrime& P = A.pr[i];
@@ -234,19 +331,18 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
         P.w = (const int8_t*)L->weights + (int64_t)i * Mp * Kp;
         P.one = L->bias ? (garble ? c->d_one0[i] : c->d_one[i]) : nullptr;
         P.in = view_of(in, i); P.out = view_of(out, i);
-        const int64_t l = n_out * c->mods[c->prime[i]].nchunk;
-        lanes = l > lanes ? l : lanes;
         const double lam = c->mods[c->prime[i]].lam;
         macs += (double)n_out * K * lam;
         bytes += ((double)n_in + n_out) * lam + (double)out_c * K;
     }
     {
         ProfScope ps(c->prof, DASH_PROF_LINEAR, s, macs, bytes);
-        // few outputs and a long reduction: 16 lanes per output
-        if (lanes <= 16384 && K >= 64)
-            hipLaunchKernelGGL(k_linear_direct<16>, dim3((uint32_t)((lanes * 16 + kThreads - 1) / kThreads), c->k), dim3(kThreads), 0, s, A);
+        if (f == LINEAR_SPLIT)
+            hipLaunchKernelGGL(k_linear_split, dim3((uint32_t)((npx * ((out_c + 7) / 8) * nch + kThreads / 64 - 1) / (kThreads / 64)), c->k), dim3(kThreads), 0, s, A);
+        else if (f == LINEAR_TILE8)
+            hipLaunchKernelGGL(k_linear_tile<8>, dim3((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, (out_c + 7) / 8), dim3(kThreads), 0, s, A);
         else
-            hipLaunchKernelGGL(k_linear_direct<1>, dim3((uint32_t)((lanes + kThreads - 1) / kThreads), c->k), dim3(kThreads), 0, s, A);
+            hipLaunchKernelGGL(k_linear_tile<4>, dim3((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, (out_c + 3) / 4), dim3(kThreads), 0, s, A);
     }
     DASH_HIP(hipGetLastError());
     return DASH_OK;

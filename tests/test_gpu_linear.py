@@ -115,3 +115,16 @@ def test_dense_mfma_both_tile_shapes(monkeypatch):
         run_linear(12, 5, 1, 1, 500, 300, 1, 1, 0, -64, 63, True, 41)
         run_linear(8, 40, 1, 1, 192, 100, 1, 1, 0, -8, 7, False, 42, garble=False)
         run_linear(12, 2, 9, 7, 8, 40, 3, 2, 1, -16, 15, True, 43)
+
+
+@pytest.mark.parametrize("form", ["1", "2", "3"])
+def test_linear_forms(monkeypatch, form):
+    """each kernel at the edges of its blocks: 4 and 8 output channels, 4 and 256 entries of the reduction, taps in the padding"""
+    monkeypatch.setenv("DASH_LINEAR_FORM", form)
+    for i, (K, out_c) in enumerate(((1, 1), (3, 4), (4, 5), (255, 8), (257, 9), (513, 33))):
+        run_linear(7, 3, 1, 1, K, out_c, 1, 1, 0, -64, 63, i % 2 == 0, 50 + i, garble=i % 3 == 0)
+    run_linear(5, 1, 1, 1, 70, 3, 1, 1, 0, -8, 7, True, 60)
+    run_linear(5, 2, 6, 7, 3, 9, 3, 2, 1, -8, 7, True, 61)
+    run_linear(8, 1, 5, 5, 7, 2, 5, 1, 2, -8, 7, True, 62, garble=False)
+    run_linear(8, 3, 9, 8, 5, 17, 4, 3, 0, -8, 7, False, 63)
+    run_linear(12, 1, 4, 4, 65, 7, 2, 2, 0, -8, 7, False, 64)
