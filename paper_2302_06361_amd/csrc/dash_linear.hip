@@ -52,7 +52,7 @@ struct LinArgs {
     const ModInfo* mods;
     const int32_t* bias;    // [out_c] or NULL
     int64_t kpad;
-    int batch, in_h, in_w, in_c, out_c, kh, kw, stride, pad, out_h, out_w;
+    int batch, in_h, in_w, in_c, out_c, kh, kw, stride, pad, out_h, out_w, co_first;
     LinPrime pr[DASH_MAX_PRIMES];
 };
 
@@ -90,7 +90,7 @@ __device__ __forceinline__ uint32_t bias_of(const int32_t* bias, int co, const M
 // for all lanes: their offsets, the weights and the loop run on the scalar unit.  Bound by vector issue: 32 permutes and 16 CO dot
 // products per four taps.  (One lane per output value repeated loads, permutes and 64-bit address arithmetic for every channel:
 // 6 -> 16 channels, 5 x 5, 14 x 14, batch 16, 8 primes: 131 us; CO = 8: 49 us.)
-template <int CO>
+template <int CO, bool Aligned>
 __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
     const LinPrime& P = A.pr[blockIdx.y];
     const ModInfo M = ld_mod(A.mods, P.p);
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
     const int iy0 = (int)oy * A.stride - A.pad, ix0 = (int)ox * A.stride - A.pad;
     const int base = (((int)b * A.in_h + iy0) * A.in_w + ix0) * A.in_c;      // (below 2^31; may be negative before the tap is added)
     const uint8_t* inc = P.in.p + (int64_t)ch * P.in.cs;
-    const int co0 = blockIdx.z * CO;
+    const int co0 = A.co_first + (int)blockIdx.z * CO;
     const int8_t* wrow = P.w + (int64_t)co0 * A.kpad;                       // rows past out_c are there (padded to 32) and zero
     typedef const __attribute__((address_space(4))) uint32_t* sptr;         // weights are wave-uniform and not written by the kernel: scalar loads
     uint32_t acc[CO][16] = {};
@@ -111,7 +111,11 @@ __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
     struct Group { uint4 v[4]; uint32_t w4[CO]; };
     auto load = [&](int k0, Group& g) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < CO; c++) g.w4[c] = *(sptr)(wrow + (int64_t)c * A.kpad + k0);
+        for (int c = 0; c < CO; c++) {
+            const int8_t* w = wrow + (int64_t)c * A.kpad + k0;
+            if constexpr (Aligned) g.w4[c] = *(sptr)w;
+            else __builtin_memcpy(&g.w4[c], w, 4);                         // (a scalar load drops the low two bits of its address)
+        }
 #pragma unroll
         for (int t = 0; t < 4; t++) {
             g.v[t] = make_uint4(0, 0, 0, 0);
@@ -337,12 +341,16 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
     }
     {
         ProfScope ps(c->prof, DASH_PROF_LINEAR, s, macs, bytes);
+        const int co = f == LINEAR_TILE4 && !((uintptr_t)L->weights & 3) ? 4 : 8, blocks = (out_c + co - 1) / co;
         if (f == LINEAR_SPLIT)
             hipLaunchKernelGGL(k_linear_split, dim3((uint32_t)((npx * ((out_c + 7) / 8) * nch + kThreads / 64 - 1) / (kThreads / 64)), c->k), dim3(kThreads), 0, s, A);
-        else if (f == LINEAR_TILE8)
-            hipLaunchKernelGGL(k_linear_tile<8>, dim3((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, (out_c + 7) / 8), dim3(kThreads), 0, s, A);
-        else
-            hipLaunchKernelGGL(k_linear_tile<4>, dim3((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, (out_c + 3) / 4), dim3(kThreads), 0, s, A);
+        else for (int at = 0; at < blocks; at += 65535) {                   // (the grid's third dimension ends at 65535)
+            A.co_first = at * co;
+            const dim3 grid((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, blocks - at < 65535 ? blocks - at : 65535);
+            if ((uintptr_t)L->weights & 3) hipLaunchKernelGGL((k_linear_tile<8, false>), grid, dim3(kThreads), 0, s, A);
+            else if (co == 8) hipLaunchKernelGGL((k_linear_tile<8, true>), grid, dim3(kThreads), 0, s, A);
+            else hipLaunchKernelGGL((k_linear_tile<4, true>), grid, dim3(kThreads), 0, s, A);
+        }
     }
     DASH_HIP(hipGetLastError());
     return DASH_OK;

@@ -10,7 +10,7 @@ from gpu_util import both, upload_bundle, assert_bundle_equal
 pytestmark = pytest.mark.gpu
 
 
-def run_linear(k, batch, in_h, in_w, in_c, out_c, kh, stride, pad, wlo, whi, bias, seed, garble=True, pool=False):
+def run_linear(k, batch, in_h, in_w, in_c, out_c, kh, stride, pad, wlo, whi, bias, seed, garble=True, pool=False, shift=0):
     from paper_2302_06361_amd import Labels, Layer, DENSE, CONV2D, SUMPOOL
     ctx, orc = both(k)
     g = np.random.default_rng(seed)
@@ -26,6 +26,8 @@ def run_linear(k, batch, in_h, in_w, in_c, out_c, kh, stride, pad, wlo, whi, bia
         ones = [orc.one0(i) if garble else orc.one(i) for i in range(k)]
         ref = [orc.conv2d(i, x[i], batch, in_h, in_w, in_c, out_c, kh, kh, stride, pad, W, b, ones[i]) for i in range(k)]
         wp = ctx.weights_prepare(W.reshape(out_c, -1))
+        if shift:                                   # a copy that starts `shift` bytes past an aligned address
+            wp = torch.cat([wp.new_zeros(shift), wp.reshape(-1)])[shift:]
         bd = torch.as_tensor(b).to(ctx.device) if bias else None
         dense = in_h == 1 and in_w == 1 and kh == 1
         lay = Layer(DENSE if dense else CONV2D, 1, batch, in_h=in_h, in_w=in_w, in_c=in_c, out_c=out_c, kh=kh, kw=kh,
@@ -128,3 +130,18 @@ def test_linear_forms(monkeypatch, form):
     run_linear(8, 1, 5, 5, 7, 2, 5, 1, 2, -8, 7, True, 62, garble=False)
     run_linear(8, 3, 9, 8, 5, 17, 4, 3, 0, -8, 7, False, 63)
     run_linear(12, 1, 4, 4, 65, 7, 2, 2, 0, -8, 7, False, 64)
+
+
+@pytest.mark.parametrize("form", ["1", "2", "3"])
+def test_linear_weights_at_odd_address(monkeypatch, form):
+    """prepared weights have no alignment of their own"""
+    monkeypatch.setenv("DASH_LINEAR_FORM", form)
+    run_linear(5, 2, 6, 7, 3, 9, 3, 2, 1, -8, 7, True, 71, shift=1)
+    run_linear(7, 3, 1, 1, 70, 5, 1, 1, 0, -8, 7, False, 72, shift=2)
+
+
+@pytest.mark.parametrize("form", ["1", "2"])
+def test_linear_more_channel_blocks_than_a_grid_holds(monkeypatch, form):
+    """blocks of 4 and 8 channels past 65535"""
+    monkeypatch.setenv("DASH_LINEAR_FORM", form)
+    run_linear(2, 1, 1, 1, 2, (4 if form == "1" else 8) * 65535 + 5, 1, 1, 0, -8, 7, False, 73)
