@@ -30,7 +30,7 @@ ALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 
 PMC_FILE = os.path.join(ROOT, "profiles", "gate_kernels_lenet_b16_pmc_per_unit.txt")
 GATE_SOURCES = ["dash_core.h", "dash_bodies.h", "dash_tabs.h", "dash_launch.h", "dash_gates.hip", "dash_gates_digits.hip", "dash_gates_eval.hip",
-                "dash_gates_digits_eval.hip", "dash_gates_cast.hip", "dash_layers.hip"]
+                "dash_gates_digits_eval.hip", "dash_gates_cast.hip", "dash_act_eval.hip", "dash_layers.hip"]
 
 
 def gate_source_hash():
@@ -646,7 +646,7 @@ def main():
     roofline = garble_roofline("k_proj_garble", kg, "gate", "garble")
     roofline_digits = garble_roofline("k_digits_garble", kd, "digits", "digits") if kd else None
     alg_eval = work["ops_eval"] / gates
-    roofline_eval = dict(kernel="k_digits_eval + k_chain_eval + k_cast_halve + k_proj_eval", bound="alu", unit=roofline["unit"], peak=ALU_PEAK_TOPS,
+    roofline_eval = dict(kernel="k_act_eval", bound="alu", unit=roofline["unit"], peak=ALU_PEAK_TOPS,
                          achieved=ke["units_per_s"] * alg_eval / 1e12, algorithmic_lane_ops_per_gate=alg_eval,
                          ms_per_step=ke["ms_per_step"], avg_launch_ms=ke["avg_launch_ms"], launches_per_step=ke["launches_per_step"],
                          gates_per_s=ke["units_per_s"], hbm_algorithmic_GBps=ke["gbytes_per_s"],
