@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include "dash_internal.h"
+#include "dash_linear_rule.h"
 
 namespace dash {
 
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
     const ModInfo M = ld_mod(A.mods, P.p);
     const uint32_t lane = threadIdx.x & 63u, n_px = (uint32_t)A.batch * A.out_h * A.out_w, njb = ((uint32_t)A.out_c + CO - 1) / CO;
     const uint32_t unit = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= n_px * njb * M.nchunk) return;                              // (n_px * njb * nchunk < 2^31 is checked on the host)
+    if (unit >= n_px * njb * M.nchunk) return;                              // (n_px * njb * nchunk < 2^26: linear_split_fits)
     const uint32_t ch = unit / (n_px * njb), u = unit - ch * (n_px * njb), px = u / njb, co0 = (u - px * njb) * CO;
     const uint32_t row = px / (uint32_t)A.out_w, ox = px - row * A.out_w, b = row / (uint32_t)A.out_h, oy = row - b * A.out_h;
     const int iy0 = (int)oy * A.stride - A.pad, ix0 = (int)ox * A.stride - A.pad;
@@ -258,26 +259,6 @@ __global__ __launch_bounds__(kThreads) void k_sumpool(const PoolArgs AA) {
     *(uint4*)(A.out.p + (int64_t)chunk * A.out.cs + o * 16) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Which kernel takes a layer (times in us, from runs over the shapes of the benchmark's and the paper's networks at batches of 1 to 64).
-//   k_linear_split: about 3 + instructions of all its waves / 290 000: 190 per 256 of K, 360 for the addition over the wave
-//   k_dense_mfma:   about 6 + 0.6 per round and 64 of K, 8 more per further round of 256 tiles (where its tiles fit the layer at all)
-//   k_linear_tile:  0.6 per four of K (a chain of loads) while its waves are one round of the chip; eight channels per lane from 256
-//                   waves on (6x6 over 28x28x1 -> 16, 139 waves: 11.4 with four, 14 with eight; 2x2 over 28x28x32 -> 32, 355 waves:
-//                   50 and 33; 3x3 over 30x30x32 -> 32, 1420 waves: 226 and 114)
-enum LinearForm { LINEAR_TILE4 = 1, LINEAR_TILE8 = 2, LINEAR_SPLIT = 3, LINEAR_MFMA = 4 };
-static int linear_form(const dash_ctx* c, const dash_layer* L, int64_t batch, int64_t npx, int64_t chunks, int out_c, int K) {
-    if (c->linear_form) return c->linear_form;
-    const double split = 3 + (double)npx * ((out_c + 7) / 8) * chunks * ((K + 255) / 256 * 190 + 360) / 290e3;
-    if (dense_mfma_wanted(L, batch)) {
-        const int64_t tiles = (npx * chunks + 31) / 32 * ((out_c + 127) / 128), rounds = (tiles + 255) / 256;
-        return split < 6 + 0.6 * rounds * ((K + 63) / 64) + 8 * (rounds - 1) ? LINEAR_SPLIT : LINEAR_MFMA;
-    }
-    const int64_t waves8 = npx * chunks * ((out_c + 7) / 8) / 64;
-    const double tile = 4 + 0.6 * ((K + 3) / 4) * (1 + waves8 / 2048);
-    if (split < tile && npx * chunks * ((out_c + 7) / 8) < (1 << 24)) return LINEAR_SPLIT;
-    return waves8 < 256 ? LINEAR_TILE4 : LINEAR_TILE8;
-}
-
 int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels* in, dash_labels* out, hipStream_t s) {
     int64_t per_out = 0;
     int st = layer_sizes(c, L, &per_out, nullptr, nullptr);
@@ -321,7 +302,7 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
     int64_t chunks = 0;
     int nch = 1;                // chunks of all primes, of the prime with the most (the others' surplus blocks exit)
     for (int i = 0; i < c->k; i++) { chunks += c->mods[c->prime[i]].nchunk; nch = (int)c->mods[c->prime[i]].nchunk > nch ? (int)c->mods[c->prime[i]].nchunk : nch; }
-    const int f = linear_form(c, L, batch, npx, chunks, out_c, K);
+    const int f = linear_form(c->linear_form, LinearShape{npx, chunks, nch, out_c, K, dense_mfma_wanted(L, batch)});
     if (f == LINEAR_MFMA) return dense_mfma(c, L, garble, in, out, s);
     LinArgs A;
     memset(&A, 0, sizeof(A));

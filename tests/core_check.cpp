@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "../paper_2302_06361_amd/csrc/dash_hostconst.h"
+#include "../paper_2302_06361_amd/csrc/dash_linear_rule.h"
 
 using namespace dash;
 using namespace dash::hostconst;
@@ -88,4 +89,8 @@ uint32_t cc_addmod4(uint32_t a, uint32_t b, int m) { ModInfo M; fill_modinfo(M, 
 uint32_t cc_submod4(uint32_t a, uint32_t b, int m) { ModInfo M; fill_modinfo(M, m, 0); return submod4(a, b, M); }
 uint32_t cc_axpymod4(uint32_t a, uint32_t c, uint32_t b, int m) { ModInfo M; fill_modinfo(M, m, 0); return axpymod4(a, c, b, M); }
 uint32_t cc_mod_m(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return mod_m(n, M); }
+// kernel of a linear layer
+int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int mfma) {
+    return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, mfma != 0});
+}
 }

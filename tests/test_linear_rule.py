@@ -1,0 +1,36 @@
+"""The choice of the kernel of a dense or convolution layer (dash_linear_rule.h), compiled for the host.  No GPU involved."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TILE4, TILE8, SPLIT, MFMA = 1, 2, 3, 4
+CHUNKS = {7: 29, 8: 31, 9: 33, 12: 39}      # 16-digit chunks of the labels of the first k primes
+
+
+@pytest.fixture(scope="module")
+def form(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rule") / "rule.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "core_check.cpp")])
+    lib = C.CDLL(so)
+
+    def f(npx, out_c, K, k=8, mfma=False, forced=0):
+        return lib.cc_linear_form(forced, C.c_int64(npx), C.c_int64(CHUNKS[k]), 8, out_c, K, int(mfma))
+    f.lib = lib
+    return f
+
+
+def test_split_form_only_where_a_grid_holds_it(form):
+    """a wave per (pixel, chunk, 8 channels): fewer than 2^32 lanes, whatever asks for the form"""
+    assert form(2 ** 22 - 1, 16, 64, forced=SPLIT) == SPLIT
+    assert form(2 ** 22, 16, 64, forced=SPLIT) != SPLIT               # 2^22 * 2 * 8 waves = 2^32 lanes
+    assert form(2 ** 31 - 1, 1, 1, forced=SPLIT) != SPLIT
+    for e in range(31):
+        for out_c in (1, 9, 257, 4097):
+            for K in (1, 64, 257, 70000):
+                for mfma in (False, True):
+                    npx = 2 ** e
+                    if npx * out_c < 2 ** 31 and form(npx, out_c, K, mfma=mfma) == SPLIT:
+                        assert npx * ((out_c + 7) // 8) * 8 < 2 ** 26, (npx, out_c, K, mfma)
