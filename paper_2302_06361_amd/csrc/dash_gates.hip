@@ -84,6 +84,7 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 template <bool Pack>
 __global__ __launch_bounds__(kThreads) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef u32x4 u32x4_at4 __attribute__((aligned(4)));              // of table rows: tables, and with rows of 20 bytes their segments, are 4-byte aligned
     constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
     __shared__ uint32_t stage[kThreads / 64][64 * kMaxDw];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_repack(const PackLaunch L) {
             typedef decltype(M) MD;
             if constexpr (cmod_m<MD>::value == 2) {
                 uint16_t* bits = (uint16_t*)(S.packed + r0 * 16);
-                u32x4* digits = (u32x4*)(const_cast<uint8_t*>(S.rows) + r0 * 128);
+                u32x4_at4* digits = (u32x4_at4*)(const_cast<uint8_t*>(S.rows) + r0 * 128);
                 uint32_t v16[8];
                 u32x4 v[8];
 #pragma unroll

@@ -156,11 +156,11 @@ def test_labels_pack_needs_the_floor_rule():
     assert bool((packed == 7).all().item())
 
 
-@pytest.mark.parametrize("k,kind,repeat", [(8, "relu", 1), (8, "scale", 2), (5, "sign", 1), (12, "relu", 1)])
-def test_tables_pack_unpack(k, kind, repeat):
+@pytest.mark.parametrize("k,kind,repeat,shift", [(8, "relu", 1, 0), (8, "scale", 2, 0), (5, "sign", 1, 0), (12, "relu", 1, 0), (8, "scale", 1, 4)])
+def test_tables_pack_unpack(k, kind, repeat, shift):
     """the packed storage format of a layer's ciphertext tables (16 bytes per row, the row compressed like a label;
     floor-rule contexts): packed bytes against the oracle's packing of the oracle's tables, unpacking gives the
-    tables back, and the layer evaluates from the unpacked copy"""
+    tables back, and the layer evaluates from the unpacked copy; also with tables that start 4 bytes past an aligned address"""
     from paper_2302_06361_amd import Labels, Layer, RELU, SCALE, SIGN
     ctx, orc = both(k, rule=1)
     P = orc.P
@@ -184,12 +184,12 @@ def test_tables_pack_unpack(k, kind, repeat):
     assert tb == rt.size and pb == want_packed.size and pb < tb
     tz, ta = upload_bundle(ctx, zero), upload_bundle(ctx, act)
     oz, oa = Labels(ctx, n, zero=True), Labels(ctx, n, zero=True)
-    tables = torch.zeros(tb, dtype=torch.uint8, device=ctx.device)
+    tables = torch.zeros(tb + shift, dtype=torch.uint8, device=ctx.device)[shift:]
     scratch = torch.zeros(sb + 256, dtype=torch.uint8, device=ctx.device)
     ctx.garble_layer(lay, tz, oz, tables, scratch)
     packed = torch.full((pb,), 0xEE, dtype=torch.uint8, device=ctx.device)
     ctx.tables_pack(lay, tables, packed)
-    back = torch.full((tb,), 0xEE, dtype=torch.uint8, device=ctx.device)
+    back = torch.full((tb + shift,), 0xEE, dtype=torch.uint8, device=ctx.device)[shift:]
     ctx.tables_unpack(lay, packed, back)
     ctx.eval_layer(lay, ta, back, oa, scratch)
     torch.cuda.synchronize()
