@@ -36,9 +36,10 @@ inline int linear_form_by_shape(const LinearShape& S) {
     return waves8 < 256 ? LINEAR_TILE4 : LINEAR_TILE8;
 }
 
-// forced: the tuning hook's form.  Whichever way k_linear_split is chosen, it takes the layer only if a grid holds it.
+// forced: the tuning and test hook's form; k_dense_mfma only for layers that it can be chosen for.  Whichever way k_linear_split is
+// chosen, it takes the layer only if a grid holds it.
 inline int linear_form(int forced, const LinearShape& S) {
-    const int f = forced ? forced : linear_form_by_shape(S);
+    const int f = forced && (forced != LINEAR_MFMA || S.mfma) ? forced : linear_form_by_shape(S);
     return f == LINEAR_SPLIT && !linear_split_fits(S) ? LINEAR_TILE8 : f;
 }
 

@@ -34,3 +34,17 @@ def test_split_form_only_where_a_grid_holds_it(form):
                     npx = 2 ** e
                     if npx * out_c < 2 ** 31 and form(npx, out_c, K, mfma=mfma) == SPLIT:
                         assert npx * ((out_c + 7) // 8) * 8 < 2 ** 26, (npx, out_c, K, mfma)
+
+
+# (batch or pixels, out_c, K, primes) of the MFMA tests on the GPU
+MFMA_SHAPES = [(5, 300, 500, 12), (7, 257, 128, 8), (3, 70, 1030, 12), (2, 96, 4096, 12), (1, 70, 13000, 12), (2, 40, 13000, 12), (3, 130, 250, 8),
+               (3, 130, 192, 8), (108, 70, 100, 8), (25, 64, 64, 8), (256, 48, 108, 12), (40, 40, 108, 12), (40, 100, 192, 8)]
+
+
+def test_mfma_form_can_be_forced_where_its_tiles_fit(form):
+    """several of the MFMA tests' layers are small enough for k_linear_split to be the faster one: they need the hook"""
+    chosen = [form(npx, out_c, K, k, mfma=True) for npx, out_c, K, k in MFMA_SHAPES]
+    assert SPLIT in chosen and form(128, 4096, 4096, 12, mfma=True) == MFMA
+    for npx, out_c, K, k in MFMA_SHAPES:
+        assert form(npx, out_c, K, k, mfma=True, forced=MFMA) == MFMA
+        assert form(npx, out_c, K, k, mfma=False, forced=MFMA) == form(npx, out_c, K, k, mfma=False) != MFMA
