@@ -157,12 +157,13 @@ __global__ __launch_bounds__(TL::T) void k_dense_mfma(const GemmArgs A) {
     // Global data is fetched two stages ahead into one of two register sets (a stage of MFMAs is shorter
     // than a miss in the L2), transposed and written to LDS one stage ahead.
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));     // (a plain vector: HIP's uint4 is a struct and was left in scratch memory)
+    typedef u32x4 u32x4_any __attribute__((aligned(1)));            // of prepared weights, which have no alignment of their own
     struct Regs { u32x4 a0, a1, a2, a3, b0, b1, b2, b3; };
     Regs Rx, Ry;
     const int arow = tid >> 2, apart = tid & 3;         // A piece i of this thread: row arow + (T / 4) i, 16-byte part apart
     auto a_src = [&](int i, int k0) __attribute__((always_inline)) {
         const int row = row0 + arow + (T / 4) * i;
-        return (const u32x4*)(wbase + (int64_t)(row < mpad ? row : mpad - 1) * kpad + k0 + apart * 16);   // rows past M are never stored
+        return (const u32x4_any*)(wbase + (int64_t)(row < mpad ? row : mpad - 1) * kpad + k0 + apart * 16);   // rows past M are never stored
     };
     auto b_src = [&](int kk, int k0) __attribute__((always_inline)) {
         const int k = k0 + 4 * bkq + kk;

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
     for (uint32_t k0 = 4 * lane; k0 < K; k0 += 256) {
         uint32_t w4[CO];
 #pragma unroll
-        for (int c = 0; c < CO; c++) w4[c] = *(const uint32_t*)(wrow + (int64_t)c * A.kpad + k0);
+        for (int c = 0; c < CO; c++) __builtin_memcpy(&w4[c], wrow + (int64_t)c * A.kpad + k0, 4);      // (at any address)
         uint32_t tap = A.kh * A.kw > 1 ? k0 / (uint32_t)A.in_c : 0u, ci = k0 - tap * A.in_c, ky = A.kw > 1 ? tap / (uint32_t)A.kw : tap, kx = tap - ky * A.kw;
         uint4 v[4];
 #pragma unroll
