@@ -84,11 +84,25 @@ void cc_draw(const uint8_t seed[16], int domain, uint32_t layer, uint32_t slot, 
     decompress(M, h, [&](int i, uint32_t w) { memcpy(out + 4 * i, &w, 4); });
     *digit0 = mod_u128(h, M);
 }
+// the digits of n 128-bit numbers, through the compile-time description of the modulus (spec) where one exists or the run-time one
+void cc_digits(const uint8_t* h, int n, int m, int rule, int spec, uint8_t* out) {
+    ModInfo M;
+    fill_modinfo(M, m, rule);
+    for (int i = 0; i < n; i++) {
+        U128 x;
+        memcpy(x.w, h + 16 * i, 16);
+        uint8_t* o = out + (size_t)i * M.ndw * 4;
+        auto put = [&](int d, uint32_t w) { memcpy(o + 4 * d, &w, 4); };
+        if (spec) with_mod(M, [&](auto D) { decompress(D, x, put); });
+        else decompress(M, x, put);
+    }
+}
 // packed-digit arithmetic on one dword
 uint32_t cc_addmod4(uint32_t a, uint32_t b, int m) { ModInfo M; fill_modinfo(M, m, 0); return addmod4(a, b, M); }
 uint32_t cc_submod4(uint32_t a, uint32_t b, int m) { ModInfo M; fill_modinfo(M, m, 0); return submod4(a, b, M); }
 uint32_t cc_axpymod4(uint32_t a, uint32_t c, uint32_t b, int m) { ModInfo M; fill_modinfo(M, m, 0); return axpymod4(a, c, b, M); }
 uint32_t cc_mod_m(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return mod_m(n, M); }
+uint32_t cc_div_any(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return div_any(n, M); }
 // kernel of a linear layer
 int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int mfma) {
     return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, mfma != 0});

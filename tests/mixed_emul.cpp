@@ -28,7 +28,7 @@ int main(int argc, char** argv) {
     const uint32_t n = (uint32_t)atoi(argv[1]);
     rng_state = (uint64_t)atoll(argv[2]);
     std::vector<ModInfo> mods(256);
-    for (int m = 2; m < 256; m++) fill_modinfo(mods[m], m, 0);
+    for (int m = 2; m < 256; m++) fill_modinfo(mods[m], m, kFloorRule);
     // the default digit sets (d_1; d, .., d) of the 8-, 12-, 7- and 9-prime bases must find their kernels with compile-time
     // moduli: accumulation moduli m_1 = d_1 and m_c = k d (Appendix, Approximated Garbled Sign)
     static const int sets[4][3] = {{8, 26, 12}, {12, 46, 17}, {7, 10, 13}, {9, 22, 10}};

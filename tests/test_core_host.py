@@ -15,13 +15,23 @@ SO = os.path.join(HERE, "libcore_check.so")
 MODULI = [2, 3, 4, 5, 7, 11, 13, 16, 17, 19, 23, 29, 31, 37, 12, 15, 26, 27, 46, 56, 60, 96, 100, 125, 128, 129, 181, 182, 204, 255]
 
 
-@pytest.fixture(scope="module")
-def cc():
-    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", SO, SRC])
-    lib = C.CDLL(SO)
-    for f in ("cc_addmod4", "cc_submod4", "cc_axpymod4", "cc_mod_m"):
+def load(so, flags):
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC"] + flags + ["-o", so, SRC])
+    lib = C.CDLL(so)
+    for f in ("cc_addmod4", "cc_submod4", "cc_axpymod4", "cc_mod_m", "cc_div_any"):
         getattr(lib, f).restype = C.c_uint32
     return lib
+
+
+@pytest.fixture(scope="module")
+def cc():
+    return load(SO, [])
+
+
+@pytest.fixture(scope="module")
+def cc_by_rule(cc, tmp_path_factory):
+    """the host build per label-length rule, like the library's kernels: its compile-time moduli have the rule's label lengths"""
+    return [cc, load(str(tmp_path_factory.mktemp("core") / "floor.so"), ["-DDASH_RULE_FLOOR"])]
 
 
 def test_label_lengths(cc):
@@ -31,7 +41,8 @@ def test_label_lengths(cc):
 
 
 @pytest.mark.parametrize("rule", [0, 1])
-def test_hash_matches_oracle(cc, rule):
+def test_hash_matches_oracle(cc_by_rule, rule):
+    cc = cc_by_rule[rule]
     orc = capi.Oracle([2, 3, 5], [2, 5, 9], bytes(range(16)), rule)
     g = np.random.default_rng(rule)
     for p in MODULI:
@@ -63,6 +74,49 @@ def test_draw_matches_oracle(cc):
         cc.cc_draw(sb.ctypes.data_as(C.c_void_p), 2, 513, 77, C.c_uint64(2 ** 40 + m), m, 0, out.ctypes.data_as(C.c_void_p), C.byref(d0))
         want = orc.draw(2, 513, 77, 2 ** 40 + m, m)
         assert (out[:lam] == want).all() and d0.value == want[0]
+
+
+# the moduli with a compile-time description
+HOT = [2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37, 26, 96, 46, 204, 10, 91, 22, 90]
+
+
+@pytest.mark.parametrize("rule", [0, 1])
+def test_digits_at_the_ends_of_the_window(cc_by_rule, rule):
+    """The conversion takes the digits off a fraction: its error shows first where the fraction is next to a multiple of a power of
+    the modulus.  k m^j - 1, k m^j and k m^j + 1 for every j with the largest k, the smallest and random ones, the ends of the
+    range, and random numbers, through the compile-time and the run-time description, against division of whole numbers."""
+    cc = cc_by_rule[rule]
+    g = np.random.default_rng(40 + rule)
+    for m in HOT:
+        lam = capi.lam(m, rule)
+        hs = {0, 1, 2 ** 128 - 1, 2 ** 128 - 2, 2 ** 127, 2 ** 64 - 1, 2 ** 64} | {int.from_bytes(g.bytes(16), "little") for _ in range(50)}
+        j = 1
+        while m ** j < 2 ** 128:
+            top = (2 ** 128 - 1) // m ** j
+            for k in {1, 2, m - 1, top, max(top - 1, 1), top // m * m or 1} | {1 + int.from_bytes(g.bytes(16), "little") % top for _ in range(3)}:
+                hs |= {h for h in (k * m ** j - 1, k * m ** j, k * m ** j + 1) if 0 <= h < 2 ** 128}
+            j += 1
+        hs = sorted(hs)
+        raw = np.frombuffer(b"".join(h.to_bytes(16, "little") for h in hs), np.uint8).copy()
+        ndw = (lam + 3) // 4
+        for spec in (0, 1):
+            out = np.full((len(hs), 4 * ndw), 0xEE, np.uint8)
+            cc.cc_digits(raw.ctypes.data_as(C.c_void_p), len(hs), m, rule, spec, out.ctypes.data_as(C.c_void_p))
+            for i, h in enumerate(hs):
+                want = []
+                for _ in range(lam):
+                    h, d = divmod(h, m)
+                    want.append(d)
+                assert out[i, :lam].tolist() == want and not out[i, lam:].any(), (m, spec, hs[i])
+
+
+def test_division_of_a_tile_start(cc):
+    """floor(n / m) for n up to 2^32 - m: the first row of a tile of 256"""
+    g = np.random.default_rng(3)
+    for m in range(2, 256):
+        ns = [0, 1, m - 1, m, 2 ** 32 - m, 2 ** 32 - m - 1, (2 ** 32 - m) // m * m, (2 ** 32 - m) // m * m - 1, 2 ** 32 - 256] + g.integers(0, 2 ** 32 - 256, 50).tolist()
+        for n in ns:
+            assert cc.cc_div_any(C.c_uint32(int(n)), m) == n // m, (n, m)
 
 
 def test_packed_digit_arithmetic(cc):

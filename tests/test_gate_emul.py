@@ -15,19 +15,26 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SEED = bytes(range(7, 23))
 
 
-EMULATIONS = ("gate_emul", "chain_emul", "digits_emul", "mixed_emul", "cast_emul", "aes_sliced_emul")
+EMULATIONS = ("gate_emul", "chain_emul", "digits_emul", "mixed_emul", "cast_emul")
+# (name, source, flags): like the library's kernels, once per label-length rule
+PROGRAMS = [(n, n, []) for n in EMULATIONS] + [(n + "_floor", n, ["-DDASH_RULE_FLOOR"]) for n in EMULATIONS] + [("aes_sliced_emul", "aes_sliced_emul", [])]
+
+
+def by_rule(exe, rule):
+    """the program whose compile-time moduli have the rule's label lengths"""
+    return exe.replace(".bin", "_floor.bin") if rule else exe
 
 
 @pytest.fixture(scope="module")
 def built():
     """all emulation programs, compiled side by side (most of this module's time is their compilation)"""
-    procs = [(name, subprocess.Popen(["g++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
-                                      "-o", os.path.join(HERE, name + ".bin"), os.path.join(HERE, name + ".cpp")],
-                                     stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)) for name in EMULATIONS]
+    procs = [(name, subprocess.Popen(["g++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"] + flags +
+                                     ["-o", os.path.join(HERE, name + ".bin"), os.path.join(HERE, src + ".cpp")],
+                                     stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)) for name, src, flags in PROGRAMS]
     for name, pr in procs:
         out, _ = pr.communicate()
         assert pr.returncode == 0, (name, out[-3000:])
-    return {name: os.path.join(HERE, name + ".bin") for name in EMULATIONS}
+    return {name: os.path.join(HERE, name + ".bin") for name, _, _ in PROGRAMS}
 
 
 @pytest.fixture(scope="module")
@@ -47,7 +54,7 @@ def run_case(emul, tmp_path, p, q, n, rule=0, shared=False, elem_base=2 ** 33 + 
     blob += orc.delta(p).tobytes() + orc.delta(q).tobytes() + in0.tobytes() + act.tobytes() + phi.tobytes()
     fin, fout = str(tmp_path / "in.bin"), str(tmp_path / "out.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([emul, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(emul, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     out = np.fromfile(fout, np.uint8)
     pitch = capi.pitch(lq)
@@ -61,8 +68,9 @@ def run_case(emul, tmp_path, p, q, n, rule=0, shared=False, elem_base=2 ** 33 + 
 
 @pytest.mark.parametrize("p,q", [(2, 2), (2, 37), (3, 3), (37, 2), (19, 96), (96, 96), (96, 26), (26, 2), (204, 46), (46, 204),
                                  (13, 204), (5, 7), (100, 60), (255, 3)])
-def test_gate_bodies_under_sanitizers(emul, tmp_path, p, q):
-    run_case(emul, tmp_path, p, q, 300)
+@pytest.mark.parametrize("rule", [0, 1])
+def test_gate_bodies_under_sanitizers(emul, tmp_path, p, q, rule):
+    run_case(emul, tmp_path, p, q, 300, rule)
 
 
 def test_gate_bodies_sizes_and_rules(emul, tmp_path):
@@ -105,7 +113,7 @@ def run_chain(chain_emul, tmp_path, m, variant, n_elem, rule=0, elem_base=2 ** 3
     blob += b"".join(s.tobytes() for s in sums) + b"".join(t.tobytes() for t in tabs)
     fin, fout = str(tmp_path / "cin.bin"), str(tmp_path / "cout.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([chain_emul, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(chain_emul, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     got = np.fromfile(fout, np.uint8).reshape(n_elem, orc.lam(2))
     for e in range(n_elem):
@@ -136,6 +144,15 @@ def test_chain_bodies_under_sanitizers(chain_emul, tmp_path):
     run_chain(chain_emul, tmp_path, [26, 96], 1, 5)                 # n = 2: no same-modulus step
     run_chain(chain_emul, tmp_path, [26] + [96] * 6, 0, 70, lam2=64)    # label length of modulus 2 given explicitly
     run_chain(chain_emul, tmp_path, [4, 60], 0, 300, lam2=100)
+
+
+def test_chain_bodies_floor_rule_under_sanitizers(chain_emul, tmp_path):
+    run_chain(chain_emul, tmp_path, [26] + [96] * 6, 1, 70, rule=1)
+    run_chain(chain_emul, tmp_path, [46] + [204] * 10, 2, 70, rule=1)
+    run_chain(chain_emul, tmp_path, [10] + [91] * 5, 3, 70, rule=1)
+    run_chain(chain_emul, tmp_path, [22] + [90] * 8, 4, 70, rule=1)
+    run_chain(chain_emul, tmp_path, [46] + [204] * 10, 2, 65, rule=1, quad=True)
+    run_chain(chain_emul, tmp_path, [26] + [96] * 6, 0, 40, rule=1)
 
 
 # ---- the evaluator's fused digit gates --------------------------------------------------------------
@@ -169,7 +186,7 @@ def run_digits(digits_emul, tmp_path, primes, m, variant, n_elem, rule=0, elem_b
     blob += b"".join(t.tobytes() for row in tabs for t in row)
     fin, fout = str(tmp_path / "din.bin"), str(tmp_path / "dout.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([digits_emul, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(digits_emul, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stderr[-3000:])
     got = np.fromfile(fout, np.uint8)
     at = 0
@@ -226,7 +243,7 @@ def run_digits_sums(digits_emul, tmp_path, primes, m, variant, n_elem, rule=0, e
     blob += b"".join(t.tobytes() for row in tabs for t in row)
     fin, fout = str(tmp_path / "sin.bin"), str(tmp_path / "sout.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([digits_emul, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(digits_emul, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stderr[-3000:])
     got = np.fromfile(fout, np.uint8)
     at = 0
@@ -265,7 +282,7 @@ def run_digits_garble(digits_emul, tmp_path, primes, m, variant, n_elem, rule=0,
     blob += b"".join(ph.tobytes() for ph in phis)
     fin, fout = str(tmp_path / "gin.bin"), str(tmp_path / "gout.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([digits_emul, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(digits_emul, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stderr[-3000:])
     got = np.fromfile(fout, np.uint8)
     at = 0
@@ -298,15 +315,25 @@ def test_digit_rows_one_per_lane_under_sanitizers(digits_emul, tmp_path):
     run_digits_garble(digits_emul, tmp_path, [13], [26], 0, 5, wide=True)
 
 
+@pytest.mark.parametrize("primes,m,variant", [([2, 3, 5, 7, 11, 13, 17, 19], [26] + [96] * 6, 1), ([2, 23, 37], [46] + [204] * 10, 2),
+                                              ([2, 3, 13, 17], [10] + [91] * 5, 3), ([2, 11, 23], [22] + [90] * 8, 4)])
+def test_digit_gates_floor_rule_under_sanitizers(digits_emul, tmp_path, primes, m, variant):
+    """every form of the digit gates with the floor rule's compile-time moduli"""
+    for wide in (False, True):
+        run_digits(digits_emul, tmp_path, primes, m, variant, 70, rule=1, wide=wide)
+        run_digits_garble(digits_emul, tmp_path, primes, m, variant, 70, rule=1, wide=wide)
+    run_digits_sums(digits_emul, tmp_path, primes, m, variant, 65, rule=1)
+
+
 # ---- one evaluator launch that mixes output moduli -------------------------------------------------
 def test_mixed_output_moduli_in_one_eval_launch_under_sanitizers(built, tmp_path):
     """the evaluator's any-modulus instantiation picks a compile-time description of the output modulus per job:
     16 jobs with 16 of the 20 described moduli as outputs in ONE launch (two lists, so that each of the 20 occurs),
     exactly-sized buffers, address sanitizer; same results as the single-modulus instantiations"""
-    exe = built["mixed_emul"]
-    for n, seed, which in ((1, 1, 0), (257, 2, 0), (300, 3, 0), (130, 4, 1)):
-        r = subprocess.run([exe, str(n), str(seed), str(which)], capture_output=True, text=True)
-        assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-3000:]
+    for exe in (built["mixed_emul"], built["mixed_emul_floor"]):
+        for n, seed, which in ((1, 1, 0), (257, 2, 0), (300, 3, 0), (130, 4, 1)):
+            r = subprocess.run([exe, str(n), str(seed), str(which)], capture_output=True, text=True)
+            assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-3000:]
 
 
 # ---- evaluator kernels that read a wire of modulus 2 ------------------------------------------------
@@ -336,7 +363,7 @@ def run_cast(tmp_path, exe, p, n, addc, rule=0, lam2=0, lam_p=0, elem_base=2 ** 
     blob += b"".join(a.tobytes() for a in (y, x, one, table, U, V, S))
     fin, fout = str(tmp_path / "kin.bin"), str(tmp_path / "kout.bin")
     open(fin, "wb").write(blob)
-    r = subprocess.run([exe, fin, fout], capture_output=True, text=True)
+    r = subprocess.run([by_rule(exe, rule), fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     b, z = np.split(np.fromfile(fout, np.uint8), 2)
     b, z = b.reshape(n, lp), z.reshape(n, lp)
@@ -354,6 +381,8 @@ def test_cast_and_half_gate_bodies_under_sanitizers(built, tmp_path):
     run_cast(tmp_path, exe, 3, 300, 0)
     run_cast(tmp_path, exe, 19, 257, 7)
     run_cast(tmp_path, exe, 7, 40, 3, rule=1)
+    run_cast(tmp_path, exe, 3, 65, 0, rule=1)
+    run_cast(tmp_path, exe, 19, 65, 1, rule=1)
     run_cast(tmp_path, exe, 5, 70, 2, lam2=64)                   # label lengths given explicitly: modulus 2 shorter than 128
     run_cast(tmp_path, exe, 13, 33, 0, lam2=100, lam_p=9)
 

@@ -18,7 +18,7 @@ def force(monkeypatch, form):
 
 
 @pytest.mark.parametrize("form", ["tiny", "shallow", "deep"])
-@pytest.mark.parametrize("k,rule", [(7, 0), (8, 0), (9, 0), (12, 0), (8, 1), (12, 1)])
+@pytest.mark.parametrize("k,rule", [(7, 0), (8, 0), (9, 0), (12, 0), (7, 1), (8, 1), (9, 1), (12, 1)])
 def test_one_launch_activation_layers(monkeypatch, k, rule, form):
     force(monkeypatch, form)
     P = int(np.prod(workloads.PRIMES[:k]))

@@ -93,12 +93,12 @@ def test_activation_one_gate_per_lane_digit_path(monkeypatch):
     run_activation(7, "scale", np.random.default_rng(78).integers(0, P7, 200), repeat=2, digits=workloads.DIGITS[7])
 
 
-@pytest.mark.parametrize("k", [7, 8, 9, 12])
-def test_activation_bank_replicated_tables_forced(monkeypatch, k):
+@pytest.mark.parametrize("k,rule", [(7, 0), (8, 0), (9, 0), (12, 0), (7, 1), (8, 1), (9, 1), (12, 1)])
+def test_activation_bank_replicated_tables_forced(monkeypatch, k, rule):
     """the instantiations with bank-replicated AES tables (taken by launches of 2^20 lanes and more: the wide layers
     of configs 2 and 5 and of the model shapes f and F) forced for small layers, for the gate kernels and for the fused
     digit garbler alike: every byte of ReLU and scaling layers of the 7-, 8-, 9- and 12-prime bases (the four digit sets
-    with compile-time kernels) against the oracle"""
+    with compile-time kernels), under both label-length rules, against the oracle"""
     monkeypatch.setenv("DASH_BANKED_MIN_LANES", "1")
     monkeypatch.setenv("DASH_DIGITS_BANKED_MIN_LANES", "1")
     monkeypatch.setenv("DASH_WIDE_MAX_LANES", "0")       # the evaluator's digit gates fused per residue, as on wide layers
@@ -106,8 +106,8 @@ def test_activation_bank_replicated_tables_forced(monkeypatch, k):
     P = int(np.prod(workloads.PRIMES[:k]))
     g = np.random.default_rng(100 + k)
     X = np.concatenate([[0, 1, P // 2 - 1, P // 2, P - 1], g.integers(0, P, 1296)])     # 1301 values: ragged tiles of 1024 lanes
-    run_activation(k, "relu", X, elem_base=2 ** 31 + 3)
-    run_activation(k, "scale", X[:333], repeat=2, elem_base=77)
+    run_activation(k, "relu", X, rule=rule, elem_base=2 ** 31 + 3)
+    run_activation(k, "scale", X[:333], repeat=2, rule=rule, elem_base=77)
 
 
 @pytest.mark.parametrize("wide,sums", [("0", "1"), ("1000000000000", "1"), ("1000000000000", "0")])
