@@ -138,7 +138,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
 
     // a hash of step 1 or 4: by the lane, or by the four lanes of its quad together
     auto hash = [&](const U128& key, uint32_t slot) __attribute__((always_inline)) {
-        if constexpr (Q == 4) return hash_block_quad(key, L.elem_base + e, slot, L.layer, qs, nullptr, tab);
+        if constexpr (Q == 4) return hash_block_quad(key, L.elem_base + e, slot, L.layer, qs, rk, tab);
         else return hash_block(key, L.elem_base + e, slot, L.layer, rk, tab);
     };
     U128 K = {{0, 0, 0, 0}};
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
             auto fetch = [&](int j) __attribute__((always_inline)) {                                   // packed sum of digit j; cleared for the next repetition
                 uint32_t* a = acc + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * EPB) + cel;
 #pragma unroll
-                for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * EPB]; a[i * 2 * EPB] = 0; }
+                for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * EPB]; DASH_WAVE_POINT(); a[i * 2 * EPB] = 0; }
             };
             fetch(n);
 #pragma unroll 1
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
                     k = compress(Mf, [&](int i) __attribute__((always_inline)) { return in[i]; }, &col);
                 }
                 const uint32_t slot = L.chain_slot + soff + (uint32_t)(j > 1 ? j - 2 : n - 1);
-                const U128 h = hash_block_quad(k, L.elem_base + ce, slot, L.layer, qk, nullptr, ctab);
+                const U128 h = hash_block_quad(k, L.elem_base + ce, slot, L.layer, qk, (const uint32_t*)L.key.rk, ctab);
                 if (j > 2) {
                     decompress(Mc, h, [&](int i, uint32_t hd) __attribute__((always_inline)) { cw[i] = submod4(rw[i], hd, Mc); });
                 } else if (j == 2) {

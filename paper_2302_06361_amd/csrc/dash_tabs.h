@@ -4,6 +4,13 @@
 #include "dash_bodies.h"
 #include "dash_internal.h"
 
+// Between a read and a write of one LDS word by different lanes of the SAME wave.  The device needs nothing there: a wave issues an
+// instruction for all its lanes at once, and its LDS accesses complete in order.  A build that runs the lanes one after the other
+// defines it.
+#ifndef DASH_WAVE_POINT
+#define DASH_WAVE_POINT() ((void)0)
+#endif
+
 namespace dash {
 inline namespace DASH_RULE_NS {
 

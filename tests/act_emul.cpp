@@ -1,5 +1,5 @@
-// The library on the CPU through tests/simt: contexts, the evaluator's one-launch activation layers and the repacking of tables, driven
-// through the C ABI over exactly-sized buffers, for the address and undefined-behaviour sanitizers.  Test code, not part of libdash.
+// The library on the CPU through tests/simt: contexts, the evaluator's one-launch activation layers, the repacking of tables and the
+// linear layers without matrix instructions, driven through the C ABI over exactly-sized buffers, for the address and undefined-behaviour sanitizers.  Test code, not part of libdash.
 //
 // One source, three kinds of object:
 //   -DPART_ACT -DDASH_SET=k [-DDASH_RULE_FLOOR]   dash_act_eval.hip
@@ -11,6 +11,12 @@
 //                                           u8 seed[16], labels per residue [n][lam], tables
 //                                      out: u8 labels per residue [n][lam]
 //        act_emul pack <in> <out>      the same in; out: u8 packed tables, tables unpacked from them
+//        act_emul linear <in> <out>    in : int32 k rule batch in_h in_w in_c out_c kh stride pad bias garble shift n_digits; u16 primes[k]
+//                                           digits[n_digits]; u8 seed[16], labels per residue [n_in][lam]; int32 weights[out_c][K], bias[out_c]
+//                                      out: u8 labels per residue [n_out][lam].  Prepared weights start shift bytes past an aligned address.
+#if !defined(PART_ACT) && !defined(PART_GATES)
+#define SIMT_MAIN
+#endif
 #include <hip/hip_runtime.h>
 
 #if defined(PART_ACT)
@@ -46,7 +52,12 @@ ABSENT(int, launch_hg_eval_quad, const dash_ctx*, HgLaunch&, int, hipStream_t)
 #include "../paper_2302_06361_amd/csrc/dash_ctx.hip"
 #include "../paper_2302_06361_amd/csrc/dash_layers.hip"
 
-namespace dash { int linear_layer(dash_ctx*, const dash_layer*, bool, const dash_labels*, dash_labels*, hipStream_t) { abort(); } }
+#include "../paper_2302_06361_amd/csrc/dash_linear.hip"
+
+namespace dash {          // (the MFMA kernel is not part of this program)
+bool dense_mfma_wanted(const dash_layer*, int64_t) { return false; }
+int dense_mfma(dash_ctx*, const dash_layer*, bool, const dash_labels*, dash_labels*, hipStream_t) { abort(); }
+}
 
 static std::vector<uint8_t> slurp(const char* name) {
     FILE* f = fopen(name, "rb");
@@ -73,13 +84,66 @@ struct Bundle {
         }
     }
     uint8_t* at(int i, int64_t e, uint32_t j) { return (uint8_t*)c.data[i] + (j / 16) * c.chunk_stride[i] + e * 16 + j % 16; }
+    // the labels, residue after residue; false if a digit past the label's length is not zero
+    bool read(dash_ctx* ctx, std::vector<uint8_t>& out) {
+        for (int i = 0; i < ctx->k; i++) {
+            const ModInfo& M = ctx->mods[ctx->prime[i]];
+            for (int64_t e = 0; e < c.n_elem; e++) {
+                for (uint32_t j = 0; j < M.lam; j++) out.push_back(*at(i, e, j));
+                for (uint32_t j = M.lam; j < M.nchunk * 16; j++) if (*at(i, e, j)) return false;
+            }
+        }
+        return true;
+    }
 };
+
+static bool write_out(const char* name, const std::vector<uint8_t>& out) {
+    FILE* f = fopen(name, "wb");
+    return f && fwrite(out.data(), 1, out.size(), f) == out.size() && !fclose(f);
+}
+
+template <class Take> static int linear_main(const char* fout, Take take) {
+    int32_t hd[14];
+    memcpy(hd, take(sizeof(hd)), sizeof(hd));
+    const int k = hd[0], nd = hd[13];
+    std::vector<uint16_t> primes(k), digits(nd);
+    memcpy(primes.data(), take(2 * k), 2 * k);
+    memcpy(digits.data(), take(2 * nd), 2 * nd);
+    const uint8_t* seed = take(16);
+    dash_ctx* ctx = nullptr;
+    check(dash_ctx_create(&ctx, primes.data(), k, hd[1], nullptr, seed, digits.data(), nd, 0), "dash_ctx_create");
+    dash_layer L;
+    memset(&L, 0, sizeof(L));
+    L.kind = hd[3] == 1 && hd[4] == 1 && hd[7] == 1 ? DASH_DENSE : DASH_CONV2D;
+    L.layer_id = 1; L.n_elem = hd[2]; L.in_h = hd[3]; L.in_w = hd[4]; L.in_c = hd[5]; L.out_c = hd[6]; L.kh = L.kw = hd[7]; L.stride = hd[8]; L.pad = hd[9];
+    const int64_t n_in = (int64_t)hd[2] * hd[3] * hd[4] * hd[5];
+    const int K = hd[7] * hd[7] * hd[5];
+    Bundle a(ctx, n_in);
+    for (int i = 0; i < k; i++)
+        for (int64_t e = 0; e < n_in; e++)
+            for (uint32_t j = 0; j < ctx->mods[primes[i]].lam; j++) *a.at(i, e, j) = *take(1);
+    std::vector<int32_t> w((size_t)hd[6] * K), bias(hd[6]);
+    memcpy(w.data(), take(4 * w.size()), 4 * w.size());
+    memcpy(bias.data(), take(4 * bias.size()), 4 * bias.size());
+    uint8_t* prepared;
+    if (hipMalloc(&prepared, hd[12] + dash_weights_bytes(ctx, hd[6], K))) return 3;
+    check(dash_weights_prepare(ctx, w.data(), hd[6], K, prepared + hd[12], nullptr), "dash_weights_prepare");
+    L.weights = prepared + hd[12];
+    L.bias = hd[10] ? bias.data() : nullptr;
+    int64_t oe;
+    check(dash_layer_sizes(ctx, &L, &oe, nullptr, nullptr), "dash_layer_sizes");
+    Bundle o(ctx, oe * hd[2]);
+    check(hd[11] ? dash_garble_layer(ctx, &L, &a.c, &o.c, nullptr, nullptr, nullptr) : dash_eval_layer(ctx, &L, &a.c, nullptr, &o.c, nullptr, nullptr), "layer");
+    std::vector<uint8_t> out;
+    return o.read(ctx, out) && write_out(fout, out) ? 0 : 5;
+}
 
 int main(int argc, char** argv) {
     if (argc != 4) return 2;
     const std::vector<uint8_t> in = slurp(argv[2]);
     const uint8_t* p = in.data();
     auto take = [&](size_t n) { if (p + n > in.data() + in.size()) exit(2); const uint8_t* at = p; p += n; return at; };
+    if (!strcmp(argv[1], "linear")) return linear_main(argv[3], take);
     int32_t hd[8];
     uint64_t elem_base;
     memcpy(hd, take(32), 32);
@@ -114,13 +178,7 @@ int main(int argc, char** argv) {
         if (hipMalloc(&scratch, sb + 256)) return 3;
         Bundle& o = hd[6] ? a : other;
         check(dash_eval_layer(ctx, &L, &a.c, tables, &o.c, scratch, nullptr), "dash_eval_layer");
-        for (int i = 0; i < k; i++) {
-            const ModInfo& M = ctx->mods[primes[i]];
-            for (int e = 0; e < n; e++) {
-                for (uint32_t j = 0; j < M.lam; j++) out.push_back(*o.at(i, e, j));
-                for (uint32_t j = M.lam; j < M.nchunk * 16; j++) if (*o.at(i, e, j)) { fprintf(stderr, "pad digits not zero\n"); return 5; }
-            }
-        }
+        if (!o.read(ctx, out)) { fprintf(stderr, "pad digits not zero\n"); return 5; }
         free(scratch);
     } else {
         size_t pb = 0;
@@ -135,8 +193,7 @@ int main(int argc, char** argv) {
         out.insert(out.end(), tables, tables + tb);
         free(packed);
     }
-    FILE* f = fopen(argv[3], "wb");
-    if (!f || fwrite(out.data(), 1, out.size(), f) != out.size() || fclose(f)) return 2;
+    if (!write_out(argv[3], out)) return 2;
     free(buf);
     for (int i = 0; i < k; i++) { free(a.c.data[i]); free(other.c.data[i]); }
     dash_ctx_destroy(ctx);

@@ -17,7 +17,6 @@
 #include <stdlib.h>
 #include <string.h>
 #include <sys/mman.h>
-#include <ucontext.h>
 
 #include <functional>
 #include <vector>
@@ -38,10 +37,10 @@ inline uint4 make_uint4(uint32_t x, uint32_t y, uint32_t z, uint32_t w) { return
 namespace simt {
 constexpr size_t kStack = 512 << 10;
 enum { RUN, AT_WAVE, AT_BLOCK, ENDED };
-struct Lane { ucontext_t ctx; char* stack; void* fake; uint32_t id; int state; int value; bool there; };
+struct Lane { void* sp; char* stack; void* fake; uint32_t id; int state; int value; bool there; };
 inline std::vector<Lane> lanes;
 inline Lane* cur;
-inline ucontext_t main_ctx;
+inline void* main_sp;
 inline void* main_fake;
 inline const void* main_stack;
 inline size_t main_size;
@@ -52,24 +51,50 @@ struct Dynamic { char* p; size_t size; };
 inline std::vector<Dynamic>& dynamic() { static std::vector<Dynamic> d; return d; }
 struct dynamic_lds { dynamic_lds(void* p, size_t size) { dynamic().push_back({(char*)p, size}); } };
 
+// saves the callee's registers and the stack pointer, goes on where another fiber did (swapcontext changes the signal mask with a system
+// call, and the sanitizer's version of it clears the shadow of the whole stack every time)
+extern "C" void simt_switch(void** save, void* to);
+#if defined(SIMT_MAIN)
+asm(R"(
+.globl simt_switch
+.type simt_switch,@function
+simt_switch:
+    pushq %rbp
+    pushq %rbx
+    pushq %r12
+    pushq %r13
+    pushq %r14
+    pushq %r15
+    movq %rsp, (%rdi)
+    movq %rsi, %rsp
+    popq %r15
+    popq %r14
+    popq %r13
+    popq %r12
+    popq %rbx
+    popq %rbp
+    retq
+)");
+#endif
+
 inline void enter() {
     __sanitizer_finish_switch_fiber(nullptr, &main_stack, &main_size);
     (*body)();
     cur->state = ENDED;
     __sanitizer_start_switch_fiber(nullptr, main_stack, main_size);
-    swapcontext(&cur->ctx, &main_ctx);
+    simt_switch(&cur->sp, main_sp);
 }
 inline void wait(int state) {
     Lane* me = cur;
     me->state = state;
     __sanitizer_start_switch_fiber(&me->fake, main_stack, main_size);
-    swapcontext(&me->ctx, &main_ctx);
+    simt_switch(&me->sp, main_sp);
     __sanitizer_finish_switch_fiber(me->fake, &main_stack, &main_size);
 }
 inline void resume(Lane& l) {
     cur = &l;
     __sanitizer_start_switch_fiber(&main_fake, l.stack, kStack);
-    swapcontext(&main_ctx, &l.ctx);
+    simt_switch(&main_sp, l.sp);
     __sanitizer_finish_switch_fiber(main_fake, nullptr, nullptr);
 }
 // opens a barrier of the lanes first .. first + n - 1 if all that are left stand at it (a barrier of a wave: all that are in the same
@@ -96,9 +121,11 @@ inline void run_block() {
     for (uint32_t i = 0; i < n; i++) {
         Lane& l = lanes[i];
         l.id = i; l.state = RUN; l.fake = nullptr; l.there = false;
-        getcontext(&l.ctx);
-        l.ctx.uc_stack.ss_sp = l.stack; l.ctx.uc_stack.ss_size = kStack; l.ctx.uc_link = nullptr;
-        makecontext(&l.ctx, enter, 0);
+        void** top = (void**)(l.stack + kStack) - 1;              // first switch: six registers, then a return into enter()
+        *top = nullptr;
+        *--top = (void*)enter;
+        for (int r = 0; r < 6; r++) *--top = nullptr;
+        l.sp = top;
     }
     for (;;) {
         for (uint32_t i = 0; i < n; i++) { Lane& l = lanes[reverse ? n - 1 - i : i]; if (l.state == RUN) resume(l); }
@@ -150,6 +177,30 @@ inline uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
     }
     return r;
 }
+inline uint32_t lane_id() { return cur->id & 63u; }
+// v_permlane32_swap / v_permlane16_swap: the upper half (odd rows of 16) of a against the lower half (even rows) of b
+struct Pair { uint32_t v[2]; uint32_t operator[](int i) const { return v[i]; } };
+inline Pair swap(uint32_t a, uint32_t b, uint32_t n) {
+    const int l = (int)lane_id(), other = l ^ (int)n;
+    const uint32_t oa = (uint32_t)shfl((int)a, other), ob = (uint32_t)shfl((int)b, other);
+    return l & (int)n ? Pair{{ob, b}} : Pair{{a, oa}};
+}
+// the data-parallel permutes that the sources use: row_ror:8 and quad_perm
+inline uint32_t dpp(uint32_t v, int ctrl) {
+    const int l = (int)lane_id();
+    if (ctrl == 0x128) return (uint32_t)shfl((int)v, (l & ~15) | ((l + 8) & 15));
+    if (ctrl < 0x100) return (uint32_t)shfl((int)v, (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3));
+    abort();
+}
+// ds_swizzle in bit mode: lane = ((lane & and) | or) ^ xor within 32 lanes
+inline uint32_t swizzle(uint32_t v, int pattern) {
+    const int l = (int)lane_id();
+    return (uint32_t)shfl((int)v, (l & 32) | (((l & pattern & 31) | ((pattern >> 5) & 31)) ^ ((pattern >> 10) & 31)));
+}
+inline uint32_t udot4(uint32_t a, uint32_t b, uint32_t c) {
+    for (int i = 0; i < 32; i += 8) c += ((a >> i) & 0xffu) * ((b >> i) & 0xffu);
+    return c;
+}
 struct Tid { uint32_t x, y, z; };
 inline Tid thread_idx() { return Tid{cur->id, 0, 0}; }
 }  // namespace simt
@@ -163,8 +214,14 @@ inline Tid thread_idx() { return Tid{cur->id, 0, 0}; }
 #define __shfl(v, src, width) simt::shfl(v, src)
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_perm simt::perm
+#define __builtin_amdgcn_udot4(a, b, c, clamp) simt::udot4(a, b, c)
+#define __builtin_amdgcn_permlane32_swap(a, b, fi, bc) simt::swap(a, b, 32)
+#define __builtin_amdgcn_permlane16_swap(a, b, fi, bc) simt::swap(a, b, 16)
+#define __builtin_amdgcn_update_dpp(old, v, ctrl, rows, banks, bc) simt::dpp((uint32_t)(v), ctrl)
+#define __builtin_amdgcn_ds_swizzle(v, pattern) simt::swizzle((uint32_t)(v), pattern)
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_wave_barrier() simt::wait(simt::AT_WAVE)
+#define DASH_WAVE_POINT() simt::wait(simt::AT_WAVE)
 #define __builtin_amdgcn_kernarg_segment_ptr() simt::kernarg
 
 typedef int hipError_t;
