@@ -7,7 +7,7 @@
 //
 //   k_weights_prepare : int32 weights -> per-prime int8 residues in [0, p), rows padded to 64
 //   k_linear_tile     : any shape; one lane per (output pixel, 16-digit chunk) and CO output channels
-//   k_linear_split    : few outputs and a long reduction; one wave per (output pixel, 16-digit chunk) and CO output channels
+//   k_linear_split    : few outputs or few channels; a wave or 16 lanes per (output pixel, 16-digit chunk) and CO output channels
 //   (dense layers that fill MFMA tiles go to k_dense_mfma in dash_gemm.hip)
 //   k_sumpool         : 2x2 sum, stride 2
 #include <string.h>
@@ -90,8 +90,10 @@ __device__ __forceinline__ uint32_t bias_of(const int32_t* bias, int co, const M
 // One lane per (output pixel, chunk), CO output channels; blockIdx.y = prime, blockIdx.z = block of CO channels.  The taps are the same
 // for all lanes: their offsets, the weights and the loop run on the scalar unit.  Bound by vector issue: 32 permutes and 16 CO dot
 // products per four taps.  (One lane per output value repeated loads, permutes and 64-bit address arithmetic for every channel:
-// 6 -> 16 channels, 5 x 5, 14 x 14, batch 16, 8 primes: 131 us; CO = 8: 49 us.)
-template <int CO, bool Aligned>
+// 6 -> 16 channels, 5 x 5, 14 x 14, batch 16, 8 primes: 131 us; CO = 8: 49 us.)  CO = 1 and 4 serve few channels.
+// D: groups of four taps in flight.  Two where the accumulators fill the registers; four for CO = 1 (5 x 5 over 28 x 28 x 6 -> 1, batch
+// 16, 8 primes: 139 us with two, 121 with four).
+template <int CO, bool Aligned, int D>
 __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
     const LinPrime& P = A.pr[blockIdx.y];
     const ModInfo M = ld_mod(A.mods, P.p);
@@ -127,15 +129,17 @@ __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
             }
         }
     };
-    // the next group's loads go out before the current one is multiplied (few waves fit beside 16 CO accumulators)
-    Group ga, gb;
-    load(0, ga);
-    for (int k0 = 0; k0 < K; k0 += 8) {
-        if (k0 + 4 < K) load(k0 + 4, gb);
-        dot_group<CO>(ga.v, ga.w4, acc);
-        if (k0 + 4 >= K) break;
-        if (k0 + 8 < K) load(k0 + 8, ga);
-        dot_group<CO>(gb.v, gb.w4, acc);
+    // the next groups' loads go out before the current one is multiplied (few waves fit beside 16 CO accumulators)
+    Group g[D];
+#pragma unroll
+    for (int d = 0; d + 1 < D; d++) if (4 * d < K) load(4 * d, g[d]);
+    for (int k0 = 0; k0 < K; k0 += 4 * D) {
+#pragma unroll
+        for (int d = 0; d < D; d++) {
+            if (k0 + 4 * d >= K) break;
+            if (k0 + 4 * (d + D - 1) < K) load(k0 + 4 * (d + D - 1), g[(d + D - 1) % D]);
+            dot_group<CO>(g[d].v, g[d].w4, acc);
+        }
     }
     uint32_t one[4] = {0, 0, 0, 0};
     if (A.bias) { const uint4 o = *(const uint4*)(P.one + 16 * ch); one[0] = o.x; one[1] = o.y; one[2] = o.z; one[3] = o.w; }
@@ -159,17 +163,22 @@ __global__ __launch_bounds__(kThreads) void k_linear_tile(const LinArgs A) {
     }
 }
 
-// One wave per (output pixel, chunk), 8 output channels; blockIdx.y = prime.  The lanes deal the reduction index out in groups of four;
-// the 128 sums are then added up over the wave so that lane l ends with the two of channel l / 8, digits 2 (l % 8) and + 1.  For layers
-// whose outputs do not fill the chip: the loop is 64 times shorter, at about 300 instructions for the addition.  (3 x 3 over 3 x 3 x 128 -> 128, 7 primes: 21 -> 11 us, the
-// rate of the host's calls; 4096 -> 256, 12 primes: 46 -> 33 us.)
+// S lanes (a wave, or a row of 16 lanes) per (output pixel, chunk), CO output channels; blockIdx.y = prime.  The lanes deal the reduction
+// index out in groups of four; the 16 CO sums are then added up over the S lanes so that lane l ends with 16 CO / S consecutive ones of
+// the CO x 16 (channel, digit).
+// S = 64, CO = 8: layers whose outputs do not fill the chip.  The loop is 64 times shorter than a lane per output's, at about 300
+// instructions for the addition.  (3 x 3 over 3 x 3 x 128 -> 128, 7 primes: 21 -> 11 us, the rate of the host's calls; 4096 -> 256, 12
+// primes: 46 -> 33 us.)
+// S = 16, CO = 1, 2, 4: layers of up to four output channels.  The 16 lanes read 1024 consecutive bytes of a pixel's channels, where
+// neighbouring lanes of k_linear_tile read a word of different pixels each (times at linear_form_by_shape).
+template <int CO, int S>
 __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
-    constexpr int CO = 8;
+    static_assert(S == 64 || S == 16, "a wave or a row of lanes");
     const LinPrime& P = A.pr[blockIdx.y];
     const ModInfo M = ld_mod(A.mods, P.p);
-    const uint32_t lane = threadIdx.x & 63u, n_px = (uint32_t)A.batch * A.out_h * A.out_w, njb = ((uint32_t)A.out_c + CO - 1) / CO;
-    const uint32_t unit = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (unit >= n_px * njb * M.nchunk) return;                              // (n_px * njb * nchunk < 2^26: linear_split_fits)
+    const uint32_t lane = threadIdx.x % S, n_px = (uint32_t)A.batch * A.out_h * A.out_w, njb = ((uint32_t)A.out_c + CO - 1) / CO;
+    const uint32_t sub = threadIdx.x / S, unit = blockIdx.x * (kThreads / S) + (S == 64 ? __builtin_amdgcn_readfirstlane(sub) : sub);
+    if (unit >= n_px * njb * M.nchunk) return;                              // (n_px * njb * nchunk < 2^32 / S: linear_split_fits)
     const uint32_t ch = unit / (n_px * njb), u = unit - ch * (n_px * njb), px = u / njb, co0 = (u - px * njb) * CO;
     const uint32_t row = px / (uint32_t)A.out_w, ox = px - row * A.out_w, b = row / (uint32_t)A.out_h, oy = row - b * A.out_h;
     const int iy0 = (int)oy * A.stride - A.pad, ix0 = (int)ox * A.stride - A.pad;
@@ -178,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
     const int8_t* wrow = P.w + (int64_t)co0 * A.kpad;
     uint32_t acc[CO][16] = {};
     const uint32_t K = (uint32_t)A.kh * A.kw * A.in_c;
-    for (uint32_t k0 = 4 * lane; k0 < K; k0 += 256) {
+    for (uint32_t k0 = 4 * lane; k0 < K; k0 += 4 * S) {
         uint32_t w4[CO];
 #pragma unroll
         for (int c = 0; c < CO; c++) __builtin_memcpy(&w4[c], wrow + (int64_t)c * A.kpad + k0, 4);      // (at any address)
@@ -193,18 +202,21 @@ __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
         }
         dot_group<CO>(v, w4, acc);
     }
-    // add up: halves of the wave, halves of 32 lanes (swaps), then within rows of 16 lanes (each lane keeps the half its bit names)
+    // add up over the S lanes: halves of the wave, halves of 32 lanes (swaps), then within rows of 16 lanes; each lane keeps the half of
+    // its sums that its bit names
     uint32_t* s = &acc[0][0];
+    if constexpr (S == 64) {
 #pragma unroll
-    for (int i = 0; i < 64; i++) { const auto r = __builtin_amdgcn_permlane32_swap(s[i], s[i + 64], false, false); s[i] = r[0] + r[1]; }
+        for (int i = 0; i < 8 * CO; i++) { const auto r = __builtin_amdgcn_permlane32_swap(s[i], s[i + 8 * CO], false, false); s[i] = r[0] + r[1]; }
 #pragma unroll
-    for (int i = 0; i < 32; i++) { const auto r = __builtin_amdgcn_permlane16_swap(s[i], s[i + 32], false, false); s[i] = r[0] + r[1]; }
+        for (int i = 0; i < 4 * CO; i++) { const auto r = __builtin_amdgcn_permlane16_swap(s[i], s[i + 4 * CO], false, false); s[i] = r[0] + r[1]; }
+    }
 #pragma unroll
-    for (int d = 8, n = 16; d >= 1; d >>= 1, n >>= 1) {
-        const bool up = (lane & d) != 0;
+    for (int d = 8, n = 128 * CO / S; d >= 1; d >>= 1, n >>= 1) {
+        const uint32_t up = (lane & d) ? ~0u : 0u;         // (a mask: selects were turned into a search for the index i + n or i in registers)
 #pragma unroll
         for (int i = 0; i < n; i++) {
-            const uint32_t keep = up ? s[i + n] : s[i], send = up ? s[i] : s[i + n];
+            const uint32_t keep = (s[i + n] & up) | (s[i] & ~up), send = (s[i] & up) | (s[i + n] & ~up);
             uint32_t got;
             if (d == 8) got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x128, 0xf, 0xf, true);         // row_ror:8
             else if (d == 4) got = (uint32_t)__builtin_amdgcn_ds_swizzle((int)send, (4 << 10) | 0x1f);           // lane ^ 4
@@ -213,16 +225,25 @@ __global__ __launch_bounds__(kThreads) void k_linear_split(const LinArgs A) {
             s[i] = keep + got;
         }
     }
-    // sum index of s[0], s[1]: 64 (lane bit 5) + 32 (bit 4) + 16, 8, 4, 2 (bits 3..0): channel lane / 8, digits 2 (lane % 8), + 1
-    const int co = (int)(co0 + lane / 8), dg = 2 * (int)(lane % 8);
+    constexpr uint32_t kSums = 16 * CO / S;
+    const int co = (int)(co0 + lane * kSums / 16), dg = (int)(lane * kSums % 16);
     if (co >= A.out_c) return;
-    uint32_t r0 = reduce_acc(s[0], M), r1 = reduce_acc(s[1], M);
-    if (A.bias) {
-        const uint32_t bm = bias_of(A.bias, co, M);
-        r0 = mod_m(r0 + mul24(bm, P.one[16 * ch + dg]), M);
-        r1 = mod_m(r1 + mul24(bm, P.one[16 * ch + dg + 1]), M);
+    const uint32_t bm = A.bias ? bias_of(A.bias, co, M) : 0;
+    uint32_t w = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kSums; i++) {
+        uint32_t r = reduce_acc(s[i], M);
+        if (A.bias) r = mod_m(r + mul24(bm, P.one[16 * ch + dg + i]), M);
+        w |= r << (8 * i);
     }
-    *(uint16_t*)(P.out.p + (int64_t)ch * P.out.cs + ((uint64_t)px * A.out_c + co) * 16 + dg) = (uint16_t)(r0 | (r1 << 8));
+    // neighbouring lanes put a dword together for one store
+    if constexpr (kSums < 4) {
+        w <<= 8 * (dg % 4);
+        w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xf, 0xf, true);                              // quad_perm:[1,0,3,2]
+        if constexpr (kSums == 1) w |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xf, 0xf, true);    // quad_perm:[2,3,0,1]
+        if (dg % 4) return;
+    }
+    *(uint32_t*)(P.out.p + (int64_t)ch * P.out.cs + ((uint64_t)px * A.out_c + co) * 16 + dg) = w;
 }
 
 struct PoolPrime { uint32_t p; LView in, out; };
@@ -302,7 +323,7 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
     int64_t chunks = 0;
     int nch = 1;                // chunks of all primes, of the prime with the most (the others' surplus blocks exit)
     for (int i = 0; i < c->k; i++) { chunks += c->mods[c->prime[i]].nchunk; nch = (int)c->mods[c->prime[i]].nchunk > nch ? (int)c->mods[c->prime[i]].nchunk : nch; }
-    const int f = linear_form(c->linear_form, LinearShape{npx, chunks, nch, out_c, K, dense_mfma_wanted(L, batch)});
+    const int f = linear_form(c->linear_form, LinearShape{npx, chunks, nch, out_c, K, L->in_c, dense_mfma_wanted(L, batch)});
     if (f == LINEAR_MFMA) return dense_mfma(c, L, garble, in, out, s);
     LinArgs A;
     memset(&A, 0, sizeof(A));
@@ -322,15 +343,17 @@ int linear_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_label
     }
     {
         ProfScope ps(c->prof, DASH_PROF_LINEAR, s, macs, bytes);
-        const int co = f == LINEAR_TILE4 && !((uintptr_t)L->weights & 3) ? 4 : 8, blocks = (out_c + co - 1) / co;
-        if (f == LINEAR_SPLIT)
-            hipLaunchKernelGGL(k_linear_split, dim3((uint32_t)((npx * ((out_c + 7) / 8) * nch + kThreads / 64 - 1) / (kThreads / 64)), c->k), dim3(kThreads), 0, s, A);
-        else for (int at = 0; at < blocks; at += 65535) {                   // (the grid's third dimension ends at 65535)
+        const bool aligned = !((uintptr_t)L->weights & 3);
+        const int lanes = linear_split_lanes(f), co = !lanes && !aligned ? 8 : linear_form_channels(f), blocks = (out_c + co - 1) / co;
+        if (lanes) {
+            const dim3 grid((uint32_t)((npx * blocks * nch * lanes + kThreads - 1) / kThreads), c->k);
+            auto kernel = f == LINEAR_ROW1 ? k_linear_split<1, 16> : f == LINEAR_ROW2 ? k_linear_split<2, 16> : f == LINEAR_ROW4 ? k_linear_split<4, 16> : k_linear_split<8, 64>;
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, A);
+        } else for (int at = 0; at < blocks; at += 65535) {                 // (the grid's third dimension ends at 65535)
             A.co_first = at * co;
             const dim3 grid((uint32_t)((npx * nch + kThreads - 1) / kThreads), c->k, blocks - at < 65535 ? blocks - at : 65535);
-            if ((uintptr_t)L->weights & 3) hipLaunchKernelGGL((k_linear_tile<8, false>), grid, dim3(kThreads), 0, s, A);
-            else if (co == 8) hipLaunchKernelGGL((k_linear_tile<8, true>), grid, dim3(kThreads), 0, s, A);
-            else hipLaunchKernelGGL((k_linear_tile<4, true>), grid, dim3(kThreads), 0, s, A);
+            auto kernel = !aligned ? k_linear_tile<8, false, 2> : co == 1 ? k_linear_tile<1, true, 4> : co == 4 ? k_linear_tile<4, true, 2> : k_linear_tile<8, true, 2>;
+            hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, A);
         }
     }
     DASH_HIP(hipGetLastError());

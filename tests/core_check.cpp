@@ -104,7 +104,7 @@ uint32_t cc_axpymod4(uint32_t a, uint32_t c, uint32_t b, int m) { ModInfo M; fil
 uint32_t cc_mod_m(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return mod_m(n, M); }
 uint32_t cc_div_any(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return div_any(n, M); }
 // kernel of a linear layer
-int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int mfma) {
-    return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, mfma != 0});
+int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int in_c, int mfma) {
+    return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, in_c, mfma != 0});
 }
 }

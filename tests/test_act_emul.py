@@ -20,7 +20,7 @@ CLANG = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "c
 FLAGS = ["-x", "c++", "-std=c++17", "-O1", "-g1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-I", os.path.join(HERE, "simt"),
          "-Wno-unknown-pragmas", "-Wno-pass-failed", "-c", os.path.join(HERE, "act_emul.cpp")]
 BIG = "1000000000"
-LINEAR_FORMS = ["1", "2", "3"]
+LINEAR_FORMS = ["1", "2", "3", "5", "6", "7", "8"]
 
 
 @pytest.fixture(scope="module")

@@ -128,9 +128,9 @@ def test_dense_mfma_both_tile_shapes(monkeypatch, mfma):
         run_linear(12, 2, 9, 7, 12, 40, 3, 2, 1, -16, 15, True, 44)
 
 
-@pytest.mark.parametrize("form", ["1", "2", "3"])
+@pytest.mark.parametrize("form", ["1", "2", "3", "5", "6", "7", "8"])
 def test_linear_forms(monkeypatch, form):
-    """each kernel at the edges of its blocks: 4 and 8 output channels, 4 and 256 entries of the reduction, taps in the padding"""
+    """each kernel at the edges of its blocks: 1, 2, 4 and 8 output channels, 4, 64 and 256 entries of the reduction, taps in the padding"""
     monkeypatch.setenv("DASH_LINEAR_FORM", form)
     for i, (K, out_c) in enumerate(((1, 1), (3, 4), (4, 5), (255, 8), (257, 9), (513, 33))):
         run_linear(7, 3, 1, 1, K, out_c, 1, 1, 0, -64, 63, i % 2 == 0, 50 + i, garble=i % 3 == 0)
@@ -139,9 +139,11 @@ def test_linear_forms(monkeypatch, form):
     run_linear(8, 1, 5, 5, 7, 2, 5, 1, 2, -8, 7, True, 62, garble=False)
     run_linear(8, 3, 9, 8, 5, 17, 4, 3, 0, -8, 7, False, 63)
     run_linear(12, 1, 4, 4, 65, 7, 2, 2, 0, -8, 7, False, 64)
+    for i, (K, out_c) in enumerate(((5, 2), (63, 3), (64, 1), (65, 2), (129, 4))):
+        run_linear(7, 21, 1, 1, K, out_c, 1, 1, 0, -64, 63, i % 2 == 0, 65 + i)
 
 
-@pytest.mark.parametrize("form", ["1", "2", "3", "4"])
+@pytest.mark.parametrize("form", ["1", "2", "3", "4", "5", "6", "7", "8"])
 def test_linear_weights_at_odd_address(monkeypatch, form):
     """prepared weights have no alignment of their own"""
     monkeypatch.setenv("DASH_LINEAR_FORM", form)

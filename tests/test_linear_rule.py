@@ -6,7 +6,9 @@ import subprocess
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-TILE4, TILE8, SPLIT, MFMA = 1, 2, 3, 4
+TILE4, TILE8, SPLIT, MFMA, TILE1, ROW1, ROW2, ROW4 = 1, 2, 3, 4, 5, 6, 7, 8
+CHANNELS = {SPLIT: 8, ROW1: 1, ROW2: 2, ROW4: 4}
+LANES = {SPLIT: 64, ROW1: 16, ROW2: 16, ROW4: 16}
 CHUNKS = {7: 29, 8: 31, 9: 33, 12: 39}      # 16-digit chunks of the labels of the first k primes
 
 
@@ -16,24 +18,37 @@ def form(tmp_path_factory):
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "core_check.cpp")])
     lib = C.CDLL(so)
 
-    def f(npx, out_c, K, k=8, mfma=False, forced=0):
-        return lib.cc_linear_form(forced, C.c_int64(npx), C.c_int64(CHUNKS[k]), 8, out_c, K, int(mfma))
+    def f(npx, out_c, K, k=8, mfma=False, forced=0, in_c=16):
+        return lib.cc_linear_form(forced, C.c_int64(npx), C.c_int64(CHUNKS[k]), 8, out_c, K, in_c, int(mfma))
     f.lib = lib
     return f
 
 
-def test_split_form_only_where_a_grid_holds_it(form):
-    """a wave per (pixel, chunk, 8 channels): fewer than 2^32 lanes, whatever asks for the form"""
+def lanes(f, npx, out_c):
+    return npx * ((out_c + CHANNELS[f] - 1) // CHANNELS[f]) * 8 * LANES[f]
+
+
+def test_split_forms_only_where_a_grid_holds_them(form):
+    """a wave or a row of lanes per (pixel, chunk, block of channels): fewer than 2^32 lanes, whatever asks for the form"""
     assert form(2 ** 22 - 1, 16, 64, forced=SPLIT) == SPLIT
-    assert form(2 ** 22, 16, 64, forced=SPLIT) != SPLIT               # 2^22 * 2 * 8 waves = 2^32 lanes
-    assert form(2 ** 31 - 1, 1, 1, forced=SPLIT) != SPLIT
+    assert form(2 ** 22, 16, 64, forced=SPLIT) == TILE8               # 2^22 * 2 * 8 waves = 2^32 lanes
+    assert form(2 ** 25 - 1, 1, 64, forced=ROW1) == ROW1 and form(2 ** 25, 1, 64, forced=ROW1) == TILE8
     for e in range(31):
-        for out_c in (1, 9, 257, 4097):
+        for out_c in (1, 2, 3, 4, 5, 9, 257, 4097):
             for K in (1, 64, 257, 70000):
-                for mfma in (False, True):
-                    npx = 2 ** e
-                    if npx * out_c < 2 ** 31 and form(npx, out_c, K, mfma=mfma) == SPLIT:
-                        assert npx * ((out_c + 7) // 8) * 8 < 2 ** 26, (npx, out_c, K, mfma)
+                for forced in (0, SPLIT, ROW1, ROW2, ROW4):
+                    for mfma in (False, True):
+                        for in_c in (1, 9):
+                            f = form(2 ** e, out_c, K, mfma=mfma, forced=forced, in_c=in_c) if 2 ** e * out_c < 2 ** 31 else 0
+                            assert f not in LANES or lanes(f, 2 ** e, out_c) < 2 ** 32, (2 ** e, out_c, K, mfma, forced)
+
+
+def test_few_channels_take_a_form_for_few_channels(form):
+    """up to four channels: a row of lanes, or a lane per pixel where neighbouring pixels share cache lines; a wave for a long reduction"""
+    assert form(64 * 784, 1, 25, in_c=1) == TILE1 and form(64 * 784, 2, 25, in_c=1) == TILE4
+    assert form(784, 1, 288, in_c=32) == ROW1 and form(784, 2, 288, in_c=32) == ROW2 and form(784, 4, 288, in_c=32) == ROW4
+    assert form(2048, 1, 100, in_c=100) == ROW1
+    assert form(1, 1, 4096, k=12, in_c=4096) == SPLIT                 # (a chain of 64 loads by a row of lanes, of 16 by a wave)
 
 
 # (batch or pixels, out_c, K, primes) of the MFMA tests on the GPU
