@@ -220,7 +220,8 @@ DASH_HD ModInfo ld_mod(const ModInfo* mods, uint32_t m) {
 }
 template <class MI> DASH_HD uint32_t div_m(uint32_t n, const MI& M) { return mulhi(n, M.mmagic); }           // n < 2^24
 template <class MI> DASH_HD uint32_t mod_m(uint32_t n, const MI& M) { return n - mul24(div_m(n, M), M.m); }  // n < 2^24
-// floor(n / m) for any n < 2^32 (wave-uniform n: scalar unit): the rounded-up reciprocal is too large by at most one
+// floor(n / m) for n <= 2^32 - m (wave-uniform n: scalar unit): the rounded-up reciprocal is too large by at most one, and q m must not
+// pass 2^32 (callers: the first row of a tile, a multiple of 256 below 2^32)
 template <class MI> DASH_HD uint32_t div_any(uint32_t n, const MI& M) { const uint32_t q = mulhi(n, M.mmagic); return q - (q * M.m > n ? 1u : 0u); }
 DASH_HD uint32_t byte_of(uint32_t w, int b) { return (w >> (8 * b)) & 0xffu; }
 

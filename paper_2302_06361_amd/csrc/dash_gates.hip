@@ -10,8 +10,8 @@
 // A launch carries up to 16 homogeneous gate batches ("jobs", blockIdx.y); every lane of a block
 // works on the same pair of moduli, so all modulus-dependent control flow is wave-uniform.  The
 // moduli that carry nearly all of the work (the CRT primes and the accumulation moduli of the
-// default digit sets, under the ceil label-length rule) run through compile-time descriptions; any
-// other modulus takes the same code with run-time constants.
+// default digit sets, with the label lengths of the rule this file is compiled for) run through compile-time
+// descriptions; any other modulus or length takes the same code with run-time constants.
 #include "dash_tabs.h"
 
 namespace dash {
@@ -80,7 +80,7 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 // need no LDS: 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.  The segments of a
 // layer differ in length by a factor of 50, so the waves share the concatenation of their tiles, a contiguous range each.
 // (One lane per row, run-time constants and the same number of blocks for every segment took 6.0 ms for the 5.1 GB of tables of a
-// LeNet batch of 4; this form takes 2.2.)
+// LeNet batch of 4; this form takes 3.3.)
 template <bool Pack>
 __global__ __launch_bounds__(kThreads) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
