@@ -28,7 +28,7 @@ def by_rule(exe, rule):
 @pytest.fixture(scope="module")
 def built():
     """all emulation programs, compiled side by side (most of this module's time is their compilation)"""
-    procs = [(name, subprocess.Popen(["g++", "-O1", "-g", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"] + flags +
+    procs = [(name, subprocess.Popen(["g++", "-O1", "-g1", "-std=c++17", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"] + flags +
                                      ["-o", os.path.join(HERE, name + ".bin"), os.path.join(HERE, src + ".cpp")],
                                      stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)) for name, src, flags in PROGRAMS]
     for name, pr in procs:
