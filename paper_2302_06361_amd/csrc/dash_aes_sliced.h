@@ -27,18 +27,6 @@ struct Bop3 {
     }
 };
 
-// bytes of (hi:lo) picked by the four selector bytes (0..3 from lo, 4..7 from hi)
-DASH_HD uint32_t pick_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_perm(hi, lo, sel);
-#else
-    const uint64_t v = ((uint64_t)hi << 32) | lo;
-    uint32_t r = 0;
-    for (int k = 0; k < 4; k++) r |= (uint32_t)((v >> (8 * ((sel >> (8 * k)) & 7u))) & 0xffu) << (8 * k);
-    return r;
-#endif
-}
-
 // One stage of the 32 x 32 bit transposition: the bits of a whose index has bit J set change places with the bits
 // of b whose index has it clear.
 template <int J> DASH_HD void swap_stage(uint32_t& a, uint32_t& b) {

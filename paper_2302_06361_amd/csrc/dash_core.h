@@ -225,11 +225,28 @@ template <class MI> DASH_HD uint32_t mod_m(uint32_t n, const MI& M) { return n -
 template <class MI> DASH_HD uint32_t div_any(uint32_t n, const MI& M) { const uint32_t q = mulhi(n, M.mmagic); return q - (q * M.m > n ? 1u : 0u); }
 DASH_HD uint32_t byte_of(uint32_t w, int b) { return (w >> (8 * b)) & 0xffu; }
 
-// Packed modular addition and subtraction on 4 digits.  The bytes that have to be corrected by m are found as a 0/1 flag per
-// byte, and flag * m is taken off (put on) the whole dword with ONE 32-bit multiplication: each byte of the result lies in
-// [0, m), so the carries and borrows between the bytes of the intermediate dwords cancel.  Six instructions; the byte mask that
-// served before (and, shift, subtract, or, and) took eight, on kernels that are bound by the number of vector instructions.
-constexpr uint32_t kOnes = 0x01010101u;
+// Packed modular addition and subtraction on 4 digits, for kernels that are bound by the number of vector instructions: four for
+// a sum, five for a difference.  Moduli below 128: the bytes of u = a + b + (128 - m) reach 128 where a + b >= m, and then u - 128 is
+// the result; where they do not, it is u - 128 + m.  The flags stay where they are (bit 7 of each byte): the high half of
+// flags * (m << 25) is m in each flagged byte.  Every byte of the result lies in [0, m), so the carries and borrows between the bytes of
+// the intermediate dwords cancel.  (Bringing the flags down to bit 0 and multiplying by m took five and seven.)
+constexpr uint32_t kOnes = 0x01010101u, kTops = 0x80808080u;
+// ~a & b (one v_bitop3_b32 on gfx950, kept from being folded into the additions around it)
+DASH_HD uint32_t andn(uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__) && __has_builtin(__builtin_amdgcn_bitop3_b32)
+    return __builtin_amdgcn_bitop3_b32(a, b, b, 0x0c);
+#else
+    return ~a & b;
+#endif
+}
+// u - 128 in every byte, + m where the byte is below 128 (m < 128).  (u is kept as it is: the compiler would take the constants of its
+// sum and of this one together, which costs an instruction more.)
+DASH_HD uint32_t settle4(uint32_t u, uint32_t m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+v"(u));
+#endif
+    return u + mulhi(andn(u, kTops), m << 25) - kTops;
+}
 // per byte (a + b + (r & 1)) >> 1, without carries between bytes
 DASH_HD uint32_t lerp4(uint32_t a, uint32_t b, uint32_t r) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -244,8 +261,9 @@ DASH_HD uint32_t lerp4(uint32_t a, uint32_t b, uint32_t r) {
 template <class MI>
 DASH_HD uint32_t addmod4(uint32_t a, uint32_t b, const MI& M) {
     if constexpr (cmod_m<MI>::value == 2) return a ^ b;          // digits are bits (one per byte)
+    if (M.m < 128) return settle4(a + b + M.c4, M.m);
     const uint32_t t = a + b;
-    if (M.m <= 128) return t - (((t + M.c4) >> 7) & kOnes) * M.m;                  // bytes of t + c4 reach 128 where t >= m
+    if (M.m == 128) return t & 0x7f7f7f7fu;
     // moduli above 128: the sum does not fit a byte, its half does.  a + b >= m iff (a + b + (m odd)) / 2 >= ceil(m / 2).
     const uint32_t h = lerp4(a, b, (M.m & 1u) * kOnes) + (128u - (M.m + 1u) / 2u) * kOnes;
     return t - ((h >> 7) & kOnes) * M.m;
@@ -254,9 +272,12 @@ DASH_HD uint32_t addmod4(uint32_t a, uint32_t b, const MI& M) {
 template <class MI>
 DASH_HD uint32_t submod4(uint32_t a, uint32_t b, const MI& M) {
     if constexpr (cmod_m<MI>::value == 2) return a ^ b;
+    if (M.m <= 128) {
+        const uint32_t u = (a ^ kTops) - b;                                        // a - b + 128: no borrow between bytes
+        return M.m < 128 ? settle4(u, M.m) : u & 0x7f7f7f7fu;
+    }
     const uint32_t t = a - b;
-    const uint32_t ge = M.m <= 128 ? t + 0x80808080u : lerp4(a, ~b, kOnes);        // top bit of a byte: a >= b
-    return t + (~(ge >> 7) & kOnes) * M.m;
+    return t + andn(lerp4(a, ~b, kOnes) >> 7, kOnes) * M.m;                        // top bit of a byte: a >= b
 }
 // (a + c * b) mod m on 4 packed digits, c < m.
 template <class MI>
@@ -392,6 +413,23 @@ DASH_HD uint32_t aes_column(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, 
         return xor3(xor3(T.template at<0, 0>(a0), T.template at<1, 1>(a1), T.template at<2, 2>(a2)), T.template at<3, 3>(a3), rk);
     }
 }
+// bytes of two words by a selector: 0..3 bytes of lo, 4..7 bytes of hi, 0x0c zero (one v_perm_b32)
+DASH_HD uint32_t pick_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_perm(hi, lo, sel);
+#else
+    const uint64_t v = ((uint64_t)hi << 32) | lo;
+    uint32_t w = 0;
+    for (int i = 0; i < 4; i++) { const uint32_t b = (sel >> (8 * i)) & 0xffu; if (b < 8) w |= (uint32_t)((v >> (8 * b)) & 0xffu) << (8 * i); }
+    return w;
+#endif
+}
+// a column of the last round (SubBytes and ShiftRows only): S[x] sits in bytes 1 and 2 of T0.  Two byte permutes and an exclusive-or
+// instead of four maskings and an exclusive-or
+template <class Tab>
+DASH_HD uint32_t last_column(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t rk, const Tab& T) {
+    return xor3(pick_bytes(T.template at<0, 1>(a1), T.template at<0, 0>(a0), 0x0c0c0501u), pick_bytes(T.template at<0, 3>(a3), T.template at<0, 2>(a2), 0x06020c0cu), rk);
+}
 // rounds R0..10 on the state a
 template <int R0, class Tab>
 DASH_HD void aes_rounds(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint32_t s[4], const uint32_t* rk, const Tab& T) {
@@ -401,19 +439,8 @@ DASH_HD void aes_rounds(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, uint
         const uint32_t b2 = aes_column(a2, a3, a0, a1, rk[4 * r + 2], T), b3 = aes_column(a3, a0, a1, a2, rk[4 * r + 3], T);
         a0 = b0; a1 = b1; a2 = b2; a3 = b3;
     }
-    if constexpr (tab_two<Tab>::value) {
-        // last round: S[x] sits in bytes 1 and 2 of T0 and in bytes 2 and 3 of T1
-        s[0] = (((T.template at<0, 0>(a0) >> 8) & 0xffu) | (T.template at<0, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ rk[40];
-        s[1] = (((T.template at<0, 0>(a1) >> 8) & 0xffu) | (T.template at<0, 1>(a2) & 0xff00u) | (T.template at<0, 2>(a3) & 0xff0000u) | (T.template at<1, 3>(a0) & 0xff000000u)) ^ rk[41];
-        s[2] = (((T.template at<0, 0>(a2) >> 8) & 0xffu) | (T.template at<0, 1>(a3) & 0xff00u) | (T.template at<0, 2>(a0) & 0xff0000u) | (T.template at<1, 3>(a1) & 0xff000000u)) ^ rk[42];
-        s[3] = (((T.template at<0, 0>(a3) >> 8) & 0xffu) | (T.template at<0, 1>(a0) & 0xff00u) | (T.template at<0, 2>(a1) & 0xff0000u) | (T.template at<1, 3>(a2) & 0xff000000u)) ^ rk[43];
-    } else {
-        // last round: SubBytes + ShiftRows only.  S[x] sits in byte 0 of T2, byte 1 of T3, byte 2 of T0, byte 3 of T1.
-        s[0] = ((T.template at<2, 0>(a0) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u) | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ rk[40];
-        s[1] = ((T.template at<2, 0>(a1) & 0xffu) | (T.template at<3, 1>(a2) & 0xff00u) | (T.template at<0, 2>(a3) & 0xff0000u) | (T.template at<1, 3>(a0) & 0xff000000u)) ^ rk[41];
-        s[2] = ((T.template at<2, 0>(a2) & 0xffu) | (T.template at<3, 1>(a3) & 0xff00u) | (T.template at<0, 2>(a0) & 0xff0000u) | (T.template at<1, 3>(a1) & 0xff000000u)) ^ rk[42];
-        s[3] = ((T.template at<2, 0>(a3) & 0xffu) | (T.template at<3, 1>(a0) & 0xff00u) | (T.template at<0, 2>(a1) & 0xff0000u) | (T.template at<1, 3>(a2) & 0xff000000u)) ^ rk[43];
-    }
+    s[0] = last_column(a0, a1, a2, a3, rk[40], T); s[1] = last_column(a1, a2, a3, a0, rk[41], T);
+    s[2] = last_column(a2, a3, a0, a1, rk[42], T); s[3] = last_column(a3, a0, a1, a2, rk[43], T);
 }
 template <class Tab>
 DASH_HD void aes128_encrypt(uint32_t s[4], const uint32_t* rk, const Tab& T) {
@@ -434,12 +461,6 @@ DASH_HD QuadKey quad_key(const uint32_t* rk, uint32_t c) {
     for (int r = 0; r < 11; r++) Q.k[r] = rk[4 * r + c];
     return Q;
 }
-// bytes 0 and 1 of the last round's column, four tables (S[x] in byte 0 of T2 and byte 1 of T3)
-template <class Tab>
-DASH_HD uint32_t last_low(uint32_t a0, uint32_t a1, const Tab& T) {
-    if constexpr (!tab_two<Tab>::value) return (T.template at<2, 0>(a0) & 0xffu) | (T.template at<3, 1>(a1) & 0xff00u);
-    else return 0;
-}
 template <class Tab>
 DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t* rk, const Tab& T) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -457,8 +478,7 @@ DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t
     }
     {
         const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
-        const uint32_t low = tab_two<Tab>::value ? (T.template at<0, 0>(a) >> 8 & 0xffu) | (T.template at<0, 1>(a1) & 0xff00u) : last_low(a, a1, T);
-        a = (low | (T.template at<0, 2>(a2) & 0xff0000u) | (T.template at<1, 3>(a3) & 0xff000000u)) ^ Q.k[10];
+        a = last_column(a, a1, a2, a3, Q.k[10], T);
     }
     s[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x00, 0xf, 0xf, true);      // quad_perm:[0,0,0,0]
     s[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x55, 0xf, 0xf, true);
