@@ -18,6 +18,9 @@
 // Three forms.  Deep (EPB = 64): a lane owns (value, residue) and works through the n digit gates.  Shallow (EPB = 16): four lanes do,
 // every fourth digit each.  Tiny (EPB = 2 or 1): four lanes own (value, residue, digit) and share the AES, for layers so small that
 // their time is the latency of one value.
+// The deep form is bound by the hashes of its waves (vector issue 0.7 of the cycles that a CU is busy; two blocks per CU).  With one copy of
+// T0..T3 two thirds of its LDS cycles were bank collisions; with HalfTab 75 264 values of the 8-prime base take 152 us a repetition instead
+// of 168, 9 216 (one block per CU) 36 instead of 45.
 // For digit sets with compile-time moduli over the first NP primes; anything else takes the launches of dash_layers.hip one by one.
 // Compiled once per digit set (DASH_SET = number of primes) and label-length rule.
 #include "dash_tabs.h"
@@ -75,22 +78,25 @@ __device__ __forceinline__ void store_bits(const LView& v, uint32_t e, int c, ui
     }
 }
 
-// tables of the hashes of step 1: shallow form one copy per LDS bank (its waves hash at the same time, and with one copy the LDS
-// serves a wave's look-ups at a third of its rate), deep form one copy
-template <bool Deep> struct step_tab { typedef BankTab type; static constexpr int words = kBankTabWords; };
-template <> struct step_tab<true> { typedef LdsTab type; static constexpr int words = 4; };
-
 template <bool RELU, int EPB, int Q>
-__global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) void k_act_eval(const ActLaunch) {
+__global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12 ? 3 : 4) : 1) void k_act_eval(const ActLaunch) {
     constexpr int JL = 64 / (EPB * Q), NW = RELU ? kNP : kNP - 1, T = 64 * NW;
     constexpr bool Deep = EPB == 64;
     // The arguments are read through the constant address space: with the by-value parameter the compiler kept a copy in scratch memory.
     const auto& L = *(const __attribute__((address_space(4))) ActLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
     auto view = [](const __attribute__((address_space(4))) LView& v) __attribute__((always_inline)) { return LView{v.p, v.cs, v.es}; };
-    __shared__ uint32_t tt[kTabWords];
-    __shared__ __attribute__((aligned(16))) uint32_t bt[step_tab<Deep>::words];
+    __shared__ uint32_t tt[Deep ? 1 : kTabWords];
+    __shared__ __attribute__((aligned(16))) uint32_t bt_static[Deep ? 4 : kBankTabWords];
     __shared__ uint32_t kb[4][EPB];                 // the mod-2 wire of the repetition (scaling) or the sign bit (ReLU): 128 bits per value
-    extern __shared__ uint32_t acc[];               // [digit dword][even, odd digits][EPB]: sums over the residues, two digits per word
+    // Dynamic LDS.  Deep form: the table's span (dynamic, so that the compiler, which takes 64 KB of it for a limit of the blocks per CU,
+    // keeps to 128 registers: two blocks, 36 instead of 64 us for a repetition of 25 088 values of the 7-prime base); else the digit sums.
+    extern __shared__ __attribute__((aligned(16))) uint32_t acc[];
+    uint32_t* const bt = Deep ? acc : bt_static;
+    // sums over the residues, two digits per word: word (digit dword i, even or odd digits h, value v) at sum0[(2 i + h) * kS + at(v)].  Deep
+    // form: in the half of the table's span that HalfTab leaves free.
+    uint32_t* const sum0 = Deep ? acc + HalfTab::hole : acc;
+    constexpr int kS = Deep ? 2 * EPB : EPB;
+    auto at = [](uint32_t v) __attribute__((always_inline)) { return Deep ? (v & 32u) + v : v; };      // (64 values: two rows of 32 words, 64 apart)
     const int n = (int)L.n;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     const uint32_t c = lane % Q, el = lane / Q % EPB, jl = lane / (Q * EPB);      // lane of the quad, value, digit
@@ -98,14 +104,15 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
     const auto& RA = L.res[wave];
     struct { uint32_t digit_slot, hg_slot, cast_slot; const uint8_t *digit_table, *g_table, *e_table, *s_table, *cast_table, *shift; LView in, out; } R = {
         RA.digit_slot, RA.hg_slot, RA.cast_slot, RA.digit_table, RA.g_table, RA.e_table, RA.s_table, RA.cast_table, RA.shift, view(RA.in), view(RA.out)};
-    const uint32_t* const rk = (const uint32_t*)(Deep ? L.key.rk : L.key_rot.rk);       // of step 1's and step 4's hashes
+    const uint32_t* const rk = (const uint32_t*)L.key_rot.rk;              // of step 1's and step 4's hashes
+    const uint32_t* const crk = (const uint32_t*)(Deep ? L.key_rot.rk : L.key.rk);      // of the carry chain's
     const ModInfo Mp = ld_mod(L.mods, RA.p);
 
     // lanes of the carry chain: four per value
     const bool chain_lane = threadIdx.x < 4 * EPB;
     const uint32_t cel = (threadIdx.x >> 2) % EPB, cc = threadIdx.x & 3u;
     const uint32_t ce_raw = blockIdx.x * EPB + cel, ce = ce_raw < L.n_elem ? ce_raw : L.n_elem - 1;
-    const QuadKey qk = quad_key((const uint32_t*)L.key.rk, cc), qs = Q == 4 ? quad_key(rk, c) : QuadKey{};
+    const QuadKey qk = quad_key(crk, cc), qs = Q == 4 ? quad_key(rk, c) : QuadKey{};
     uint32_t x[kMaxX];                                                      // scaling: the residue (with the constants of the repetition before)
     uint32_t one = 0, up0 = 0;                                              // scaling, chain lanes: 32 bits of the constant-one wire and of the first mod-2 wire
     if constexpr (!RELU) {
@@ -127,14 +134,18 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
         }
     }
     const uint32_t sums = M1::ndw + (uint32_t)(n - 1) * MC::ndw;           // dwords of the n digit sums
-    for (uint32_t i = threadIdx.x; i < sums * 2 * EPB; i += T) acc[i] = 0;
+    for (uint32_t i = threadIdx.x; i < sums * 2 * EPB; i += T) sum0[i / EPB * kS + at(i % EPB)] = 0;
     if (chain_lane && !RELU) kb[cc][cel] = up0;
-    const LdsTab ctab = load_ttab(tt, L.ttab);                            // (ends with a barrier)
-    auto step_table = [&]() __attribute__((always_inline)) {
-        if constexpr (Deep) return ctab;
+    auto step_table = [&]() __attribute__((always_inline)) {               // (ends with a barrier)
+        if constexpr (Deep) return load_halftab(bt, L.ttab);
         else return load_banktab(bt, L.ttab);
     };
     const auto tab = step_table();
+    auto chain_table = [&]() __attribute__((always_inline)) {
+        if constexpr (Deep) return tab;
+        else return load_ttab(tt, L.ttab);
+    };
+    const auto ctab = chain_table();
 
     // a hash of step 1 or 4: by the lane, or by the four lanes of its quad together
     auto hash = [&](const U128& key, uint32_t slot) __attribute__((always_inline)) {
@@ -188,11 +199,11 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
                     for (int i = (int)MC::ndw; i < (int)M1::ndw; i++) rw[i] = row[i];
                 }
                 const U128 h = Deep ? H.get(slot, rk, tab) : hash(K, slot);
-                uint32_t* a = acc + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * EPB) + el;
+                uint32_t* a = sum0 + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * kS) + at(el);
                 auto put = [&](int i, uint32_t w) __attribute__((always_inline)) {
                     if (Q == 4 && c != (uint32_t)(i & 3)) return;           // (the lanes of a quad hold the same label)
-                    sum_add(a + 2 * EPB * i, w & 0x00ff00ffu);
-                    sum_add(a + 2 * EPB * i + EPB, (w >> 8) & 0x00ff00ffu);
+                    sum_add(a + 2 * kS * i, w & 0x00ff00ffu);
+                    sum_add(a + 2 * kS * i + kS, (w >> 8) & 0x00ff00ffu);
                 };
                 if (j == 1) { const M1 M{nullptr}; decompress(M, h, [&](int i, uint32_t hd) __attribute__((always_inline)) { put(i, submod4(rw[i], hd, M)); }); }
                 else { const MC M{nullptr}; decompress(M, h, [&](int i, uint32_t hd) __attribute__((always_inline)) { put(i, submod4(rw[i], hd, M)); }); }
@@ -202,11 +213,11 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
         // ---- step 2: the sums mod m_j (fields below 16 * 255)
         for (uint32_t t = threadIdx.x; t < sums * EPB; t += T) {
             const uint32_t i = t / EPB, c = t % EPB;
-            uint32_t* a = acc + i * (2 * EPB) + c;
-            const uint32_t ev = a[0], od = a[EPB];
+            uint32_t* a = sum0 + i * (2 * kS) + at(c);
+            const uint32_t ev = a[0], od = a[kS];
             auto reduce = [&](auto M) __attribute__((always_inline)) { return mod_m(ev & 0xffffu, M) | (mod_m(ev >> 16, M) << 16) | (mod_m(od & 0xffffu, M) << 8) | (mod_m(od >> 16, M) << 24); };
             a[0] = i < M1::ndw ? reduce(M1{nullptr}) : reduce(MC{nullptr});
-            a[EPB] = 0;
+            a[kS] = 0;
         }
         __syncthreads();
         // ---- step 3: the carry chain.  One loop over its n gates, one copy of the hash; the sum of the next digit is fetched under the
@@ -217,9 +228,9 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
             constexpr int kIn = (int)(M1::ndw > MC::ndw ? M1::ndw : MC::ndw);
             uint32_t cw[kIn] = {}, sm[kIn];
             auto fetch = [&](int j) __attribute__((always_inline)) {                                   // packed sum of digit j; cleared for the next repetition
-                uint32_t* a = acc + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * EPB) + cel;
+                uint32_t* a = sum0 + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * kS) + at(cel);
 #pragma unroll
-                for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * EPB]; DASH_WAVE_POINT(); a[i * 2 * EPB] = 0; }
+                for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * kS]; DASH_WAVE_POINT(); a[i * 2 * kS] = 0; }
             };
             fetch(n);
 #pragma unroll 1
@@ -249,7 +260,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? 4 : 1) voi
                     k = compress(Mf, [&](int i) __attribute__((always_inline)) { return in[i]; }, &col);
                 }
                 const uint32_t slot = L.chain_slot + soff + (uint32_t)(j > 1 ? j - 2 : n - 1);
-                const U128 h = hash_block_quad(k, L.elem_base + ce, slot, L.layer, qk, (const uint32_t*)L.key.rk, ctab);
+                const U128 h = hash_block_quad(k, L.elem_base + ce, slot, L.layer, qk, crk, ctab);
                 if (j > 2) {
                     decompress(Mc, h, [&](int i, uint32_t hd) __attribute__((always_inline)) { cw[i] = submod4(rw[i], hd, Mc); });
                 } else if (j == 2) {
@@ -359,12 +370,15 @@ int DASH_FN(DASH_PASTE(launch_act_eval_, DASH_SET))(const dash_ctx* c, ActLaunch
     constexpr int kShallow = 16, kTiny = kNP >= 9 ? 1 : 2;                  // values per block (tiny: 16 or 8 digits of 4 lanes each)
     // Tiny and shallow blocks have a CU each (64 KB of tables), so a form is taken while its blocks are one round of the 256 CUs: a
     // second round costs the whole latency again (320 values of the 9-prime base: 50 us in 320 tiny blocks, 28 in shallow ones).
-    // From two rounds of shallow blocks on the deep form is the faster one.
-    const int form = L.n_elem < c->act_shallow_min_elems && L.n_elem <= 256u * kTiny ? ACT_TINY : L.n_elem < c->act_deep_min_elems ? ACT_SHALLOW : ACT_DEEP;
-    const uint32_t epb = form == ACT_DEEP ? 64 : form == ACT_SHALLOW ? kShallow : kTiny;
+    // From two rounds of shallow blocks on the deep form is the faster one (6 400 values, us a repetition, scaling: 44 shallow and 39 deep on
+    // the 8-prime base, 45 and 37 on 7, 54 and 48 on 9, 73 and 65 on 12; 4 096 values: 24 and 39 on 8).
+    // (The deep form's digit sums lie in the table's span, which holds 64 dwords of them: the default sets have 35 to 56.)
     const uint32_t sums = M1::ndw + (L.n - 1) * MC::ndw;
+    const int form = L.n_elem < c->act_shallow_min_elems && L.n_elem <= 256u * kTiny ? ACT_TINY
+                   : L.n_elem < c->act_deep_min_elems || sums > 64 ? ACT_SHALLOW : ACT_DEEP;
+    const uint32_t epb = form == ACT_DEEP ? 64 : form == ACT_SHALLOW ? kShallow : kTiny;
     const dim3 grid((L.n_elem + epb - 1) / epb), block(64 * (relu ? kNP : kNP - 1));
-    const size_t lds = (size_t)sums * 2 * epb * 4;
+    const size_t lds = form == ACT_DEEP ? HalfTab::words * 4 : (size_t)sums * 2 * epb * 4;
     if (relu) {
         if (form == ACT_DEEP) hipLaunchKernelGGL((k_act_eval<true, 64, 1>), grid, block, lds, s, L);
         else if (form == ACT_SHALLOW) hipLaunchKernelGGL((k_act_eval<true, kShallow, 1>), grid, block, lds, s, L);

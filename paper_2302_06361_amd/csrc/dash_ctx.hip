@@ -243,7 +243,7 @@ int dash_ctx_create(dash_ctx** out, const uint16_t* primes, int k, int lambda_ru
     c->act_eval = 1;
     for (const char* v : {"DASH_FUSED_MIN_ELEMS_EVAL", "DASH_WIDE_MAX_LANES", "DASH_SUM_IN_LAUNCH", "DASH_QUAD_MAX_LANES"}) if (getenv(v)) c->act_eval = 0;
     if (const char* e = getenv("DASH_ACT_EVAL")) c->act_eval = atoi(e) != 0;
-    c->act_deep_min_elems = 6144;
+    c->act_deep_min_elems = 4097;
     c->act_shallow_min_elems = ~0ull;      // (the size of a tiny launch decides)
     if (const char* e = getenv("DASH_ACT_SHALLOW_MIN_ELEMS")) c->act_shallow_min_elems = strtoull(e, nullptr, 10);   // tuning and test hook
     if (const char* e = getenv("DASH_ACT_DEEP_MIN_ELEMS")) c->act_deep_min_elems = strtoull(e, nullptr, 10);         // tuning and test hook

@@ -74,6 +74,33 @@ __device__ __forceinline__ BankTab load_banktab(uint32_t* lds, const uint32_t* g
     return BankTab{(const uint8_t*)lds, (threadIdx.x & 31u) << 2};
 }
 
+// HalfTab: 16 copies of T0 and T1 in the first 128 bytes of every 256, which leaves the other 128 of each entry (32 KB) to the kernel:
+// byte address of entry x of table R  x * 256 + R * 64 + 4 * copy.  One instruction per address and one rotation per column as with
+// BankTab; the lanes l and l + 16 share a copy, so a look-up takes four LDS cycles instead of two.  For kernels that need LDS of their own
+// and have LDS cycles to spare.
+struct HalfTab {
+    static constexpr bool two_tables = true, rotated_keys = true;
+    static constexpr int words = 16384, hole = 32;     // the kernel's words: hole + 64 i + (0..31)
+    const uint8_t* t;
+    uint32_t lane;       // byte 0: 4 * copy
+    template <int R, int B> __device__ __forceinline__ uint32_t at(uint32_t w) const {
+        static_assert(R < 2, "T0 and T1 only");
+        constexpr uint32_t sel = 0x0c0c0000u | ((4u + B) << 8);
+        const uint32_t a = B == 1 ? (w & 0xff00u) | lane : __builtin_amdgcn_perm(w, lane, sel);
+        return *(const uint32_t*)(t + a + R * 64);
+    }
+};
+__device__ __forceinline__ HalfTab load_halftab(uint32_t* lds, const uint32_t* g) {
+    for (int e = threadIdx.x; e < 512; e += blockDim.x) {
+        const uint32_t v = g[e];
+        uint4* dst = (uint4*)(lds + (e & 255) * 64 + (e >> 8) * 16);
+#pragma unroll
+        for (int i = 0; i < 4; i++) dst[i] = make_uint4(v, v, v, v);
+    }
+    __syncthreads();
+    return HalfTab{(const uint8_t*)lds, (threadIdx.x & 15u) << 2};
+}
+
 template <bool Banked> struct gate_tab {
     typedef LdsTab type;
     static constexpr int threads = kThreads, words = kTabWords;

@@ -82,6 +82,15 @@ def test_one_launch_activation_layers(emul, tmp_path, k, rule, form):
             assert got.size == ref.size and bad.size == 0, (kind, n, order, bad[:1])
 
 
+def test_deep_layers_whose_digit_sums_exceed_the_table_span(emul, tmp_path, monkeypatch):
+    """the same moduli with more digits: 7 + 13 * 5 = 72 dwords of sums, 64 fit beside the deep form's tables"""
+    monkeypatch.setitem(workloads.DIGITS, 8, (26,) + (12,) * 13)
+    env = {"DASH_ACT_SHALLOW_MIN_ELEMS": "0", "DASH_ACT_DEEP_MIN_ELEMS": "0"}
+    for kind, n in (("relu", 65), ("scale", 17)):
+        got, orc, want, _ = run(emul, tmp_path, "act", 8, 0, kind, n, env=env)
+        assert (got == np.concatenate([a.reshape(-1) for a in want])).all(), kind
+
+
 @pytest.mark.parametrize("k,kind,n,repeat", [(8, "relu", 3, 1), (8, "scale", 67, 2), (12, "relu", 65, 1), (7, "scale", 17, 1)])
 def test_tables_repacked_from_a_4_byte_address(emul, tmp_path, k, kind, n, repeat):
     """tables are 4-byte aligned, and with an odd number of values so is the segment of every modulus"""
