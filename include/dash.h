@@ -128,7 +128,8 @@ int dash_ctx_one(const dash_ctx *ctx, int i, int which, uint8_t *host_out);
 int dash_ctx_digits(const dash_ctx *ctx, uint16_t *host_digits);
 
 /* Sizes of one layer call: output elements (values, or batch elements for the linear kinds:
- * then *out_elems is values per batch element), bytes of ciphertext tables, bytes of scratch. */
+ * then *out_elems is values per batch element), bytes of ciphertext tables, bytes of scratch.  The scratch of a
+ * SCALE layer does not depend on its repetitions and grows with its values: one buffer serves smaller layers. */
 int dash_layer_sizes(const dash_ctx *ctx, const dash_layer *layer, int64_t *out_elems, size_t *table_bytes,
                      size_t *scratch_bytes);
 

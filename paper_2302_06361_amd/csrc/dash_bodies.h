@@ -51,6 +51,20 @@ DASH_HD void draw_body(const DrawLaunch& L, uint32_t bx, uint32_t by, uint32_t t
     });
 }
 
+// ... of a gadget's gates: one lane per (job, element)
+template <class Tab>
+DASH_HD void draw_many_body(const DrawManyLaunch& L, uint32_t bx, uint32_t by, uint32_t rep, uint32_t tx, const Tab& T) {
+    const DrawManyJob& J = L.jobs[by];
+    const uint32_t e = bx * kThreads + tx;
+    if (e >= L.n_elem) return;
+    const U128 h = prg_block(L.elem_base + e, J.slot + rep * L.reps.slots, L.layer, DOM_GATE, J.m, L.key.rk, T);
+    const LView out{L.base + J.off + rep * L.reps.wires, 16 * (int64_t)L.n_elem, 16u};
+    with_mod(ld_mod(L.mods, J.m), [&](auto Q) {
+        decompress(Q, h, [&](int i, uint32_t w) { st_dw(out, e, i, w); });
+        for (int i = (int)Q.ndw; i < (int)Q.nchunk * 4; i++) st_dw(out, e, i, 0);
+    });
+}
+
 // free gates: out = sum_t coef_t * term_t mod m.  One lane per (element, 16-digit chunk): a 16-byte load
 // per term.  Sums with unit coefficients (the mixed-radix additions of the sign gadget) accumulate two
 // digits per 32-bit word in 16-bit fields; general coefficients go digit by digit.
@@ -85,6 +99,78 @@ DASH_HD void affine_body(const AffineLaunch& L, uint32_t bx, uint32_t by, uint32
     for (int q = 0; q < 4; q++) dst[q] = out[q];
 }
 
+// (x - cast) * 2^-1 mod p on four digits (scaling gadget)
+template <class P>
+DASH_HD uint32_t halve4(uint32_t x, uint32_t cast, uint32_t inv2, const P& Pm) {
+    if (Pm.m <= 127) {
+        // four digits at once (p odd): t = (x - cast) mod p, then t / 2 for even t and (t + p) / 2 for odd t.  Bytes stay
+        // below 2p <= 254, and the bit that the shift brings in from the byte above is masked off.
+        const uint32_t t = submod4(x, cast, Pm);
+        const uint32_t odd = t & 0x01010101u;
+        return ((t + odd * Pm.m) >> 1) & 0x7f7f7f7fu;
+    }
+    uint32_t b = 0;
+    // digits past lambda: x and cast are 0 there, and inv2 * p = 0 mod p
+    for (int b8 = 0; b8 < 4; b8++) b |= mod_m(mul24(inv2, byte_of(x, b8) + Pm.m - byte_of(cast, b8)), Pm) << (8 * b8);
+    return b;
+}
+// the same view t repetitions on
+DASH_HD LView rep_view(const LView& v, const Reps& R, uint32_t t) { return LView{v.p + (int64_t)t * R.wires, v.cs, v.es}; }
+
+// garbler, scaling gadget: by < n the sum of digit by + 1 (one repetition per call); by = n the mod-2 wire and by > n the halving of an odd
+// residue, whose repetitions follow from each other and are walked by the lane.  One lane per (element, 16-digit chunk).
+DASH_HD void scale_free_body(const ScaleFreeLaunch& L, uint32_t bx, uint32_t by, uint32_t rep, uint32_t tx) {
+    const uint32_t reps = rep_count(L.reps);
+    if (by >= L.n && rep != 0) return;
+    const HalveJob& J = L.halve[by > L.n ? by - L.n - 1 : 0];
+    const ModInfo M = ld_mod(L.mods, by < L.n ? L.m[by + 1] : by == L.n ? 2u : J.p);
+    const uint64_t idx = (uint64_t)bx * kThreads + tx;
+    if (idx >= (uint64_t)L.n_elem * M.nchunk) return;
+    const uint32_t ch = (uint32_t)(idx / L.n_elem), e = (uint32_t)(idx - (uint64_t)ch * L.n_elem);
+    if (by < L.n) {
+        const uint32_t j = by + 1;
+        const int64_t at = (int64_t)rep * L.reps.wires + (int64_t)ch * L.cs + (int64_t)e * 16;
+        uint32_t ev[4] = {0, 0, 0, 0}, od[4] = {0, 0, 0, 0};          // digits 0, 2 / 1, 3 of each dword, 16 bits each
+        auto add = [&](const uint8_t* p) {
+            const Dw4 d = *(const Dw4*)(p + at);
+            for (int q = 0; q < 4; q++) { ev[q] += d.w[q] & 0x00ff00ffu; od[q] += (d.w[q] >> 8) & 0x00ff00ffu; }
+        };
+        for (uint32_t i = 0; i < L.nres; i++) add(L.a1 + L.a_prefix[j] + (int64_t)i * L.res_step);
+        if (j < L.n) add(L.C[j]);
+        Dw4 out;
+        for (int q = 0; q < 4; q++)
+            out.w[q] = mod_m(ev[q] & 0xffffu, M) | (mod_m(od[q] & 0xffffu, M) << 8) | (mod_m(ev[q] >> 16, M) << 16) | (mod_m(od[q] >> 16, M) << 24);
+        *(Dw4*)(L.S[j] + at) = out;
+    } else if (by == L.n) {
+        const Dw4 one = ld_chunk(L.one2, e, (int)ch);
+        auto plus = [&](Dw4 d, uint32_t coef) {
+            for (int q = 0; q < 4; q++) d.w[q] ^= coef ? one.w[q] : 0u;
+            return d;
+        };
+        st_chunk(L.up, e, (int)ch, plus(ld_chunk(L.x0, e, (int)ch), L.x0_coef));
+        for (uint32_t t = 0; t < reps; t++) {
+            const Dw4 bit = ld_chunk(rep_view(L.bit, L.reps, t), e, (int)ch);
+            if (t + 1 < reps) st_chunk(rep_view(L.up, L.reps, t + 1), e, (int)ch, plus(bit, L.up_coef));
+            else st_chunk(L.last, e, (int)ch, plus(bit, L.last_coef));
+        }
+    } else {
+        const Dw4 one = ld_chunk(J.one, e, (int)ch);
+        const uint32_t inv2 = (M.m + 1) / 2;
+        Dw4 x = ld_chunk(J.x, e, (int)ch), shift;
+        for (int q = 0; q < 4; q++) {
+            shift.w[q] = axpymod4(0u, J.addc, one.w[q], M);
+            if (J.addc0) x.w[q] = axpymod4(x.w[q], J.addc0, one.w[q], M);
+        }
+        for (uint32_t t = 0; t < reps; t++) {
+            const Dw4 cast = ld_chunk(rep_view(J.cast, L.reps, t), e, (int)ch);
+            Dw4 b;
+            for (int q = 0; q < 4; q++) { b.w[q] = halve4(x.w[q], cast.w[q], inv2, M); x.w[q] = addmod4(b.w[q], shift.w[q], M); }
+            st_chunk(rep_view(J.b, L.reps, t), e, (int)ch, b);
+        }
+        if (J.out.p) st_chunk(J.out, e, (int)ch, x);
+    }
+}
+
 // Where a finished ciphertext row goes.  DirectSink stores it dword by dword at its place in the table;
 // the kernel for long rows stages rows in LDS instead and writes them out cooperatively.
 struct DirectSink {
@@ -99,8 +185,10 @@ struct PerJobMod {};
 // garble: one lane per ciphertext row r = gate * p + a.  QD: description type of the output modulus
 // (every job of a launch has the same output modulus), fixed at compile time for the hot moduli.
 template <class QD, class Tab, class Sink>
-DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink) {
+DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink, uint32_t rep = 0) {
     const GateJob& J = L.jobs[by];
+    const LView Jin = rep_view(J.in, L.reps, rep), Jout = rep_view(J.out, L.reps, rep);
+    uint8_t* const table = J.table + (int64_t)rep * L.reps.tables;
     const ModInfo Mp = ld_mod(L.mods, J.p), Mq = ld_mod(L.mods, J.q);
     // The block's first row is divided once (scalar unit; rows of a job are below 2^32); the lane's offset from it is small
     // enough for the 24-bit magic division.
@@ -116,9 +204,9 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
     U128 K = {{0, 0, 0, 0}};
     with_mod(Mp, [&](auto P) {
         const uint32_t* da = P.dtab + a * P.ndw;
-        K = compress(P, [&](int i) { return addmod4(ld_dw(J.in, g, i), gload32(da + i), P); }, &colour);
+        K = compress(P, [&](int i) { return addmod4(ld_dw(Jin, g, i), gload32(da + i), P); }, &colour);
     });
-    U128 h = hash_block(K, J.elem_base + g, J.slot, L.layer, L.key.rk, T);
+    U128 h = hash_block(K, J.elem_base + g, J.slot + rep * L.reps.slots, L.layer, L.key.rk, T);
 
     // the output modulus: the kernel's compile-time description, or the run-time record (the instantiation for any
     // modulus, which also serves launches that mix output moduli; choosing a compile-time description per job inside
@@ -129,15 +217,15 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
         typedef std::decay_t<decltype(Q)> QT;
         if (J.mode == PAY_SHORT) {
             uint32_t v = mod_m(a + J.r[g] + mod_u128(h, Q), Q);
-            *(uint32_t*)(J.table + ((size_t)g * Mp.m + colour) * 4) = v;
+            *(uint32_t*)(table + ((size_t)g * Mp.m + colour) * 4) = v;
             return;
         }
-        sink.begin(J.table, (uint64_t)g * Mp.m + colour, Q.ndw * 4);
+        sink.begin(table, (uint64_t)g * Mp.m + colour, Q.ndw * 4);
         if (J.mode == PAY_EHALF) {
             uint32_t cf = mod_m(a + J.r[g], Q);
             cf = cf ? Q.m - cf : 0;                          // minus (a + r) * x0
             decompress(Q, h, [&](int i, uint32_t hd) {
-                uint32_t pay = axpymod4(ld_dw(J.out, g, i), cf, ld_dw(J.x0, g, i), Q);
+                uint32_t pay = axpymod4(ld_dw(Jout, g, i), cf, ld_dw(J.x0, g, i), Q);
                 sink.put(i, addmod4(pay, hd, Q));
             });
             return;
@@ -150,11 +238,11 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
             // payload first (its loads do not wait behind the row stores), then one pass over the hash digits
             uint32_t pay[QT::ndw];
 #pragma unroll
-            for (int i = 0; i < (int)QT::ndw; i++) pay[i] = addmod4(ld_dw(J.out, g, i), gload32(df + i), Q);
+            for (int i = 0; i < (int)QT::ndw; i++) pay[i] = addmod4(ld_dw(Jout, g, i), gload32(df + i), Q);
             decompress(Q, h, [&](int i, uint32_t hd) { sink.put(i, addmod4(pay[i], hd, Q)); });
         } else {
             decompress(Q, h, [&](int i, uint32_t hd) {
-                sink.put(i, addmod4(addmod4(ld_dw(J.out, g, i), gload32(df + i), Q), hd, Q));
+                sink.put(i, addmod4(addmod4(ld_dw(Jout, g, i), gload32(df + i), Q), hd, Q));
             });
         }
     };
@@ -413,10 +501,10 @@ DASH_HD void digits_eval_wide_body(const DigitsLaunch& L, uint32_t bx, uint32_t 
 // One lane per (element g, value a) of a residue: the label of a is formed and compressed once, then one
 // ciphertext row per digit: rows[colour] = out0 + phi_j(a) R_{m_j} + H_{m_j}(label, slot_j).
 template <class MO>
-DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& h, uint32_t f, uint32_t colour, uint32_t g, int j) {
-    uint8_t* seg = R.table + (size_t)L.n_elem * R.p * L.row_prefix[j];
+DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& h, uint32_t f, uint32_t colour, uint32_t g, int j, uint32_t rep) {
+    uint8_t* seg = R.table + (int64_t)rep * L.reps.tables + (size_t)L.n_elem * R.p * L.row_prefix[j];
     uint32_t* row = (uint32_t*)(seg + ((size_t)g * R.p + colour) * (Mo.ndw * 4));
-    const LView out0{R.out + L.out_prefix[j], L.out_cs, 16u};
+    const LView out0{R.out + (int64_t)rep * L.reps.wires + L.out_prefix[j], L.out_cs, 16u};
     const uint32_t* df = Mo.dtab + f * Mo.ndw;
     if constexpr (cmod_m<MO>::value != 0) {
         uint32_t pay[MO::ndw];
@@ -430,8 +518,10 @@ DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, 
 // j0 = 0: all n digits of the lane's (element, value); j0 = 1..n: digit j0 only (gadgets over few elements: a lane per
 // row, a chain of one hash)
 template <class MC, class M1, class Tab>
-DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, uint32_t j0 = 0) {
+DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, uint32_t j0 = 0, uint32_t rep = 0) {
     const DigitsRes& R = L.res[by];
+    const LView in = rep_view(R.in, L.reps, rep);
+    const uint32_t slot0 = R.slot0 + rep * L.reps.slots;
     const ModInfo Mp = ld_mod(L.mods, R.p);
     const uint32_t r0 = bx * kThreads;
     if ((uint64_t)bx * kThreads >= (uint64_t)L.n_elem * Mp.m) return;
@@ -443,39 +533,25 @@ DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by,
     U128 K = {{0, 0, 0, 0}};
     with_mod(Mp, [&](auto P) {
         const uint32_t* da = P.dtab + a * P.ndw;
-        K = compress(P, [&](int i) { return addmod4(ld_dw(R.in, g, i), gload32(da + i), P); }, &colour);
+        K = compress(P, [&](int i) { return addmod4(ld_dw(in, g, i), gload32(da + i), P); }, &colour);
     });
     const int jlo = j0 ? (int)j0 : 1, jhi = j0 ? (int)j0 : (int)L.n;
     SlotHasher H(K, L.elem_base + g, L.layer);
     for (int j = jlo; j <= jhi; j++) {
         const uint32_t f = R.phi[(size_t)(j - 1) * R.p + a];
-        const U128 h = H.get(R.slot0 + (uint32_t)(j - 1), L.key.rk, T);
+        const U128 h = H.get(slot0 + (uint32_t)(j - 1), L.key.rk, T);
         if constexpr (cmod_m<MC>::value != 0) {
-            if (j == 1) digit_row(L, R, M1{ld_mod(L.mods, L.m[1]).dtab}, h, f, colour, g, 1);
-            else digit_row(L, R, MC{ld_mod(L.mods, L.m[2]).dtab}, h, f, colour, g, j);
+            if (j == 1) digit_row(L, R, M1{ld_mod(L.mods, L.m[1]).dtab}, h, f, colour, g, 1, rep);
+            else digit_row(L, R, MC{ld_mod(L.mods, L.m[2]).dtab}, h, f, colour, g, j, rep);
         } else {
             const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
-            digit_row(L, R, Mo, h, f, colour, g, j);
+            digit_row(L, R, Mo, h, f, colour, g, j, rep);
         }
     }
 }
 
 // evaluator, scaling gadget: cast = rows[colour(y)] - H_p(y) (two-row gate Z_2 -> Z_p, identity function), then
 // b = (x + addc * one - cast) * 2^-1 mod p.  The cast label itself is not stored.
-template <class P>
-DASH_HD uint32_t halve4(uint32_t x, uint32_t cast, uint32_t inv2, const P& Pm) {
-    if (Pm.m <= 127) {
-        // four digits at once (p odd): t = (x - cast) mod p, then t / 2 for even t and (t + p) / 2 for odd t.  Bytes stay
-        // below 2p <= 254, and the bit that the shift brings in from the byte above is masked off.
-        const uint32_t t = submod4(x, cast, Pm);
-        const uint32_t odd = t & 0x01010101u;
-        return ((t + odd * Pm.m) >> 1) & 0x7f7f7f7fu;
-    }
-    uint32_t b = 0;
-    // digits past lambda: x and cast are 0 there, and inv2 * p = 0 mod p
-    for (int b8 = 0; b8 < 4; b8++) b |= mod_m(mul24(inv2, byte_of(x, b8) + Pm.m - byte_of(cast, b8)), Pm) << (8 * b8);
-    return b;
-}
 // compile-time label length: b of element e in registers (xw: its chunks), 16-byte loads
 template <class PD>
 DASH_HD void cast_halve_regs(const CastJob& J, const PD& P, uint32_t e, uint32_t colour, const U128& h, Dw4* xw) {

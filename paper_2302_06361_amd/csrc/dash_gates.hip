@@ -48,6 +48,58 @@ int DASH_FN(launch_draw)(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_
     return DASH_OK;
 }
 
+// the same for the zero labels of a gadget's gates: blockIdx.y = label, blockIdx.z = repetition
+template <bool Banked>
+__global__ __launch_bounds__(gate_tab<Banked>::threads) void k_draw_many(const DrawManyLaunch L) {
+    constexpr int kGateTiles = gate_tab<Banked>::threads / kThreads;
+    __shared__ uint32_t tt[gate_tab<Banked>::words];
+    const auto T = gate_tab<Banked>::load(tt, L.ttab);
+    const uint32_t tiles = (L.n_elem + kThreads - 1) / kThreads;
+    const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;
+    for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) draw_many_body(L, tile, blockIdx.y, blockIdx.z, tx, T);
+}
+
+int DASH_FN(launch_draw_many)(const dash_ctx* c, DrawManyLaunch& L, int njobs, hipStream_t s) {
+    static_assert(sizeof(DrawManyLaunch) <= 4096, "kernel argument block");
+    if (njobs < 1 || njobs > kMaxDrawMany) return DASH_EINVAL;
+    if (L.n_elem == 0) return DASH_OK;
+    if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
+    const uint32_t reps = rep_count(L.reps);
+    const bool banked = (uint64_t)L.n_elem * njobs * reps >= c->banked_min_lanes;
+    L.key = banked ? c->seed_rot : c->seed; L.ttab = c->d_ttab; L.mods = c->d_mods;
+    const dim3 grid(gate_grid_x_for((L.n_elem + kThreads - 1) / kThreads, njobs * (int)reps, banked), njobs, reps);
+    if (banked) hipLaunchKernelGGL(k_draw_many<true>, grid, dim3(kBigThreads), 0, s, L);
+    else hipLaunchKernelGGL(k_draw_many<false>, grid, dim3(kThreads), 0, s, L);
+    DASH_HIP(hipGetLastError());
+    return DASH_OK;
+}
+
+// ------------------------------------------------------------------ free gates of the scaling gadget, garbler
+__global__ __launch_bounds__(kThreads) void k_scale_free(const ScaleFreeLaunch L) {
+    scale_free_body(L, blockIdx.x, blockIdx.y, blockIdx.z, threadIdx.x);
+}
+
+int DASH_FN(launch_scale_free)(const dash_ctx* c, ScaleFreeLaunch& L, hipStream_t s) {
+    static_assert(sizeof(ScaleFreeLaunch) <= 4096, "kernel argument block");
+    if (L.n < 1 || L.n > (uint32_t)kMaxChain || L.nres < 1 || L.nres > 14) return DASH_EINVAL;
+    if (L.n_elem == 0) return DASH_OK;
+    if (L.n_elem > (1u << 28)) return DASH_ESIZE;      // lane offsets into a chunk are 32-bit byte offsets
+    L.mods = c->d_mods;
+    uint32_t nchunk = c->mods[2].nchunk;
+    for (uint32_t j = 1; j <= L.n; j++) {
+        if (L.m[j] < 2 || L.m[j] > 255 || !L.S[j] || (j < L.n && !L.C[j])) return DASH_EINVAL;
+        nchunk = c->mods[L.m[j]].nchunk > nchunk ? c->mods[L.m[j]].nchunk : nchunk;
+    }
+    for (uint32_t i = 0; i < L.nres; i++) {
+        if (L.halve[i].p < 3 || L.halve[i].p > 255) return DASH_EINVAL;
+        nchunk = c->mods[L.halve[i].p].nchunk > nchunk ? c->mods[L.halve[i].p].nchunk : nchunk;
+    }
+    const dim3 grid((uint32_t)(((uint64_t)L.n_elem * nchunk + kThreads - 1) / kThreads), L.n + 1 + L.nres, rep_count(L.reps));
+    hipLaunchKernelGGL(k_scale_free, grid, dim3(kThreads), 0, s, L);
+    DASH_HIP(hipGetLastError());
+    return DASH_OK;
+}
+
 // ---------------------------------------------------------------------------------------- affine
 __global__ __launch_bounds__(kThreads) void k_affine(const AffineLaunch L) {
     affine_body(L, blockIdx.x, blockIdx.y, threadIdx.x);
@@ -256,15 +308,16 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         auto tiles_of = [&](uint32_t j) { return (uint32_t)(((uint64_t)L.jobs[j].n_elem * L.jobs[j].p + kThreads - 1) / kThreads); };
         uint32_t total = 0;
         for (uint32_t j = 0; j < L.njobs; j++) total += tiles_of(j);
-        uint32_t job = 0, base = 0, next = tiles_of(0);
+        total *= rep_count(L.reps);
+        uint32_t job = 0, rep = 0, base = 0, next = tiles_of(0);
         // (every wave stages and writes out its own 64 rows: no barrier between waves)
         const uint32_t rounds = (total + gridDim.x * kGateTiles - 1) / (gridDim.x * kGateTiles);
         for (uint32_t r = 0; r < rounds; r++) {
             const uint32_t t = (r * gridDim.x + blockIdx.x) * kGateTiles + sub;
             RegSink<ndw> sink;
             if (t < total) {
-                while (t >= next) { job++; base = next; next += tiles_of(job); }
-                garble_body<QD>(L, t - base, job, tx, T, sink);
+                while (t >= next) { if (++job == L.njobs) { job = 0; rep++; } base = next; next += tiles_of(job); }
+                garble_body<QD>(L, t - base, job, tx, T, sink, rep);
             }
             sdst[threadIdx.x] = sink.addr;
 #pragma unroll
@@ -297,12 +350,12 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         constexpr int ndw = stage_rows<QD>::ndw, stride = ndw + 1, pieces = ndw / 4;
         __shared__ uint32_t stage[kThreads * stride];
         __shared__ uint32_t srow[kThreads];
-        uint8_t* table = L.jobs[blockIdx.y].table;
+        uint8_t* table = L.jobs[blockIdx.y].table + (int64_t)blockIdx.z * L.reps.tables;
         const int lane = threadIdx.x & 63, w0 = threadIdx.x & ~63;       // this wave's rows: w0 .. w0 + 63
         for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
             srow[threadIdx.x] = 0xffffffffu;
             StagedSink sink{stage + threadIdx.x * stride, srow + threadIdx.x};
-            garble_body<QD>(L, tile, blockIdx.y, threadIdx.x, T, sink);
+            garble_body<QD>(L, tile, blockIdx.y, threadIdx.x, T, sink, blockIdx.z);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             for (int id = lane; id < 64 * pieces; id += 64) {
@@ -328,16 +381,17 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
             auto tiles_of = [&](uint32_t j) { return (uint32_t)(((uint64_t)L.jobs[j].n_elem * L.jobs[j].p + kThreads - 1) / kThreads); };
             uint32_t total = 0;
             for (uint32_t j = 0; j < L.njobs; j++) total += tiles_of(j);
-            uint32_t job = 0, base = 0, next = tiles_of(0);
+            total *= rep_count(L.reps);
+            uint32_t job = 0, rep = 0, base = 0, next = tiles_of(0);
             for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
-                while (t >= next) { job++; base = next; next += tiles_of(job); }
+                while (t >= next) { if (++job == L.njobs) { job = 0; rep++; } base = next; next += tiles_of(job); }
                 DirectSink sink;
-                garble_body<QD>(L, t - base, job, tx, T, sink);
+                garble_body<QD>(L, t - base, job, tx, T, sink, rep);
             }
         } else {
             for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) {
                 DirectSink sink;
-                garble_body<QD>(L, tile, blockIdx.y, tx, T, sink);
+                garble_body<QD>(L, tile, blockIdx.y, tx, T, sink, blockIdx.z);
             }
         }
     }
@@ -374,6 +428,8 @@ int DASH_FN(launch_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStrea
         bytes += (double)J.n_elem * (lp + (J.phi_stride ? J.p : 0) + lq + J.p * lq + (J.mode == PAY_EHALF ? lq : 0));
     }
     if (rows == 0) return DASH_OK;
+    const uint32_t reps = rep_count(L.reps);
+    units *= reps; bytes *= reps; tiles_sum *= reps;
     const uint64_t blocks = (rows + kThreads - 1) / kThreads;
     if (blocks > 0x7fffffffull || tiles_sum > 0x7fffffffull) return DASH_ESIZE;
     // jobs with one output modulus run its instantiation; a mix of output moduli (many small batches
@@ -385,7 +441,7 @@ int DASH_FN(launch_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStrea
     const bool banked = (uint64_t)units >= c->banked_min_lanes;
     if (banked) L.key = c->fixed_rot;
     L.njobs = (uint32_t)njobs;
-    dim3 grid(gate_grid_x_for(blocks, njobs, banked), njobs);
+    dim3 grid(gate_grid_x_for(blocks, njobs * (int)reps, banked), njobs, reps);
     if (banked) {       // one-dimensional: all jobs' tiles, 1024 lanes (4 tiles) per block at a time, two blocks per CU
         const uint64_t nb = (tiles_sum + 3) / 4;
         const uint64_t cap = staged ? 256 : 512;      // (long rows also stage in LDS: one block per CU)

@@ -24,14 +24,15 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_d
     auto tiles_of = [&](uint32_t i) { return (uint32_t)(((uint64_t)L.n_elem * L.res[i].p + kThreads - 1) / kThreads); };
     uint32_t total = 0;
     for (uint32_t i = 0; i < L.nres; i++) total += tiles_of(i);
-    uint32_t res = 0, base = 0, next = tiles_of(0);
+    total *= rep_count(L.reps);
+    uint32_t res = 0, rep = 0, base = 0, next = tiles_of(0);
     for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
-        while (t >= next) { res++; base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, res, tx, T);
+        while (t >= next) { if (++res == L.nres) { res = 0; rep++; } base = next; next += tiles_of(res); }
+        digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep);
     }
 }
 
-// the same with one lane per ciphertext row: blockIdx.y = digit - 1 (gadgets over few elements)
+// the same with one lane per ciphertext row: blockIdx.y = digit - 1, blockIdx.z = repetition (gadgets over few elements)
 template <class MC, class M1>
 __global__ __launch_bounds__(kThreads) void k_digits_garble_wide(const DigitsLaunch L) {
     __shared__ uint32_t tt[kTabWords];
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void k_digits_garble_wide(const DigitsLau
     uint32_t res = 0, base = 0, next = tiles_of(0);
     for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
         while (t >= next) { res++; base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, res, threadIdx.x, T, blockIdx.y + 1);
+        digits_garble_body<MC, M1>(L, t - base, res, threadIdx.x, T, blockIdx.y + 1, blockIdx.z);
     }
 }
 
@@ -67,11 +68,13 @@ int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_
         units += (double)rows * L.n;
         for (uint32_t j = 1; j <= L.n; j++) bytes += (double)L.n_elem * (c->mods[R.p].lam + (1.0 + R.p) * c->mods[L.m[j]].lam);
     }
-    if (tiles > 0x7fffffffull) return DASH_ESIZE;
+    const uint32_t reps = rep_count(L.reps);
+    units *= reps; bytes *= reps;
+    if (tiles * reps > 0x7fffffffull) return DASH_ESIZE;
     const int typed = uniform ? digit_set_index(c->mods[L.m[L.n >= 2 ? 2 : 1]], c->mods[L.m[1]]) : 0;
     ProfScope ps(c->prof, DASH_PROF_GARBLE_DIGITS, s, units, bytes);
     if ((uint64_t)units <= c->few_rows_max) {      // few rows: a lane per row, so that a lane's chain is one hash
-        dim3 grid(grid_x_for(tiles, (int)L.n), L.n);
+        dim3 grid(grid_x_for(tiles, (int)(L.n * reps)), L.n, reps);
         with_digit_set(typed, [&](auto ds) {
             typedef decltype(ds) DS;
             hipLaunchKernelGGL((k_digits_garble_wide<typename DS::MC, typename DS::M1>), grid, dim3(kThreads), 0, s, L);
@@ -81,7 +84,7 @@ int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_
     }
     const bool banked = (uint64_t)(units / L.n) >= c->digits_banked_min_lanes;
     if (banked) L.key = c->fixed_rot;
-    dim3 grid(gate_grid_x_for(tiles, 1, banked));
+    dim3 grid(gate_grid_x_for(tiles * reps, 1, banked));
     const dim3 block(banked ? kBigThreads : kThreads);
     with_digit_set(typed, [&](auto ds) {
         typedef decltype(ds) DS;

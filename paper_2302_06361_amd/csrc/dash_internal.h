@@ -91,6 +91,8 @@ namespace dash {
     inline namespace floor_rule { ret name##_floor params; }                      \
     inline ret name params { return c->rule == DASH_LAMBDA_FLOOR ? name##_floor args : name##_ceil args; }
 DASH_BY_RULE(int, launch_draw, (const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_draw_many, (const dash_ctx* c, DrawManyLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
+DASH_BY_RULE(int, launch_scale_free, (const dash_ctx* c, ScaleFreeLaunch& L, hipStream_t s), (c, L, s))
 DASH_BY_RULE(int, launch_affine, (const dash_ctx* c, AffineLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 DASH_BY_RULE(int, launch_garble, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 DASH_BY_RULE(int, launch_eval, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))

@@ -52,12 +52,21 @@ struct GateJob {
 
 struct AesKey { uint32_t rk[44]; };
 
+// Repetitions of one gadget in one launch (the garbler's scaling layers): repetition t's slots, wires and tables lie t steps on.
+// n = 0 or 1: one.
+struct Reps {
+    uint32_t n, slots;       // repetitions; step of the slots
+    int64_t wires, tables;   // steps in bytes
+};
+DASH_HD uint32_t rep_count(const Reps& R) { return R.n ? R.n : 1u; }
+
 struct GateLaunch {
     AesKey key;
     const uint32_t* ttab;       // device [4][256]
     const ModInfo* mods;        // device [256]
     uint32_t layer;
     uint32_t njobs;             // set by the launcher
+    Reps reps;
     GateJob jobs[kMaxJobs];
 };
 
@@ -75,6 +84,43 @@ struct DrawLaunch {
     uint32_t layer;
     uint32_t pad_;
     DrawJob jobs[kMaxDrawJobs];
+};
+
+// the zero labels of a gadget's gates (domain DOM_GATE), all of one element range and in one arena: label j at base + off
+struct DrawManyJob { uint32_t m, slot; uint64_t off; };
+constexpr int kMaxDrawMany = 200;
+struct DrawManyLaunch {
+    AesKey key;
+    const uint32_t* ttab;
+    const ModInfo* mods;
+    uint64_t elem_base;
+    uint32_t layer, n_elem;
+    Reps reps;
+    uint8_t* base;
+    DrawManyJob jobs[kMaxDrawMany];
+};
+
+// garbler, scaling gadget: everything that its repetitions form from drawn zero labels without a hash, in one launch
+struct HalveJob {
+    uint32_t p, addc0, addc, pad_;   // constant added before the first halving, and after each (the ShiftDown)
+    LView x, one, cast, b, out;      // residue, constant-one wire; cast wire and halved residue of the first repetition; out.p null: no output
+};
+struct ScaleFreeLaunch {
+    const ModInfo* mods;
+    uint32_t n_elem, n, nres, pad_;
+    Reps reps;
+    // sums of the digit wires: wire (residue i, digit j) at a1 + i res_step + a_prefix[j]; C[j] the carry into digit j (j < n)
+    const uint8_t* a1;
+    int64_t res_step, cs;
+    uint32_t m[kMaxChain + 1];
+    uint64_t a_prefix[kMaxChain + 1];
+    const uint8_t* C[kMaxChain + 1];
+    uint8_t* S[kMaxChain + 1];
+    // the mod-2 wire: up of the first repetition = x0 + x0_coef one, of each further one = bit of the one before + up_coef one
+    LView x0, one2, up, bit;
+    LView last;                      // bit of the last repetition + last_coef one: the layer's output or the next launch's x0
+    uint32_t x0_coef, up_coef, last_coef, pad2_;
+    HalveJob halve[14];
 };
 
 struct AffineJob {
@@ -192,6 +238,7 @@ struct DigitsLaunch {
     uint8_t* sum1;                        // label tensor of S_1 (chunk stride out_cs), or null
     uint64_t sum_prefix[kMaxChain + 1];   // S_j starts this many bytes after S_1
     uint32_t sums_in_launch;
+    Reps reps;                            // garbler
     DigitsRes res[16];
 };
 

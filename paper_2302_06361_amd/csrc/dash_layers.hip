@@ -102,6 +102,7 @@ struct GateBatcher {
         memset(L, 0, sizeof(L));
         for (int t = 0; t < kSlots; t++) { L[t].layer = layer; nj[t] = 0; }
     }
+    void repeat(const Reps& R) { for (int t = 0; t < kSlots; t++) L[t].reps = R; }      // of every job
     void launch(int t) {
         if (nj[t] && status == DASH_OK) status = garble ? launch_garble(c, L[t], nj[t], s) : launch_eval(c, L[t], nj[t], s);
         nj[t] = 0;
@@ -173,12 +174,14 @@ bool few_rows(const dash_ctx* c, uint64_t rows) { return rows <= c->few_rows_max
 int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64_t elem_base, const LView* x, int first_res,
               int negate, uint32_t slot_base, uint8_t* seg, const SignWires& w, hipStream_t s, const LView* up = nullptr,
               const LView* up_one = nullptr, uint32_t up_coef = 0, CastLaunch* pre = nullptr, int pre_jobs = 0, bool drawn = false,
-              const std::function<void(AffineBatcher&)>* pre_affine = nullptr, const std::vector<GateJob>* extra_gates = nullptr) {
+              const std::function<void(AffineBatcher&)>* pre_affine = nullptr, const std::vector<GateJob>* extra_gates = nullptr,
+              const Reps* reps = nullptr) {
     // pre (evaluator of the scaling gadget): the cast-and-halve step that produces x[first_res..]; it runs in the
     // launch of the digit gates when they are fused, else in a launch of its own before them
     // drawn (garbler): the caller has drawn the zero labels (sign_draws) in a launch of its own
     // pre_affine, extra_gates (garbler): free gates and projection gates of the caller that depend on drawn labels only; they
     // share the gadget's free-gate launch and, where the launches have few rows, its launch of the carry chain's gates
+    // reps (garbler of the scaling gadget): so many repetitions at once, their zero labels drawn and their free gates done by the caller
     const int k = c->k, n = c->n;
     size_t off[DASH_MAX_PRIMES * DASH_MAX_DIGITS + DASH_MAX_DIGITS], cum = 0;
     for (int sl = 0; sl < sign_nslots(c); sl++) { off[sl] = cum * E; cum += sign_slot_bytes(c, sl, first_res); }
@@ -192,7 +195,8 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
     // mixed-radix addition, least significant digit first: carry out of digit j into digit j-1.  The garbler knows every
     // zero label up front (all are drawn), so it forms all digit sums first, in one free-gate launch, and garbles the n gates
     // of the chain in one launch at the end; the evaluator has to follow the chain.
-    if (garble) {
+    const uint64_t nrep = reps ? rep_count(*reps) : 1;
+    if (garble && !reps) {
         AffineBatcher ab(c, E, s);
         if (pre_affine) (*pre_affine)(ab);
         for (int j = n; j >= 1; j--) {
@@ -202,14 +206,11 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
             if (j < n) t[nt++] = Term{w.C[j], 1};
             ab.add(c->mj[j], w.S[j], t, nt);
         }
-        if (up) {       // the output wire's zero label is drawn, so its shifted copy can be formed here already
-            Term tu[2] = {Term{w.bit, 1}, Term{*up_one, up_coef}};
-            ab.add(2, *up, tu, 2);
-        }
         ab.flush();
         if (ab.status) return ab.status;
     }
     GateBatcher gb(c, garble, E, layer, elem_base, s);
+    if (reps) gb.repeat(*reps);
     bool sums_done = false;
     // digit gates: residue i -> digit j of its rounded CRT fraction.  The n gates of a residue share their input
     // label: one launch for all k n gates, whose lanes form and compress a label once for n rows (garbler) or n
@@ -230,6 +231,7 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
         memset(&DL, 0, sizeof(DL));
         DL.n_elem = E; DL.layer = layer; DL.elem_base = elem_base; DL.n = (uint32_t)n; DL.nres = (uint32_t)(k - first_res);
         DL.out_cs = w.A[first_res][1].cs;
+        if (reps) DL.reps = *reps;
         for (int j = 1; j <= n; j++) {
             DL.m[j] = (uint32_t)c->mj[j];
             DL.row_prefix[j] = j == 1 ? 0 : DL.row_prefix[j - 1] + (uint32_t)pitch_of(c, c->mj[j - 1]);
@@ -275,14 +277,15 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
     };
     if (garble) {
         uint64_t rows = 0, extra_rows = 0;
-        for (int j = 1; j <= n; j++) rows += (uint64_t)E * c->mj[j];
-        if (extra_gates) for (const GateJob& J : *extra_gates) extra_rows += (uint64_t)E * J.p;
+        for (int j = 1; j <= n; j++) rows += nrep * E * c->mj[j];
+        if (extra_gates) for (const GateJob& J : *extra_gates) extra_rows += nrep * E * J.p;
         gb.mixed = few_rows(c, rows + extra_rows);
         if (extra_gates) {
             if (gb.mixed) {
                 for (const GateJob& J : *extra_gates) gb.add(J);
             } else {      // a launch of their own, mixed if they are few; else one per output modulus, its compile-time code
                 GateBatcher ge(c, true, E, layer, elem_base, s, few_rows(c, extra_rows));
+                if (reps) ge.repeat(*reps);
                 for (const GateJob& J : *extra_gates) ge.add(J);
                 ge.flush();
                 if (ge.status) return ge.status;
@@ -550,12 +553,122 @@ int signact_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labe
 
 // ---- scaling by 2, `repeat` times ------------------------------------------------------------
 struct ScalePlan { LView buf[2][DASH_MAX_PRIMES]; LView up, cast[DASH_MAX_PRIMES], b[DASH_MAX_PRIMES]; SignWires w; };
+// evaluator, step by step: one repetition at a time, halved residues and the shifted mod-2 wire in two buffers each
 void plan_scale(const dash_ctx* c, Arena& ar, int64_t E, ScalePlan& p) {
     for (int t = 0; t < 2; t++)
         for (int i = 0; i < c->k; i++) p.buf[t][i] = ar.labels(c, c->prime[i], E);
     p.up = ar.labels(c, 2, E);
     for (int i = 1; i < c->k; i++) { p.cast[i] = ar.labels(c, c->prime[i], E); p.b[i] = ar.labels(c, c->prime[i], E); }
     plan_sign(c, ar, E, 1, p.w);
+}
+// garbler: all repetitions of a group side by side, every zero label being drawn or a combination of drawn ones.  The wires of one
+// repetition, ar.off bytes on from those of the one before.
+void plan_scale_rep(const dash_ctx* c, Arena& ar, int64_t E, ScalePlan& p) {
+    p.up = ar.labels(c, 2, E);
+    for (int i = 1; i < c->k; i++) { p.cast[i] = ar.labels(c, c->prime[i], E); p.b[i] = ar.labels(c, c->prime[i], E); }
+    plan_sign(c, ar, E, 1, p.w);
+}
+// Repetitions in one set of launches: as many as fit kScaleScratch together (at most kScaleReps), and always one.  A small layer's
+// garbling is a chain of launches that do not fill the chip: six repetitions of 128 values at a time take 4 launches instead of 24, 62 us
+// instead of 200 (the whole network 269 -> 132); six of 1 920 values 0.9 ms of a LeNet batch less.
+// Layers of more than about 5 000 values of the 8-prime base keep one repetition at a time, whose launches fill the chip by themselves.
+constexpr size_t kScaleScratch = 32u << 20;
+constexpr int kScaleReps = 16;
+struct ScaleScratch { size_t step, next, bytes; int reps; };    // bytes of a repetition and of the wire between groups; in all; repetitions of a group
+ScaleScratch scale_scratch(const dash_ctx* c, int64_t E) {
+    Arena one{nullptr, 0}, rep{nullptr, 0};
+    ScalePlan p;
+    plan_scale(c, one, E, p);
+    plan_scale_rep(c, rep, E, p);
+    ScaleScratch r;
+    r.step = rep.off; r.next = label_bytes(c, 2, E);
+    // Like the evaluator's need the figure does not depend on the number of repetitions and grows with E, so that a buffer for one
+    // layer call serves smaller ones.  (One repetition and the wire between groups are within the evaluator's need, with its spare
+    // buffers of k residues.)
+    const size_t wanted = r.next + kScaleReps * r.step;
+    r.bytes = std::max(one.off, std::min(kScaleScratch, wanted));
+    r.reps = r.step ? (int)std::max<size_t>(1, std::min<size_t>(kScaleReps, (r.bytes - r.next) / r.step)) : 1;
+    return r;
+}
+
+// One layer of the scaling gadget, garbler.  Per group of repetitions four launches: the zero labels, everything that follows from them
+// without a hash, the digit gates, the gates of the carry chains and the casts.
+int scale_garble(dash_ctx* c, const dash_layer* L, const dash_labels* in, dash_labels* out, uint8_t* tables, uint8_t* scratch, hipStream_t s) {
+    const int k = c->k, n = c->n;
+    const uint32_t E = (uint32_t)L->n_elem, layer = (uint32_t)L->layer_id;
+    const uint64_t eb = (uint64_t)L->elem_base;
+    const ScaleScratch sc = scale_scratch(c, E);
+    const LView between{scratch, (int64_t)16 * E, 16u};          // the mod-2 wire that one group hands to the next
+    Arena ar{scratch + sc.next, 0};
+    ScalePlan pl;
+    plan_scale_rep(c, ar, E, pl);
+    const SignWires& w = pl.w;
+    const size_t bpe = scale_bytes(c);
+    const uint32_t slots = (uint32_t)(k - 1 + sign_nslots(c));
+    const uint64_t quarter = c->P / 4;
+    const uint32_t c0 = (uint32_t)((2 - quarter % 2) % 2);
+    auto shift_of = [&](int p) { return (uint32_t)((p - quarter % p) % p); };
+    auto one = [&](int i) { return LView{c->d_one0[i], 16, 0u}; };
+    const int groups = (L->repeat + sc.reps - 1) / sc.reps, per = (L->repeat + groups - 1) / groups;
+    Reps R{0, slots, (int64_t)sc.step, (int64_t)(bpe * E)};
+    for (int r0 = 0, before = 0; r0 < L->repeat; before = (int)R.n, r0 += per) {
+        R.n = (uint32_t)std::min(per, L->repeat - r0);
+        const bool last = r0 + (int)R.n == L->repeat;
+        uint8_t* tb = tables + (size_t)r0 * bpe * E;
+        const uint32_t sb = (uint32_t)r0 * slots;
+        DrawManyLaunch D;
+        memset(&D, 0, sizeof(D));
+        int nd = 0, st = DASH_OK;
+        auto draw = [&](int m, uint32_t slot, const LView& v) {
+            if (nd == kMaxDrawMany && st == DASH_OK) { st = launch_draw_many(c, D, nd, s); nd = 0; }
+            D.jobs[nd++] = DrawManyJob{(uint32_t)m, slot, (uint64_t)(v.p - ar.base)};
+        };
+        D.elem_base = eb; D.layer = layer; D.n_elem = E; D.reps = R; D.base = ar.base;
+        for (int i = 1; i < k; i++) draw(c->prime[i], sb + (i - 1), pl.cast[i]);
+        const uint32_t ss = sb + (uint32_t)(k - 1);              // slots of the sign gadget
+        for (int i = 1; i < k; i++)
+            for (int j = 1; j <= n; j++) draw(c->mj[j], ss + i * n + (j - 1), w.A[i][j]);
+        for (int j = n; j >= 2; j--) draw(c->mj[j - 1], ss + k * n + (j - 2), w.C[j - 1]);
+        draw(2, ss + k * n + n - 1, w.bit);
+        if (st == DASH_OK) st = launch_draw_many(c, D, nd, s);
+        if (st) return st;
+
+        ScaleFreeLaunch F;
+        memset(&F, 0, sizeof(F));
+        F.n_elem = E; F.n = (uint32_t)n; F.nres = (uint32_t)(k - 1); F.reps = R;
+        F.a1 = w.A[1][1].p; F.cs = w.A[1][1].cs; F.res_step = k > 2 ? w.A[2][1].p - w.A[1][1].p : 0;
+        for (int j = 1; j <= n; j++) {
+            F.m[j] = (uint32_t)c->mj[j];
+            F.a_prefix[j] = (uint64_t)(w.A[1][j].p - w.A[1][1].p);
+            if (j < n) F.C[j] = w.C[j].p;
+            F.S[j] = w.S[j].p;
+            for (int i = 1; i < k; i++)                          // the kernel's address rule must be the layout planned above
+                if (w.A[i][j].p != F.a1 + (i - 1) * F.res_step + F.a_prefix[j]) return DASH_EINVAL;
+        }
+        // ShiftUp: + P/2, i.e. + 1 on the mod-2 residue only
+        F.x0 = r0 ? between : view_of(in, 0); F.x0_coef = r0 ? 0u : 1u;
+        F.one2 = one(0); F.up = pl.up; F.bit = w.bit; F.up_coef = (c0 + 1) % 2;
+        F.last = last ? view_of(out, 0) : between; F.last_coef = last ? c0 : F.up_coef;
+        for (int i = 1; i < k; i++) {
+            HalveJob& J = F.halve[i - 1];
+            const int p = c->prime[i];
+            const LView end{pl.b[i].p + (before - 1) * (int64_t)sc.step, pl.b[i].cs, 16u};
+            J.p = (uint32_t)p; J.addc = shift_of(p); J.addc0 = r0 ? J.addc : 0u;
+            J.x = r0 ? end : view_of(in, i); J.one = one(i); J.cast = pl.cast[i]; J.b = pl.b[i];
+            if (last) J.out = view_of(out, i);
+        }
+        if ((st = launch_scale_free(c, F, s)) != DASH_OK) return st;
+
+        std::vector<GateJob> casts;
+        size_t cum = 0;
+        for (int i = 1; i < k; i++) {
+            casts.push_back(phi_job(2, c->prime[i], pl.up, c->phi_ident, sb + (i - 1), pl.cast[i], tb + cum * E));
+            cum += 2 * pitch_of(c, c->prime[i]);
+        }
+        st = sign_core(c, true, E, layer, eb, pl.b, 1, 0, ss, tb + cum * E, w, s, nullptr, nullptr, 0, nullptr, 0, true, nullptr, &casts, &R);
+        if (st) return st;
+    }
+    return DASH_OK;
 }
 
 int scale_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels* in, dash_labels* out, uint8_t* tables,
@@ -565,49 +678,43 @@ int scale_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels
     if (L->repeat < 1) return DASH_EINVAL;
     const uint32_t E = (uint32_t)L->n_elem, layer = (uint32_t)L->layer_id;
     const uint64_t eb = (uint64_t)L->elem_base;
+    if (garble) return scale_garble(c, L, in, out, tables, scratch, s);
     Arena ar{scratch, 0};
     ScalePlan pl;
     plan_scale(c, ar, E, pl);
     const size_t bpe = scale_bytes(c);
     const uint32_t slots_per_rep = (uint32_t)(k - 1 + ns);
-    // constant-one wires: zero labels for the garbler, active labels for the evaluator
-    LView one[DASH_MAX_PRIMES];
-    for (int i = 0; i < k; i++) one[i] = LView{garble ? c->d_one0[i] : c->d_one[i], 16, 0u};
+    LView one[DASH_MAX_PRIMES];       // constant-one wires
+    for (int i = 0; i < k; i++) one[i] = LView{c->d_one[i], 16, 0u};
     const uint64_t quarter = c->P / 4;
 
-    // Per repetition: the casts of the mod-2 wire into the odd primes and b_i = (x_i - cast_i) / 2 (evaluator: one
-    // cast-and-halve launch; garbler: the cast gates, then the halving of the zero labels as a free-gate launch), then the
-    // sign gadget, whose free-gate (garbler) or chain (evaluator) launch also writes the next repetition's shifted mod-2
-    // wire.  The ShiftDown of the odd residues is a constant that the next repetition's halving adds first; only the
-    // last repetition writes it out.
+    // Per repetition: the casts of the mod-2 wire into the odd primes and b_i = (x_i - cast_i) / 2, then the sign gadget, whose chain
+    // launch also writes the next repetition's shifted mod-2 wire.  The ShiftDown of the odd residues is a constant that the next
+    // repetition's halving adds first; only the last repetition writes it out.
     LView x[DASH_MAX_PRIMES];
     for (int i = 0; i < k; i++) x[i] = view_of(in, i);
     const uint32_t c0 = (uint32_t)((2 - quarter % 2) % 2);
-    // ShiftUp: + P/2, i.e. +1 on the mod-2 residue only (the garbler forms it in its first free-gate launch)
-    auto shift_up = [&](AffineBatcher& ab) {
-        Term t[2] = {Term{x[0], 1}, Term{one[0], 1}};
-        ab.add(2, pl.up, t, 2);
-    };
-    if (!garble) {
-        if (const int set = act_set(c)) {
-            ActLaunch A;
-            memset(&A, 0, sizeof(A));
-            A.elem_base = eb; A.layer = layer; A.n_elem = E; A.repeat = (uint32_t)L->repeat;
-            A.rep_bytes = (uint64_t)bpe * E; A.rep_slots = slots_per_rep;
-            A.in2 = x[0]; A.out2 = view_of(out, 0); A.one2 = c->d_one[0];
-            A.up_coef = (c0 + 1) % 2; A.last_coef = c0;
-            size_t cum = 0;
-            for (int i = 1; i < k; i++) {
-                ActRes& R = A.res[i - 1];
-                R.p = (uint32_t)c->prime[i]; R.in = x[i]; R.out = view_of(out, i);
-                R.cast_table = tables + cum * E; R.cast_slot = (uint32_t)(i - 1); R.shift = c->d_shift[i];
-                cum += 2 * pitch_of(c, c->prime[i]);
-            }
-            act_sign(c, A, E, tables + cum * E, 1, (uint32_t)(k - 1));
-            return launch_act_eval(c, set, A, false, s);
+    if (const int set = act_set(c)) {
+        ActLaunch A;
+        memset(&A, 0, sizeof(A));
+        A.elem_base = eb; A.layer = layer; A.n_elem = E; A.repeat = (uint32_t)L->repeat;
+        A.rep_bytes = (uint64_t)bpe * E; A.rep_slots = slots_per_rep;
+        A.in2 = x[0]; A.out2 = view_of(out, 0); A.one2 = c->d_one[0];
+        A.up_coef = (c0 + 1) % 2; A.last_coef = c0;
+        size_t cum = 0;
+        for (int i = 1; i < k; i++) {
+            ActRes& R = A.res[i - 1];
+            R.p = (uint32_t)c->prime[i]; R.in = x[i]; R.out = view_of(out, i);
+            R.cast_table = tables + cum * E; R.cast_slot = (uint32_t)(i - 1); R.shift = c->d_shift[i];
+            cum += 2 * pitch_of(c, c->prime[i]);
         }
+        act_sign(c, A, E, tables + cum * E, 1, (uint32_t)(k - 1));
+        return launch_act_eval(c, set, A, false, s);
+    }
+    {
         AffineBatcher ab(c, E, s);
-        shift_up(ab);
+        Term t[2] = {Term{x[0], 1}, Term{one[0], 1}};       // ShiftUp: + P/2, i.e. +1 on the mod-2 residue only
+        ab.add(2, pl.up, t, 2);
         ab.flush();
         if (ab.status) return ab.status;
     }
@@ -618,58 +725,30 @@ int scale_layer(dash_ctx* c, const dash_layer* L, bool garble, const dash_labels
         // b of this repetition alternates between two buffer sets (the halving reads the one before)
         LView* bnew = rep & 1 ? pl.buf[0] : pl.b;
         const LView* bold = rep & 1 ? pl.b : pl.buf[0];
-        // the shifted mod-2 wire likewise: this repetition reads one buffer (its cast gates: the garbler's run in the gadget's
-        // last launch) while the sign gadget writes the next repetition's into the other
+        // the shifted mod-2 wire likewise: this repetition reads one buffer while the sign gadget writes the next one's into the other
         const LView up_cur = rep & 1 ? pl.buf[1][0] : pl.up, up_next = rep & 1 ? pl.up : pl.buf[1][0];
         auto addc_of = [&](uint32_t p) { return rep == 0 ? 0u : (uint32_t)((p - quarter % p) % p); };
         size_t cum = 0;
-        if (garble) {
-            DrawBatcher db(c, E, layer, eb, s);      // with the zero labels of this repetition's sign gadget
-            for (int i = 1; i < k; i++) db.add(c->prime[i], DOM_GATE, sb + (i - 1), pl.cast[i]);
-            sign_draws(c, db, 1, sb + (k - 1), pl.w);
-            db.flush();
-            if (db.status) return db.status;
-            // the cast gates and the halving of the zero labels depend on drawn labels only: they go into the sign gadget's
-            // launches (its free-gate launch; its carry-chain launch where the rows are few)
-            std::vector<GateJob> casts;
-            for (int i = 1; i < k; i++) {
-                casts.push_back(phi_job(2, c->prime[i], up_cur, c->phi_ident, sb + (i - 1), pl.cast[i], tb + cum * E));
-                cum += 2 * pitch_of(c, c->prime[i]);
-            }
-            const std::function<void(AffineBatcher&)> halving = [&](AffineBatcher& ab) {
-                if (rep == 0) shift_up(ab);
-                for (int i = 1; i < k; i++) {
-                    const uint32_t p = c->prime[i], inv2 = (p + 1) / 2, addc = addc_of(p);
-                    Term t[3] = {Term{rep == 0 ? x[i] : bold[i], inv2}, Term{pl.cast[i], p - inv2}, Term{one[i], (inv2 * addc) % p}};
-                    ab.add(p, bnew[i], t, addc ? 3 : 2);
-                }
-            };
-            const uint32_t upc = (c0 + 1) % 2;
-            const int st = sign_core(c, true, E, layer, eb, bnew, 1, 0, sb + (k - 1), tb + cum * E, pl.w, s, last ? nullptr : &up_next,
-                                     last ? nullptr : &one[0], upc, nullptr, 0, true, &halving, &casts);
-            if (st) return st;
-        } else {
-            CastLaunch CL;
-            memset(&CL, 0, sizeof(CL));
-            CL.n_elem = E; CL.layer = layer; CL.elem_base = eb; CL.y = up_cur;
-            int nj = 0;
-            for (int i = 1; i < k; i++) {
-                const uint32_t p = c->prime[i];
-                CastJob& J = CL.jobs[nj++];
-                J.p = p; J.slot = sb + (i - 1); J.table = tb + cum * E;
-                J.x = rep == 0 ? x[i] : bold[i];
-                // the constant comes as a label of its own (the context holds addc * one): coefficient 1, a packed addition
-                J.one = LView{c->d_shift[i], 16, 0u};
-                J.addc = addc_of(p) ? 1u : 0u;
-                J.out = bnew[i];
-                cum += 2 * pitch_of(c, p);
-            }
-            // (k - 1 <= kMaxJobs: one launch, which sign_core merges with the digit gates' when those are fused)
-            const uint32_t upc = (c0 + 1) % 2;
-            const int st = sign_core(c, false, E, layer, eb, bnew, 1, 0, sb + (k - 1), tb + cum * E, pl.w, s, last ? nullptr : &up_next,
-                                     last ? nullptr : &one[0], upc, &CL, nj);
-            if (st) return st;
+        CastLaunch CL;
+        memset(&CL, 0, sizeof(CL));
+        CL.n_elem = E; CL.layer = layer; CL.elem_base = eb; CL.y = up_cur;
+        int nj = 0;
+        for (int i = 1; i < k; i++) {
+            const uint32_t p = c->prime[i];
+            CastJob& J = CL.jobs[nj++];
+            J.p = p; J.slot = sb + (i - 1); J.table = tb + cum * E;
+            J.x = rep == 0 ? x[i] : bold[i];
+            // the constant comes as a label of its own (the context holds addc * one): coefficient 1, a packed addition
+            J.one = LView{c->d_shift[i], 16, 0u};
+            J.addc = addc_of(p) ? 1u : 0u;
+            J.out = bnew[i];
+            cum += 2 * pitch_of(c, p);
         }
+        // (k - 1 <= kMaxJobs: one launch, which sign_core merges with the digit gates' when those are fused)
+        const uint32_t upc = (c0 + 1) % 2;
+        const int st = sign_core(c, false, E, layer, eb, bnew, 1, 0, sb + (k - 1), tb + cum * E, pl.w, s, last ? nullptr : &up_next,
+                                 last ? nullptr : &one[0], upc, &CL, nj);
+        if (st) return st;
         if (last) {
             AffineBatcher ab(c, E, s);
             Term t0[2] = {Term{pl.w.bit, 1}, Term{one[0], c0}};
@@ -711,7 +790,7 @@ int layer_sizes(const dash_ctx* c, const dash_layer* L, int64_t* out_elems, size
         case DASH_SIGN: { SignWires w; plan_sign(c, ar, E, 0, w); oe = E; tb = signact_bytes(c) * (size_t)E; sb = ar.off; break; }
         case DASH_SCALE: {
             if (L->repeat < 1) return DASH_EINVAL;
-            ScalePlan p; plan_scale(c, ar, E, p); oe = E; tb = scale_bytes(c) * (size_t)E * (size_t)L->repeat; sb = ar.off; break;
+            oe = E; tb = scale_bytes(c) * (size_t)E * (size_t)L->repeat; sb = scale_scratch(c, E).bytes; break;
         }
         case DASH_PROJ: {
             if (L->p_index < 0 || L->p_index >= c->k || L->q_index < 0 || L->q_index >= c->k) return DASH_EINVAL;

@@ -180,6 +180,24 @@ def test_activation_sizes_around_a_block_of_the_small_gadget_kernels(n):
     run_activation(8, "scale", X, repeat=2, elem_base=2 ** 33)
 
 
+@pytest.mark.parametrize("k,n,repeat", [(2, 3, 17), (3, 5, 33), (8, 2700, 4), (12, 40, 18), (8, 12000, 2)])
+def test_scaling_repetitions_garbled_in_groups(k, n, repeat):
+    """the garbler takes as many repetitions at once as fit 32 MiB of scratch, at most 16: two groups of unequal length, three, two of
+    two, two of nine with more labels than one drawing launch holds, and one repetition at a time; out over in"""
+    P = int(np.prod([int(p) for p in workloads.PRIMES[:k]], dtype=object))
+    X = np.random.default_rng(k * 1000 + n).integers(0, P, n)
+    run_activation(k, "scale", X, repeat=repeat, elem_base=2 ** 32 - 2, in_place=n != 2700)
+
+
+def test_scaling_scratch_grows_with_the_layer_and_not_with_the_repetitions():
+    """a scratch buffer sized for one scaling layer serves smaller ones and other numbers of repetitions"""
+    from paper_2302_06361_amd import Layer, SCALE
+    ctx, _ = both(8)
+    sizes = [ctx.layer_sizes(Layer(SCALE, 1, n, repeat=1))[2] for n in (1, 2, 100, 700, 701, 5000, 6000, 9000, 20000)]
+    assert sizes == sorted(sizes)
+    assert ctx.layer_sizes(Layer(SCALE, 1, 700, repeat=16))[2] == sizes[3]
+
+
 def test_activation_single_element():
     run_activation(8, "relu", np.array([12345]))
     run_activation(8, "scale", np.array([9699689]), repeat=3)
