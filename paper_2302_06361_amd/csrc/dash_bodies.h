@@ -27,6 +27,51 @@ struct alignas(16) Dw4 { uint32_t w[4]; };
 DASH_HD Dw4 ld_chunk(const LView& v, uint32_t e, int ch) { return *(const Dw4*)(v.p + (int64_t)ch * v.cs + lane_off(v, e)); }
 DASH_HD void st_chunk(const LView& v, uint32_t e, int ch, const Dw4& d) { *(Dw4*)(v.p + (int64_t)ch * v.cs + lane_off(v, e)) = d; }
 
+// N dwords at base + off (base the same in all lanes: scalar base and 32-bit offset), 4-byte aligned, as wide as the hardware takes them
+template <int N> DASH_HD void ld_dwords(const void* base, uint32_t off, uint32_t* w) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto* src = (const __attribute__((address_space(1))) uint8_t*)base + off;
+#pragma unroll
+    for (int i = 0; i < N; i++) w[i] = *(const __attribute__((address_space(1))) uint32_t*)(src + 4 * i);
+#else
+    const uint32_t* src = (const uint32_t*)((const uint8_t*)base + off);
+    for (int i = 0; i < N; i++) w[i] = src[i];
+#endif
+}
+// 16 bytes at base + off, 16-byte aligned
+DASH_HD Dw4 ld_dw4(const uint8_t* base, uint32_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)((const __attribute__((address_space(1))) uint8_t*)base + off);
+    return Dw4{{v.x, v.y, v.z, v.w}};
+#else
+    return *(const Dw4*)(base + off);
+#endif
+}
+// dword i of a row at base + off
+DASH_HD void st_row(uint8_t* base, uint32_t off, int i, uint32_t w) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    *(__attribute__((address_space(1))) uint32_t*)((__attribute__((address_space(1))) uint8_t*)base + off + 4 * i) = w;
+#else
+    *(uint32_t*)(base + off + 4 * i) = w;
+#endif
+}
+// dwords 0..N-1 of the label at element offset eo (16 bytes an element) of a tensor of chunk stride cs, es = 16
+template <int N> DASH_HD void ld_label(const uint8_t* p, int64_t cs, uint32_t eo, uint32_t* w) {
+#pragma unroll
+    for (int ch = 0; ch < (N + 3) / 4; ch++) {
+        const Dw4 d = ld_dw4(p + (int64_t)ch * cs, eo);
+#pragma unroll
+        for (int q = 0; q < 4; q++) if (4 * ch + q < N) w[4 * ch + q] = d.w[q];
+    }
+}
+// keeps what stands before it from being moved behind what follows, and the other way round (loads ahead of a hash)
+DASH_HD void schedule_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // compressed label and colour of a wire of modulus 2 (a sign bit or a mod-2 residue): the 128-digit description
 // when that is the context's label length of modulus 2, the run-time record otherwise
 template <class LoadDw>
@@ -250,6 +295,57 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
     else if constexpr (std::is_same<QD, PerJobMod>::value) with_mod(Mq, finish);
     else finish(Mq);
 }
+
+// Garbler, a batch of gates of one input modulus and one function table (carry gates of the sign gadget): the lane keeps its value a.
+// The rows of a batch, gate * m + a in order, are dealt to V waves in tiles of 64, and V tiles are a multiple of the input modulus m: a, with it
+// the multiple of R_p that forms the label and the one of R_q that the row carries, stays the same from tile to tile and is held in
+// registers, and so is the lane's place relative to the tile's first gate.  What is left per row is the label's addition and
+// compression, the hash, and two packed additions.  keys(): the round keys.
+struct ChainRows {
+    const uint8_t *in, *out0, *phi;      // zero labels of the input and the output wires; function table
+    int64_t in_cs, out_cs;
+    uint8_t* table;
+    uint64_t elem_base;
+    uint32_t n, slot, layer;             // gates
+};
+template <class MP, class QD, class Keys, class Tab>
+DASH_HD void chain_garble_rows(const ChainRows& J, const MP& P, const QD& Q, uint32_t V, uint32_t t0, uint32_t lane, Keys keys, const Tab& T) {
+    constexpr uint32_t m = MP::m, pitch = QD::ndw * 4;
+    constexpr int NP = (int)MP::ndw, NQ = (int)QD::ndw;
+    const uint32_t n = J.n, tiles = (uint32_t)(((uint64_t)n * m + 63) / 64);
+    if (t0 >= tiles) return;
+    const uint32_t off = t0 * 64 % m + lane;                          // (rows of a batch are below 2^32)
+    const uint32_t dg = off / m, a = off - dg * m, step = 64 * V / m;
+    uint32_t da[NP], df[NQ];
+    ld_dwords<NP>(P.dtab, a * (MP::ndw * 4), da);
+    ld_dwords<NQ>(Q.dtab, J.phi[a] * pitch, df);
+#pragma unroll
+    for (int i = 0; i < NP; i++) da[i] = offset4(da[i], P);
+#pragma unroll
+    for (int i = 0; i < NQ; i++) df[i] = offset4(df[i], Q);
+    const uint32_t row0 = dg * m;
+    uint32_t gb = t0 * 64 / m, z[NP], o[NQ];                          // first gate of the tile
+    // the lane's gate as an offset from gate b; past the end the last one (read, never stored)
+    auto eo = [&](uint32_t b) { return 16 * (dg < n - b ? dg : n - 1 - b); };
+    ld_label<NP>(J.in + (uint64_t)gb * 16, J.in_cs, eo(gb), z);
+    for (uint32_t t = t0; t < tiles; t += V) {
+        const uint32_t next = t + V < tiles ? gb + step : gb;
+        ld_label<NQ>(J.out0 + (uint64_t)gb * 16, J.out_cs, eo(gb), o);
+        uint32_t colour;
+        const U128 K = compress(P, [&](int i) { return addmod4_off(z[i], da[i], P); }, &colour);
+        ld_label<NP>(J.in + (uint64_t)next * 16, J.in_cs, eo(next), z);
+        schedule_fence();
+        const U128 h = hash_block(K, J.elem_base + gb + dg, J.slot, J.layer, keys(), T);
+#pragma unroll
+        for (int i = 0; i < NQ; i++) o[i] = offset4(addmod4_off(o[i], df[i], Q), Q);
+        uint8_t* rows = J.table + (uint64_t)gb * (m * pitch);
+        const uint32_t ro = (row0 + colour) * pitch;
+        if (dg < n - gb) decompress(Q, h, [&](int i, uint32_t hd) { st_row(rows, ro, i, addmod4_off(hd, o[i], Q)); });
+        gb = next;
+    }
+}
+// tiles of 64 rows after which a lane comes back to its value
+DASH_HD uint32_t chain_quantum(uint32_t m) { uint32_t q = m; for (int i = 0; i < 6 && !(q & 1); i++) q /= 2; return q; }
 
 // eval: one lane per gate
 template <class QD, class Tab>
@@ -500,19 +596,40 @@ DASH_HD void digits_eval_wide_body(const DigitsLaunch& L, uint32_t bx, uint32_t 
 // ---- garbler, digit gates of the sign gadget ---------------------------------------------------
 // One lane per (element g, value a) of a residue: the label of a is formed and compressed once, then one
 // ciphertext row per digit: rows[colour] = out0 + phi_j(a) R_{m_j} + H_{m_j}(label, slot_j).
-template <class MO>
-DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const MO& Mo, const U128& h, uint32_t f, uint32_t colour, uint32_t g, int j, uint32_t rep) {
+DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const ModInfo& Mo, const U128& h, uint32_t f, uint32_t colour, uint32_t g, int j, uint32_t rep) {
     uint8_t* seg = R.table + (int64_t)rep * L.reps.tables + (size_t)L.n_elem * R.p * L.row_prefix[j];
     uint32_t* row = (uint32_t*)(seg + ((size_t)g * R.p + colour) * (Mo.ndw * 4));
     const LView out0{R.out + (int64_t)rep * L.reps.wires + L.out_prefix[j], L.out_cs, 16u};
     const uint32_t* df = Mo.dtab + f * Mo.ndw;
-    if constexpr (cmod_m<MO>::value != 0) {
-        uint32_t pay[MO::ndw];
+    decompress(Mo, h, [&](int i, uint32_t hd) { row[i] = addmod4(addmod4(ld_dw(out0, g, i), gload32(df + i), Mo), hd, Mo); });
+}
+// Compile-time moduli: the rows of digits j0..j1 (j0 = 1 or 2 and up) of one (element, value a).  Everything but the hash costs as little as can be, the
+// kernel being bound by vector issue: the tile's first element is in the scalar base addresses and the lane's part in 32-bit offsets
+// that serve every digit; what a row adds to its hash is fetched before the hash.
+template <class MO, class Tab>
+DASH_HD void digit_rows(const DigitsLaunch& L, const uint8_t* phi, uint32_t p, const uint8_t* out0, int64_t out_step, uint8_t* seg, int64_t seg_step, const MO& Mo,
+                        SlotHash& S, uint32_t& hi, uint32_t& slot, int count, uint32_t a, uint32_t eo, uint32_t row, const Tab& T) {
+    constexpr int N = (int)MO::ndw;
+    const uint32_t ro = row * (MO::ndw * 4);
+    uint32_t f = phi[a];
+    for (int j = 0; j < count; j++) {
+        uint32_t pay[N], o[N];
+        ld_label<N>(out0, L.out_cs, eo, o);
+        ld_dwords<N>(Mo.dtab, f * (MO::ndw * 4), pay);
+        phi += p;
+        if (j + 1 < count) f = phi[a];
+        schedule_fence();
+        if ((slot & ~0xffu) != hi) {                // another upper part of the slot: what the hashes share is formed again
+            S.x[2] ^= hi ^ (slot & ~0xffu);
+            hi = slot & ~0xffu;
+            S = slot_hash_start(S.x, L.key.rk, T);
+        }
+        const U128 h = slot_hash(S, slot, L.key.rk, T);
+        slot++;
 #pragma unroll
-        for (int i = 0; i < (int)MO::ndw; i++) pay[i] = addmod4(ld_dw(out0, g, i), gload32(df + i), Mo);
-        decompress(Mo, h, [&](int i, uint32_t hd) { row[i] = addmod4(pay[i], hd, Mo); });
-    } else {
-        decompress(Mo, h, [&](int i, uint32_t hd) { row[i] = addmod4(addmod4(ld_dw(out0, g, i), gload32(df + i), Mo), hd, Mo); });
+        for (int i = 0; i < N; i++) pay[i] = offset4(addmod4(o[i], pay[i], Mo), Mo);
+        decompress(Mo, h, [&](int i, uint32_t hd) { st_row(seg, ro, i, addmod4_off(hd, pay[i], Mo)); });
+        out0 += out_step; seg += seg_step;
     }
 }
 // j0 = 0: all n digits of the lane's (element, value); j0 = 1..n: digit j0 only (gadgets over few elements: a lane per
@@ -536,17 +653,36 @@ DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by,
         K = compress(P, [&](int i) { return addmod4(ld_dw(in, g, i), gload32(da + i), P); }, &colour);
     });
     const int jlo = j0 ? (int)j0 : 1, jhi = j0 ? (int)j0 : (int)L.n;
+    if constexpr (cmod_m<MC>::value != 0) {
+        const uint64_t elem = L.elem_base + g;
+        const uint32_t s0 = slot0 + (uint32_t)(jlo - 1);
+        const uint32_t x[4] = {K.w[0] ^ (uint32_t)elem, K.w[1] ^ (uint32_t)(elem >> 32), K.w[2] ^ (s0 & ~0xffu), K.w[3] ^ (L.layer & 0xffffu)};
+        SlotHash S = slot_hash_start(x, L.key.rk, T);
+        uint32_t slot = s0, hi = s0 & ~0xffu;
+        const uint32_t eo = dg * 16, row = dg * Mp.m + colour;
+        uint8_t* seg = R.table + (int64_t)rep * L.reps.tables;
+        const uint8_t* out0 = R.out + (int64_t)rep * L.reps.wires + (uint64_t)g0 * 16;
+        const int64_t rows = (int64_t)L.n_elem * Mp.m, before = (int64_t)g0 * Mp.m;       // of a segment; before the tile's first element
+        int j = jlo;
+        if (j == 1) {
+            const M1 Mf{ld_mod(L.mods, L.m[1]).dtab};
+            digit_rows(L, R.phi, R.p, out0, 0, seg + before * (int64_t)(M1::ndw * 4), 0, Mf, S, hi, slot, 1, a, eo, row, T);
+            j = 2;
+        }
+        if (j <= jhi) {
+            const MC Mc{ld_mod(L.mods, L.m[2]).dtab};
+            const int64_t step = rows * (int64_t)(MC::ndw * 4);
+            digit_rows(L, R.phi + (uint32_t)(j - 1) * R.p, R.p, out0 + L.out_prefix[j], (int64_t)(L.out_prefix[j < (int)L.n ? j + 1 : j] - L.out_prefix[j]),
+                       seg + rows * (int64_t)(M1::ndw * 4) + (j - 2) * step + before * (int64_t)(MC::ndw * 4), step, Mc, S, hi, slot, jhi - j + 1, a, eo, row, T);
+        }
+        return;
+    }
     SlotHasher H(K, L.elem_base + g, L.layer);
     for (int j = jlo; j <= jhi; j++) {
         const uint32_t f = R.phi[(size_t)(j - 1) * R.p + a];
         const U128 h = H.get(slot0 + (uint32_t)(j - 1), L.key.rk, T);
-        if constexpr (cmod_m<MC>::value != 0) {
-            if (j == 1) digit_row(L, R, M1{ld_mod(L.mods, L.m[1]).dtab}, h, f, colour, g, 1, rep);
-            else digit_row(L, R, MC{ld_mod(L.mods, L.m[2]).dtab}, h, f, colour, g, j, rep);
-        } else {
-            const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
-            digit_row(L, R, Mo, h, f, colour, g, j, rep);
-        }
+        const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
+        digit_row(L, R, Mo, h, f, colour, g, j, rep);
     }
 }
 

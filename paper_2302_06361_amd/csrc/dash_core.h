@@ -268,6 +268,12 @@ DASH_HD uint32_t addmod4(uint32_t a, uint32_t b, const MI& M) {
     const uint32_t h = lerp4(a, b, (M.m & 1u) * kOnes) + (128u - (M.m + 1u) / 2u) * kOnes;
     return t - ((h >> 7) & kOnes) * M.m;
 }
+// the same with b prepared once for several sums: offset4(b) = b + (128 - m) where that fits a byte
+template <class MI> DASH_HD uint32_t offset4(uint32_t b, const MI& M) { return cmod_m<MI>::value != 2 && M.m < 128 ? b + M.c4 : b; }
+template <class MI>
+DASH_HD uint32_t addmod4_off(uint32_t a, uint32_t b_off, const MI& M) {
+    return cmod_m<MI>::value != 2 && M.m < 128 ? settle4(a + b_off, M.m) : addmod4(a, b_off, M);
+}
 // (a - b) mod m on 4 packed digits.
 template <class MI>
 DASH_HD uint32_t submod4(uint32_t a, uint32_t b, const MI& M) {
@@ -511,10 +517,11 @@ DASH_HD U128 hash_block(const U128& K, uint64_t elem, uint32_t slot, uint32_t la
 // the state, it reaches one column in round 1 and one byte of every column in round 2.  Everything else of the two rounds is done
 // once: each further hash looks up 5 entries in them instead of 32.
 struct SlotHash { uint32_t x[4], b2, c[4]; };      // hash input; column 2 after round 1 and the columns after round 2, without what the slot's low byte contributes
+// (from the hash input, its slot's low byte zero)
 template <class Tab>
-DASH_HD SlotHash slot_hash_start(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const uint32_t* rk, const Tab& T) {
+DASH_HD SlotHash slot_hash_start(const uint32_t x[4], const uint32_t* rk, const Tab& T) {
     SlotHash S;
-    S.x[0] = K.w[0] ^ (uint32_t)elem; S.x[1] = K.w[1] ^ (uint32_t)(elem >> 32); S.x[2] = K.w[2] ^ (slot & ~0xffu); S.x[3] = K.w[3] ^ (layer & 0xffffu);
+    S.x[0] = x[0]; S.x[1] = x[1]; S.x[2] = x[2]; S.x[3] = x[3];
     const uint32_t a0 = S.x[0] ^ rk[0], a1 = S.x[1] ^ rk[1], a2 = S.x[2] ^ rk[2], a3 = S.x[3] ^ rk[3];
     const uint32_t b0 = aes_column(a0, a1, a2, a3, rk[4], T), b1 = aes_column(a1, a2, a3, a0, rk[5], T), b3 = aes_column(a3, a0, a1, a2, rk[7], T);
     if constexpr (tab_two<Tab>::value) {
@@ -535,6 +542,11 @@ DASH_HD SlotHash slot_hash_start(const U128& K, uint64_t elem, uint32_t slot, ui
         S.c[3] = xor3(T.template at<0, 0>(b3), T.template at<1, 1>(b0), T.template at<2, 2>(b1)) ^ rk[11];
     }
     return S;
+}
+template <class Tab>
+DASH_HD SlotHash slot_hash_start(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const uint32_t* rk, const Tab& T) {
+    const uint32_t x[4] = {K.w[0] ^ (uint32_t)elem, K.w[1] ^ (uint32_t)(elem >> 32), K.w[2] ^ (slot & ~0xffu), K.w[3] ^ (layer & 0xffffu)};
+    return slot_hash_start(x, rk, T);
 }
 // the hash for a slot with the same upper 24 bits
 template <class Tab>
@@ -618,6 +630,19 @@ DASH_HD uint32_t take_superdigit(U128& x, const MI& M, uint32_t bits) {
 // two: 89 vector instructions instead of 197 for m = 96 (20 digits), 110 instead of 283 for m = 204, 136 instead of 333 for m = 37.
 template <uint32_t MOD> struct Frac { static constexpr cm::FracPlan P = cm::frac_plan(MOD); };
 
+// acc += a * b (b the same in all lanes), and 1 to over where the 64-bit sum overflows and Carry asks for it.  (As assembly because the compiler takes sums of
+// products apart, products first, and forms the carry by a comparison: 25 instead of 14 instructions for the product of m = 96.)
+template <bool Carry>
+DASH_HD void mad64(uint64_t& acc, uint32_t& over, uint32_t a, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (Carry) asm("v_mad_u64_u32 %0, vcc, %2, %3, %0\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc" : "+v"(acc), "+v"(over) : "v"(a), "s"(b) : "vcc");
+    else asm("v_mad_u64_u32 %0, vcc, %1, %2, %0" : "+v"(acc) : "v"(a), "s"(b) : "vcc");
+#else
+    const uint64_t p = (uint64_t)a * b;
+    acc += p;
+    if (Carry) over += acc < p;
+#endif
+}
 // products h.w[I..3] * R.w[C - I] of column C; an overflow of the 64-bit sum is watched for only where the constants allow one
 template <uint32_t MOD, int C, int I>
 DASH_HD void frac_column(const U128& h, uint64_t& acc, uint32_t& over) {
@@ -631,9 +656,7 @@ DASH_HD void frac_column(const U128& h, uint64_t& acc, uint32_t& over) {
                     for (int i = 0; i <= I; i++) if (C - i >= 0 && C - i < 10) b += (unsigned __int128)0xffffffffu * Frac<MOD>::P.R.w[C - i];
                     return b;
                 };
-                const uint64_t p = (uint64_t)h.w[I] * r;
-                acc += p;
-                if constexpr ((bound() >> 64) != 0) over += acc < p;
+                mad64<(bound() >> 64) != 0>(acc, over, h.w[I], r);
             }
         }
         frac_column<MOD, C, I + 1>(h, acc, over);

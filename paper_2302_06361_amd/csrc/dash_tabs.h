@@ -46,16 +46,24 @@ __device__ __forceinline__ LdsTab load_ttab(uint32_t* lds, const uint32_t* g) {
     return LdsTab{lds};
 }
 
+// byte 1 of w in place and the lane's constant in byte 0: (w & 0xff00) | lane as one three-input bit operation (half the issue cost of the
+// and-or that the compiler makes of it, and of a permute)
+__device__ __forceinline__ uint32_t in_place(uint32_t w, uint32_t lane) {
+#if __has_builtin(__builtin_amdgcn_bitop3_b32)
+    return __builtin_amdgcn_bitop3_b32(w, 0xff00u, lane, 0xea);
+#else
+    return (w & 0xff00u) | lane;
+#endif
+}
 struct BankTab {
     static constexpr bool two_tables = true, rotated_keys = true;
     const uint8_t* t;
     uint32_t lane;       // byte 0: 4 * bank
     template <int R, int B> __device__ __forceinline__ uint32_t at(uint32_t w) const {
         static_assert(R < 2, "T0 and T1 only");
-        // v_perm_b32(hi = w, lo = lane): selector 0..3 bytes of lane, 4..7 bytes of w, 0x0c zero.  (Byte 1 is in place already: an
-        // and-or, half the issue cost of a permute.)
+        // v_perm_b32(hi = w, lo = lane): selector 0..3 bytes of lane, 4..7 bytes of w, 0x0c zero.
         constexpr uint32_t sel = 0x0c0c0000u | ((4u + B) << 8);
-        const uint32_t a = B == 1 ? (w & 0xff00u) | lane : __builtin_amdgcn_perm(w, lane, sel);
+        const uint32_t a = B == 1 ? in_place(w, lane) : __builtin_amdgcn_perm(w, lane, sel);
         return *(const uint32_t*)(t + a + R * 128);
     }
 };
@@ -86,7 +94,7 @@ struct HalfTab {
     template <int R, int B> __device__ __forceinline__ uint32_t at(uint32_t w) const {
         static_assert(R < 2, "T0 and T1 only");
         constexpr uint32_t sel = 0x0c0c0000u | ((4u + B) << 8);
-        const uint32_t a = B == 1 ? (w & 0xff00u) | lane : __builtin_amdgcn_perm(w, lane, sel);
+        const uint32_t a = B == 1 ? in_place(w, lane) : __builtin_amdgcn_perm(w, lane, sel);
         return *(const uint32_t*)(t + a + R * 64);
     }
 };
