@@ -448,6 +448,11 @@ int DASH_FN(launch_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStrea
         grid = dim3((uint32_t)(nb < cap ? nb : cap));
     }
     ProfScope ps(c->prof, DASH_PROF_GARBLE, s, units, bytes);
+    if (banked) {       // carry gates: a kernel of their own
+        bool done = false;
+        const int st = DASH_FN(launch_chain_garble)(c, L, njobs, s, &done);
+        if (st || done) return st;
+    }
     GateKernel k = banked ? kGarbleKernelsBanked[ki] : kGarbleKernels[ki];
     if (ki == 0 && !banked && (uint64_t)units <= c->few_rows_max) k = k_proj_garble<PerJobMod, false>;      // few rows: see garble_body
     hipLaunchKernelGGL(k, grid, dim3(banked ? kBigThreads : kThreads), 0, s, L);

@@ -1,0 +1,81 @@
+// dash_gates_chain.hip -- the garbler's kernel for large batches of carry gates of the sign gadget (Appendix, Garbled Mixed-Radix Addition):
+// many gates with one function table, over the accumulation moduli of the digit sets with compile-time kernels.
+//
+// Bound by vector issue like k_proj_garble, which takes these batches where this file's kernels do not apply; a row costs it the index
+// of its gate and value, four loads of labels and tables and their addresses on top.  Here a lane keeps its value a (chain_garble_body),
+// and the labels of the next tile are fetched under the hash of the current one.
+#include "dash_tabs.h"
+
+namespace dash {
+inline namespace DASH_RULE_NS {
+
+// Units (repetition, batch) of V waves each, one after the other over the grid's waves.
+template <class MP, class QD>
+__global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble(const GateLaunch, uint32_t V) {
+    // (the arguments through the constant address space, as in k_act_eval)
+    const auto& L = *(const __attribute__((address_space(4))) GateLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ uint32_t tt[kBankTabWords];
+    const BankTab T = load_banktab(tt, L.ttab);
+    const uint32_t reps = L.reps.n ? L.reps.n : 1u, njobs = L.njobs, units = njobs * reps, waves = gridDim.x * (kBigThreads / 64);
+    const MP P{ld_mod(L.mods, MP::m).dtab};
+    const QD Q{ld_mod(L.mods, QD::m).dtab};
+    // The round keys are read again for every tile (scalar loads): kept over the loop they push its other scalars into vector registers, and
+    // every use of one is then an instruction more (41 of them in the loop).
+    auto keys = [&]() __attribute__((always_inline)) {
+        const __attribute__((address_space(4))) uint32_t* rk = L.key.rk;
+        asm volatile("" : "+s"(rk));
+        return (const uint32_t*)rk;
+    };
+    for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
+        const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs);
+        const auto& J = L.jobs[unit - rep * njobs];
+        const int64_t wires = (int64_t)rep * L.reps.wires;
+        const ChainRows R{J.in.p + wires, J.out.p + wires, J.phi, J.in.cs, J.out.cs, J.table + (int64_t)rep * L.reps.tables,
+                          J.elem_base, J.n_elem, J.slot + rep * L.reps.slots, L.layer};
+        chain_garble_rows(R, P, Q, V, vw - unit * V, threadIdx.x & 63u, keys, T);
+    }
+}
+
+// waves per batch: a multiple of the quantum that keeps the rounds of the resident waves full.  A round of waves costs its longest batch share.
+static uint32_t chain_waves(uint64_t tiles, uint32_t units, uint32_t quantum, uint32_t resident) {
+    uint32_t best = quantum;
+    double cost = 1e300;
+    for (uint64_t V = quantum; V < tiles + quantum && V <= 4u * resident; V += quantum) {
+        const double c = (double)((units * V + resident - 1) / resident) * ((double)((tiles + V - 1) / V) + 0.5);
+        if (c < cost) { cost = c; best = (uint32_t)V; }
+    }
+    return best;
+}
+
+int DASH_FN(launch_chain_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s, bool* done) {
+    *done = false;
+    const GateJob& J0 = L.jobs[0];
+    const uint64_t rows = (uint64_t)J0.n_elem * J0.p;
+    for (int j = 0; j < njobs; j++) {
+        const GateJob& J = L.jobs[j];
+        if (J.mode != PAY_PHI || J.phi_stride != 0 || J.p != J0.p || J.q != J0.q || J.n_elem != J0.n_elem || J.in.es != 16u || J.out.es != 16u) return DASH_OK;
+    }
+    const ModInfo &Mp = c->mods[J0.p], &Mq = c->mods[J0.q];
+    constexpr uint32_t kBlocks = 512;                   // two per CU
+    const uint32_t units = (uint32_t)njobs * rep_count(L.reps);
+    const uint32_t V = chain_waves((rows + 63) / 64, units, chain_quantum(J0.p), kBlocks * (kBigThreads / 64));
+    if (rows + 64ull * V >= (1ull << 32) || (uint64_t)units * V >= (1ull << 31)) return DASH_OK;
+    const uint32_t need = (units * V + kBigThreads / 64 - 1) / (kBigThreads / 64);
+    const dim3 grid(need < kBlocks ? need : kBlocks), block(kBigThreads);
+#define DASH_CHAIN(MC, LC, M1, L1)                                                                                                        \
+    if (!*done && J0.p == MC && Mp.lam == LC && J0.q == MC) {                                                                             \
+        hipLaunchKernelGGL((k_chain_garble<CMod<MC, LC>, CMod<MC, LC>>), grid, block, 0, s, L, V);                                        \
+        *done = true;                                                                                                                     \
+    }                                                                                                                                     \
+    if (!*done && J0.p == MC && Mp.lam == LC && J0.q == M1 && Mq.lam == L1) {                                                             \
+        hipLaunchKernelGGL((k_chain_garble<CMod<MC, LC>, CMod<M1, L1>>), grid, block, 0, s, L, V);                                        \
+        *done = true;                                                                                                                     \
+    }
+    DASH_DIGIT_SETS(DASH_CHAIN)
+#undef DASH_CHAIN
+    DASH_HIP(hipGetLastError());
+    return DASH_OK;
+}
+
+}  // inline namespace
+}  // namespace dash

@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SEED = bytes(range(7, 23))
 
 
-EMULATIONS = ("gate_emul", "chain_emul", "digits_emul", "mixed_emul", "cast_emul")
+EMULATIONS = ("gate_emul", "chain_emul", "digits_emul", "mixed_emul", "cast_emul", "rows_emul")
 # (name, source, flags): like the library's kernels, once per label-length rule
 PROGRAMS = [(n, n, []) for n in EMULATIONS] + [(n + "_floor", n, ["-DDASH_RULE_FLOOR"]) for n in EMULATIONS] + [("aes_sliced_emul", "aes_sliced_emul", [])]
 
@@ -334,6 +334,15 @@ def test_mixed_output_moduli_in_one_eval_launch_under_sanitizers(built, tmp_path
         for n, seed, which in ((1, 1, 0), (257, 2, 0), (300, 3, 0), (130, 4, 1)):
             r = subprocess.run([exe, str(n), str(seed), str(which)], capture_output=True, text=True)
             assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-3000:]
+
+
+@pytest.mark.parametrize("n,quanta", [(1, 1), (2, 3), (63, 1), (64, 2), (130, 1), (201, 2)])
+def test_carry_gates_by_lanes_that_keep_their_value(built, n, quanta):
+    """the garbler's kernel for large batches of carry gates against the general one, both label-length rules: fewer rows than a round
+    of waves, whole rounds, a last tile that ends inside a gate"""
+    for exe in (built["rows_emul"], built["rows_emul_floor"]):
+        r = subprocess.run([exe, str(n), str(quanta), str(n + quanta)], capture_output=True, text=True)
+        assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-3000:]
 
 
 # ---- evaluator kernels that read a wire of modulus 2 ------------------------------------------------
