@@ -344,6 +344,48 @@ DASH_HD void chain_garble_rows(const ChainRows& J, const MP& P, const QD& Q, uin
         gb = next;
     }
 }
+// The same for the final gates (output modulus 2, rows of 128 bytes), in two steps.  A lane forms its row as 128 bits without the output
+// wire's zero label; then the wave writes the tile's rows, 16 bytes a lane and eight lanes a row, and each lane spreads its 16 bits and puts the
+// 16 digits of the zero label to them, so that nobody handles a row of 32 dwords.
+struct BitsLane { uint32_t da[10], f, dg, row0; };                  // (labels of m_1 have at most ten dwords)
+template <class MP>
+DASH_HD BitsLane chain_bits_lane(const ChainRows& J, const MP& P, uint32_t t0, uint32_t lane) {
+    static_assert(MP::ndw <= 10, "BitsLane");
+    BitsLane B;
+    const uint32_t off = t0 * 64 % MP::m + lane, a = off % MP::m;
+    B.dg = off / MP::m; B.row0 = B.dg * MP::m;
+    ld_dwords<(int)MP::ndw>(P.dtab, a * (MP::ndw * 4), B.da);
+#pragma unroll
+    for (int i = 0; i < (int)MP::ndw; i++) B.da[i] = offset4(B.da[i], P);
+    B.f = 0u - (J.phi[a] & 1u);
+    return B;
+}
+// z: zero label of the lane's gate gb + dg.  Bits of the row, and its index past the rows of gate gb
+template <class MP, class Tab>
+DASH_HD U128 chain_bits_row(const ChainRows& J, const MP& P, const U128& R2, const BitsLane& B, uint32_t gb, const uint32_t* z, const uint32_t* rk, const Tab& T, uint32_t& row) {
+    uint32_t colour;
+    const U128 K = compress(P, [&](int i) { return addmod4_off(z[i], B.da[i], P); }, &colour);
+    const U128 h = hash_block(K, J.elem_base + gb + B.dg, J.slot, J.layer, rk, T);
+    row = B.row0 + colour;
+    return U128{{h.w[0] ^ (R2.w[0] & B.f), h.w[1] ^ (R2.w[1] & B.f), h.w[2] ^ (R2.w[2] & B.f), h.w[3] ^ (R2.w[3] & B.f)}};
+}
+// digits 16 part .. 16 part + 15 of the row with that index past the rows of gate gb: what the row adds to its bits, and the row's piece
+// (stored if its gate is one of the batch's)
+template <uint32_t m>
+DASH_HD Dw4 chain_bits_label(const ChainRows& J, uint32_t gb, uint32_t row, uint32_t part) {
+    const uint32_t dg = row / m, last = J.n - 1 - gb;
+    return ld_dw4(J.out0 + (int64_t)part * J.out_cs + (uint64_t)gb * 16, (dg < last ? dg : last) * 16);
+}
+template <uint32_t m>
+DASH_HD void chain_bits_store(const ChainRows& J, uint32_t gb, uint32_t row, uint32_t part, uint32_t bits16, Dw4 d) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) d.w[q] ^= mul24((bits16 >> (4 * q)) & 0xfu, 0x00204081u) & kOnes;
+    uint8_t* rows = J.table + (uint64_t)gb * (m * 128u);
+    if (row / m < J.n - gb) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) st_row(rows, row * 128 + part * 16, q, d.w[q]);
+    }
+}
 // tiles of 64 rows after which a lane comes back to its value
 DASH_HD uint32_t chain_quantum(uint32_t m) { uint32_t q = m; for (int i = 0; i < 6 && !(q & 1); i++) q /= 2; return q; }
 
@@ -377,6 +419,64 @@ DASH_HD void eval_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t t
     };
     if constexpr (cmod_m<QD>::value != 0) finish(make_mod<QD>::from(Mq));
     else with_mod(Mq, finish);
+}
+
+// The same for launches that mix output moduli, all of them with compile-time descriptions: the hash stands between two dispatches on the
+// output modulus (one copy of its code), the first of which sends the row's loads out.  (Rows of bits are loaded after the hash: 32
+// dwords held over it would halve the waves per SIMD.)  J: a job of the launch.
+struct EvalGate {
+    const uint8_t *in, *table;       // label tensor and segment
+    uint8_t* out;
+    int64_t in_cs, out_cs;
+    uint64_t elem_base;
+    uint32_t n, p, q;
+};
+template <class Tab>
+DASH_HD void eval_many_body(const EvalGate& J, const ModInfo* mods, uint32_t layer, const uint32_t* rk, uint32_t bx, uint32_t tx, const Tab& T) {
+    const uint32_t g0 = bx * kThreads;
+    if (g0 + tx >= J.n) return;
+    const ModInfo Mp = ld_mod(mods, J.p), Mq = ld_mod(mods, J.q);
+    const uint8_t *in = J.in + (uint64_t)g0 * 16, *rows = J.table + (uint64_t)g0 * (Mp.m * Mq.ndw * 4);     // of the tile
+    uint8_t* out = J.out + (uint64_t)g0 * 16;
+    const uint32_t eo = tx * 16;
+    uint32_t colour = 0;
+    U128 K = {{0, 0, 0, 0}};
+    with_mod(Mp, [&](auto P) {
+        typedef decltype(P) PT;
+        if constexpr (cmod_m<PT>::value != 0) {
+            uint32_t x[PT::ndw];
+            ld_label<(int)PT::ndw>(in, J.in_cs, eo, x);
+            K = compress(P, [&](int i) { return x[i]; }, &colour);
+        }
+    });
+    const uint32_t row = (tx * Mp.m + colour) * (Mq.ndw * 4);
+    constexpr int kMax = 21;                // dwords of the longest row but those of bits
+    uint32_t rw[kMax];
+    with_mod(Mq, [&](auto Q) {
+        typedef decltype(Q) QT;
+        if constexpr (cmod_m<QT>::value > 2) { static_assert(QT::ndw <= kMax, "row"); ld_dwords<(int)QT::ndw>(rows, row, rw); }
+    });
+    schedule_fence();
+    const U128 h = hash_block(K, J.elem_base + g0 + tx, 0, layer, rk, T);
+    with_mod(Mq, [&](auto Q) {
+        typedef decltype(Q) QT;
+        if constexpr (cmod_m<QT>::value == 2) {
+#pragma unroll
+            for (int ch = 0; ch < 8; ch++) {
+                uint32_t r[4];
+                ld_dwords<4>(rows, row + 16 * ch, r);
+                Dw4 w;
+#pragma unroll
+                for (int q = 0; q < 4; q++) w.w[q] = r[q] ^ (mul24((h.w[ch >> 1] >> (16 * (ch & 1) + 4 * q)) & 0xfu, 0x00204081u) & kOnes);
+                *(Dw4*)(out + (int64_t)ch * J.out_cs + eo) = w;
+            }
+        } else if constexpr (cmod_m<QT>::value != 0) {
+            Dw4 w[QT::nchunk] = {};
+            decompress(Q, h, [&](int i, uint32_t hd) { w[i >> 2].w[i & 3] = submod4(rw[i], hd, Q); });
+#pragma unroll
+            for (int ch = 0; ch < (int)QT::nchunk; ch++) *(Dw4*)(out + (int64_t)ch * J.out_cs + eo) = w[ch];
+        }
+    });
 }
 
 // ---- evaluator, carry chain of the sign gadget ------------------------------------------------

@@ -448,10 +448,14 @@ int DASH_FN(launch_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStrea
         grid = dim3((uint32_t)(nb < cap ? nb : cap));
     }
     ProfScope ps(c->prof, DASH_PROF_GARBLE, s, units, bytes);
-    if (banked) {       // carry gates: a kernel of their own
+    // carry gates: kernels of their own, whose blocks have the bank-replicated tables.  (665 600 rows of the final gate: 46 us in
+    // k_proj_garble with one copy of the tables, 31 in k_chain_garble_bits.)
+    if ((uint64_t)units >= c->banked_min_lanes / 4) {
+        L.key = c->fixed_rot;
         bool done = false;
         const int st = DASH_FN(launch_chain_garble)(c, L, njobs, s, &done);
         if (st || done) return st;
+        if (!banked) L.key = c->fixed;
     }
     GateKernel k = banked ? kGarbleKernelsBanked[ki] : kGarbleKernels[ki];
     if (ki == 0 && !banked && (uint64_t)units <= c->few_rows_max) k = k_proj_garble<PerJobMod, false>;      // few rows: see garble_body

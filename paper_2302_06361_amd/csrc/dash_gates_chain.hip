@@ -36,6 +36,76 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble(const GateLaunc
     }
 }
 
+// Final gates: 16 KB of LDS beside the tables for the tile's bits, so that two blocks fit a CU.  (Rows kept in registers and staged as 32
+// dwords a lane, with 140 KB of LDS and one block per CU: 115 us for the 1.96 M rows of 75 264 gates; this form takes 69.)
+template <class MP>
+__global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const GateLaunch, uint32_t V) {
+    const auto& L = *(const __attribute__((address_space(4))) GateLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
+    __shared__ uint32_t tt[kBankTabWords];
+    __shared__ __attribute__((aligned(16))) uint32_t stage[kBigThreads * 4];
+    const BankTab T = load_banktab(tt, L.ttab);
+    const uint32_t reps = L.reps.n ? L.reps.n : 1u, njobs = L.njobs, units = njobs * reps, waves = gridDim.x * (kBigThreads / 64);
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t* const st = stage + (threadIdx.x & ~63u) * 4;
+    const MP P{ld_mod(L.mods, MP::m).dtab};
+    U128 R2;                                            // the offset label of modulus 2
+    {
+        const uint32_t* d = ld_mod(L.mods, 2).dtab + 32;
+        uint32_t colour;
+        R2 = compress(CMod<2, 128>{nullptr}, [&](int i) { return gload32(d + i); }, &colour);
+#pragma unroll
+        for (int i = 0; i < 4; i++) R2.w[i] = __builtin_amdgcn_readfirstlane(R2.w[i]);
+    }
+    auto keys = [&]() __attribute__((always_inline)) {
+        const __attribute__((address_space(4))) uint32_t* rk = L.key.rk;
+        asm volatile("" : "+s"(rk));
+        return (const uint32_t*)rk;
+    };
+    for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
+        const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs), t0 = vw - unit * V;
+        const auto& J = L.jobs[unit - rep * njobs];
+        const int64_t wires = (int64_t)rep * L.reps.wires;
+        const ChainRows R{J.in.p + wires, J.out.p + wires, J.phi, J.in.cs, J.out.cs, J.table + (int64_t)rep * L.reps.tables,
+                          J.elem_base, J.n_elem, J.slot + rep * L.reps.slots, L.layer};
+        constexpr int NP = (int)MP::ndw;
+        const uint32_t n = R.n, tiles = (uint32_t)(((uint64_t)n * MP::m + 63) / 64), step = 64 * V / MP::m;
+        if (t0 >= tiles) continue;
+        const BitsLane B = chain_bits_lane(R, P, t0, lane);
+        uint32_t gb = t0 * 64 / MP::m, z[NP];
+        auto eo = [&](uint32_t b) __attribute__((always_inline)) { return 16 * (B.dg < n - b ? B.dg : n - 1 - b); };      // (past the end: the last gate, never stored)
+        ld_label<NP>(R.in + (uint64_t)gb * 16, R.in_cs, eo(gb), z);
+        for (uint32_t t = t0; t < tiles; t += V) {
+            const uint32_t next = t + V < tiles ? gb + step : gb;
+            uint32_t row;
+            const U128 w = chain_bits_row(R, P, R2, B, gb, z, keys(), T, row);
+            ld_label<NP>(R.in + (uint64_t)next * 16, R.in_cs, eo(next), z);
+            *(uint4*)(st + lane * 4) = make_uint4(w.w[0], w.w[1], w.w[2], w.w[3]);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            uint32_t sl = lane;               // (opaque: its products are formed here and not held over the hash)
+            asm volatile("" : "+v"(sl));
+            const uint32_t part = sl & 7u;
+#pragma unroll
+            for (uint32_t half = 0; half < 2; half++) {               // four loads at a time
+                uint32_t r[4], bits[4];
+                Dw4 d[4];
+#pragma unroll
+                for (uint32_t i = 0; i < 4; i++) {
+                    const uint32_t k = half * 32 + i * 8 + (sl >> 3);
+                    r[i] = (uint32_t)__shfl((int)row, (int)k, 64);
+                    d[i] = chain_bits_label<MP::m>(R, gb, r[i], part);
+                    bits[i] = ((const uint16_t*)st)[k * 8 + part];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < 4; i++) chain_bits_store<MP::m>(R, gb, r[i], part, bits[i], d[i]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            gb = next;
+        }
+    }
+}
+
 // waves per batch: a multiple of the quantum that keeps the rounds of the resident waves full.  A round of waves costs its longest batch share.
 static uint32_t chain_waves(uint64_t tiles, uint32_t units, uint32_t quantum, uint32_t resident) {
     uint32_t best = quantum;
@@ -69,6 +139,10 @@ int DASH_FN(launch_chain_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hi
     }                                                                                                                                     \
     if (!*done && J0.p == MC && Mp.lam == LC && J0.q == M1 && Mq.lam == L1) {                                                             \
         hipLaunchKernelGGL((k_chain_garble<CMod<MC, LC>, CMod<M1, L1>>), grid, block, 0, s, L, V);                                        \
+        *done = true;                                                                                                                     \
+    }                                                                                                                                     \
+    if (!*done && J0.p == M1 && Mp.lam == L1 && J0.q == 2 && Mq.lam == 128) {                                                             \
+        hipLaunchKernelGGL((k_chain_garble_bits<CMod<M1, L1>>), grid, block, 0, s, L, V);                                                 \
         *done = true;                                                                                                                     \
     }
     DASH_DIGIT_SETS(DASH_CHAIN)

@@ -70,6 +70,24 @@ struct GateLaunch {
     GateJob jobs[kMaxJobs];
 };
 
+// evaluator: up to 64 batches of independent gates of any moduli with compile-time descriptions in one launch
+struct EvalManyJob {
+    const uint8_t *in, *table;
+    uint8_t* out;
+    int64_t in_cs, out_cs;
+    uint64_t elem_base;
+    uint32_t n_elem;
+    uint16_t p, q;
+};
+constexpr int kMaxEvalMany = 64;
+struct EvalManyLaunch {
+    AesKey key;
+    const uint32_t* ttab;
+    const ModInfo* mods;
+    uint32_t layer, njobs;
+    EvalManyJob jobs[kMaxEvalMany];
+};
+
 struct DrawJob {
     uint32_t m, domain, slot, digit0_only;
     LView out;       // digit0_only: out.p is a byte array [n_elem]

@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <functional>
+#include <iterator>
 #include <vector>
 
 #include "dash_internal.h"
@@ -921,6 +922,7 @@ static int check_proj(const dash_ctx* c, const dash_layer* L, const dash_labels*
     return DASH_OK;
 }
 
+static constexpr int kHotPrimes[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};      // (DASH_HOT_MODS)
 // Several independent PROJ calls at once: calls with the same layer id and output modulus share gate launches (up to
 // kMaxJobs per launch, each job with its own gate count and element base), and all fresh zero labels of a layer id
 // are drawn in shared launches.
@@ -948,6 +950,28 @@ int proj_layers(dash_ctx* c, bool garble, int n, const dash_layer* Ls, const das
             }
             db.flush();
             if (db.status) return db.status;
+        }
+        // the evaluator's batches share launches whatever their moduli, where these have compile-time descriptions
+        bool many = !garble;
+        for (size_t r = r0; r < r1 && many; r++)
+            for (int m : {c->prime[Ls[order[r]].p_index], c->prime[Ls[order[r]].q_index]})
+                many = many && std::find(std::begin(kHotPrimes), std::end(kHotPrimes), m) != std::end(kHotPrimes) &&
+                       c->mods[m].lam == cm::lam_of((uint32_t)m, c->rule == DASH_LAMBDA_FLOOR);
+        if (many) {
+            EvalManyLaunch M;
+            memset(&M, 0, sizeof(M));
+            M.layer = layer;
+            int nj = 0, st = DASH_OK;
+            for (size_t r = r0; r < r1 && st == DASH_OK; r++) {
+                const dash_layer& L = Ls[order[r]];
+                const LView in = view_of(ins + order[r], L.p_index), out = view_of(outs + order[r], L.q_index);
+                M.jobs[nj++] = EvalManyJob{in.p, tables[order[r]], out.p, in.cs, out.cs, (uint64_t)L.elem_base, (uint32_t)L.n_elem,
+                                           (uint16_t)c->prime[L.p_index], (uint16_t)c->prime[L.q_index]};
+                if (nj == kMaxEvalMany || r + 1 == r1) { st = launch_eval_many(c, M, nj, s); nj = 0; }
+            }
+            if (st) return st;
+            r0 = r1;
+            continue;
         }
         GateBatcher gb(c, garble, 0, layer, 0, s);
         for (size_t r = r0; r < r1; r++) {

@@ -1,4 +1,4 @@
-// Host emulation of the garbler's kernel for batches of carry gates: chain_garble_rows, wave by wave and lane by lane over exactly-sized
+// Host emulation of the garbler's kernels for batches of carry gates and of the evaluator's for gates of any moduli: chain_garble_rows, wave by wave and lane by lane over exactly-sized
 // buffers under the sanitizers, against garble_body on the same gates: every table byte, for the pairs of moduli that the kernel is
 // compiled for.  Test code, not part of libdash.   usage: rows_emul <gates> <quanta of tiles per round of waves> <seed>
 #include <stdint.h>
@@ -55,6 +55,64 @@ static bool same() {
     return true;
 }
 
+// the final gates: rows of bits, written 16 bytes a lane
+template <class MP>
+static bool same_bits() {
+    const ModInfo &Mp = mods[MP::m], &M2 = mods[2];
+    std::vector<uint8_t> in = labels(Mp), out0 = labels(M2), phi(MP::m), want((size_t)n * MP::m * 128, 0xDD), got(want.size(), 0xEE);
+    for (auto& v : phi) v = (uint8_t)(rnd() % 2);
+    GateJob& J = G.jobs[0];
+    memset(&J, 0, sizeof(J));
+    J.p = MP::m; J.q = 2; J.slot = 91; J.mode = PAY_PHI; J.elem_base = (1ull << 32) - 2; J.n_elem = n;
+    J.in = LView{in.data(), (int64_t)16 * n, 16u}; J.out = LView{out0.data(), (int64_t)16 * n, 16u};
+    J.phi = phi.data(); J.table = want.data();
+    const uint32_t blocks = (uint32_t)(((uint64_t)n * MP::m + kThreads - 1) / kThreads);
+    for (uint32_t bx = 0; bx < blocks; bx++)
+        for (uint32_t tx = 0; tx < (uint32_t)kThreads; tx++) { DirectSink sink; garble_body<CMod<2, 128>>(G, bx, 0, tx, HostTab(), sink); }
+    const uint32_t V = quanta * chain_quantum(MP::m), tiles = (n * MP::m + 63) / 64;
+    const ChainRows R{in.data(), out0.data(), phi.data(), (int64_t)16 * n, (int64_t)16 * n, got.data(), J.elem_base, n, J.slot, G.layer};
+    uint32_t colour;
+    const U128 R2 = compress(CMod<2, 128>{nullptr}, [&](int i) { return M2.dtab[32 + i]; }, &colour);
+    for (uint32_t t0 = 0; t0 < V; t0++)
+        for (uint32_t t = t0, gb = t0 * 64 / MP::m; t < tiles; t += V, gb += 64 * V / MP::m) {
+            U128 bits[64];
+            uint32_t row[64];
+            for (uint32_t lane = 0; lane < 64; lane++) {
+                const BitsLane B = chain_bits_lane(R, MP{Mp.dtab}, t0, lane);
+                uint32_t z[MP::ndw];
+                ld_label<(int)MP::ndw>(in.data() + (uint64_t)gb * 16, R.in_cs, 16 * (B.dg < n - gb ? B.dg : n - 1 - gb), z);
+                bits[lane] = chain_bits_row(R, MP{Mp.dtab}, R2, B, gb, z, G.key.rk, HostTab(), row[lane]);
+            }
+            for (uint32_t i = 0; i < 8; i++)
+                for (uint32_t lane = 0; lane < 64; lane++) {
+                    const uint32_t k = i * 8 + lane / 8, part = lane % 8, b16 = (bits[k].w[part / 2] >> (16 * (part % 2))) & 0xffffu;
+                    chain_bits_store<MP::m>(R, gb, row[k], part, b16, chain_bits_label<MP::m>(R, gb, row[k], part));
+                }
+        }
+    if (got != want) { fprintf(stderr, "%u -> 2: tables differ\n", MP::m); return false; }
+    return true;
+}
+
+// the evaluator's gates of any moduli (eval_many_body) against eval_body
+static bool same_eval(uint32_t p, uint32_t q) {
+    const ModInfo &Mp = mods[p], &Mq = mods[q];
+    std::vector<uint8_t> in = labels(Mp), table((size_t)n * p * Mq.ndw * 4, 0), want((size_t)Mq.nchunk * n * 16, 0xDD), got(want.size(), 0xEE);
+    for (size_t r = 0; r < (size_t)n * p; r++)
+        for (uint32_t d = 0; d < Mq.lam; d++) table[r * Mq.ndw * 4 + d] = (uint8_t)(rnd() % q);
+    GateJob& J = G.jobs[0];
+    memset(&J, 0, sizeof(J));
+    J.p = p; J.q = q; J.mode = PAY_PHI; J.elem_base = (1ull << 32) - 5; J.n_elem = n;
+    J.in = LView{in.data(), (int64_t)16 * n, 16u}; J.out = LView{want.data(), (int64_t)16 * n, 16u}; J.table = table.data();
+    const EvalGate E{in.data(), table.data(), got.data(), (int64_t)16 * n, (int64_t)16 * n, J.elem_base, n, p, q};
+    for (uint32_t bx = 0; bx < (n + kThreads - 1) / kThreads; bx++)
+        for (uint32_t tx = 0; tx < (uint32_t)kThreads; tx++) {
+            eval_body<ModInfo>(G, bx, 0, tx, HostTab());
+            eval_many_body(E, mods.data(), G.layer, G.key.rk, bx, tx, HostTab());
+        }
+    if (got != want) { fprintf(stderr, "eval %u -> %u: labels differ\n", p, q); return false; }
+    return true;
+}
+
 int main(int argc, char** argv) {
     if (argc != 4) return 2;
     n = (uint32_t)atoi(argv[1]); quanta = (uint32_t)atoi(argv[2]);
@@ -78,9 +136,11 @@ int main(int argc, char** argv) {
     }
     G.mods = mods.data(); G.layer = 11; G.njobs = 1;
     bool ok = true;
-#define PAIR(MC, LC, M1, L1) ok = ok && same<CMod<MC, LC>, CMod<MC, LC>>() && same<CMod<MC, LC>, CMod<M1, L1>>();
+#define PAIR(MC, LC, M1, L1) ok = ok && same<CMod<MC, LC>, CMod<MC, LC>>() && same<CMod<MC, LC>, CMod<M1, L1>>() && same_bits<CMod<M1, L1>>();
     DASH_DIGIT_SETS(PAIR)
 #undef PAIR
+    static const int primes[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
+    for (int i = 0; i < 12; i++) ok = ok && same_eval(primes[i], primes[(i + 5) % 12]) && same_eval(primes[(i + 1) % 12], primes[i]);
     if (ok) printf("ok\n");
     return ok ? 0 : 1;
 }
