@@ -37,6 +37,8 @@ const simt::dynamic_lds announce(acc, sizeof(acc));
 namespace dash { inline namespace DASH_RULE_NS {
 #define ABSENT(ret, name, ...) ret DASH_FN(name)(__VA_ARGS__) { fprintf(stderr, "act_emul: " #name " is not part of this program\n"); abort(); }
 ABSENT(int, launch_eval, const dash_ctx*, GateLaunch&, int, hipStream_t)
+ABSENT(int, launch_eval_many, const dash_ctx*, EvalManyLaunch&, int, hipStream_t)
+ABSENT(int, launch_chain_garble, const dash_ctx*, GateLaunch&, int, hipStream_t, bool*)
 ABSENT(int, launch_chain_eval, const dash_ctx*, ChainLaunch&, hipStream_t)
 ABSENT(int, launch_digits_eval, const dash_ctx*, DigitsLaunch&, hipStream_t)
 ABSENT(int, launch_digits_garble, const dash_ctx*, DigitsLaunch&, hipStream_t)
