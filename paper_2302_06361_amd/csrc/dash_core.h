@@ -627,40 +627,76 @@ DASH_HD uint32_t take_superdigit(U128& x, const MI& M, uint32_t bits) {
 // up at compile time (FracPlan) and must stay below half the window.
 // Against the long division over 16-bit half-words that the run-time description below uses, this is a 32 x 32 -> 64-bit
 // multiply-add per word instead of two steps of five instructions, with super-digits up to 2^32 instead of 2^15 times a power of
-// two: 89 vector instructions instead of 197 for m = 96 (20 digits), 110 instead of 283 for m = 204, 136 instead of 333 for m = 37.
+// two: 83 vector instructions instead of 197 for m = 96 (20 digits), 104 instead of 283 for m = 204, 122 instead of 333 for m = 37.
 template <uint32_t MOD> struct Frac { static constexpr cm::FracPlan P = cm::frac_plan(MOD); };
 
-// acc += a * b (b the same in all lanes), and 1 to over where the 64-bit sum overflows and Carry asks for it.  (As assembly because the compiler takes sums of
-// products apart, products first, and forms the carry by a comparison: 25 instead of 14 instructions for the product of m = 96.)
-template <bool Carry>
-DASH_HD void mad64(uint64_t& acc, uint32_t& over, uint32_t a, uint32_t b) {
+// acc += a * b, b the same in all lanes (see mad64_carries)
+DASH_HD void mad64(uint64_t& acc, uint32_t a, uint32_t b) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (Carry) asm("v_mad_u64_u32 %0, vcc, %2, %3, %0\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc" : "+v"(acc), "+v"(over) : "v"(a), "s"(b) : "vcc");
-    else asm("v_mad_u64_u32 %0, vcc, %1, %2, %0" : "+v"(acc) : "v"(a), "s"(b) : "vcc");
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, %0" : "+v"(acc) : "v"(a), "s"(b) : "vcc");
 #else
-    const uint64_t p = (uint64_t)a * b;
-    acc += p;
-    if (Carry) over += acc < p;
+    acc += (uint64_t)a * b;
 #endif
 }
-// products h.w[I..3] * R.w[C - I] of column C; an overflow of the 64-bit sum is watched for only where the constants allow one
-template <uint32_t MOD, int C, int I>
-DASH_HD void frac_column(const U128& h, uint64_t& acc, uint32_t& over) {
-    if constexpr (I < 4) {
-        constexpr int J = C - I;
-        if constexpr (J >= 0 && J < 10) {
-            constexpr uint32_t r = Frac<MOD>::P.R.w[J];
-            if constexpr (r != 0) {
-                constexpr auto bound = [] {
-                    unsigned __int128 b = (unsigned __int128)1 << 35;        // carry from the column before and the start value
-                    for (int i = 0; i <= I; i++) if (C - i >= 0 && C - i < 10) b += (unsigned __int128)0xffffffffu * Frac<MOD>::P.R.w[C - i];
-                    return b;
-                };
-                mad64<(bound() >> 64) != 0>(acc, over, h.w[I], r);
-            }
-        }
-        frac_column<MOD, C, I + 1>(h, acc, over);
+// acc += a[0] b[0] + .. + a[N-1] b[N-1]; the number of times that the 64-bit sum overflows.  (As assembly because the compiler forms a carry
+// by a comparison and takes sums of products apart: 6 vector instructions more for the conversion of m = 96, 10 for m = 13, 14 for m = 22.)
+// Two wait states must pass between a vector instruction that writes a carry and one that reads it, and nothing watches over that inside
+// an assembly block: the carries are added up behind the products, and where these are fewer than three, s_nop fills the rest.
+template <int N>
+DASH_HD uint32_t mad64_carries(uint64_t& acc, const uint32_t* a, const uint32_t* b) {
+    static_assert(N >= 1 && N <= 3, "no modulus has a column with more");
+    uint32_t over = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t c0, c1;
+    if constexpr (N == 1)
+        asm("v_mad_u64_u32 %0, vcc, %2, %3, %0\n\ts_nop 1\n\tv_addc_co_u32_e64 %1, vcc, 0, 0, vcc"
+            : "+v"(acc), "=v"(over) : "v"(a[0]), "s"(b[0]) : "vcc");
+    else if constexpr (N == 2)
+        asm("v_mad_u64_u32 %0, %2, %3, %5, %0\n\tv_mad_u64_u32 %0, vcc, %4, %6, %0\n\ts_nop 0\n\t"
+            "v_addc_co_u32_e64 %1, %2, 0, 0, %2\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc"
+            : "+v"(acc), "=v"(over), "=&s"(c0) : "v"(a[0]), "v"(a[1]), "s"(b[0]), "s"(b[1]) : "vcc");
+    else
+        asm("v_mad_u64_u32 %0, %2, %4, %7, %0\n\tv_mad_u64_u32 %0, %3, %5, %8, %0\n\tv_mad_u64_u32 %0, vcc, %6, %9, %0\n\t"
+            "v_addc_co_u32_e64 %1, %2, 0, 0, %2\n\tv_addc_co_u32_e64 %1, %3, 0, %1, %3\n\tv_addc_co_u32_e32 %1, vcc, 0, %1, vcc"
+            : "+v"(acc), "=v"(over), "=&s"(c0), "=&s"(c1) : "v"(a[0]), "v"(a[1]), "v"(a[2]), "s"(b[0]), "s"(b[1]), "s"(b[2]) : "vcc");
+#else
+    for (int i = 0; i < N; i++) {
+        const uint64_t p = (uint64_t)a[i] * b[i];
+        acc += p;
+        over += acc < p;
     }
+#endif
+    return over;
+}
+// products h.w[I..3] * R.w[C - I] of column C, and how often the 64-bit sum overflows: counted from the first product on after which
+// the constants allow an overflow
+template <uint32_t MOD, int C>
+struct FracColumn {
+    static constexpr uint32_t r(int I) { return C - I >= 0 && C - I < 10 ? Frac<MOD>::P.R.w[C - I] : 0u; }
+    static constexpr int first_carry() {
+        unsigned __int128 b = (unsigned __int128)1 << 35;        // carry from the column before and the start value
+        for (int I = 0; I < 4; I++) {
+            b += (unsigned __int128)0xffffffffu * r(I);
+            if ((b >> 64) != 0) return I;
+        }
+        return 4;
+    }
+    static constexpr int carries() { int n = 0; for (int I = first_carry(); I < 4; I++) n += r(I) != 0; return n; }
+};
+template <uint32_t MOD, int C>
+DASH_HD uint32_t frac_column(const U128& h, uint64_t& acc) {
+    typedef FracColumn<MOD, C> F;
+    constexpr int first = F::first_carry(), N = F::carries();
+    uint32_t a[4], b[4];
+    int n = 0;
+#pragma unroll
+    for (int I = 0; I < 4; I++) {
+        if (F::r(I) == 0) continue;
+        if (I < first) mad64(acc, h.w[I], F::r(I));
+        else { a[n] = h.w[I]; b[n] = F::r(I); n++; }
+    }
+    if constexpr (N > 0) return mad64_carries<N>(acc, a, b);
+    else return 0;
 }
 // columns C..8 of h R: columns 8 - w[0] .. 7 are the fraction, column 8 the top super-digit
 template <uint32_t MOD, int C>
@@ -669,9 +705,8 @@ DASH_HD void frac_product(const U128& h, uint64_t acc, uint32_t* f, uint32_t& to
     if constexpr (C == 8) {
         top = (uint32_t)acc;
     } else {
-        uint32_t over = 0;
         if constexpr (C == (int)P.bcol) acc += P.bword;
-        frac_column<MOD, C, 0>(h, acc, over);
+        const uint32_t over = frac_column<MOD, C>(h, acc);
         if constexpr (C >= 8 - (int)P.w[0]) f[C - (8 - (int)P.w[0])] = (uint32_t)acc;
         frac_product<MOD, C + 1>(h, (acc >> 32) | ((uint64_t)over << 32), f, top);
     }
