@@ -275,22 +275,27 @@ class Context:
                                         C.c_void_p(scratch.data_ptr() if scratch is not None else 0), _stream()),
                "dash_garble_layer")
 
-    def _labels_array(self, bundles, residues):
-        """array of dash_labels; residues: of each bundle the one residue that its call reads or writes (PROJ calls), or None"""
-        n = len(bundles)
+    def _labels_array(self, n, bundles, residues):
+        """n dash_labels; residues: of each bundle the one residue that its call reads or writes (PROJ calls), or None"""
         if residues is None:
             return (CLabels * n)(*[t.c() for t in bundles])
         arr = (CLabels * n)()
-        flat = np.frombuffer(arr, np.int64).reshape(n, 2 * MAX_PRIMES + 1)
-        tensors = [b.tensors[i] for b, i in zip(bundles, residues)]
-        row, col = np.arange(n), np.array(residues)
-        flat[row, col] = [0 if t is None else t.data_ptr() for t in tensors]
-        flat[row, MAX_PRIMES + col] = [0 if t is None else t.stride(0) for t in tensors]
-        flat[:, 2 * MAX_PRIMES] = [b.n_elem for b in bundles]
+        m = len(bundles)
+        if m:
+            flat = np.frombuffer(arr, np.int64).reshape(n, 2 * MAX_PRIMES + 1)[:m]
+            tensors = [b.tensors[i] for b, i in zip(bundles, residues)]
+            row, col = np.arange(m), np.array(residues[:m])
+            flat[row, col] = [0 if t is None else t.data_ptr() for t in tensors]
+            flat[row, MAX_PRIMES + col] = [0 if t is None else t.stride(0) for t in tensors]
+            flat[:, 2 * MAX_PRIMES] = [b.n_elem for b in bundles]
         return arr
 
     def _layer_lists(self, layers, ins, outs, tables, scratch):
         n = len(layers)
+        # the library reads n entries of every list: what a shorter one lacks stays null, a longer one is refused here
+        ins, outs, tables, scratch = [None if x is None else list(x) for x in (ins, outs, tables, scratch)]
+        if max(len(x) for x in (ins, outs, tables, scratch or ())) > n:
+            raise IndexError("a list has more entries than there are layers")
         structs = [l.c for l in layers]
         cl = (CLayer * n).from_buffer_copy(b"".join(structs))
         # lists of PROJ calls are long and touch one residue per bundle (144 calls: 270 -> 150 us of host time)
@@ -299,10 +304,14 @@ class Context:
             pi, qi = [c.p_index for c in structs], [c.q_index for c in structs]
             if min(min(pi), min(qi)) < 0 or max(max(pi), max(qi)) >= self.k:
                 pi = qi = None                           # the library refuses the call
-        ci = self._labels_array(ins, pi)
-        co = self._labels_array(outs, qi)
+        ci = self._labels_array(n, ins, pi)
+        co = self._labels_array(n, outs, qi)
+
         def pointers(tensors):
-            return (C.c_void_p * n).from_buffer(np.array([0 if t is None else t.data_ptr() for t in tensors], np.int64)) if n else None
+            arr = (C.c_void_p * n)()
+            if tensors:
+                np.frombuffer(arr, np.int64)[:len(tensors)] = [0 if t is None else t.data_ptr() for t in tensors]
+            return arr
         ct = pointers(tables)
         cs = None if scratch is None else pointers(scratch)
         return n, cl, ci, co, ct, cs

@@ -74,3 +74,43 @@ def test_product_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower(), os.path.join(dirpath, f)
+
+
+def _lists(residues, n_bundles, n_tables, kind):
+    """Context._layer_lists without a GPU: as many layers as residues, and lists of other lengths"""
+    import torch
+    from paper_2302_06361_amd import binding as B
+    ctx = B.Context.__new__(B.Context)
+    ctx.k, ctx.primes = 3, [2, 3, 5]
+    layers = [B.Layer(kind, 1, 4, p_index=r, q_index=r) for r in residues]
+
+    def bundle():
+        b = B.Labels.__new__(B.Labels)
+        b.n_elem, b.tensors = 4, [torch.zeros((2, 4, 16), dtype=torch.uint8) for _ in range(3)]
+        return b
+    bundles = [bundle() for _ in range(n_bundles)]
+    tables = [torch.zeros(8, dtype=torch.uint8) for _ in range(n_tables)]
+    return (layers, bundles, tables) + ctx._layer_lists(layers, (b for b in bundles), bundles, tables, tables)
+
+
+@pytest.mark.parametrize("kind", ["PROJ", "RELU"])
+def test_layer_lists_have_an_entry_per_layer(kind):
+    """what a list lacks stays null, which the library refuses where it needs it (it reads n entries of every list); longer lists raise"""
+    from paper_2302_06361_amd import binding as B
+    residues = [2, 0, 1]
+    for nb, nt in ((3, 3), (1, 3), (2, 1), (0, 0)):
+        _, bundles, tables, n, cl, ci, co, ct, cs = _lists(residues, nb, nt, getattr(B, kind))
+        assert n == len(cl) == len(ci) == len(co) == len(ct) == len(cs) == 3
+        for i in range(3):
+            for arr in (ci, co):
+                assert arr[i].n_elem == (4 if i < nb else 0)
+                for r in range(3):
+                    there = i < nb and (kind == "RELU" or r == residues[i])
+                    assert arr[i].data[r] == (bundles[i].tensors[r].data_ptr() if there else None)
+                    assert arr[i].chunk_stride[r] == (64 if there else 0)
+            for arr in (ct, cs):
+                assert arr[i] == (tables[i].data_ptr() if i < nt else None)
+    for nb, nt in ((4, 3), (3, 4)):
+        with pytest.raises(IndexError):
+            _lists(residues, nb, nt, getattr(B, kind))
+    assert _lists([], 0, 0, getattr(B, kind))[3] == 0
