@@ -23,6 +23,8 @@
 // of 168, 9 216 (one block per CU) 36 instead of 45.
 // For digit sets with compile-time moduli over the first NP primes; anything else takes the launches of dash_layers.hip one by one.
 // Compiled once per digit set (DASH_SET = number of primes) and label-length rule.
+#include <algorithm>
+
 #include "dash_tabs.h"
 
 #ifndef DASH_SET
@@ -44,6 +46,10 @@ typedef CMod<204, cm::lam_of(204, kFloorRule)> MC; typedef CMod<46, cm::lam_of(4
 #endif
 constexpr int kNP = DASH_SET;
 constexpr uint32_t kPrimeMax = kNP == 7 ? 17 : kNP == 8 ? 19 : kNP == 9 ? 23 : 37;
+// Deep form: dwords of digit sums (whole digits) that lie beside the table and behind it in rows as beside it; the digits after them take the
+// half of the rows behind the table that these leave free.
+constexpr uint32_t kSpanSums = 64, kCut = M1::ndw + (75 - M1::ndw) / MC::ndw * MC::ndw;
+static_assert(kSpanSums + M1::ndw + (kMaxChain - 1) * MC::ndw - kCut <= 78, "two deep blocks fit a CU");
 constexpr int kMaxX = 24;                           // dwords of the longest label of an odd prime (81 digits in six chunks)
 
 // f(description) for the primes of the base; bit labels (p = 2) only where the caller asks for them
@@ -92,10 +98,12 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
     // keeps to 128 registers: two blocks, 36 instead of 64 us for a repetition of 25 088 values of the 7-prime base); else the digit sums.
     extern __shared__ __attribute__((aligned(16))) uint32_t acc[];
     uint32_t* const bt = Deep ? acc : bt_static;
-    // sums over the residues, two digits per word: word (digit dword i, even or odd digits h, value v) at sum0[(2 i + h) * kS + at(v)].  Deep
-    // form: in the half of the table's span that HalfTab leaves free.
+    // sums over the residues, two digits per word: word (digit dword i, even or odd digits h, value v) at sum0[at_dword(i) + h * kS + at(v)].
+    // Deep form: in the half of the table's span that HalfTab leaves free, and behind the span (a 16-digit set needs 77 KB this way, two blocks
+    // per CU; 87 KB in rows as beside the table: 75 264 values of 8 primes 409 us a repetition in 87, 276 in 77).
     uint32_t* const sum0 = Deep ? acc + HalfTab::hole : acc;
     constexpr int kS = Deep ? 2 * EPB : EPB;
+    auto at_dword = [](uint32_t i) __attribute__((always_inline)) { return i * (2 * kS) + (Deep && i >= kCut ? (kSpanSums - kCut) * (2 * kS) - HalfTab::hole : 0u); };
     auto at = [](uint32_t v) __attribute__((always_inline)) { return Deep ? (v & 32u) + v : v; };      // (64 values: two rows of 32 words, 64 apart)
     const int n = (int)L.n;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
@@ -134,7 +142,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
         }
     }
     const uint32_t sums = M1::ndw + (uint32_t)(n - 1) * MC::ndw;           // dwords of the n digit sums
-    for (uint32_t i = threadIdx.x; i < sums * 2 * EPB; i += T) sum0[i / EPB * kS + at(i % EPB)] = 0;
+    for (uint32_t i = threadIdx.x; i < sums * 2 * EPB; i += T) sum0[at_dword(i / (2 * EPB)) + i / EPB % 2 * kS + at(i % EPB)] = 0;
     if (chain_lane && !RELU) kb[cc][cel] = up0;
     auto step_table = [&]() __attribute__((always_inline)) {               // (ends with a barrier)
         if constexpr (Deep) return load_halftab(bt, L.ttab);
@@ -199,7 +207,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
                     for (int i = (int)MC::ndw; i < (int)M1::ndw; i++) rw[i] = row[i];
                 }
                 const U128 h = Deep ? H.get(slot, rk, tab) : hash(K, slot);
-                uint32_t* a = sum0 + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * kS) + at(el);
+                uint32_t* a = sum0 + at_dword(j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) + at(el);
                 auto put = [&](int i, uint32_t w) __attribute__((always_inline)) {
                     if (Q == 4 && c != (uint32_t)(i & 3)) return;           // (the lanes of a quad hold the same label)
                     sum_add(a + 2 * kS * i, w & 0x00ff00ffu);
@@ -213,7 +221,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
         // ---- step 2: the sums mod m_j (fields below 16 * 255)
         for (uint32_t t = threadIdx.x; t < sums * EPB; t += T) {
             const uint32_t i = t / EPB, c = t % EPB;
-            uint32_t* a = sum0 + i * (2 * kS) + at(c);
+            uint32_t* a = sum0 + at_dword(i) + at(c);
             const uint32_t ev = a[0], od = a[kS];
             auto reduce = [&](auto M) __attribute__((always_inline)) { return mod_m(ev & 0xffffu, M) | (mod_m(ev >> 16, M) << 16) | (mod_m(od & 0xffffu, M) << 8) | (mod_m(od >> 16, M) << 24); };
             a[0] = i < M1::ndw ? reduce(M1{nullptr}) : reduce(MC{nullptr});
@@ -228,7 +236,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
             constexpr int kIn = (int)(M1::ndw > MC::ndw ? M1::ndw : MC::ndw);
             uint32_t cw[kIn] = {}, sm[kIn];
             auto fetch = [&](int j) __attribute__((always_inline)) {                                   // packed sum of digit j; cleared for the next repetition
-                uint32_t* a = sum0 + (j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) * (2 * kS) + at(cel);
+                uint32_t* a = sum0 + at_dword(j == 1 ? 0u : M1::ndw + (uint32_t)(j - 2) * MC::ndw) + at(cel);
 #pragma unroll
                 for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * kS]; DASH_WAVE_POINT(); a[i * 2 * kS] = 0; }
             };
@@ -372,13 +380,15 @@ int DASH_FN(DASH_PASTE(launch_act_eval_, DASH_SET))(const dash_ctx* c, ActLaunch
     // second round costs the whole latency again (320 values of the 9-prime base: 50 us in 320 tiny blocks, 28 in shallow ones).
     // From two rounds of shallow blocks on the deep form is the faster one (6 400 values, us a repetition, scaling: 44 shallow and 39 deep on
     // the 8-prime base, 45 and 37 on 7, 54 and 48 on 9, 73 and 65 on 12; 4 096 values: 24 and 39 on 8).
-    // (The deep form's digit sums lie in the table's span, which holds 64 dwords of them: the default sets have 35 to 56.)
+    // The deep form's digit sums lie in the table's span, which holds 64 dwords of them (the default sets have 35 to 56), and go on behind it.
     const uint32_t sums = M1::ndw + (L.n - 1) * MC::ndw;
     const int form = L.n_elem < c->act_shallow_min_elems && L.n_elem <= 256u * kTiny ? ACT_TINY
-                   : L.n_elem < c->act_deep_min_elems || sums > 64 ? ACT_SHALLOW : ACT_DEEP;
+                   : L.n_elem < c->act_deep_min_elems ? ACT_SHALLOW : ACT_DEEP;
     const uint32_t epb = form == ACT_DEEP ? 64 : form == ACT_SHALLOW ? kShallow : kTiny;
     const dim3 grid((L.n_elem + epb - 1) / epb), block(64 * (relu ? kNP : kNP - 1));
-    const size_t lds = form == ACT_DEEP ? HalfTab::words * 4 : (size_t)sums * 2 * epb * 4;
+    static_assert(HalfTab::words == kSpanSums * 4 * 64, "rows of the deep form");
+    const uint32_t rows = sums <= kSpanSums ? kSpanSums : sums <= kCut ? sums : std::max(kCut, kSpanSums + sums - kCut);
+    const size_t lds = form == ACT_DEEP ? (size_t)rows * 4 * epb * 4 : (size_t)sums * 2 * epb * 4;
     if (relu) {
         if (form == ACT_DEEP) hipLaunchKernelGGL((k_act_eval<true, 64, 1>), grid, block, lds, s, L);
         else if (form == ACT_SHALLOW) hipLaunchKernelGGL((k_act_eval<true, kShallow, 1>), grid, block, lds, s, L);

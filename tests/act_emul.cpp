@@ -23,7 +23,7 @@
 
 #include "../paper_2302_06361_amd/csrc/dash_act_eval.hip"
 namespace dash { inline namespace DASH_RULE_NS { namespace {
-thread_local uint32_t acc[16384];                      // the kernel's dynamic LDS
+thread_local uint32_t acc[85 * 256];                     // the kernel's dynamic LDS
 const simt::dynamic_lds announce(acc, sizeof(acc));
 } } }
 

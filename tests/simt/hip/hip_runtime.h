@@ -5,6 +5,7 @@
 // A lane runs until it meets a barrier of its block or of its wave, or ends; a barrier opens when every lane of the block or wave that
 // has not ended stands at it.  Lanes run in ascending or (SIMT_REVERSE set)
 // descending order between barriers: a result that depends on the order shows a missing barrier.
+// SIMT_TRACE set: a line per launch on stderr.
 // Dynamic LDS is the array whose name the source gives it, at namespace scope; simt::dynamic_lds announces it, and what a launch does
 // not ask for is poisoned.
 #pragma once
@@ -140,6 +141,7 @@ inline void run_block() {
 template <class K, class... A>
 void launch(K* kernel, dim3 grid, dim3 block, size_t lds, void*, const A&... args) {
     grid_dim = grid; block_dim = block;
+    if (getenv("SIMT_TRACE")) fprintf(stderr, "simt: grid %u %u %u block %u lds %zu\n", grid.x, grid.y, grid.z, block.x, lds);
     const void* ptrs[] = {(const void*)&args...};
     kernarg = ptrs[0];
     std::function<void()> f = [&] { kernel(args...); };

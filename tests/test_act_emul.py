@@ -64,6 +64,7 @@ def run(emul, tmp_path, mode, k, rule, kind, n, repeat=1, layer=5, in_place=Fals
     e = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:detect_stack_use_after_return=0", **(env or {}))
     r = subprocess.run([emul, mode, fin, fout], capture_output=True, text=True, env=e)
     assert r.returncode == 0, r.stderr[-3000:]
+    run.stderr = r.stderr
     return np.fromfile(fout, np.uint8), orc, want, rt
 
 
@@ -82,13 +83,16 @@ def test_one_launch_activation_layers(emul, tmp_path, k, rule, form):
             assert got.size == ref.size and bad.size == 0, (kind, n, order, bad[:1])
 
 
-def test_deep_layers_whose_digit_sums_exceed_the_table_span(emul, tmp_path, monkeypatch):
-    """the same moduli with more digits: 7 + 13 * 5 = 72 dwords of sums, 64 fit beside the deep form's tables"""
-    monkeypatch.setitem(workloads.DIGITS, 8, (26,) + (12,) * 13)
-    env = {"DASH_ACT_SHALLOW_MIN_ELEMS": "0", "DASH_ACT_DEEP_MIN_ELEMS": "0"}
+@pytest.mark.parametrize("k,n_digits", [(8, 13), (8, 14), (7, 16), (12, 16)])
+def test_deep_layers_whose_digit_sums_exceed_the_table_span(emul, tmp_path, monkeypatch, k, n_digits):
+    """the same moduli with more digits: 67 to 85 dwords of sums, 64 lie beside the deep form's tables; large layers keep that form"""
+    monkeypatch.setitem(workloads.DIGITS, k, workloads.DIGITS[k][:2] + workloads.DIGITS[k][1:2] * (n_digits - 2))
+    rows = {13: 67, 14: 72, 16: 75 if k == 7 else 74}[n_digits]       # (16 digits: 85 and 81 dwords, the last ten in the free half of rows 64 to 73)
+    env = {"DASH_ACT_SHALLOW_MIN_ELEMS": "0", "DASH_ACT_DEEP_MIN_ELEMS": "0", "SIMT_TRACE": "1"}
     for kind, n in (("relu", 65), ("scale", 17)):
-        got, orc, want, _ = run(emul, tmp_path, "act", 8, 0, kind, n, env=env)
+        got, orc, want, _ = run(emul, tmp_path, "act", k, 0, kind, n, env=env)
         assert (got == np.concatenate([a.reshape(-1) for a in want])).all(), kind
+        assert "grid %d 1 1 block %d lds %d" % ((n + 63) // 64, 64 * (k if kind == "relu" else k - 1), rows * 1024) in run.stderr
 
 
 @pytest.mark.parametrize("k,kind,n,repeat", [(8, "relu", 3, 1), (8, "scale", 67, 2), (12, "relu", 65, 1), (7, "scale", 17, 1)])

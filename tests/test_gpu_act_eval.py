@@ -35,3 +35,13 @@ def test_one_launch_activation_layers_short_digit_set(monkeypatch, form):
     X = np.random.default_rng(5).integers(0, int(np.prod(workloads.PRIMES[:8])), 70)
     run_activation(8, "relu", X, digits=workloads.DIGITS_REDUCED[8], exact=False)
     run_activation(8, "scale", X, repeat=6, digits=workloads.DIGITS_REDUCED[8], exact=False)
+
+
+@pytest.mark.parametrize("k,n_digits", [(8, 14), (7, 16), (12, 16)])
+def test_deep_layers_of_long_digit_sets(monkeypatch, k, n_digits):
+    """digit sums that go on behind the span of the deep form's tables (72, 85 and 81 dwords; 64 fit)"""
+    force(monkeypatch, "deep")
+    digits = workloads.DIGITS[k][:2] + workloads.DIGITS[k][1:2] * (n_digits - 2)
+    X = np.random.default_rng(k).integers(0, int(np.prod(workloads.PRIMES[:k])), 65)
+    run_activation(k, "relu", X, digits=digits)
+    run_activation(k, "scale", X, repeat=2, digits=digits)
