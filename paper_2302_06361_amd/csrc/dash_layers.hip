@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "dash_internal.h"
+#include "dash_proj_rule.h"
 
 namespace dash {
 namespace {
@@ -923,9 +924,10 @@ static int check_proj(const dash_ctx* c, const dash_layer* L, const dash_labels*
 }
 
 static constexpr int kHotPrimes[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};      // (DASH_HOT_MODS)
-// Several independent PROJ calls at once: calls with the same layer id and output modulus share gate launches (up to
-// kMaxJobs per launch, each job with its own gate count and element base), and all fresh zero labels of a layer id
-// are drawn in shared launches.
+// Several independent PROJ calls at once, each with its own gate count and element base.  Garbler: calls with the same layer id and output
+// modulus share gate launches (up to kMaxJobs per launch), and all fresh zero labels of a layer id are drawn in shared launches.  Evaluator:
+// calls with the same layer id share launches whatever their moduli (up to kMaxEvalMany), but for those of an output modulus that
+// dash_proj_rule.h gives launches of its own; with a modulus that has no compile-time description among them, by output modulus.
 int proj_layers(dash_ctx* c, bool garble, int n, const dash_layer* Ls, const dash_labels* ins, dash_labels* outs, uint8_t* const* tables,
                 hipStream_t s) {
     for (int i = 0; i < n; i++) {
@@ -951,37 +953,41 @@ int proj_layers(dash_ctx* c, bool garble, int n, const dash_layer* Ls, const das
             db.flush();
             if (db.status) return db.status;
         }
-        // the evaluator's batches share launches whatever their moduli, where these have compile-time descriptions
+        // the evaluator's batches may share launches where all their moduli have compile-time descriptions
         bool many = !garble;
         for (size_t r = r0; r < r1 && many; r++)
             for (int m : {c->prime[Ls[order[r]].p_index], c->prime[Ls[order[r]].q_index]})
                 many = many && std::find(std::begin(kHotPrimes), std::end(kHotPrimes), m) != std::end(kHotPrimes) &&
                        c->mods[m].lam == cm::lam_of((uint32_t)m, c->rule == DASH_LAMBDA_FLOOR);
-        if (many) {
-            EvalManyLaunch M;
-            memset(&M, 0, sizeof(M));
-            M.layer = layer;
-            int nj = 0, st = DASH_OK;
-            for (size_t r = r0; r < r1 && st == DASH_OK; r++) {
+        GateBatcher gb(c, garble, 0, layer, 0, s);
+        EvalManyLaunch M;
+        int nm = 0, st = DASH_OK;
+        if (many) { memset(&M, 0, sizeof(M)); M.layer = layer; }
+        for (size_t q0 = r0, q1; q0 < r1; q0 = q1) {          // calls with one output modulus
+            ProjRun R{(uint32_t)c->prime[Ls[order[q0]].q_index], 0, 0, true, false};
+            for (q1 = q0; q1 < r1 && Ls[order[q1]].q_index == Ls[order[q0]].q_index; q1++) {
+                R.gates += (uint64_t)Ls[order[q1]].n_elem;
+                R.bits_only = R.bits_only && c->prime[Ls[order[q1]].p_index] == 2;
+            }
+            R.calls = q1 - q0;
+            R.alone = q0 == r0 && q1 == r1;
+            const bool own = !many || proj_own_launches(R, c->banked_min_lanes);
+            for (size_t r = q0; r < q1; r++) {
                 const dash_layer& L = Ls[order[r]];
                 const LView in = view_of(ins + order[r], L.p_index), out = view_of(outs + order[r], L.q_index);
-                M.jobs[nj++] = EvalManyJob{in.p, tables[order[r]], out.p, in.cs, out.cs, (uint64_t)L.elem_base, (uint32_t)L.n_elem,
-                                           (uint16_t)c->prime[L.p_index], (uint16_t)c->prime[L.q_index]};
-                if (nj == kMaxEvalMany || r + 1 == r1) { st = launch_eval_many(c, M, nj, s); nj = 0; }
+                if (!own) {
+                    M.jobs[nm++] = EvalManyJob{in.p, tables[order[r]], out.p, in.cs, out.cs, (uint64_t)L.elem_base, (uint32_t)L.n_elem,
+                                               (uint16_t)c->prime[L.p_index], (uint16_t)c->prime[L.q_index]};
+                    if (nm == kMaxEvalMany) { if ((st = launch_eval_many(c, M, nm, s)) != DASH_OK) return st; nm = 0; }
+                    continue;
+                }
+                GateJob J = phi_job(c->prime[L.p_index], c->prime[L.q_index], in, L.phi, 0, out, tables[order[r]]);
+                J.phi_stride = (uint32_t)L.phi_stride;
+                J.n_elem = (uint32_t)L.n_elem; J.elem_base = (uint64_t)L.elem_base;
+                gb.add(J, true);
             }
-            if (st) return st;
-            r0 = r1;
-            continue;
         }
-        GateBatcher gb(c, garble, 0, layer, 0, s);
-        for (size_t r = r0; r < r1; r++) {
-            const dash_layer& L = Ls[order[r]];
-            GateJob J = phi_job(c->prime[L.p_index], c->prime[L.q_index], view_of(ins + order[r], L.p_index), L.phi, 0,
-                                view_of(outs + order[r], L.q_index), tables[order[r]]);
-            J.phi_stride = (uint32_t)L.phi_stride;
-            J.n_elem = (uint32_t)L.n_elem; J.elem_base = (uint64_t)L.elem_base;
-            gb.add(J, true);
-        }
+        if (nm && (st = launch_eval_many(c, M, nm, s)) != DASH_OK) return st;
         gb.flush();
         if (gb.status) return gb.status;
         r0 = r1;

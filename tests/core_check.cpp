@@ -5,6 +5,7 @@
 
 #include "../paper_2302_06361_amd/csrc/dash_hostconst.h"
 #include "../paper_2302_06361_amd/csrc/dash_linear_rule.h"
+#include "../paper_2302_06361_amd/csrc/dash_proj_rule.h"
 
 using namespace dash;
 using namespace dash::hostconst;
@@ -104,6 +105,9 @@ uint32_t cc_axpymod4(uint32_t a, uint32_t c, uint32_t b, int m) { ModInfo M; fil
 uint32_t cc_mod_m(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return mod_m(n, M); }
 uint32_t cc_div_any(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return div_any(n, M); }
 // kernel of a linear layer
+int cc_proj_own(int q, uint64_t calls, uint64_t gates, int bits_only, int alone, uint64_t banked_min) {
+    return proj_own_launches(ProjRun{(uint32_t)q, calls, gates, bits_only != 0, alone != 0}, banked_min);
+}
 int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int in_c, int mfma) {
     return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, in_c, mfma != 0});
 }

@@ -153,3 +153,34 @@ def test_projection_groups_in_one_call(monkeypatch, threshold):
         assert_tables_equal(tables[i], rtable.reshape(-1), "group %d" % i)
         assert (outs[i].to_numpy(qi) == rout).all(), ("evaluated labels", i)
         assert outs[i].pad_is_zero(qi) and out0s[i].pad_is_zero(qi)
+
+
+def test_an_output_modulus_with_launches_of_its_own_beside_shared_ones():
+    """one call in which the 270 000 gates with output modulus 2 fill launches of their own and 3 000 others share one: against a call per
+    pair of moduli, and the ends of every group against the oracle"""
+    from paper_2302_06361_amd import ProjectionBatch
+    ctx, orc = both(12)
+    g = np.random.default_rng(123)
+    pi = g.integers(0, 12, 273000)
+    qi = np.concatenate([np.zeros(270000, np.int64), g.integers(1, 12, 3000)])
+    pb = ProjectionBatch(ctx, pi, qi, layer_id=4)
+    for G in pb.groups:
+        p, q = ctx.primes[G["pi"]], ctx.primes[G["qi"]]
+        labels = workloads.uniform_labels(g, G["count"], ctx.lam(p), p)
+        G["in0"].from_numpy(G["pi"], labels)
+        G["act"].from_numpy(G["pi"], ((labels.astype(np.int16) + orc.delta(p).astype(np.int16)) % p).astype(np.uint8))      # value 1
+        G["phi"].copy_(torch.as_tensor(workloads.proj_phi(g, G["count"], p, q)))
+    pb.garble()
+    pb.evaluate()
+    got = [G["out"].tensors[G["qi"]].clone() for G in pb.groups]
+    pb.evaluate(one_call_per_group=True)
+    torch.cuda.synchronize()
+    for t, G in zip(got, pb.groups):
+        p, q, n = ctx.primes[G["pi"]], ctx.primes[G["qi"]], G["count"]
+        assert bool((t == G["out"].tensors[G["qi"]]).all().item()), (p, q)
+        rb, act = p * ctx.pitch(q), G["act"].to_numpy(G["pi"])
+        for e0 in (0, max(0, n - 3)):
+            e1 = min(n, e0 + 3)
+            table = G["table"][e0 * rb:e1 * rb].cpu().numpy().reshape(e1 - e0, p, -1)
+            want = orc.proj_eval(p, q, act[e0:e1], table, 4, 0, G["start"] + e0)
+            assert (G["out"].slice(e0, e1).to_numpy(G["qi"]) == want).all(), (p, q, e0)
