@@ -4,6 +4,7 @@
 // Bound by vector issue like k_proj_garble, which takes these batches where this file's kernels do not apply; a row costs it the index
 // of its gate and value, four loads of labels and tables and their addresses on top.  Here a lane keeps its value a (chain_garble_body),
 // and the labels of the next tile are fetched under the hash of the current one.
+#include "dash_chain_rule.h"
 #include "dash_tabs.h"
 
 namespace dash {
@@ -104,17 +105,6 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const Gate
             gb = next;
         }
     }
-}
-
-// waves per batch: a multiple of the quantum that keeps the rounds of the resident waves full.  A round of waves costs its longest batch share.
-static uint32_t chain_waves(uint64_t tiles, uint32_t units, uint32_t quantum, uint32_t resident) {
-    uint32_t best = quantum;
-    double cost = 1e300;
-    for (uint64_t V = quantum; V < tiles + quantum && V <= 4u * resident; V += quantum) {
-        const double c = (double)((units * V + resident - 1) / resident) * ((double)((tiles + V - 1) / V) + 0.5);
-        if (c < cost) { cost = c; best = (uint32_t)V; }
-    }
-    return best;
 }
 
 int DASH_FN(launch_chain_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s, bool* done) {

@@ -3,6 +3,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include "../paper_2302_06361_amd/csrc/dash_chain_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_hostconst.h"
 #include "../paper_2302_06361_amd/csrc/dash_linear_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_proj_rule.h"
@@ -105,6 +106,19 @@ uint32_t cc_axpymod4(uint32_t a, uint32_t c, uint32_t b, int m) { ModInfo M; fil
 uint32_t cc_mod_m(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return mod_m(n, M); }
 uint32_t cc_div_any(uint32_t n, int m) { ModInfo M; fill_modinfo(M, m, 0); return div_any(n, M); }
 // kernel of a linear layer
+uint32_t cc_chain_waves(uint64_t tiles, uint32_t units, uint32_t quantum, uint32_t resident, uint32_t* tried) {
+    return chain_waves(tiles, units, quantum, resident, tried);
+}
+// every multiple of the quantum up to four rounds of a unit: the same V by exhaustion
+uint32_t cc_chain_waves_all(uint64_t tiles, uint32_t units, uint32_t quantum, uint32_t resident) {
+    uint32_t best = quantum;
+    double cost = 1e300;
+    for (uint64_t V = quantum; V < tiles + quantum && V <= 4u * resident; V += quantum) {
+        const double c = (double)((units * V + resident - 1) / resident) * ((double)((tiles + V - 1) / V) + 0.5);
+        if (c < cost) { cost = c; best = (uint32_t)V; }
+    }
+    return best;
+}
 int cc_proj_own(int q, uint64_t calls, uint64_t gates, int bits_only, int alone, uint64_t banked_min) {
     return proj_own_launches(ProjRun{(uint32_t)q, calls, gates, bits_only != 0, alone != 0}, banked_min);
 }
