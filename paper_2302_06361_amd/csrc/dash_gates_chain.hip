@@ -2,13 +2,22 @@
 // many gates with one function table, over the accumulation moduli of the digit sets with compile-time kernels.
 //
 // Bound by vector issue like k_proj_garble, which takes these batches where this file's kernels do not apply; a row costs it the index
-// of its gate and value, four loads of labels and tables and their addresses on top.  Here a lane keeps its value a (chain_garble_body),
+// of its gate and value, four loads of labels and tables and their addresses on top.  Here a lane keeps its value a (chain_garble_rows),
 // and the labels of the next tile are fetched under the hash of the current one.
 #include "dash_chain_rule.h"
 #include "dash_tabs.h"
 
 namespace dash {
 inline namespace DASH_RULE_NS {
+
+// The round keys are read again for every tile (scalar loads): kept over the loop they push its other scalars into vector registers, and
+// every use of one is then an instruction more (41 of them in the loop).
+__device__ __forceinline__ const uint32_t* read_again(const __attribute__((address_space(4))) uint32_t* rk) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(rk));
+#endif
+    return (const uint32_t*)rk;
+}
 
 // Units (repetition, batch) of V waves each, one after the other over the grid's waves.
 template <class MP, class QD>
@@ -20,13 +29,7 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble(const GateLaunc
     const uint32_t reps = L.reps.n ? L.reps.n : 1u, njobs = L.njobs, units = njobs * reps, waves = gridDim.x * (kBigThreads / 64);
     const MP P{ld_mod(L.mods, MP::m).dtab};
     const QD Q{ld_mod(L.mods, QD::m).dtab};
-    // The round keys are read again for every tile (scalar loads): kept over the loop they push its other scalars into vector registers, and
-    // every use of one is then an instruction more (41 of them in the loop).
-    auto keys = [&]() __attribute__((always_inline)) {
-        const __attribute__((address_space(4))) uint32_t* rk = L.key.rk;
-        asm volatile("" : "+s"(rk));
-        return (const uint32_t*)rk;
-    };
+    auto keys = [&]() __attribute__((always_inline)) { return read_again(L.key.rk); };
     for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
         const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs);
         const auto& J = L.jobs[unit - rep * njobs];
@@ -57,11 +60,7 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const Gate
 #pragma unroll
         for (int i = 0; i < 4; i++) R2.w[i] = __builtin_amdgcn_readfirstlane(R2.w[i]);
     }
-    auto keys = [&]() __attribute__((always_inline)) {
-        const __attribute__((address_space(4))) uint32_t* rk = L.key.rk;
-        asm volatile("" : "+s"(rk));
-        return (const uint32_t*)rk;
-    };
+    auto keys = [&]() __attribute__((always_inline)) { return read_again(L.key.rk); };
     for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
         const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs), t0 = vw - unit * V;
         const auto& J = L.jobs[unit - rep * njobs];
@@ -84,7 +83,9 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const Gate
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             uint32_t sl = lane;               // (opaque: its products are formed here and not held over the hash)
+#if defined(__HIP_DEVICE_COMPILE__)
             asm volatile("" : "+v"(sl));
+#endif
             const uint32_t part = sl & 7u;
 #pragma unroll
             for (uint32_t half = 0; half < 2; half++) {               // four loads at a time
