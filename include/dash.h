@@ -154,9 +154,10 @@ int dash_eval_layer(dash_ctx *ctx, const dash_layer *layer, const dash_labels *i
 /* n independent layer calls in one (Sec. LabelTensors: gates of the same kind are processed together as tensors): the
  * result is that of dash_garble_layer (dash_eval_layer) on (layers[i], in[i], out[i], tables[i], scratch[i]) for
  * i = 0 .. n-1, and no call of the list may read what another one writes.  The library may serve several calls with
- * one kernel launch: PROJ calls with the same layer_id and the same output modulus share launches of up to 16 calls
- * (the 144 (p, q) groups of a mixed batch of independent gates take 12 gate launches instead of 144); other kinds are
- * run in turn.  layers, in, out: host arrays of n entries; tables, scratch: host arrays of n device pointers (an entry
+ * one kernel launch: PROJ calls with the same layer_id share launches, when garbling those with the same output modulus, up to
+ * 16 a launch (the 144 (p, q) groups of a mixed batch of independent gates take 12 gate launches instead of 144), when evaluating
+ * over the primes up to 37 those of any moduli, up to 64 a launch (3 instead of 144), unless an output modulus has gates enough
+ * for launches of its own; other kinds are run in turn.  layers, in, out: host arrays of n entries; tables, scratch: host arrays of n device pointers (an entry
  * may be NULL where dash_layer_sizes gives 0; scratch itself may be NULL if no call needs scratch).  If the list holds
  * PROJ calls only, nothing is launched when the argument check of any call fails; otherwise the calls before the
  * failing one have been enqueued. */

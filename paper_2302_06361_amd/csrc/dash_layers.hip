@@ -575,6 +575,7 @@ void plan_scale_rep(const dash_ctx* c, Arena& ar, int64_t E, ScalePlan& p) {
 // instead of 200 (the whole network 269 -> 132); six of 1 920 values 0.9 ms of a LeNet batch less.
 // Layers of more than about 5 000 values of the 8-prime base keep one repetition at a time, whose launches fill the chip by themselves.
 constexpr size_t kScaleScratch = 32u << 20;
+static_assert(kScaleScratch <= DASH_NOALLOC_SCRATCH_BYTES, "dash_eval_layer_noalloc would refuse layers that it can take");
 constexpr int kScaleReps = 16;
 struct ScaleScratch { size_t step, next, bytes; int reps; };    // bytes of a repetition and of the wire between groups; in all; repetitions of a group
 ScaleScratch scale_scratch(const dash_ctx* c, int64_t E) {

@@ -14,7 +14,7 @@ class ProjectionBatch:
     and position j is the gate's element index (its tweak).  Per group the buffers are
     in0 / act (input zero and active labels), out0 / out (output labels), phi [count][p], table.
     garble() and evaluate() hand all groups to the library in ONE call (dash_garble_layers / dash_eval_layers),
-    which serves the groups that share an output modulus with one kernel launch."""
+    which garbles the groups that share an output modulus with one kernel launch and evaluates up to 64 groups with one."""
 
     def __init__(self, ctx, pi, qi, layer_id=1):
         import torch

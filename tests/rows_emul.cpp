@@ -1,6 +1,8 @@
-// Host emulation of the garbler's kernels for batches of carry gates and of the evaluator's for gates of any moduli: chain_garble_rows, wave by wave and lane by lane over exactly-sized
-// buffers under the sanitizers, against garble_body on the same gates: every table byte, for the pairs of moduli that the kernel is
-// compiled for.  Test code, not part of libdash.   usage: rows_emul <gates> <quanta of tiles per round of waves> <seed>
+// Host emulation of the bodies of the garbler's kernels for batches of carry gates (the kernels themselves: carry_emul.cpp) and of the
+// evaluator's for gates of any moduli: chain_garble_rows and the helpers of the final gates, wave by wave and lane by lane over
+// exactly-sized buffers under the sanitizers, against garble_body on the same gates, every table byte, for the pairs of moduli that the
+// kernels are compiled for; eval_many_body against eval_body.  Test code, not part of libdash.
+// usage: rows_emul <gates> <quanta of tiles per round of waves> <seed>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
