@@ -133,8 +133,9 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 // layer differ in length by a factor of 50, so the waves share the concatenation of their tiles, a contiguous range each.
 // (One lane per row, run-time constants and the same number of blocks for every segment took 6.0 ms for the 5.1 GB of tables of a
 // LeNet batch of 4; this form takes 3.3.)
+// Unpacking is held to 128 registers, four waves per SIMD: left to itself the compiler takes 136 for the base conversions of all moduli.
 template <bool Pack>
-__global__ __launch_bounds__(kThreads) void k_rows_repack(const PackLaunch L) {
+__global__ __launch_bounds__(kThreads, Pack ? 1 : 4) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_at4 __attribute__((aligned(4)));              // of table rows: tables, and with rows of 20 bytes their segments, are 4-byte aligned
     constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
