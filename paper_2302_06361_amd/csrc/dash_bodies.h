@@ -229,8 +229,9 @@ struct PerJobMod {};
 
 // garble: one lane per ciphertext row r = gate * p + a.  QD: description type of the output modulus
 // (every job of a launch has the same output modulus), fixed at compile time for the hot moduli.
-template <class QD, class Tab, class Sink>
-DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink, uint32_t rep = 0) {
+// keys(): the round keys.
+template <class QD, class Tab, class Sink, class Keys>
+DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink, uint32_t rep, Keys keys) {
     const GateJob& J = L.jobs[by];
     const LView Jin = rep_view(J.in, L.reps, rep), Jout = rep_view(J.out, L.reps, rep);
     uint8_t* const table = J.table + (int64_t)rep * L.reps.tables;
@@ -251,7 +252,7 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
         const uint32_t* da = P.dtab + a * P.ndw;
         K = compress(P, [&](int i) { return addmod4(ld_dw(Jin, g, i), gload32(da + i), P); }, &colour);
     });
-    U128 h = hash_block(K, J.elem_base + g, J.slot + rep * L.reps.slots, L.layer, L.key.rk, T);
+    U128 h = hash_block(K, J.elem_base + g, J.slot + rep * L.reps.slots, L.layer, keys(), T);
 
     // the output modulus: the kernel's compile-time description, or the run-time record (the instantiation for any
     // modulus, which also serves launches that mix output moduli; choosing a compile-time description per job inside
@@ -294,6 +295,11 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
     if constexpr (cmod_m<QD>::value != 0) finish(make_mod<QD>::from(Mq));
     else if constexpr (std::is_same<QD, PerJobMod>::value) with_mod(Mq, finish);
     else finish(Mq);
+}
+
+template <class QD, class Tab, class Sink>
+DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, Sink& sink, uint32_t rep = 0) {
+    garble_body<QD>(L, bx, by, tx, T, sink, rep, [&] { return (const uint32_t*)L.key.rk; });
 }
 
 // Garbler, a batch of gates of one input modulus and one function table (carry gates of the sign gadget): the lane keeps its value a.

@@ -378,6 +378,15 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         __shared__ uint32_t tt[gate_tab<Banked>::words];
         const auto T = gate_tab<Banked>::load(tt, L.ttab);
         const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
+        // Run-time modulus: its record and the round keys together are more than the scalar registers hold, and 826 places of the code brought one
+        // back from a vector register (61 with the keys read again; a repetition of 40 000 values of 10 primes garbled in 3.0 ms instead of 4.9).
+        auto body = [&](uint32_t tile, uint32_t job, uint32_t rep) __attribute__((always_inline)) {
+            DirectSink sink;
+            if constexpr (std::is_same<QD, ModInfo>::value)
+                garble_body<QD>(L, tile, job, tx, T, sink, rep, [] { return read_again((const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr()); });
+            else
+                garble_body<QD>(L, tile, job, tx, T, sink, rep);
+        };
         if constexpr (Banked) {
             // one-dimensional grid: the jobs differ in length (n_elem * p rows), so the blocks share the
             // concatenation of all jobs' tiles evenly.  job, base and next are the same in all lanes of a wave.
@@ -388,14 +397,10 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
             uint32_t job = 0, rep = 0, base = 0, next = tiles_of(0);
             for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
                 while (t >= next) { if (++job == L.njobs) { job = 0; rep++; } base = next; next += tiles_of(job); }
-                DirectSink sink;
-                garble_body<QD>(L, t - base, job, tx, T, sink, rep);
+                body(t - base, job, rep);
             }
         } else {
-            for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) {
-                DirectSink sink;
-                garble_body<QD>(L, tile, blockIdx.y, tx, T, sink, blockIdx.z);
-            }
+            for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) body(tile, blockIdx.y, blockIdx.z);
         }
     }
 }

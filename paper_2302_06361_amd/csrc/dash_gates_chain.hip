@@ -10,15 +10,6 @@
 namespace dash {
 inline namespace DASH_RULE_NS {
 
-// The round keys are read again for every tile (scalar loads): kept over the loop they push its other scalars into vector registers, and
-// every use of one is then an instruction more (41 of them in the loop).
-__device__ __forceinline__ const uint32_t* read_again(const __attribute__((address_space(4))) uint32_t* rk) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+s"(rk));
-#endif
-    return (const uint32_t*)rk;
-}
-
 // Units (repetition, batch) of V waves each, one after the other over the grid's waves.
 template <class MP, class QD>
 __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble(const GateLaunch, uint32_t V) {

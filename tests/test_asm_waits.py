@@ -1,4 +1,4 @@
-"""Wait states in the kernels' assembly.  A vector instruction that writes VCC or another scalar register has to stand two wait states
+"""The kernels' assembly.  Wait states: a vector instruction that writes VCC or another scalar register has to stand two wait states
 before a vector instruction that reads it (gfx950); the compiler sees to that in its own code, but not inside inline assembly.  The base
 conversions of every modulus with a compile-time description, compiled for gfx950 as the library's are.  No GPU involved."""
 import os
@@ -77,3 +77,15 @@ def test_scalar_results_of_vector_instructions_in_the_base_conversions(tmp_path,
     text = out.read_text()
     assert text.count("v_mad_u64_u32") > 300         # (the conversions are there)
     assert violations(text) == []
+
+
+def test_the_run_time_garbler_keeps_its_scalars(tmp_path):
+    """k_proj_garble for any modulus holds a modulus record and the launch's arguments in scalar registers; what these do not hold comes back from
+    vector registers one instruction at a time, in the loop over the tiles (826 of them with the round keys held as well)"""
+    src, out = tmp_path / "garble.hip", tmp_path / "garble.s"
+    src.write_text('#include "%s/dash_tabs.h"\n#undef DASH_HOT_MODS\n#define DASH_HOT_MODS(X) X(2, 128)\n#include "%s/dash_gates.hip"\n' % (build.CSRC, build.CSRC))
+    r = subprocess.run([HIPCC] + build.FLAGS + ["--cuda-device-only", "-S", str(src), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    kernels = dict(re.findall(r"^(_Z\S*k_proj_garble\S*):(.*?)s_endpgm", out.read_text(), re.S | re.M))
+    bodies = [v for k, v in kernels.items() if "7ModInfoELb1E" in k]
+    assert len(bodies) == 1 and bodies[0].count("v_readlane_b32") < 200
