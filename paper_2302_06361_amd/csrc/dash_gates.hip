@@ -383,7 +383,7 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         auto body = [&](uint32_t tile, uint32_t job, uint32_t rep) __attribute__((always_inline)) {
             DirectSink sink;
             if constexpr (std::is_same<QD, ModInfo>::value)
-                garble_body<QD>(L, tile, job, tx, T, sink, rep, [] { return read_again((const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr()); });
+                garble_body<QD>(L, tile, job, tx, T, sink, rep, [] { return read_again(((const __attribute__((address_space(4))) GateLaunch*)__builtin_amdgcn_kernarg_segment_ptr())->key.rk); });
             else
                 garble_body<QD>(L, tile, job, tx, T, sink, rep);
         };

@@ -110,7 +110,7 @@ __device__ __forceinline__ HalfTab load_halftab(uint32_t* lds, const uint32_t* g
 }
 
 // The round keys are read again for every tile (scalar loads): kept over the loop they push its other scalars into vector registers, and
-// every use of one is then an instruction more (41 of them in the loop).
+// every use of one is then an instruction more (carry gates: 41 of them in the loop; k_proj_garble for any modulus: see there).
 __device__ __forceinline__ const uint32_t* read_again(const __attribute__((address_space(4))) uint32_t* rk) {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("" : "+s"(rk));
