@@ -306,7 +306,7 @@ DASH_HD void garble_body(const GateLaunch& L, uint32_t bx, uint32_t by, uint32_t
 // The rows of a batch, gate * m + a in order, are dealt to V waves in tiles of 64, and V tiles are a multiple of the input modulus m: a, with it
 // the multiple of R_p that forms the label and the one of R_q that the row carries, stays the same from tile to tile and is held in
 // registers, and so is the lane's place relative to the tile's first gate.  What is left per row is the label's addition and
-// compression, the hash, and two packed additions.  keys(): the round keys.
+// compression, the hash, and two packed additions.  keys(): the round keys; tick(): called once per tile.
 struct ChainRows {
     const uint8_t *in, *out0, *phi;      // zero labels of the input and the output wires; function table
     int64_t in_cs, out_cs;
@@ -314,8 +314,9 @@ struct ChainRows {
     uint64_t elem_base;
     uint32_t n, slot, layer;             // gates
 };
-template <class MP, class QD, class Keys, class Tab>
-DASH_HD void chain_garble_rows(const ChainRows& J, const MP& P, const QD& Q, uint32_t V, uint32_t t0, uint32_t lane, Keys keys, const Tab& T) {
+struct NoTick { DASH_HD void operator()() const {} };
+template <class MP, class QD, class Keys, class Tab, class Tick = NoTick>
+DASH_HD void chain_garble_rows(const ChainRows& J, const MP& P, const QD& Q, uint32_t V, uint32_t t0, uint32_t lane, Keys keys, const Tab& T, Tick tick = Tick()) {
     constexpr uint32_t m = MP::m, pitch = QD::ndw * 4;
     constexpr int NP = (int)MP::ndw, NQ = (int)QD::ndw;
     const uint32_t n = J.n, tiles = (uint32_t)(((uint64_t)n * m + 63) / 64);
@@ -336,6 +337,7 @@ DASH_HD void chain_garble_rows(const ChainRows& J, const MP& P, const QD& Q, uin
     ld_label<NP>(J.in + (uint64_t)gb * 16, J.in_cs, eo(gb), z);
     for (uint32_t t = t0; t < tiles; t += V) {
         const uint32_t next = t + V < tiles ? gb + step : gb;
+        tick();
         ld_label<NQ>(J.out0 + (uint64_t)gb * 16, J.out_cs, eo(gb), o);
         uint32_t colour;
         const U128 K = compress(P, [&](int i) { return addmod4_off(z[i], da[i], P); }, &colour);
@@ -712,14 +714,15 @@ DASH_HD void digit_row(const DigitsLaunch& L, const DigitsRes& R, const ModInfo&
 // Compile-time moduli: the rows of digits j0..j1 (j0 = 1 or 2 and up) of one (element, value a).  Everything but the hash costs as little as can be, the
 // kernel being bound by vector issue: the tile's first element is in the scalar base addresses and the lane's part in 32-bit offsets
 // that serve every digit; what a row adds to its hash is fetched before the hash.
-template <class MO, class Tab>
+template <class MO, class Tab, class Tick>
 DASH_HD void digit_rows(const DigitsLaunch& L, const uint8_t* phi, uint32_t p, const uint8_t* out0, int64_t out_step, uint8_t* seg, int64_t seg_step, const MO& Mo,
-                        SlotHash& S, uint32_t& hi, uint32_t& slot, int count, uint32_t a, uint32_t eo, uint32_t row, const Tab& T) {
+                        SlotHash& S, uint32_t& hi, uint32_t& slot, int count, uint32_t a, uint32_t eo, uint32_t row, const Tab& T, Tick tick) {
     constexpr int N = (int)MO::ndw;
     const uint32_t ro = row * (MO::ndw * 4);
     uint32_t f = phi[a];
     for (int j = 0; j < count; j++) {
         uint32_t pay[N], o[N];
+        tick();
         ld_label<N>(out0, L.out_cs, eo, o);
         ld_dwords<N>(Mo.dtab, f * (MO::ndw * 4), pay);
         phi += p;
@@ -739,9 +742,9 @@ DASH_HD void digit_rows(const DigitsLaunch& L, const uint8_t* phi, uint32_t p, c
     }
 }
 // j0 = 0: all n digits of the lane's (element, value); j0 = 1..n: digit j0 only (gadgets over few elements: a lane per
-// row, a chain of one hash)
-template <class MC, class M1, class Tab>
-DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, uint32_t j0 = 0, uint32_t rep = 0) {
+// row, a chain of one hash).  tick(): called once per digit (of compile-time moduli)
+template <class MC, class M1, class Tab, class Tick = NoTick>
+DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by, uint32_t tx, const Tab& T, uint32_t j0 = 0, uint32_t rep = 0, Tick tick = Tick()) {
     const DigitsRes& R = L.res[by];
     const LView in = rep_view(R.in, L.reps, rep);
     const uint32_t slot0 = R.slot0 + rep * L.reps.slots;
@@ -772,14 +775,14 @@ DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by,
         int j = jlo;
         if (j == 1) {
             const M1 Mf{ld_mod(L.mods, L.m[1]).dtab};
-            digit_rows(L, R.phi, R.p, out0, 0, seg + before * (int64_t)(M1::ndw * 4), 0, Mf, S, hi, slot, 1, a, eo, row, T);
+            digit_rows(L, R.phi, R.p, out0, 0, seg + before * (int64_t)(M1::ndw * 4), 0, Mf, S, hi, slot, 1, a, eo, row, T, tick);
             j = 2;
         }
         if (j <= jhi) {
             const MC Mc{ld_mod(L.mods, L.m[2]).dtab};
             const int64_t step = rows * (int64_t)(MC::ndw * 4);
             digit_rows(L, R.phi + (uint32_t)(j - 1) * R.p, R.p, out0 + L.out_prefix[j], (int64_t)(L.out_prefix[j < (int)L.n ? j + 1 : j] - L.out_prefix[j]),
-                       seg + rows * (int64_t)(M1::ndw * 4) + (j - 2) * step + before * (int64_t)(MC::ndw * 4), step, Mc, S, hi, slot, jhi - j + 1, a, eo, row, T);
+                       seg + rows * (int64_t)(M1::ndw * 4) + (j - 2) * step + before * (int64_t)(MC::ndw * 4), step, Mc, S, hi, slot, jhi - j + 1, a, eo, row, T, tick);
         }
         return;
     }

@@ -315,9 +315,11 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
         uint32_t job = 0, rep = 0, base = 0, next = tiles_of(0);
         // (every wave stages and writes out its own 64 rows: no barrier between waves)
         const uint32_t rounds = (total + gridDim.x * kGateTiles - 1) / (gridDim.x * kGateTiles);
+        Pace pace(rounds);
         for (uint32_t r = 0; r < rounds; r++) {
-            const uint32_t t = (r * gridDim.x + blockIdx.x) * kGateTiles + sub;
+            const uint32_t t = (r * kGateTiles + sub) * gridDim.x + blockIdx.x;
             RegSink<ndw> sink;
+            pace.tick();
             if (t < total) {
                 while (t >= next) { if (++job == L.njobs) { job = 0; rep++; } base = next; next += tiles_of(job); }
                 garble_body<QD>(L, t - base, job, tx, T, sink, rep);
@@ -395,7 +397,11 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_p
             for (uint32_t j = 0; j < L.njobs; j++) total += tiles_of(j);
             total *= rep_count(L.reps);
             uint32_t job = 0, rep = 0, base = 0, next = tiles_of(0);
-            for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
+            // (one tile of each block, then the next of each: what is left over for a last, partial round lies on as many CUs as it has tiles)
+            const uint32_t first = sub * gridDim.x + blockIdx.x, step = gridDim.x * kGateTiles;
+            Pace pace(first, total, step);
+            for (uint32_t t = first; t < total; t += step) {
+                pace.tick();
                 while (t >= next) { if (++job == L.njobs) { job = 0; rep++; } base = next; next += tiles_of(job); }
                 body(t - base, job, rep);
             }

@@ -21,13 +21,15 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble(const GateLaunc
     const MP P{ld_mod(L.mods, MP::m).dtab};
     const QD Q{ld_mod(L.mods, QD::m).dtab};
     auto keys = [&]() __attribute__((always_inline)) { return read_again(L.key.rk); };
+    const uint32_t share = ((uint32_t)(((uint64_t)L.jobs[0].n_elem * MP::m + 63) / 64) + V - 1) / V;      // tiles of a unit's wave, at most
+    Pace pace((units * V + waves - 1) / waves * share);
     for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
         const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs);
         const auto& J = L.jobs[unit - rep * njobs];
         const int64_t wires = (int64_t)rep * L.reps.wires;
         const ChainRows R{J.in.p + wires, J.out.p + wires, J.phi, J.in.cs, J.out.cs, J.table + (int64_t)rep * L.reps.tables,
                           J.elem_base, J.n_elem, J.slot + rep * L.reps.slots, L.layer};
-        chain_garble_rows(R, P, Q, V, vw - unit * V, threadIdx.x & 63u, keys, T);
+        chain_garble_rows(R, P, Q, V, vw - unit * V, threadIdx.x & 63u, keys, T, [&]() __attribute__((always_inline)) { pace.tick(); });
     }
 }
 
@@ -52,6 +54,8 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const Gate
         for (int i = 0; i < 4; i++) R2.w[i] = __builtin_amdgcn_readfirstlane(R2.w[i]);
     }
     auto keys = [&]() __attribute__((always_inline)) { return read_again(L.key.rk); };
+    const uint32_t share = ((uint32_t)(((uint64_t)L.jobs[0].n_elem * MP::m + 63) / 64) + V - 1) / V;      // tiles of a unit's wave, at most
+    Pace pace((units * V + waves - 1) / waves * share);
     for (uint32_t vw = blockIdx.x * (kBigThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); vw < units * V; vw += waves) {
         const uint32_t unit = __builtin_amdgcn_readfirstlane(vw / V), rep = __builtin_amdgcn_readfirstlane(unit / njobs), t0 = vw - unit * V;
         const auto& J = L.jobs[unit - rep * njobs];
@@ -67,6 +71,7 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_chain_garble_bits(const Gate
         ld_label<NP>(R.in + (uint64_t)gb * 16, R.in_cs, eo(gb), z);
         for (uint32_t t = t0; t < tiles; t += V) {
             const uint32_t next = t + V < tiles ? gb + step : gb;
+            pace.tick();
             uint32_t row;
             const U128 w = chain_bits_row(R, P, R2, B, gb, z, keys(), T, row);
             ld_label<NP>(R.in + (uint64_t)next * 16, R.in_cs, eo(next), z);

@@ -26,9 +26,14 @@ __global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_d
     for (uint32_t i = 0; i < L.nres; i++) total += tiles_of(i);
     total *= rep_count(L.reps);
     uint32_t res = 0, rep = 0, base = 0, next = tiles_of(0);
-    for (uint32_t t = blockIdx.x * kGateTiles + sub; t < total; t += gridDim.x * kGateTiles) {
+    // (one tile of each block, then the next of each: what is left over for a last, partial round lies on as many CUs as it has tiles)
+    const uint32_t first = sub * gridDim.x + blockIdx.x, step = gridDim.x * kGateTiles;
+    constexpr bool kDigits = cmod_m<MC>::value != 0;                   // (run-time moduli: paced by tiles)
+    Pace pace(first, total, step, kDigits ? L.n : 1);
+    for (uint32_t t = first; t < total; t += step) {
+        if constexpr (!kDigits) pace.tick();
         while (t >= next) { if (++res == L.nres) { res = 0; rep++; } base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep);
+        digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep, [&]() __attribute__((always_inline)) { pace.tick(); });
     }
 }
 
@@ -84,7 +89,8 @@ int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_
     }
     const bool banked = (uint64_t)(units / L.n) >= c->digits_banked_min_lanes;
     if (banked) L.key = c->fixed_rot;
-    dim3 grid(gate_grid_x_for(tiles * reps, 1, banked));
+    const uint64_t blocks = banked ? (tiles * reps + 3) / 4 : tiles * reps, cap = banked ? 512 : 2560;      // (banked: two per CU, one round)
+    const dim3 grid((uint32_t)(blocks < cap ? blocks : cap));
     const dim3 block(banked ? kBigThreads : kThreads);
     with_digit_set(typed, [&](auto ds) {
         typedef decltype(ds) DS;
