@@ -7,7 +7,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 SO = os.path.join(HERE, "libdash.so")
-GATE_SOURCES = ["dash_gates_cast.hip", "dash_gates_chain.hip", "dash_gates.hip", "dash_gates_eval.hip", "dash_gates_digits_eval.hip", "dash_gates_digits.hip"]
+GATE_SOURCES = ["dash_gates_cast.hip", "dash_gates_bit.hip", "dash_gates_chain.hip", "dash_gates.hip", "dash_gates_eval.hip", "dash_gates_digits_eval.hip", "dash_gates_digits.hip"]
 SOURCES = ["dash_ctx.hip", "dash_layers.hip", "dash_linear.hip", "dash_gemm.hip", "dash_aesprof.hip"]
 # (source, extra flags, object): the gate kernels once per label-length rule, the evaluator's whole layers also once per digit set
 UNITS = []

@@ -38,6 +38,14 @@ template <int N> DASH_HD void ld_dwords(const void* base, uint32_t off, uint32_t
     for (int i = 0; i < N; i++) w[i] = src[i];
 #endif
 }
+// a dword of a table that is never written while a kernel runs, at an address that is the same in all lanes (a scalar load)
+DASH_HD uint32_t ld_const(const uint32_t* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(4))) uint32_t*)p;
+#else
+    return *p;
+#endif
+}
 // 16 bytes at base + off, 16-byte aligned
 DASH_HD Dw4 ld_dw4(const uint8_t* base, uint32_t off) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -64,6 +72,13 @@ template <int N> DASH_HD void ld_label(const uint8_t* p, int64_t cs, uint32_t eo
 #pragma unroll
         for (int q = 0; q < 4; q++) if (4 * ch + q < N) w[4 * ch + q] = d.w[q];
     }
+}
+// the same number, of which nothing is known (what is formed from it is formed where it stands); the same in all lanes
+DASH_HD uint32_t opaque(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v));
+#endif
+    return v;
 }
 // keeps what stands before it from being moved behind what follows, and the other way round (loads ahead of a hash)
 DASH_HD void schedule_fence() {
@@ -792,6 +807,96 @@ DASH_HD void digits_garble_body(const DigitsLaunch& L, uint32_t bx, uint32_t by,
         const U128 h = H.get(slot0 + (uint32_t)(j - 1), L.key.rk, T);
         const ModInfo Mo = ld_mod(L.mods, L.m[j]);      // a copy in registers: through the reference every use is a load
         digit_row(L, R, Mo, h, f, colour, g, j, rep);
+    }
+}
+
+// Garbler, gates on ONE wire of modulus 2 (128 digits): the casts of the scaling gadget, the evaluator's halves and known inputs of the half gates.
+// A lane has (element, value a): it packs and forms the label of a once, and the hashes of its jobs j0 .. j1 - 1, whose slots are
+// neighbours, share their first two rounds.  The jobs have compile-time output moduli, labels of 16-byte elements, and in, n_elem and elem_base
+// in common; the hash stands between two dispatches on the output modulus, the first of which sends the loads of the output wire's label out.
+// R2: the offset label of modulus 2.  keys(): the round keys; tick(): called once per job.  Half: the jobs are PAY_EHALF and PAY_SHORT, else
+// PAY_PHI.
+template <bool Half, class Launch, class Tab, class Keys, class Tick = NoTick>
+DASH_HD void bit_garble_body(const Launch& L, uint32_t tile, uint32_t rep, uint32_t j0, uint32_t j1, uint32_t tx, const U128& R2, const Tab& T, Keys keys, Tick tick = Tick()) {
+    constexpr int kMax = 12;                // labels of more dwords (moduli 2, 3 and 5) are loaded after the hash: registers
+    const uint32_t n = L.jobs[j0].n_elem, e0 = tile * (kThreads / 2), e = e0 + (tx >> 1), a = tx & 1u, eo = (tx >> 1) * 16;
+    if (e >= n) return;
+    const int64_t wires = (int64_t)rep * L.reps.wires;
+    const uint64_t elem = L.jobs[j0].elem_base + e;
+    const uint8_t* in = L.jobs[j0].in.p + wires + (uint64_t)e0 * 16;
+    const int64_t in_cs = L.jobs[j0].in.cs;
+    U128 K;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int ch = 0; ch < 2; ch++) {
+            const Dw4 d = ld_dw4(in + (2 * c + ch) * in_cs, eo);
+#pragma unroll
+            for (int q = 0; q < 4; q++) w |= dot4(d.w[q], 0x08040201u) << (16 * ch + 4 * q);
+        }
+        K.w[c] = w ^ (R2.w[c] & (0u - a));
+    }
+    const uint32_t row = (tx & ~1u) | (K.w[0] & 1u);                     // past the tile's first row
+    uint32_t hi = L.jobs[j0].slot + rep * L.reps.slots & ~0xffu;
+    const uint32_t x[4] = {K.w[0] ^ (uint32_t)elem, K.w[1] ^ (uint32_t)(elem >> 32), K.w[2] ^ hi, K.w[3] ^ (L.layer & 0xffffu)};
+    SlotHash S = slot_hash_start(x, keys(), T);
+    for (uint32_t j = j0; j < j1; j++) {
+        const auto& J = L.jobs[j];
+        const uint32_t slot = J.slot + rep * L.reps.slots;
+        const bool digit = Half && J.mode == PAY_SHORT;                  // one digit and no output label
+        tick();
+        uint32_t o[kMax], r = 0;
+        if (Half) r = J.r[e];
+        if (!digit) with_mod(ld_mod(L.mods, J.q), [&](auto Q) {
+            typedef decltype(Q) QT;
+            if constexpr (cmod_m<QT>::value != 0) { if constexpr (QT::ndw <= kMax) ld_label<(int)QT::ndw>(J.out.p + wires + (uint64_t)e0 * 16, J.out.cs, eo, o); }
+        });
+        schedule_fence();
+        if ((slot & ~0xffu) != hi) {
+            S.x[2] ^= hi ^ (slot & ~0xffu);
+            hi = slot & ~0xffu;
+            S = slot_hash_start(S.x, keys(), T);
+        }
+        const U128 h = slot_hash(S, slot, keys(), T);
+        const auto& A = L.jobs[opaque(j)];                               // (J, read again: its fields don't stay in registers over the hash)
+        with_mod(ld_mod(L.mods, A.q), [&](auto Q) {
+            typedef decltype(Q) QT;
+            if constexpr (cmod_m<QT>::value != 0) {
+                constexpr uint32_t m = QT::m, pitch = QT::ndw * 4;
+                uint8_t* const table = A.table + (int64_t)rep * L.reps.tables;
+                const uint8_t* const out0 = A.out.p + wires + (uint64_t)e0 * 16;
+                const int64_t out_cs = A.out.cs;
+                if (digit) { st_row(table + (uint64_t)e0 * 8, row * 4, 0, mod_m(a + r + mod_u128(h, Q), Q)); return; }
+                uint8_t* const rows = table + (uint64_t)e0 * (2 * pitch);
+                // PAY_PHI: phi(a) R_q, its two values the same in all lanes; PAY_EHALF: - (a + r) x0
+                const uint32_t f0 = Half ? 0u : A.phi[0], f1 = Half ? 0u : A.phi[1], s = mod_m(a + r, Q), cf = s ? m - s : 0u;
+                const uint32_t *df0 = Q.dtab + f0 * QT::ndw, *df1 = Q.dtab + f1 * QT::ndw;
+                const uint8_t* const x0 = Half ? A.x0.p + (uint64_t)e0 * 16 : nullptr;
+                auto payload = [&](int i, uint32_t z, uint32_t xd) { return Half ? axpymod4(z, cf, xd, Q) : addmod4(z, a ? ld_const(df1 + i) : ld_const(df0 + i), Q); };
+                if constexpr (m == 2) {
+#pragma unroll
+                    for (int ch = 0; ch < 8; ch++) {
+                        const Dw4 d = ld_dw4(out0 + (int64_t)ch * out_cs, eo);
+                        Dw4 xd = {};
+                        if (Half) xd = ld_dw4(x0 + (int64_t)ch * A.x0.cs, eo);
+#pragma unroll
+                        for (int q = 0; q < 4; q++)
+                            st_row(rows, row * pitch, 4 * ch + q, payload(4 * ch + q, d.w[q], xd.w[q]) ^ (mul24((h.w[ch >> 1] >> (16 * (ch & 1) + 4 * q)) & 0xfu, 0x00204081u) & kOnes));
+                    }
+                } else {
+                    uint32_t z[QT::ndw], xd[QT::ndw] = {};
+                    if constexpr (QT::ndw <= kMax) {
+#pragma unroll
+                        for (int i = 0; i < (int)QT::ndw; i++) z[i] = o[i];
+                    } else ld_label<(int)QT::ndw>(out0, out_cs, eo, z);
+                    if (Half) ld_label<(int)QT::ndw>(x0, A.x0.cs, eo, xd);
+#pragma unroll
+                    for (int i = 0; i < (int)QT::ndw; i++) z[i] = payload(i, z[i], xd[i]);
+                    decompress(Q, h, [&](int i, uint32_t hd) { st_row(rows, row * pitch, i, addmod4(hd, z[i], Q)); });
+                }
+            }
+        });
     }
 }
 

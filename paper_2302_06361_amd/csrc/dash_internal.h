@@ -97,6 +97,7 @@ DASH_BY_RULE(int, launch_affine, (const dash_ctx* c, AffineLaunch& L, int njobs,
 DASH_BY_RULE(int, launch_garble, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 // (done: whether the launch is one of the kernel's; else nothing is launched)
 DASH_BY_RULE(int, launch_chain_garble, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s, bool* done), (c, L, njobs, s, done))
+DASH_BY_RULE(int, launch_bit_garble, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s, bool* done), (c, L, njobs, s, done))
 DASH_BY_RULE(int, launch_eval, (const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 DASH_BY_RULE(int, launch_eval_many, (const dash_ctx* c, EvalManyLaunch& L, int njobs, hipStream_t s), (c, L, njobs, s))
 DASH_BY_RULE(int, launch_chain_eval, (const dash_ctx* c, ChainLaunch& L, hipStream_t s), (c, L, s))

@@ -285,10 +285,32 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
         if (extra_gates) {
             if (gb.mixed) {
                 for (const GateJob& J : *extra_gates) gb.add(J);
-            } else {      // a launch of their own, mixed if they are few; else one per output modulus, its compile-time code
+            } else {      // launches of their own: the gates on the mod-2 wire together; the rest mixed if they are few, else per output modulus
+                std::vector<GateJob> rest;
+                GateLaunch GL;
+                memset(&GL, 0, sizeof(GL));
+                GL.layer = layer;
+                if (reps) GL.reps = *reps;
+                int nj = 0;
+                auto bits = [&]() {
+                    bool done = false;
+                    const int st = nj ? launch_bit_garble(c, GL, nj, s, &done) : DASH_OK;
+                    if (st == DASH_OK && !done) rest.insert(rest.end(), GL.jobs, GL.jobs + nj);
+                    nj = 0;
+                    return st;
+                };
+                for (const GateJob& J : *extra_gates) {
+                    if (J.p != 2 || J.mode == PAY_MULR) { rest.push_back(J); continue; }
+                    GL.jobs[nj] = J;
+                    GL.jobs[nj].n_elem = E; GL.jobs[nj].elem_base = elem_base;
+                    if (++nj == kMaxJobs) if (const int st = bits()) return st;
+                }
+                if (const int st = bits()) return st;
+                extra_rows = 0;
+                for (const GateJob& J : rest) extra_rows += nrep * E * J.p;
                 GateBatcher ge(c, true, E, layer, elem_base, s, few_rows(c, extra_rows));
                 if (reps) ge.repeat(*reps);
-                for (const GateJob& J : *extra_gates) ge.add(J);
+                for (const GateJob& J : rest) ge.add(J);
                 ge.flush();
                 if (ge.status) return ge.status;
                 gb.mixed = few_rows(c, rows);
