@@ -15,11 +15,11 @@ inline namespace DASH_RULE_NS {
 // One launch for the k n digit gates of a sign gadget: lane = (element, value a) of a residue, which forms and
 // compresses the label of a once for the n rows it garbles.  The residues differ in length (n_elem * p rows):
 // the blocks share the concatenation of their tiles (one-dimensional grid).
-template <class MC, class M1, bool Banked>
-__global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_digits_garble(const DigitsLaunch L) {
-    constexpr int kGateTiles = gate_tab<Banked>::threads / kThreads;
-    __shared__ uint32_t tt[gate_tab<Banked>::words];
-    const auto T = gate_tab<Banked>::load(tt, L.ttab);
+template <class MC, class M1>
+__global__ __launch_bounds__(kBigThreads, 8) void k_digits_garble(const DigitsLaunch L) {
+    constexpr int kGateTiles = kBigThreads / kThreads;
+    __shared__ uint32_t tt[kBankTabWords];
+    const BankTab T = load_banktab(tt, L.ttab);
     const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     auto tiles_of = [&](uint32_t i) { return (uint32_t)(((uint64_t)L.n_elem * L.res[i].p + kThreads - 1) / kThreads); };
     uint32_t total = 0;
@@ -87,15 +87,13 @@ int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_
         DASH_HIP(hipGetLastError());
         return DASH_OK;
     }
-    const bool banked = (uint64_t)(units / L.n) >= c->digits_banked_min_lanes;
-    if (banked) L.key = c->fixed_rot;
-    const uint64_t blocks = banked ? (tiles * reps + 3) / 4 : tiles * reps, cap = banked ? 512 : 2560;      // (banked: two per CU, one round)
-    const dim3 grid((uint32_t)(blocks < cap ? blocks : cap));
-    const dim3 block(banked ? kBigThreads : kThreads);
+    // The bank-replicated tables for every launch that is not one of few rows: two blocks per CU, one round.  (With one copy of the tables from 2^20
+    // rows up to 2^20 lanes: LeNet of one image 1 770 us instead of 1 500 garbling, of four 4 940 and 4 600.)
+    L.key = c->fixed_rot;
+    const uint64_t blocks = (tiles * reps + 3) / 4;
     with_digit_set(typed, [&](auto ds) {
         typedef decltype(ds) DS;
-        if (banked) hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1, true>), grid, block, 0, s, L);
-        else hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1, false>), grid, block, 0, s, L);
+        hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1>), dim3((uint32_t)(blocks < 512 ? blocks : 512)), dim3(kBigThreads), 0, s, L);
     });
     DASH_HIP(hipGetLastError());
     return DASH_OK;

@@ -74,7 +74,6 @@ struct dash_ctx {
     uint64_t quad_max_lanes;         // evaluator: carry chains of at most this many lanes (4 per element) run four lanes per element
     uint64_t few_rows_max;           // garbler: launches of at most this many rows take the forms for few rows (a lane per row of the
                                      // digit gates; gates of different output moduli in one launch)
-    uint64_t digits_banked_min_lanes;   // the banked-table threshold of the fused garbling kernel (n hashes per lane)
     const uint8_t* phi_pm1[DASH_MAX_PRIMES];                         // {1, p-1}
     int linear_form;                 // form of the linear layers: 0 by layer shape, else a LinearForm (dash_linear_rule.h; tuning and test hook)
     int gemm_tile;                   // tile shape of the MFMA contraction: 0 by layer shape, 1 big, 2 wide (tuning and test hook)
