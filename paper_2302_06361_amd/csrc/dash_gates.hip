@@ -126,123 +126,141 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 }
 
 // ------------------------------------------------------------------------------- packed table rows
-// Working format [pitch_q bytes, one digit each] <-> 16-byte integer sum_j row[j] q^j.  What the kernel has to do is move bytes
-// (36 per 20-byte row), so a wave brings its 64 rows through LDS: the rows are contiguous in memory and every access to them is a
-// dword per lane, consecutive lanes consecutive dwords, whatever the pitch; the packed side is 16 bytes per lane.  It does so at 2.5 TB/s: one
-// tile in flight per wave (2.4 waves per SIMD on average, waiting in 57 % of their cycles), and 3 530 scalar instructions a wave, mostly the walk to
-// its segment.  Rows of bits (q = 2)
-// need no LDS: 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.  The segments of a
-// layer differ in length by a factor of 50, so the waves share the concatenation of their tiles, a contiguous range each.
-// (One lane per row, run-time constants and the same number of blocks for every segment took 6.0 ms for the 5.1 GB of tables of a
-// LeNet batch of 4; this form takes 3.3.)
-// Unpacking is held to 128 registers, four waves per SIMD: left to itself the compiler takes 136 for the base conversions of all moduli.
+// Working format [pitch_q bytes, one digit each] <-> 16-byte integer sum_j row[j] q^j.  What the kernel has to do is move bytes (36 per 20-byte
+// row).  The segments of a layer differ in length by a factor of 50, so the waves share the concatenation of their tiles of 64 rows, four at a
+// time, neighbouring waves neighbouring tiles (a contiguous range for each wave was 16 384 streams through 8 GB: 2.7 ms instead of 2.3 below).
+// Packing: a lane reads its own row and has those of up to four tiles in flight.  (Rows through LDS, a dword per lane, one tile at a time and the
+// segment looked for at every tile: 2.5 TB/s, 3.4 ms for the 5.1 GB of tables of a LeNet batch of 4; this way 2.3 ms, 3.7 TB/s.)
+// Unpacking: a wave brings its 64 rows through LDS, so that every access to them is a dword per lane, consecutive lanes consecutive dwords,
+// whatever the pitch; the 16-byte rows of two tiles are read at a time (one, two: 4.22, 3.88 ms with the evaluation behind it).  It is held to
+// 128 registers, four waves per SIMD: left to itself the compiler takes 136 for the base conversions of all moduli.
+// Rows of bits (q = 2): 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.
 template <bool Pack>
-__global__ __launch_bounds__(kThreads, Pack ? 1 : 4) void k_rows_repack(const PackLaunch L) {
+__global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_at4 __attribute__((aligned(4)));              // of table rows: tables, and with rows of 20 bytes their segments, are 4-byte aligned
+    constexpr uint32_t kRun = 4;                                      // tiles that a wave takes at a time
     constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
-    __shared__ uint32_t stage[kThreads / 64][64 * kMaxDw];
+    __shared__ uint32_t stage[Pack ? 1 : kThreads / 64][Pack ? 1 : 64 * kMaxDw];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    uint32_t* st = stage[wave];
+    uint32_t* st = stage[Pack ? 0 : wave];
     auto rows_of = [&](uint32_t i) { return (uint64_t)L.n_elem * L.seg[i].rows_per_gate; };
     // one-digit rows: 1024 bytes of the packed segment per tile (padded with zeros to a multiple of 16 bytes)
     auto tiles_of = [&](uint32_t i) { return L.seg[i].q ? (rows_of(i) + 63) / 64 : (rows_of(i) + 1023) / 1024; };
-    uint64_t total = 0;
-    for (uint32_t i = 0; i < L.nseg; i++) total += tiles_of(i);
-    const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64), per = (total + waves - 1) / waves;
-    uint64_t t = ((uint64_t)blockIdx.x * (kThreads / 64) + wave) * per;
-    const uint64_t t_end = t + per < total ? t + per : total;
-    if (t >= t_end) return;
+    auto runs_of = [&](uint32_t i) { return (tiles_of(i) + kRun - 1) / kRun; };
+    const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64);
     uint32_t seg = 0;
-    uint64_t base = 0, next = tiles_of(0);
-    for (; t < t_end; t++) {
-        while (t >= next) { seg++; base = next; next += tiles_of(seg); }
+    uint64_t base = 0, next = runs_of(0);
+    for (uint64_t run = (uint64_t)blockIdx.x * (kThreads / 64) + wave;; run += waves) {
+        while (run >= next) {
+            if (++seg == L.nseg) return;
+            base = next;
+            next += runs_of(seg);
+        }
         const PackSeg& S = L.seg[seg];
-        const uint64_t rows = rows_of(seg);
+        const uint64_t rows = rows_of(seg), first = (run - base) * kRun, last = tiles_of(seg), stop = first + kRun < last ? first + kRun : last;
         if (S.q == 0) {
-            const uint64_t r0 = (t - base) * 1024 + lane * 16, padded = (rows + 15) & ~(uint64_t)15;
-            for (int k = 0; k < 16 && r0 + k < padded; k++) {
-                const uint64_t r = r0 + k;
-                if (Pack) S.packed[r] = r < rows ? S.rows[r * 4] : 0;
-                else if (r < rows) *(uint32_t*)(const_cast<uint8_t*>(S.rows) + r * 4) = S.packed[r];
+            for (uint64_t tile = first; tile < stop; tile++) {
+                const uint64_t r0 = tile * 1024 + lane * 16, padded = (rows + 15) & ~(uint64_t)15;
+                for (int k = 0; k < 16 && r0 + k < padded; k++) {
+                    const uint64_t r = r0 + k;
+                    if (Pack) S.packed[r] = r < rows ? S.rows[r * 4] : 0;
+                    else if (r < rows) *(uint32_t*)(const_cast<uint8_t*>(S.rows) + r * 4) = S.packed[r];
+                }
             }
             continue;
         }
-        const uint64_t r0 = (t - base) * 64;
-        const uint32_t n = rows - r0 < 64 ? (uint32_t)(rows - r0) : 64u;
-        u32x4* packed = (u32x4*)(S.packed + (r0 + lane) * 16);
         with_mod(ld_mod(L.mods, S.q), [&](auto M) {
             typedef decltype(M) MD;
             if constexpr (cmod_m<MD>::value == 2) {
-                uint16_t* bits = (uint16_t*)(S.packed + r0 * 16);
-                u32x4_at4* digits = (u32x4_at4*)(const_cast<uint8_t*>(S.rows) + r0 * 128);
-                uint32_t v16[8];
-                u32x4 v[8];
+                for (uint64_t tile = first; tile < stop; tile++) {
+                    const uint64_t r0 = tile * 64;
+                    const uint32_t n = rows - r0 < 64 ? (uint32_t)(rows - r0) : 64u;
+                    uint16_t* bits = (uint16_t*)(S.packed + r0 * 16);
+                    u32x4_at4* digits = (u32x4_at4*)(const_cast<uint8_t*>(S.rows) + r0 * 128);
+                    uint32_t v16[8];
+                    u32x4 v[8];
 #pragma unroll
-                for (uint32_t i = 0; i < 8; i++) {                       // piece i * 64 + lane: row / 8, 16 digits of it
-                    const uint32_t d = i * 64 + lane < n * 8 ? i * 64 + lane : 0;
-                    if (Pack) v[i] = digits[d];
-                    else v16[i] = bits[d];
-                }
+                    for (uint32_t i = 0; i < 8; i++) {                   // piece i * 64 + lane: row / 8, 16 digits of it
+                        const uint32_t d = i * 64 + lane < n * 8 ? i * 64 + lane : 0;
+                        if (Pack) v[i] = digits[d];
+                        else v16[i] = bits[d];
+                    }
 #pragma unroll
-                for (uint32_t i = 0; i < 8; i++) {
-                    if (i * 64 + lane >= n * 8) continue;
-                    if (Pack) {
-                        uint32_t w = 0;
+                    for (uint32_t i = 0; i < 8; i++) {
+                        if (i * 64 + lane >= n * 8) continue;
+                        if (Pack) {
+                            uint32_t w = 0;
 #pragma unroll
-                        for (int q = 0; q < 4; q++) w |= dot4(v[i][q], 0x08040201u) << (4 * q);
-                        bits[i * 64 + lane] = (uint16_t)w;
-                    } else {
-                        u32x4 w;
+                            for (int q = 0; q < 4; q++) w |= dot4(v[i][q], 0x08040201u) << (4 * q);
+                            bits[i * 64 + lane] = (uint16_t)w;
+                        } else {
+                            u32x4 w;
 #pragma unroll
-                        for (int q = 0; q < 4; q++) w[q] = mul24((v16[i] >> (4 * q)) & 0xfu, 0x00204081u) & kOnes;
-                        digits[i * 64 + lane] = w;
+                            for (int q = 0; q < 4; q++) w[q] = mul24((v16[i] >> (4 * q)) & 0xfu, 0x00204081u) & kOnes;
+                            digits[i * 64 + lane] = w;
+                        }
                     }
                 }
             } else if constexpr (cmod_m<MD>::value != 0) {
                 constexpr uint32_t ndw = MD::ndw, stride = ndw | 1;      // (odd: a lane's own row without bank conflicts)
                 static_assert(stride <= kMaxDw, "stage");
-                uint32_t* rowbase = (uint32_t*)(const_cast<uint8_t*>(S.rows) + r0 * (ndw * 4));
-                if (Pack) {
-                    uint32_t v[ndw];                                     // all loads before the first wait
+                constexpr uint32_t U = !Pack ? 2 : ndw <= 5 ? 4 : ndw <= 10 ? 2 : 1;      // tiles in flight
+                for (uint64_t tile = first; tile < stop; tile += U) {
+                    const uint64_t r0 = tile * 64, left = (stop * 64 < rows ? stop * 64 : rows) - r0;
+                    const uint32_t n = left < U * 64 ? (uint32_t)left : U * 64;      // rows; lanes past them read the last one and store nothing
+                    uint8_t* const rowbase = const_cast<uint8_t*>(S.rows) + r0 * (ndw * 4);
+                    uint8_t* const packed = S.packed + r0 * 16;
+                    if constexpr (Pack) {
+                        uint32_t v[U][ndw];
 #pragma unroll
-                    for (uint32_t i = 0; i < ndw; i++) v[i] = rowbase[i * 64 + lane < n * ndw ? i * 64 + lane : 0];
+                        for (uint32_t u = 0; u < U; u++) ld_dwords<(int)ndw>(rowbase, (u * 64 + lane < n ? u * 64 + lane : n - 1) * (ndw * 4), v[u]);
+                        schedule_fence();
 #pragma unroll
-                    for (uint32_t i = 0; i < ndw; i++) {
-                        const uint32_t d = i * 64 + lane;
-                        st[(d / ndw) * stride + d % ndw] = v[i];
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < n) {
-                        uint32_t colour;
-                        const U128 x = compress(M, [&](int i) { return st[lane * stride + i]; }, &colour);
-                        *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
-                    }
-                } else {
-                    if (lane < n) {
-                        const u32x4 v = *packed;
-                        decompress(M, U128{{v.x, v.y, v.z, v.w}}, [&](int i, uint32_t w) { st[lane * stride + i] = w; });
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
+                        for (uint32_t u = 0; u < U; u++) {
+                            uint32_t colour;
+                            const U128 x = compress(M, [&](int i) { return v[u][i]; }, &colour);
+                            if (u * 64 + lane < n) *(u32x4*)(packed + (u * 64 + lane) * 16) = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
+                        }
+                    } else {
+                        u32x4 v[U];
 #pragma unroll
-                    for (uint32_t i = 0; i < ndw; i++) {
-                        const uint32_t d = i * 64 + lane;
-                        if (d < n * ndw) rowbase[d] = st[(d / ndw) * stride + d % ndw];
+                        for (uint32_t u = 0; u < U; u++) v[u] = *(const u32x4*)(packed + (u * 64 + lane < n ? u * 64 + lane : n - 1) * 16);
+                        schedule_fence();
+#pragma unroll 1
+                        for (uint32_t u = 0; u * 64 < n; u++) {
+                            decompress(M, U128{{v[0].x, v[0].y, v[0].z, v[0].w}}, [&](int i, uint32_t w) { st[lane * stride + i] = w; });
+#pragma unroll
+                            for (uint32_t k = 0; k + 1 < U; k++) v[k] = v[k + 1];
+                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                            DASH_WAVE_POINT();
+                            const uint32_t m = n - u * 64 < 64 ? n - u * 64 : 64u;
+#pragma unroll
+                            for (uint32_t i = 0; i < ndw; i++) {
+                                const uint32_t d = i * 64 + lane;
+                                if (d < m * ndw) *(uint32_t*)(rowbase + (u * (64 * ndw) + d) * 4) = st[(d / ndw) * stride + d % ndw];
+                            }
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                            DASH_WAVE_POINT();
+                        }
                     }
                 }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            } else if (lane < n) {                                       // any other modulus or length: run-time constants, a row per lane
-                uint32_t* row = (uint32_t*)(const_cast<uint8_t*>(S.rows) + (r0 + lane) * (M.ndw * 4));
-                if (Pack) {
-                    uint32_t colour;
-                    const U128 x = compress(M, [&](int i) { return row[i]; }, &colour);
-                    *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
-                } else {
-                    const u32x4 v = *packed;
-                    decompress(M, U128{{v.x, v.y, v.z, v.w}}, [&](int i, uint32_t w) { row[i] = w; });
+            } else {                                                     // any other modulus or length: run-time constants, a row per lane
+                for (uint64_t tile = first; tile < stop; tile++) {
+                    const uint64_t r = tile * 64 + lane;
+                    if (r >= rows) continue;
+                    uint32_t* row = (uint32_t*)(const_cast<uint8_t*>(S.rows) + r * (M.ndw * 4));
+                    u32x4* packed = (u32x4*)(S.packed + r * 16);
+                    if (Pack) {
+                        uint32_t colour;
+                        const U128 x = compress(M, [&](int i) { return row[i]; }, &colour);
+                        *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
+                    } else {
+                        const u32x4 v = *packed;
+                        decompress(M, U128{{v.x, v.y, v.z, v.w}}, [&](int i, uint32_t w) { row[i] = w; });
+                    }
                 }
             }
         });
@@ -257,7 +275,7 @@ int DASH_FN(launch_pack)(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_
     uint64_t tiles = 0;
     for (uint32_t i = 0; i < L.nseg; i++) tiles += ((uint64_t)L.n_elem * L.seg[i].rows_per_gate + 63) / 64;
     const uint64_t blocks = (tiles + kThreads / 64 - 1) / (kThreads / 64);
-    dim3 grid((uint32_t)(blocks < 4096 ? blocks : 4096));              // seven blocks per CU fit at a time (LDS)
+    dim3 grid((uint32_t)(blocks < 4096 ? blocks : 4096));              // (four blocks per CU fit at a time)
     if (pack) hipLaunchKernelGGL(k_rows_repack<true>, grid, dim3(kThreads), 0, s, L);
     else hipLaunchKernelGGL(k_rows_repack<false>, grid, dim3(kThreads), 0, s, L);
     DASH_HIP(hipGetLastError());

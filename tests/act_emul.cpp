@@ -30,15 +30,21 @@ const simt::dynamic_lds announce(acc, sizeof(acc));
 #elif defined(PART_GATES)
 
 #include "../paper_2302_06361_amd/csrc/dash_tabs.h"
-// (the garbling kernels are not launched here: one instantiation instead of twenty)
+// (the garbling kernels are not launched here: four instantiations instead of twenty, for the repacking of rows of bits and of one, two and
+// four tiles at a time; the other moduli take its form for any modulus)
 #undef DASH_HOT_MODS
-#define DASH_HOT_MODS(X) X(2, 128)
+#if defined(DASH_RULE_FLOOR)
+#define DASH_HOT_MODS(X) X(2, 128) X(3, 80) X(26, 27) X(96, 19)
+#else
+#define DASH_HOT_MODS(X) X(2, 128) X(3, 81) X(26, 28) X(96, 20)
+#endif
 #include "../paper_2302_06361_amd/csrc/dash_gates.hip"
 namespace dash { inline namespace DASH_RULE_NS {
 #define ABSENT(ret, name, ...) ret DASH_FN(name)(__VA_ARGS__) { fprintf(stderr, "act_emul: " #name " is not part of this program\n"); abort(); }
 ABSENT(int, launch_eval, const dash_ctx*, GateLaunch&, int, hipStream_t)
 ABSENT(int, launch_eval_many, const dash_ctx*, EvalManyLaunch&, int, hipStream_t)
 ABSENT(int, launch_chain_garble, const dash_ctx*, GateLaunch&, int, hipStream_t, bool*)
+ABSENT(int, launch_bit_garble, const dash_ctx*, GateLaunch&, int, hipStream_t, bool*)
 ABSENT(int, launch_chain_eval, const dash_ctx*, ChainLaunch&, hipStream_t)
 ABSENT(int, launch_digits_eval, const dash_ctx*, DigitsLaunch&, hipStream_t)
 ABSENT(int, launch_digits_garble, const dash_ctx*, DigitsLaunch&, hipStream_t)
