@@ -240,6 +240,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
 #pragma unroll
                 for (int i = 0; i < kIn; i++) if (i < (int)MC::ndw || j == 1) { sm[i] = a[i * 2 * kS]; DASH_WAVE_POINT(); a[i * 2 * kS] = 0; }
             };
+            wave_priority<3>();
             fetch(n);
 #pragma unroll 1
             for (int j = n; j >= 1; j--) {
@@ -284,6 +285,7 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
                     kb[cc][cel] = bit;
                 }
             }
+            wave_priority<0>();
         }
         __syncthreads();
     }

@@ -129,6 +129,11 @@ template <> struct gate_tab<true> {
     static __device__ __forceinline__ type load(uint32_t* lds, const uint32_t* g) { return load_banktab(lds, g); }
 };
 
+template <int P> __device__ __forceinline__ void wave_priority() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_setprio(P);
+#endif
+}
 // A SIMD issues from the oldest of its waves that can, so waves with equal shares of a launch finish one after the other: of the eight waves
 // on a SIMD the first was through with its share of the carry gates at 0.38 of the launch, the next ones at 0.41, 0.50, 0.60 .. 1.0, and the ones
 // that were left had ever fewer others to hide their LDS look-ups behind.  Pace gives waves that are ahead a lower priority: 3 down to a
