@@ -477,8 +477,24 @@ DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t
     uint32_t a = (c & 2u ? s23 : s01) ^ Q.k[0];
 #pragma unroll
     for (int r = 1; r < 10; r++) {
-        const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
-        a = aes_column(a, a1, a2, a3, Q.k[r], T);
+        // A lane looks up the bytes of its own column, and the entries, not the columns, go to their neighbours: as the operand of the
+        // exclusive-or that takes them (keep: or the compiler makes three-input operations of them, which have no such operand).  With the columns
+        // exchanged before the look-ups every round had three moves and their wait states more.
+        auto keep = [](uint32_t v) { asm("" : "+v"(v)); return v; };
+        if constexpr (tab_two<Tab>::value) {
+            const uint32_t k = tab_rot<Tab>::value ? Q.k[r] : rot16(Q.k[r]);
+            const uint32_t t0 = T.template at<0, 0>(a), t1 = T.template at<1, 1>(a), t2 = T.template at<0, 2>(a), t3 = T.template at<1, 3>(a);
+            uint32_t w = keep(up2(t2) ^ k);
+            w = keep(up3(t3) ^ w);
+            const uint32_t v = keep(up1(t1) ^ t0);
+            a = v ^ rot16(w);
+        } else {
+            const uint32_t t0 = T.template at<0, 0>(a), t1 = T.template at<1, 1>(a), t2 = T.template at<2, 2>(a), t3 = T.template at<3, 3>(a);
+            a = keep(t0 ^ Q.k[r]);
+            a = keep(up1(t1) ^ a);
+            a = keep(up2(t2) ^ a);
+            a = up3(t3) ^ a;
+        }
     }
     {
         const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
