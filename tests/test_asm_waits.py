@@ -89,3 +89,13 @@ def test_the_run_time_garbler_keeps_its_scalars(tmp_path):
     kernels = dict(re.findall(r"^(_Z\S*k_proj_garble\S*):(.*?)s_endpgm", out.read_text(), re.S | re.M))
     bodies = [v for k, v in kernels.items() if "7ModInfoELb1E" in k]
     assert len(bodies) == 1 and bodies[0].count("v_readlane_b32") < 200
+
+
+def test_deep_evaluator_has_no_static_lds(tmp_path):
+    """the table of the evaluator's deep form is read at LDS address 0: its kernels have dynamic LDS only"""
+    out = str(tmp_path / "act.s")
+    subprocess.run([HIPCC] + build.FLAGS + ["-DDASH_SET=7", "--cuda-device-only", "-S", os.path.join(build.CSRC, "dash_act_eval.hip"), "-o", out], check=True,
+                   stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    kernels = re.findall(r"\.amdhsa_kernel (\S+)\s+\.amdhsa_group_segment_fixed_size (\d+)", open(out).read())
+    deep = {name: int(size) for name, size in kernels if re.search(r"k_act_evalILb[01]ELi64ELi1E", name)}
+    assert len(deep) == 2 and not any(deep.values()), kernels
