@@ -23,6 +23,8 @@
 // of 168, 9 216 (one block per CU) 36 instead of 45.
 // For digit sets with compile-time moduli over the first NP primes; anything else takes the launches of dash_layers.hip one by one.
 // Compiled once per digit set (DASH_SET = number of primes) and label-length rule.
+#include <algorithm>
+
 #include "dash_tabs.h"
 
 #ifndef DASH_SET
@@ -48,10 +50,6 @@ constexpr uint32_t kPrimeMax = kNP == 7 ? 17 : kNP == 8 ? 19 : kNP == 9 ? 23 : 3
 // half of the rows behind the table that these leave free.
 constexpr uint32_t kSpanSums = 64, kCut = M1::ndw + (75 - M1::ndw) / MC::ndw * MC::ndw;
 static_assert(kSpanSums + M1::ndw + (kMaxChain - 1) * MC::ndw - kCut <= 78, "two deep blocks fit a CU");
-// rows of 1 KB that the table and so many dwords of sums take; the mod-2 wire has the row behind them
-__host__ __device__ inline uint32_t deep_rows(uint32_t sums) {
-    return sums <= kSpanSums ? kSpanSums : sums <= kCut ? sums : kSpanSums + sums - kCut > kCut ? kSpanSums + sums - kCut : kCut;
-}
 constexpr int kMaxX = 24;                           // dwords of the longest label of an odd prime (81 digits in six chunks)
 
 // f(description) for the primes of the base; bit labels (p = 2) only where the caller asks for them
@@ -95,15 +93,12 @@ __global__ __launch_bounds__(64 * (RELU ? kNP : kNP - 1), EPB == 64 ? (kNP == 12
     auto view = [](const __attribute__((address_space(4))) LView& v) __attribute__((always_inline)) { return LView{v.p, v.cs, v.es}; };
     __shared__ uint32_t tt[Deep ? 1 : kTabWords];
     __shared__ __attribute__((aligned(16))) uint32_t bt_static[Deep ? 4 : kBankTabWords];
-    __shared__ uint32_t kb_static[4][Deep ? 1 : EPB];
+    __shared__ uint32_t kb[4][EPB];                 // the mod-2 wire of the repetition (scaling) or the sign bit (ReLU): 128 bits per value
+    static_assert(!Deep || sizeof(kb) == HalfTab::base, "the static LDS in front of the table");
     // Dynamic LDS.  Deep form: the table's span (dynamic, so that the compiler, which takes 64 KB of it for a limit of the blocks per CU,
     // keeps to 128 registers: two blocks, 36 instead of 64 us for a repetition of 25 088 values of the 7-prime base); else the digit sums.
-    // The deep form has no static LDS, so that its table lies at address 0 and a look-up's address is what the byte permute gives (HalfTab): with 1 KB
-    // in front of it every one of the 160 addresses of a hash took an addition more.
     extern __shared__ __attribute__((aligned(16))) uint32_t acc[];
     uint32_t* const bt = Deep ? acc : bt_static;
-    // the mod-2 wire of the repetition (scaling) or the sign bit (ReLU): 128 bits per value
-    uint32_t (*const kb)[EPB] = Deep ? (uint32_t (*)[EPB])(acc + deep_rows(M1::ndw + (L.n - 1) * MC::ndw) * (4 * EPB)) : (uint32_t (*)[EPB])kb_static;
     // sums over the residues, two digits per word: word (digit dword i, even or odd digits h, value v) at sum0[at_dword(i) + h * kS + at(v)].
     // Deep form: in the half of the table's span that HalfTab leaves free, and behind the span (a 16-digit set needs 77 KB this way, two blocks
     // per CU; 87 KB in rows as beside the table: 75 264 values of 8 primes 409 us a repetition in 87, 276 in 77).
@@ -395,7 +390,8 @@ int DASH_FN(DASH_PASTE(launch_act_eval_, DASH_SET))(const dash_ctx* c, ActLaunch
     const uint32_t epb = form == ACT_DEEP ? 64 : form == ACT_SHALLOW ? kShallow : kTiny;
     const dim3 grid((L.n_elem + epb - 1) / epb), block(64 * (relu ? kNP : kNP - 1));
     static_assert(HalfTab::words == kSpanSums * 4 * 64, "rows of the deep form");
-    const size_t lds = form == ACT_DEEP ? (size_t)(deep_rows(sums) + 1) * 1024 : (size_t)sums * 2 * epb * 4;
+    const uint32_t rows = sums <= kSpanSums ? kSpanSums : sums <= kCut ? sums : std::max(kCut, kSpanSums + sums - kCut);
+    const size_t lds = form == ACT_DEEP ? (size_t)rows * 4 * epb * 4 : (size_t)sums * 2 * epb * 4;
     if (relu) {
         if (form == ACT_DEEP) hipLaunchKernelGGL((k_act_eval<true, 64, 1>), grid, block, lds, s, L);
         else if (form == ACT_SHALLOW) hipLaunchKernelGGL((k_act_eval<true, kShallow, 1>), grid, block, lds, s, L);

@@ -85,10 +85,12 @@ __device__ __forceinline__ BankTab load_banktab(uint32_t* lds, const uint32_t* g
 // HalfTab: 16 copies of T0 and T1 in the first 128 bytes of every 256, which leaves the other 128 of each entry (32 KB) to the kernel:
 // byte address of entry x of table R  x * 256 + R * 64 + 4 * copy.  One instruction per address and one rotation per column as with
 // BankTab; the lanes l and l + 16 share a copy, so a look-up takes four LDS cycles instead of two.  For kernels that need LDS of their own
-// and have LDS cycles to spare.  The table lies at LDS address 0 (dynamic LDS of a kernel without static LDS; test_asm_waits.py looks at that): the
-// address of dynamic LDS is filled in so late that an addition of it, of 0, stays in front of every look-up.
+// and have LDS cycles to spare.  The table is the start of the dynamic LDS of a kernel with `base` bytes of static LDS (test_asm_waits.py looks at
+// that), which go into the instruction's offset: the address of dynamic LDS is filled in so late that the compiler's own addition of it
+// stays in front of every look-up.
 struct HalfTab {
     static constexpr bool two_tables = true, rotated_keys = true;
+    static constexpr uint32_t base = 1024;
     static constexpr int words = 16384, hole = 32;     // the kernel's words: hole + 64 i + (0..31)
     const uint8_t* t;
     uint32_t lane;       // byte 0: 4 * copy
@@ -97,7 +99,7 @@ struct HalfTab {
         constexpr uint32_t sel = 0x0c0c0000u | ((4u + B) << 8);
         const uint32_t a = B == 1 ? in_place(w, lane) : __builtin_amdgcn_perm(w, lane, sel);
 #if defined(__HIP_DEVICE_COMPILE__)
-        return *(const __attribute__((address_space(3))) uint32_t*)(a + R * 64);
+        return *(const __attribute__((address_space(3))) uint32_t*)(a + (base + R * 64));
 #else
         return *(const uint32_t*)(t + a + R * 64);
 #endif

@@ -91,11 +91,12 @@ def test_the_run_time_garbler_keeps_its_scalars(tmp_path):
     assert len(bodies) == 1 and bodies[0].count("v_readlane_b32") < 200
 
 
-def test_deep_evaluator_has_no_static_lds(tmp_path):
-    """the table of the evaluator's deep form is read at LDS address 0: its kernels have dynamic LDS only"""
+def test_static_lds_of_the_deep_evaluator(tmp_path):
+    """the table of the evaluator's deep form is read behind HalfTab::base bytes of static LDS: its kernels have as many"""
     out = str(tmp_path / "act.s")
     subprocess.run([HIPCC] + build.FLAGS + ["-DDASH_SET=7", "--cuda-device-only", "-S", os.path.join(build.CSRC, "dash_act_eval.hip"), "-o", out], check=True,
                    stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     kernels = re.findall(r"\.amdhsa_kernel (\S+)\s+\.amdhsa_group_segment_fixed_size (\d+)", open(out).read())
     deep = {name: int(size) for name, size in kernels if re.search(r"k_act_evalILb[01]ELi64ELi1E", name)}
-    assert len(deep) == 2 and not any(deep.values()), kernels
+    base = int(re.search(r"static constexpr uint32_t base = (\d+);", open(os.path.join(build.CSRC, "dash_tabs.h")).read()).group(1))
+    assert len(deep) == 2 and set(deep.values()) == {base}, kernels
