@@ -48,15 +48,25 @@ int DASH_FN(launch_draw)(const dash_ctx* c, DrawLaunch& L, int njobs, hipStream_
     return DASH_OK;
 }
 
-// the same for the zero labels of a gadget's gates: blockIdx.y = label, blockIdx.z = repetition
+// the same for the zero labels of a gadget's gates (few: blockIdx.y = label, blockIdx.z = repetition)
 template <bool Banked>
-__global__ __launch_bounds__(gate_tab<Banked>::threads) void k_draw_many(const DrawManyLaunch L) {
+__global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_draw_many(const DrawManyLaunch L) {
     constexpr int kGateTiles = gate_tab<Banked>::threads / kThreads;
     __shared__ uint32_t tt[gate_tab<Banked>::words];
     const auto T = gate_tab<Banked>::load(tt, L.ttab);
     const uint32_t tiles = (L.n_elem + kThreads - 1) / kThreads;
     const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;
-    for (uint32_t tile = blockIdx.x * kGateTiles + sub; tile < tiles; tile += gridDim.x * kGateTiles) draw_many_body(L, tile, blockIdx.y, blockIdx.z, tx, T);
+    if constexpr (Banked) {      // one-dimensional grid over the tiles of all labels and repetitions: two blocks per CU, one round
+        const uint32_t njobs = L.njobs, total = tiles * njobs * rep_count(L.reps), first = sub * gridDim.x + blockIdx.x, step = gridDim.x * kGateTiles;
+        Pace pace(first, total, step);
+        for (uint32_t t = first; t < total; t += step) {
+            pace.tick();
+            const uint32_t unit = __builtin_amdgcn_readfirstlane(t / tiles), rep = __builtin_amdgcn_readfirstlane(unit / njobs);
+            draw_many_body(L, t - unit * tiles, unit - rep * njobs, rep, tx, T);
+        }
+    } else {
+        for (uint32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) draw_many_body(L, tile, blockIdx.y, blockIdx.z, tx, T);
+    }
 }
 
 int DASH_FN(launch_draw_many)(const dash_ctx* c, DrawManyLaunch& L, int njobs, hipStream_t s) {
@@ -67,7 +77,10 @@ int DASH_FN(launch_draw_many)(const dash_ctx* c, DrawManyLaunch& L, int njobs, h
     const uint32_t reps = rep_count(L.reps);
     const bool banked = (uint64_t)L.n_elem * njobs * reps >= c->banked_min_lanes;
     L.key = banked ? c->seed_rot : c->seed; L.ttab = c->d_ttab; L.mods = c->d_mods;
-    const dim3 grid(gate_grid_x_for((L.n_elem + kThreads - 1) / kThreads, njobs * (int)reps, banked), njobs, reps);
+    const uint64_t tiles = (L.n_elem + kThreads - 1) / kThreads, all = tiles * njobs * reps;
+    if (all > 0x7fffffffull) return DASH_ESIZE;
+    L.njobs = (uint32_t)njobs;
+    const dim3 grid = banked ? dim3((uint32_t)(all < 512 ? all : 512)) : dim3(grid_x_for(tiles, njobs * (int)reps), njobs, reps);
     if (banked) hipLaunchKernelGGL(k_draw_many<true>, grid, dim3(kBigThreads), 0, s, L);
     else hipLaunchKernelGGL(k_draw_many<false>, grid, dim3(kThreads), 0, s, L);
     DASH_HIP(hipGetLastError());

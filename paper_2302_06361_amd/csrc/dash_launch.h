@@ -113,6 +113,7 @@ struct DrawManyLaunch {
     const ModInfo* mods;
     uint64_t elem_base;
     uint32_t layer, n_elem;
+    uint32_t njobs, pad_;          // set by the launcher
     Reps reps;
     uint8_t* base;
     DrawManyJob jobs[kMaxDrawMany];
