@@ -254,6 +254,8 @@ int dash_ctx_create(dash_ctx** out, const uint16_t* primes, int k, int lambda_ru
     if (const char* e = getenv("DASH_FUSED_MIN_ELEMS_GARBLE")) c->fused_min_elems[0] = strtoull(e, nullptr, 10);
     if (const char* e = getenv("DASH_FUSED_MIN_ELEMS_EVAL")) c->fused_min_elems[1] = strtoull(e, nullptr, 10);
     if (const char* e = getenv("DASH_LINEAR_FORM")) c->linear_form = e[0] >= '1' && e[0] <= '8' ? e[0] - '0' : 0;         // tuning and test hook
+    c->pack_run_log2 = -1;
+    if (const char* e = getenv("DASH_PACK_RUN_LOG2")) c->pack_run_log2 = e[0] >= '0' && e[0] <= '9' ? e[0] - '0' : -1;    // tuning and test hook
     if (const char* e = getenv("DASH_GEMM_TILE")) c->gemm_tile = e[0] == 'w' ? 2 : e[0] == 'b' ? 1 : 0;      // "wide" / "big"
     c->prof = new (std::nothrow) ProfState();
     c->P = 1;

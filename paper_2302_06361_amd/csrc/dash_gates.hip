@@ -12,6 +12,7 @@
 // moduli that carry nearly all of the work (the CRT primes and the accumulation moduli of the
 // default digit sets, with the label lengths of the rule this file is compiled for) run through compile-time
 // descriptions; any other modulus or length takes the same code with run-time constants.
+#include "dash_pack_rule.h"
 #include "dash_tabs.h"
 
 namespace dash {
@@ -140,19 +141,21 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 
 // ------------------------------------------------------------------------------- packed table rows
 // Working format [pitch_q bytes, one digit each] <-> 16-byte integer sum_j row[j] q^j.  What the kernel has to do is move bytes (36 per 20-byte
-// row).  The segments of a layer differ in length by a factor of 50, so the waves share the concatenation of their tiles of 64 rows, four at a
-// time, neighbouring waves neighbouring tiles (a contiguous range for each wave was 16 384 streams through 8 GB: 2.7 ms instead of 2.3 below).
+// row).  The segments of a layer differ in length by a factor of 50, so the waves share the concatenation of their tiles of 64 rows, a run of up to
+// four at a time (dash_pack_rule.h), neighbouring waves neighbouring runs (a contiguous range for each wave was 16 384 streams through 8 GB: 2.7
+// ms instead of 2.3 below).
 // Packing: a lane reads its own row and has those of up to four tiles in flight.  (Rows through LDS, a dword per lane, one tile at a time and the
 // segment looked for at every tile: 2.5 TB/s, 3.4 ms for the 5.1 GB of tables of a LeNet batch of 4; this way 2.3 ms, 3.7 TB/s.)
 // Unpacking: a wave brings its 64 rows through LDS, so that every access to them is a dword per lane, consecutive lanes consecutive dwords,
 // whatever the pitch; the 16-byte rows of two tiles are read at a time (one, two: 4.22, 3.88 ms with the evaluation behind it).  It is held to
 // 128 registers, four waves per SIMD: left to itself the compiler takes 136 for the base conversions of all moduli.
+// Packing: 64 registers, eight waves per SIMD.
 // Rows of bits (q = 2): 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.
 template <bool Pack>
 __global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_at4 __attribute__((aligned(4)));              // of table rows: tables, and with rows of 20 bytes their segments, are 4-byte aligned
-    constexpr uint32_t kRun = 4;                                      // tiles that a wave takes at a time
+    const uint32_t lg = L.run_log2;                                   // a wave takes 2^lg tiles at a time
     constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
     __shared__ uint32_t stage[Pack ? 1 : kThreads / 64][Pack ? 1 : 64 * kMaxDw];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
@@ -160,18 +163,17 @@ __global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const Pa
     auto rows_of = [&](uint32_t i) { return (uint64_t)L.n_elem * L.seg[i].rows_per_gate; };
     // one-digit rows: 1024 bytes of the packed segment per tile (padded with zeros to a multiple of 16 bytes)
     auto tiles_of = [&](uint32_t i) { return L.seg[i].q ? (rows_of(i) + 63) / 64 : (rows_of(i) + 1023) / 1024; };
-    auto runs_of = [&](uint32_t i) { return (tiles_of(i) + kRun - 1) / kRun; };
+    auto runs_of = [&](uint32_t i) { return (tiles_of(i) + (1u << lg) - 1) >> lg; };
     const uint64_t waves = (uint64_t)gridDim.x * (kThreads / 64);
     uint32_t seg = 0;
     uint64_t base = 0, next = runs_of(0);
-    for (uint64_t run = (uint64_t)blockIdx.x * (kThreads / 64) + wave;; run += waves) {
+    for (uint64_t run = (uint64_t)blockIdx.x * (kThreads / 64) + wave; run < L.runs; run += waves) {
         while (run >= next) {
-            if (++seg == L.nseg) return;
             base = next;
-            next += runs_of(seg);
+            next += runs_of(++seg);
         }
         const PackSeg& S = L.seg[seg];
-        const uint64_t rows = rows_of(seg), first = (run - base) * kRun, last = tiles_of(seg), stop = first + kRun < last ? first + kRun : last;
+        const uint64_t rows = rows_of(seg), first = (run - base) << lg, last = tiles_of(seg), stop = first + (1u << lg) < last ? first + (1u << lg) : last;
         if (S.q == 0) {
             for (uint64_t tile = first; tile < stop; tile++) {
                 const uint64_t r0 = tile * 1024 + lane * 16, padded = (rows + 15) & ~(uint64_t)15;
@@ -285,10 +287,18 @@ int DASH_FN(launch_pack)(const dash_ctx* c, PackLaunch& L, bool pack, hipStream_
     if (L.nseg < 1 || L.nseg > (uint32_t)kMaxPackSegs) return DASH_EINVAL;
     if (L.n_elem == 0) return DASH_OK;
     L.mods = c->d_mods;
+    auto tiles_of = [&](uint32_t i) {
+        const uint64_t rows = (uint64_t)L.n_elem * L.seg[i].rows_per_gate;
+        return L.seg[i].q ? (rows + 63) / 64 : (rows + 1023) / 1024;
+    };
     uint64_t tiles = 0;
-    for (uint32_t i = 0; i < L.nseg; i++) tiles += ((uint64_t)L.n_elem * L.seg[i].rows_per_gate + 63) / 64;
-    const uint64_t blocks = (tiles + kThreads / 64 - 1) / (kThreads / 64);
-    dim3 grid((uint32_t)(blocks < 4096 ? blocks : 4096));              // (four blocks per CU fit at a time)
+    for (uint32_t i = 0; i < L.nseg; i++) tiles += tiles_of(i);
+    const PackShape shape = pack_shape(tiles, L.nseg, pack);
+    L.run_log2 = c->pack_run_log2 < 0 ? shape.run_log2 : (uint32_t)c->pack_run_log2;
+    L.runs = 0;
+    for (uint32_t i = 0; i < L.nseg; i++) L.runs += (tiles_of(i) + (1u << L.run_log2) - 1) >> L.run_log2;
+    const uint64_t blocks = (L.runs + kThreads / 64 - 1) / (kThreads / 64);
+    const dim3 grid((uint32_t)(blocks < shape.max_blocks ? blocks : shape.max_blocks));
     if (pack) hipLaunchKernelGGL(k_rows_repack<true>, grid, dim3(kThreads), 0, s, L);
     else hipLaunchKernelGGL(k_rows_repack<false>, grid, dim3(kThreads), 0, s, L);
     DASH_HIP(hipGetLastError());

@@ -76,6 +76,7 @@ struct dash_ctx {
                                      // digit gates; gates of different output moduli in one launch)
     const uint8_t* phi_pm1[DASH_MAX_PRIMES];                         // {1, p-1}
     int linear_form;                 // form of the linear layers: 0 by layer shape, else a LinearForm (dash_linear_rule.h; tuning and test hook)
+    int pack_run_log2;               // repacking of tables: a wave takes 2^this tiles at a time; -1 by their number (dash_pack_rule.h; tuning and test hook)
     int gemm_tile;                   // tile shape of the MFMA contraction: 0 by layer shape, 1 big, 2 wide (tuning and test hook)
 };
 

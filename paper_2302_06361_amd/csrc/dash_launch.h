@@ -225,6 +225,8 @@ constexpr int kMaxPackSegs = 96;
 struct PackLaunch {
     const ModInfo* mods;
     uint32_t n_elem, nseg;
+    uint64_t runs;                 // of 2^run_log2 tiles; set by the launcher
+    uint32_t run_log2, pad_;
     PackSeg seg[kMaxPackSegs];
 };
 

@@ -6,6 +6,7 @@
 #include "../paper_2302_06361_amd/csrc/dash_chain_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_hostconst.h"
 #include "../paper_2302_06361_amd/csrc/dash_linear_rule.h"
+#include "../paper_2302_06361_amd/csrc/dash_pack_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_proj_rule.h"
 
 using namespace dash;
@@ -121,6 +122,11 @@ uint32_t cc_chain_waves_all(uint64_t tiles, uint32_t units, uint32_t quantum, ui
 }
 int cc_proj_own(int q, uint64_t calls, uint64_t gates, int bits_only, int alone, uint64_t banked_min) {
     return proj_own_launches(ProjRun{(uint32_t)q, calls, gates, bits_only != 0, alone != 0}, banked_min);
+}
+uint32_t cc_pack_shape(uint64_t tiles, uint32_t nseg, int pack, uint32_t* max_blocks) {
+    const PackShape s = pack_shape(tiles, nseg, pack != 0);
+    *max_blocks = s.max_blocks;
+    return s.run_log2;
 }
 int cc_linear_form(int forced, int64_t npx, int64_t chunks, int nch, int out_c, int K, int in_c, int mfma) {
     return linear_form(forced, LinearShape{npx, chunks, nch, out_c, K, in_c, mfma != 0});

@@ -105,6 +105,17 @@ def test_tables_repacked_from_a_4_byte_address(emul, tmp_path, k, kind, n, repea
     assert (got[want.size:] == rt).all(), "unpacked tables"
 
 
+@pytest.mark.parametrize("run_log2,kind,n", [(0, "scale", 240), (1, "relu", 5), (2, "scale", 67), (2, "relu", 3), (3, "scale", 67), (3, "relu", 5)])
+def test_tables_repacked_in_runs_of_tiles(emul, tmp_path, run_log2, kind, n):
+    """waves that take 1, 2, 4 and 8 tiles of 64 rows at a time (by the number of tiles; here forced): segments that end within a run, within the tiles
+    that are read together and within a tile; 240 values: more runs than waves"""
+    got, orc, _, rt = run(emul, tmp_path, "pack", 8, 1, kind, n, env={"DASH_PACK_RUN_LOG2": str(run_log2)})
+    want = orc.tables_pack(kind, n, rt, 1)
+    assert got.size == want.size + rt.size
+    assert (got[:want.size] == want).all(), "packed bytes"
+    assert (got[want.size:] == rt).all(), "unpacked tables"
+
+
 def run_linear(emul, tmp_path, form, k, batch, in_h, in_w, in_c, out_c, kh, stride, pad, bias, garble=False, shift=0, seed=1):
     primes, digits = workloads.PRIMES[:k], workloads.DIGITS[k]
     orc = capi.Oracle(primes, digits, SEED, 0)

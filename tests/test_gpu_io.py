@@ -199,6 +199,27 @@ def test_tables_pack_unpack(k, kind, repeat, shift):
     print("%s, %d primes: %.1f KB per value unpacked, %.1f KB packed" % (kind, k, tb / n / 1e3, pb / n / 1e3))
 
 
+@pytest.mark.parametrize("k,kind,n", [(8, "scale", 500), (8, "relu", 1500), (8, "scale", 5001), (12, "relu", 400), (5, "scale", 2500), (8, "scale", 60000)])
+def test_tables_pack_unpack_by_number_of_tiles(k, kind, n):
+    """every way the tiles are dealt to waves: a wave takes two from 8 192 tiles on (18 a value here with 8 primes), four from 16 384, over different numbers of
+    blocks from 2^16 and 2^20; packed bytes against the oracle's packing of the same tables (up to 10 M rows), unpacking gives them back"""
+    from paper_2302_06361_amd import Labels, Layer, RELU, SCALE
+    ctx, orc = both(k, rule=1)
+    lay = Layer(dict(relu=RELU, scale=SCALE)[kind], 3, n, repeat=1)
+    oe, tb, sb = ctx.layer_sizes(lay)
+    z, o = Labels(ctx, n), Labels(ctx, n)
+    ctx.input_labels(9, z)
+    tables = torch.zeros(tb, dtype=torch.uint8, device=ctx.device)
+    ctx.garble_layer(lay, z, o, tables, torch.zeros(sb + 256, dtype=torch.uint8, device=ctx.device))
+    packed = torch.full((ctx.tables_packed_bytes(lay),), 0xEE, dtype=torch.uint8, device=ctx.device)
+    ctx.tables_pack(lay, tables, packed)
+    back = torch.full((tb,), 0xEE, dtype=torch.uint8, device=ctx.device)
+    ctx.tables_unpack(lay, packed, back)
+    assert torch.equal(back, tables)
+    if n < 10000:
+        assert (packed.cpu().numpy() == orc.tables_pack(kind, n, tables.cpu().numpy(), 1)).all()
+
+
 def test_tables_pack_needs_rows_below_128_bits():
     from paper_2302_06361_amd import Layer, RELU, DashError
     ctx, orc = both(8)                       # ceil rule: 3^81 > 2^128
