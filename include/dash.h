@@ -106,7 +106,7 @@ typedef struct {
  * primes[i], 1..128; the accumulation moduli of the sign gadget keep the rule).
  * Draws the offset label R_m of every modulus in use (colour digit forced to 1) and the
  * constant-one wire of every prime.  Allocates a few hundred KB of device memory.  Tuning variables of
- * the environment (DASH_BANKED_MIN_LANES, DASH_GARBLE_FEW_ROWS, DASH_FUSED_MIN_ELEMS_GARBLE,
+ * the environment (DASH_BANKED_MIN_LANES, DASH_DIGITS_BANKED_MIN_LANES, DASH_GARBLE_FEW_ROWS, DASH_FUSED_MIN_ELEMS_GARBLE,
  * DASH_FUSED_MIN_ELEMS_EVAL, DASH_WIDE_MAX_LANES, DASH_SUM_IN_LAUNCH, DASH_QUAD_MAX_LANES, DASH_GEMM_TILE, DASH_LINEAR_FORM,
  * DASH_PACK_RUN_LOG2, DASH_ACT_EVAL, DASH_ACT_SHALLOW_MIN_ELEMS, DASH_ACT_DEEP_MIN_ELEMS) are read here, once per context, and nowhere else.
  * Naming one of the four that belong to the evaluator's path by step (DASH_FUSED_MIN_ELEMS_EVAL, DASH_WIDE_MAX_LANES,

@@ -15,7 +15,7 @@ for _rule, _flags in (("", []), ("_floor", ["-DDASH_RULE_FLOOR"])):
     UNITS += [(s, _flags, s.replace(".hip", _rule + ".o")) for s in GATE_SOURCES]
     UNITS += [("dash_act_eval.hip", _flags + ["-DDASH_SET=%d" % k], "dash_act_eval_%d%s.o" % (k, _rule)) for k in (12, 9, 8, 7)]
 UNITS += [(s, [], s.replace(".hip", ".o")) for s in SOURCES]
-HEADERS = ["dash_chain_rule.h", "dash_core.h", "dash_launch.h", "dash_bodies.h", "dash_hostconst.h", "dash_internal.h", "dash_linear_rule.h", "dash_pack_rule.h", "dash_proj_rule.h", "dash_tabs.h", "dash_aes_sliced.h", "dash_sbox_circuit.h", os.path.join("..", "..", "include", "dash.h"),
+HEADERS = ["dash_chain_rule.h", "dash_core.h", "dash_launch.h", "dash_bodies.h", "dash_gadget_rule.h", "dash_hostconst.h", "dash_internal.h", "dash_linear_rule.h", "dash_pack_rule.h", "dash_proj_rule.h", "dash_tabs.h", "dash_aes_sliced.h", "dash_sbox_circuit.h", os.path.join("..", "..", "include", "dash.h"),
            os.path.join("..", "..", "include", "dash_profile.h")]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-Wno-pass-failed",
          # packed FP32 instructions are kept out of every code object of this library

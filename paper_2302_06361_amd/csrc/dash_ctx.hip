@@ -251,6 +251,8 @@ int dash_ctx_create(dash_ctx** out, const uint16_t* primes, int k, int lambda_ru
     if (const char* e = getenv("DASH_QUAD_MAX_LANES")) c->quad_max_lanes = strtoull(e, nullptr, 10);                 // tuning and test hook
     c->few_rows_max = 1u << 20;
     if (const char* e = getenv("DASH_GARBLE_FEW_ROWS")) c->few_rows_max = strtoull(e, nullptr, 10);                 // tuning and test hook
+    c->digits_by_rule = 1;
+    if (const char* e = getenv("DASH_DIGITS_BANKED_MIN_LANES")) { c->digits_by_rule = 0; c->digits_banked_min_lanes = strtoull(e, nullptr, 10); }    // tuning and test hook
     if (const char* e = getenv("DASH_FUSED_MIN_ELEMS_GARBLE")) c->fused_min_elems[0] = strtoull(e, nullptr, 10);
     if (const char* e = getenv("DASH_FUSED_MIN_ELEMS_EVAL")) c->fused_min_elems[1] = strtoull(e, nullptr, 10);
     if (const char* e = getenv("DASH_LINEAR_FORM")) c->linear_form = e[0] >= '1' && e[0] <= '8' ? e[0] - '0' : 0;         // tuning and test hook

@@ -6,6 +6,7 @@
 //   k_digits_garble_wide : the same rows, one per lane, for gadgets of few rows
 //
 // Jobs, table layouts and compile-time moduli as in dash_gates.hip.
+#include "dash_gadget_rule.h"
 #include "dash_tabs.h"
 
 namespace dash {
@@ -15,11 +16,11 @@ inline namespace DASH_RULE_NS {
 // One launch for the k n digit gates of a sign gadget: lane = (element, value a) of a residue, which forms and
 // compresses the label of a once for the n rows it garbles.  The residues differ in length (n_elem * p rows):
 // the blocks share the concatenation of their tiles (one-dimensional grid).
-template <class MC, class M1>
-__global__ __launch_bounds__(kBigThreads, 8) void k_digits_garble(const DigitsLaunch L) {
-    constexpr int kGateTiles = kBigThreads / kThreads;
-    __shared__ uint32_t tt[kBankTabWords];
-    const BankTab T = load_banktab(tt, L.ttab);
+template <class MC, class M1, bool Banked>
+__global__ __launch_bounds__(gate_tab<Banked>::threads, Banked ? 8 : 1) void k_digits_garble(const DigitsLaunch L) {
+    constexpr int kGateTiles = gate_tab<Banked>::threads / kThreads;
+    __shared__ uint32_t tt[gate_tab<Banked>::words];
+    const auto T = gate_tab<Banked>::load(tt, L.ttab);
     const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tx = threadIdx.x % kThreads;      // (the same in all lanes of a wave: scalar unit)
     auto tiles_of = [&](uint32_t i) { return (uint32_t)(((uint64_t)L.n_elem * L.res[i].p + kThreads - 1) / kThreads); };
     uint32_t total = 0;
@@ -31,9 +32,10 @@ __global__ __launch_bounds__(kBigThreads, 8) void k_digits_garble(const DigitsLa
     constexpr bool kDigits = cmod_m<MC>::value != 0;                   // (run-time moduli: paced by tiles)
     Pace pace(first, total, step, kDigits ? L.n : 1);
     for (uint32_t t = first; t < total; t += step) {
-        if constexpr (!kDigits) pace.tick();
+        if constexpr (Banked && !kDigits) pace.tick();
         while (t >= next) { if (++res == L.nres) { res = 0; rep++; } base = next; next += tiles_of(res); }
-        digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep, [&]() __attribute__((always_inline)) { pace.tick(); });
+        if constexpr (Banked) digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep, [&]() __attribute__((always_inline)) { pace.tick(); });
+        else digits_garble_body<MC, M1>(L, t - base, res, tx, T, 0, rep);
     }
 }
 
@@ -87,13 +89,17 @@ int DASH_FN(launch_digits_garble)(const dash_ctx* c, DigitsLaunch& L, hipStream_
         DASH_HIP(hipGetLastError());
         return DASH_OK;
     }
-    // The bank-replicated tables for every launch that is not one of few rows: two blocks per CU, one round.  (With one copy of the tables from 2^20
-    // rows up to 2^20 lanes: LeNet of one image 1 770 us instead of 1 500 garbling, of four 4 940 and 4 600.)
-    L.key = c->fixed_rot;
-    const uint64_t blocks = (tiles * reps + 3) / 4;
+    const bool banked = c->digits_by_rule ? digits_banked(typed != 0, uniform, c->k) : (uint64_t)(units / L.n) >= c->digits_banked_min_lanes;
+    if (banked) L.key = c->fixed_rot;
+    // Bank-replicated tables: two blocks per CU, one round, and a tile on every CU before a second one on any.  (Blocks for four tiles each, half of the
+    // CUs idle or with a second block that the others do not have: 850 values of 10 primes, 428 tiles, 185 us instead of 168; 7 000 of 6 primes, 1 077
+    // tiles, 220 and 202.)
+    const uint64_t all = tiles * reps;
+    const dim3 grid(banked ? (uint32_t)(all < 512 ? all : 512) : grid_x_for(all, 1)), block(banked ? kBigThreads : kThreads);
     with_digit_set(typed, [&](auto ds) {
         typedef decltype(ds) DS;
-        hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1>), dim3((uint32_t)(blocks < 512 ? blocks : 512)), dim3(kBigThreads), 0, s, L);
+        if (banked) hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1, true>), grid, block, 0, s, L);
+        else hipLaunchKernelGGL((k_digits_garble<typename DS::MC, typename DS::M1, false>), grid, block, 0, s, L);
     });
     DASH_HIP(hipGetLastError());
     return DASH_OK;

@@ -74,6 +74,8 @@ struct dash_ctx {
     uint64_t quad_max_lanes;         // evaluator: carry chains of at most this many lanes (4 per element) run four lanes per element
     uint64_t few_rows_max;           // garbler: launches of at most this many rows take the forms for few rows (a lane per row of the
                                      // digit gates; gates of different output moduli in one launch)
+    int digits_by_rule;              // garbler: tables of the fused digit-gate kernel by dash_gadget_rule.h (1), or bank-replicated from digits_banked_min_lanes on (0)
+    uint64_t digits_banked_min_lanes;
     const uint8_t* phi_pm1[DASH_MAX_PRIMES];                         // {1, p-1}
     int linear_form;                 // form of the linear layers: 0 by layer shape, else a LinearForm (dash_linear_rule.h; tuning and test hook)
     int pack_run_log2;               // repacking of tables: a wave takes 2^this tiles at a time; -1 by their number (dash_pack_rule.h; tuning and test hook)

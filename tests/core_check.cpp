@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "../paper_2302_06361_amd/csrc/dash_chain_rule.h"
+#include "../paper_2302_06361_amd/csrc/dash_gadget_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_hostconst.h"
 #include "../paper_2302_06361_amd/csrc/dash_linear_rule.h"
 #include "../paper_2302_06361_amd/csrc/dash_pack_rule.h"
@@ -123,6 +124,7 @@ uint32_t cc_chain_waves_all(uint64_t tiles, uint32_t units, uint32_t quantum, ui
 int cc_proj_own(int q, uint64_t calls, uint64_t gates, int bits_only, int alone, uint64_t banked_min) {
     return proj_own_launches(ProjRun{(uint32_t)q, calls, gates, bits_only != 0, alone != 0}, banked_min);
 }
+int cc_digits_banked(int typed, int uniform, int k) { return digits_banked(typed != 0, uniform != 0, k); }
 uint32_t cc_pack_shape(uint64_t tiles, uint32_t nseg, int pack, uint32_t* max_blocks) {
     const PackShape s = pack_shape(tiles, nseg, pack != 0);
     *max_blocks = s.max_blocks;

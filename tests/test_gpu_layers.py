@@ -110,6 +110,19 @@ def test_activation_bank_replicated_tables_forced(monkeypatch, k, rule):
     run_activation(k, "scale", X[:333], repeat=2, rule=rule, elem_base=77)
 
 
+@pytest.mark.parametrize("lanes", ["0", "1000000000000"])
+def test_garblers_digit_gates_with_either_layout_of_the_aes_tables(monkeypatch, lanes):
+    """the garbler's fused digit gates of many rows with bank-replicated AES tables and with one copy, run-time digit sets (different and equal
+    digits) and a compile-time one: ragged last tiles, fewer tiles than places and more, every byte against the oracle"""
+    monkeypatch.setenv("DASH_DIGITS_BANKED_MIN_LANES", lanes)
+    monkeypatch.setenv("DASH_GARBLE_FEW_ROWS", "0")
+    for k, n, default in ((2, 5, False), (5, 701, False), (6, 700, True), (8, 1801, False)):
+        P = int(np.prod(workloads.PRIMES[:k]))
+        X = np.random.default_rng(400 + k).integers(0, P, n)
+        run_activation(k, "relu", X[:400], elem_base=5, default_digits=default)
+        run_activation(k, "scale", X, repeat=1 + k % 2, elem_base=2 ** 32 + 1, default_digits=default)
+
+
 @pytest.mark.parametrize("wide,sums", [("0", "1"), ("1000000000000", "1"), ("1000000000000", "0")])
 def test_activation_both_forms_of_the_evaluators_digit_gates(monkeypatch, wide, sums):
     """The evaluator runs the digit gates of a sign gadget one lane per (element, residue, digit) for gadgets over few
