@@ -11,6 +11,7 @@
 #include <iterator>
 #include <vector>
 
+#include "dash_gadget_rule.h"
 #include "dash_internal.h"
 #include "dash_proj_rule.h"
 
@@ -287,25 +288,31 @@ int sign_core(const dash_ctx* c, bool garble, uint32_t E, uint32_t layer, uint64
                 for (const GateJob& J : *extra_gates) gb.add(J);
             } else {      // launches of their own: the gates on the mod-2 wire together; the rest mixed if they are few, else per output modulus
                 std::vector<GateJob> rest;
-                GateLaunch GL;
-                memset(&GL, 0, sizeof(GL));
-                GL.layer = layer;
-                if (reps) GL.reps = *reps;
-                int nj = 0;
-                auto bits = [&]() {
-                    bool done = false;
-                    const int st = nj ? launch_bit_garble(c, GL, nj, s, &done) : DASH_OK;
-                    if (st == DASH_OK && !done) rest.insert(rest.end(), GL.jobs, GL.jobs + nj);
-                    nj = 0;
-                    return st;
-                };
-                for (const GateJob& J : *extra_gates) {
-                    if (J.p != 2 || J.mode == PAY_MULR) { rest.push_back(J); continue; }
-                    GL.jobs[nj] = J;
-                    GL.jobs[nj].n_elem = E; GL.jobs[nj].elem_base = elem_base;
-                    if (++nj == kMaxJobs) if (const int st = bits()) return st;
+                std::vector<size_t> bits;
+                for (size_t i = 0; i < extra_gates->size(); i++)
+                    if ((*extra_gates)[i].p == 2 && (*extra_gates)[i].mode != PAY_MULR) bits.push_back(i);
+                std::vector<bool> done(extra_gates->size(), false);
+                if (bits_own_launch((uint32_t)bits.size(), (uint32_t)(extra_gates->size() - bits.size()), extra_rows, few_rows(c, extra_rows), kMaxJobs)) {
+                    GateLaunch GL;
+                    memset(&GL, 0, sizeof(GL));
+                    GL.layer = layer;
+                    if (reps) GL.reps = *reps;
+                    for (size_t i0 = 0; i0 < bits.size(); i0 += kMaxJobs) {
+                        const int nj = (int)std::min(bits.size() - i0, (size_t)kMaxJobs);
+                        for (int j = 0; j < nj; j++) {
+                            GL.jobs[j] = (*extra_gates)[bits[i0 + j]];
+                            GL.jobs[j].n_elem = E; GL.jobs[j].elem_base = elem_base;
+                        }
+                        bool launched = false;
+                        if (const int st = launch_bit_garble(c, GL, nj, s, &launched)) return st;
+                        for (int j = 0; j < nj; j++) done[bits[i0 + j]] = launched;
+                    }
                 }
-                if (const int st = bits()) return st;
+                for (size_t i = 0; i < extra_gates->size(); i++) if (!done[i]) rest.push_back((*extra_gates)[i]);
+                // in one launch the long gates begin first (ReLU, 6 000 values: primes 2, 3, 5, 41 and 43 272 us, 302 in the gates' order; 2 to 11
+                // 244 and 249; not those of 2 to 7, 8 500 values: 168 and 163)
+                if (few_rows(c, extra_rows) && rest.size() <= (size_t)kMaxJobs && *std::max_element(c->prime, c->prime + k) > 7)
+                    std::stable_partition(rest.begin(), rest.end(), [](const GateJob& J) { return J.p != 2; });
                 extra_rows = 0;
                 for (const GateJob& J : rest) extra_rows += nrep * E * J.p;
                 GateBatcher ge(c, true, E, layer, elem_base, s, few_rows(c, extra_rows));

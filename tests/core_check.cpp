@@ -125,6 +125,7 @@ int cc_proj_own(int q, uint64_t calls, uint64_t gates, int bits_only, int alone,
     return proj_own_launches(ProjRun{(uint32_t)q, calls, gates, bits_only != 0, alone != 0}, banked_min);
 }
 int cc_digits_banked(int typed, int uniform, int k) { return digits_banked(typed != 0, uniform != 0, k); }
+int cc_bits_own(uint32_t bits, uint32_t others, uint64_t rows, int few, uint32_t max_jobs) { return bits_own_launch(bits, others, rows, few != 0, max_jobs); }
 uint32_t cc_pack_shape(uint64_t tiles, uint32_t nseg, int pack, uint32_t* max_blocks) {
     const PackShape s = pack_shape(tiles, nseg, pack != 0);
     *max_blocks = s.max_blocks;
