@@ -80,6 +80,13 @@ DASH_HD uint32_t opaque(uint32_t v) {
 #endif
     return v;
 }
+// the same for a number of each lane's
+DASH_HD uint32_t opaque_lane(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(v));
+#endif
+    return v;
+}
 // keeps what stands before it from being moved behind what follows, and the other way round (loads ahead of a hash)
 DASH_HD void schedule_fence() {
 #if defined(__HIP_DEVICE_COMPILE__)

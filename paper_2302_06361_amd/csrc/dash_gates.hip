@@ -146,19 +146,21 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 // ms instead of 2.3 below).
 // Packing: a lane reads its own row and has those of up to four tiles in flight.  (Rows through LDS, a dword per lane, one tile at a time and the
 // segment looked for at every tile: 2.5 TB/s, 3.4 ms for the 5.1 GB of tables of a LeNet batch of 4; this way 2.3 ms, 3.7 TB/s.)
+// Packing: 64 registers, eight waves per SIMD.  A modulus without compile-time code reads its row in pieces of four dwords (dword by dword, with so many
+// waves beside each other: 4 primes, 160 000 values, 913 us; 387 this way).
 // Unpacking: a wave brings its 64 rows through LDS, so that every access to them is a dword per lane, consecutive lanes consecutive dwords,
-// whatever the pitch; the 16-byte rows of two tiles are read at a time (one, two: 4.22, 3.88 ms with the evaluation behind it).  It is held to
-// 128 registers, four waves per SIMD: left to itself the compiler takes 136 for the base conversions of all moduli.
-// Packing: 64 registers, eight waves per SIMD.
+// whatever the pitch; the 16-byte rows of two tiles are read at a time (one, two: 4.22, 3.88 ms with the evaluation behind it).  The lane's number
+// is taken anew for every run: else the addresses that follow from it, for all moduli, are formed before the loop, 128 registers and 88 bytes of
+// scratch memory a lane (65 and none this way, seven waves per SIMD instead of four: 12 primes, ReLU, 20 000 values, 795 us and 634; 2 primes, 40 000, 48 and 30).
 // Rows of bits (q = 2): 16 digits are 16 bits, a lane moves 16 bytes on one side and 2 on the other.
 template <bool Pack>
-__global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const PackLaunch L) {
+__global__ __launch_bounds__(kThreads, Pack ? 8 : 7) void k_rows_repack(const PackLaunch L) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_at4 __attribute__((aligned(4)));              // of table rows: tables, and with rows of 20 bytes their segments, are 4-byte aligned
     const uint32_t lg = L.run_log2;                                   // a wave takes 2^lg tiles at a time
     constexpr int kMaxDw = 21;                                        // dwords of the longest row that goes through LDS (81 digits)
     __shared__ uint32_t stage[Pack ? 1 : kThreads / 64][Pack ? 1 : 64 * kMaxDw];
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t* st = stage[Pack ? 0 : wave];
     auto rows_of = [&](uint32_t i) { return (uint64_t)L.n_elem * L.seg[i].rows_per_gate; };
     // one-digit rows: 1024 bytes of the packed segment per tile (padded with zeros to a multiple of 16 bytes)
@@ -172,6 +174,7 @@ __global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const Pa
             base = next;
             next += runs_of(++seg);
         }
+        const uint32_t lane = Pack ? threadIdx.x & 63u : opaque_lane(threadIdx.x & 63u);
         const PackSeg& S = L.seg[seg];
         const uint64_t rows = rows_of(seg), first = (run - base) << lg, last = tiles_of(seg), stop = first + (1u << lg) < last ? first + (1u << lg) : last;
         if (S.q == 0) {
@@ -270,7 +273,16 @@ __global__ __launch_bounds__(kThreads, Pack ? 8 : 4) void k_rows_repack(const Pa
                     u32x4* packed = (u32x4*)(S.packed + r * 16);
                     if (Pack) {
                         uint32_t colour;
-                        const U128 x = compress(M, [&](int i) { return row[i]; }, &colour);
+                        U128 x;
+                        if (M.ndw >= 4) {                                // from the top, the last piece overlapping the one before
+                            u32x4 piece = {};
+                            int at = 0;
+                            x = compress(M, [&](int i) {
+                                if ((((int)M.ndw - 1 - i) & 3) == 0) { at = i >= 3 ? i - 3 : 0; piece = *(const u32x4_at4*)(row + at); }
+                                const int q = i - at;
+                                return q & 2 ? (q & 1 ? piece[3] : piece[2]) : (q & 1 ? piece[1] : piece[0]);
+                            }, &colour);
+                        } else x = compress(M, [&](int i) { return row[i]; }, &colour);
                         *packed = u32x4{x.w[0], x.w[1], x.w[2], x.w[3]};
                     } else {
                         const u32x4 v = *packed;

@@ -220,6 +220,26 @@ def test_tables_pack_unpack_by_number_of_tiles(k, kind, n):
         assert (packed.cpu().numpy() == orc.tables_pack(kind, n, tables.cpu().numpy(), 1)).all()
 
 
+@pytest.mark.parametrize("k,lam", [(4, [128, 3, 9, 13]), (4, [5, 80, 4, 17]), (3, [128, 33, 12])])
+def test_tables_pack_unpack_of_short_labels(k, lam):
+    """explicit label lengths: rows of one to five dwords and one of nine without compile-time code, which packing reads in pieces of four dwords"""
+    from paper_2302_06361_amd import Labels, Layer, RELU
+    ctx, orc = both(k, rule=1, lam=lam)
+    n = 333
+    lay = Layer(RELU, 3, n)
+    oe, tb, sb = ctx.layer_sizes(lay)
+    z, o = Labels(ctx, n), Labels(ctx, n)
+    ctx.input_labels(9, z)
+    tables = torch.zeros(tb, dtype=torch.uint8, device=ctx.device)
+    ctx.garble_layer(lay, z, o, tables, torch.zeros(sb + 256, dtype=torch.uint8, device=ctx.device))
+    packed = torch.full((ctx.tables_packed_bytes(lay),), 0xEE, dtype=torch.uint8, device=ctx.device)
+    ctx.tables_pack(lay, tables, packed)
+    back = torch.full((tb,), 0xEE, dtype=torch.uint8, device=ctx.device)
+    ctx.tables_unpack(lay, packed, back)
+    assert torch.equal(back, tables)
+    assert (packed.cpu().numpy() == orc.tables_pack("relu", n, tables.cpu().numpy(), 1)).all()
+
+
 def test_tables_pack_needs_rows_below_128_bits():
     from paper_2302_06361_amd import Layer, RELU, DashError
     ctx, orc = both(8)                       # ceil rule: 3^81 > 2^128
