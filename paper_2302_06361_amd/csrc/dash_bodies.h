@@ -523,7 +523,7 @@ DASH_HD void chain_gate(const ChainLaunch& L, const MI& Mi, const MO& Mo, uint32
         for (int i = 0; i < (int)MO::ndw; i++) rw[i] = row[i];
     }
     U128 K = compress(Mi, in_dw, &colour);
-    U128 h = QUAD ? hash_block_quad(K, L.elem_base + e, L.slot[j], L.layer, Q, L.key.rk, T)
+    U128 h = QUAD ? hash_block_quad<cmod_m<MO>::value != 0>(K, L.elem_base + e, L.slot[j], L.layer, Q, L.key.rk, T)
                   : hash_block(K, L.elem_base + e, L.slot[j], L.layer, L.key.rk, T);
     if constexpr (cmod_m<MO>::value != 0) {
         decompress(Mo, h, [&](int i, uint32_t hd) { out(i, submod4(rw[i], hd, Mo)); });

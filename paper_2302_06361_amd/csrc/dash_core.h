@@ -465,7 +465,8 @@ DASH_HD QuadKey quad_key(const uint32_t* rk, uint32_t c) {
     for (int r = 0; r < 11; r++) Q.k[r] = rk[4 * r + c];
     return Q;
 }
-template <class Tab>
+// Columns: the columns go to the neighbours, before the look-ups; else the entries, after them.
+template <bool Columns = false, class Tab>
 DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t* rk, const Tab& T) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const uint32_t c = __lane_id() & 3u;
@@ -479,9 +480,14 @@ DASH_HD void aes128_encrypt_quad(uint32_t s[4], const QuadKey& Q, const uint32_t
     for (int r = 1; r < 10; r++) {
         // A lane looks up the bytes of its own column, and the entries, not the columns, go to their neighbours: as the operand of the
         // exclusive-or that takes them (keep: or the compiler makes three-input operations of them, which have no such operand).  With the columns
-        // exchanged before the look-ups every round had three moves and their wait states more.
+        // exchanged before the look-ups every round had three moves and their wait states more (one launch per layer, scaling, 1 000 values: 7 primes
+        // 21.2 us instead of 20.5, 12 primes 37.7 and 35.2).  In the kernel of a carry chain alone the columns are the faster way: signs of 1 000 values,
+        // 8 primes, 26.5 us instead of 27.0, 9 primes 29.9 and 30.7.
         auto keep = [](uint32_t v) { asm("" : "+v"(v)); return v; };
-        if constexpr (tab_two<Tab>::value) {
+        if constexpr (Columns) {
+            const uint32_t a1 = up1(a), a2 = up2(a), a3 = up3(a);
+            a = aes_column(a, a1, a2, a3, Q.k[r], T);
+        } else if constexpr (tab_two<Tab>::value) {
             const uint32_t k = tab_rot<Tab>::value ? Q.k[r] : rot16(Q.k[r]);
             const uint32_t t0 = T.template at<0, 0>(a), t1 = T.template at<1, 1>(a), t2 = T.template at<0, 2>(a), t3 = T.template at<1, 3>(a);
             uint32_t w = keep(up2(t2) ^ k);
@@ -578,11 +584,11 @@ DASH_HD U128 slot_hash(const SlotHash& S, uint32_t slot, const uint32_t* rk, con
     return h;
 }
 // the same by the four lanes of a quad together (aes128_encrypt_quad): same arguments and same result in all four
-template <class Tab>
+template <bool Columns = false, class Tab>
 DASH_HD U128 hash_block_quad(const U128& K, uint64_t elem, uint32_t slot, uint32_t layer, const QuadKey& Q, const uint32_t* rk, const Tab& T) {
     uint32_t x[4] = {K.w[0] ^ (uint32_t)elem, K.w[1] ^ (uint32_t)(elem >> 32), K.w[2] ^ slot, K.w[3] ^ (layer & 0xffffu)};
     uint32_t s[4] = {x[0], x[1], x[2], x[3]};
-    aes128_encrypt_quad(s, Q, rk, T);
+    aes128_encrypt_quad<Columns>(s, Q, rk, T);
     U128 h = {{s[0] ^ x[0], s[1] ^ x[1], s[2] ^ x[2], s[3] ^ x[3]}};
     return h;
 }
