@@ -392,6 +392,11 @@ int DASH_FN(DASH_PASTE(launch_act_eval_, DASH_SET))(const dash_ctx* c, ActLaunch
     static_assert(HalfTab::words == kSpanSums * 4 * 64, "rows of the deep form");
     const uint32_t rows = sums <= kSpanSums ? kSpanSums : sums <= kCut ? sums : std::max(kCut, kSpanSums + sums - kCut);
     const size_t lds = form == ACT_DEEP ? (size_t)rows * 4 * epb * 4 : (size_t)sums * 2 * epb * 4;
+    if (form == ACT_DEEP) {      // the kernel reads its table at HalfTab::base, whatever static LDS it was built with
+        hipFuncAttributes attr;
+        DASH_HIP(hipFuncGetAttributes(&attr, relu ? (const void*)k_act_eval<true, 64, 1> : (const void*)k_act_eval<false, 64, 1>));
+        if (attr.sharedSizeBytes != HalfTab::base) return DASH_EUNSUPPORTED;
+    }
     if (relu) {
         if (form == ACT_DEEP) hipLaunchKernelGGL((k_act_eval<true, 64, 1>), grid, block, lds, s, L);
         else if (form == ACT_SHALLOW) hipLaunchKernelGGL((k_act_eval<true, kShallow, 1>), grid, block, lds, s, L);

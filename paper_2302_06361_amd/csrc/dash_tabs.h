@@ -85,8 +85,8 @@ __device__ __forceinline__ BankTab load_banktab(uint32_t* lds, const uint32_t* g
 // HalfTab: 16 copies of T0 and T1 in the first 128 bytes of every 256, which leaves the other 128 of each entry (32 KB) to the kernel:
 // byte address of entry x of table R  x * 256 + R * 64 + 4 * copy.  One instruction per address and one rotation per column as with
 // BankTab; the lanes l and l + 16 share a copy, so a look-up takes four LDS cycles instead of two.  For kernels that need LDS of their own
-// and have LDS cycles to spare.  The table is the start of the dynamic LDS of a kernel with `base` bytes of static LDS (test_asm_waits.py looks at
-// that), which go into the instruction's offset: the address of dynamic LDS is filled in so late that the compiler's own addition of it
+// and have LDS cycles to spare.  The table is the start of the dynamic LDS of a kernel with `base` bytes of static LDS (its launcher refuses
+// any other, and test_static_lds.py looks at all of them), which go into the instruction's offset: the address of dynamic LDS is filled in so late that the compiler's own addition of it
 // stays in front of every look-up.
 struct HalfTab {
     static constexpr bool two_tables = true, rotated_keys = true;

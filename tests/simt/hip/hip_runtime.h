@@ -232,6 +232,13 @@ typedef void* hipEvent_t;
 enum { hipSuccess = 0, hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 };
 #define HIP_SYMBOL(x) x
 inline hipError_t hipGetLastError() { return 0; }
+// static LDS of a kernel as the device's build has it (SIMT_STATIC_LDS: another)
+struct hipFuncAttributes { size_t sharedSizeBytes; };
+inline hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) {
+    const char* e = getenv("SIMT_STATIC_LDS");
+    a->sharedSizeBytes = e ? (size_t)atoll(e) : 1024;
+    return 0;
+}
 inline hipError_t hipSetDevice(int) { return 0; }
 inline hipError_t hipDeviceSynchronize() { return 0; }
 template <class T> hipError_t hipMalloc(T** p, size_t n) { void* v; const int st = posix_memalign(&v, 256, n); *p = (T*)v; return st; }

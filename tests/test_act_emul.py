@@ -105,6 +105,15 @@ def test_tables_repacked_from_a_4_byte_address(emul, tmp_path, k, kind, n, repea
     assert (got[want.size:] == rt).all(), "unpacked tables"
 
 
+def test_deep_form_with_another_static_lds_is_refused(emul, tmp_path):
+    """its table would lie elsewhere than where the kernel reads it; the other forms don't mind"""
+    env = {"SIMT_STATIC_LDS": "1040", "DASH_ACT_SHALLOW_MIN_ELEMS": "0", "DASH_ACT_DEEP_MIN_ELEMS": "0"}
+    for kind in ("relu", "scale"):
+        with pytest.raises(AssertionError, match="not implemented"):
+            run(emul, tmp_path, "act", 7, 0, kind, 65, env=env)
+        run(emul, tmp_path, "act", 7, 0, kind, 65, env=dict(env, DASH_ACT_DEEP_MIN_ELEMS=BIG))
+
+
 @pytest.mark.parametrize("run_log2,kind,n", [(0, "scale", 240), (1, "relu", 5), (2, "scale", 67), (2, "relu", 3), (3, "scale", 67), (3, "relu", 5)])
 def test_tables_repacked_in_runs_of_tiles(emul, tmp_path, run_log2, kind, n):
     """waves that take 1, 2, 4 and 8 tiles of 64 rows at a time (by the number of tiles; here forced): segments that end within a run, within the tiles
