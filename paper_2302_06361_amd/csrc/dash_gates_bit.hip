@@ -36,6 +36,14 @@ __global__ __launch_bounds__(kBigThreads, 4) void k_bit_garble(const GateLaunch,
     }
 }
 
+// One block fits a CU (registers): 1024 tiles at a time.  Where the values have fewer, the jobs are shared out to groups of lanes, none of them empty.
+// tiles: of all repetitions
+inline uint32_t bit_groups(uint64_t tiles, uint32_t njobs) {
+    const uint64_t wanted = tiles < 1024 ? 1024 / tiles : 1;
+    const uint32_t groups = wanted < njobs ? (uint32_t)wanted : njobs, per = (njobs + groups - 1) / groups;
+    return (njobs + per - 1) / per;
+}
+
 int DASH_FN(launch_bit_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipStream_t s, bool* done) {
     *done = false;
     if (njobs < 1 || njobs > kMaxJobs) return DASH_EINVAL;
@@ -54,11 +62,7 @@ int DASH_FN(launch_bit_garble)(const dash_ctx* c, GateLaunch& L, int njobs, hipS
     if (J0.n_elem == 0) return DASH_OK;
     const uint32_t reps = rep_count(L.reps);
     const uint64_t tiles = ((uint64_t)J0.n_elem * 2 + kThreads - 1) / kThreads * reps;
-    // one block fits a CU (registers): 1024 tiles at a time.  Where the values have fewer, the jobs are shared out to groups of lanes.
-    uint32_t groups = tiles < 1024 ? (uint32_t)(1024 / tiles) : 1u;
-    if (groups > (uint32_t)njobs) groups = (uint32_t)njobs;
-    const uint32_t per = ((uint32_t)njobs + groups - 1) / groups;
-    groups = ((uint32_t)njobs + per - 1) / per;
+    const uint32_t groups = bit_groups(tiles, (uint32_t)njobs);
     if (tiles * groups > 0x7fffffffull) { *done = false; return DASH_OK; }
     L.key = c->fixed_rot; L.ttab = c->d_ttab; L.mods = c->d_mods; L.njobs = (uint32_t)njobs;
     ProfScope ps(c->prof, DASH_PROF_GARBLE, s, 2.0 * J0.n_elem * njobs * reps, bytes * reps);

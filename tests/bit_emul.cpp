@@ -1,7 +1,9 @@
 // The garbler's kernel for gates on one wire of modulus 2 (dash_gates_bit.hip) through tests/simt: every prime with a compile-time description, casts
 // and both gates of the half gates, several repetitions, jobs dealt out to groups of lanes, over exactly-sized buffers under the sanitizers;
 // against garble_body on the same gates, every table byte.  Test code, not part of libdash.
-// usage: bit_emul <gates> <jobs> <repetitions> <first slot> <seed>
+// usage: bit_emul <gates> <jobs> <repetitions> <first slot> <seed> [<groups> <blocks>]
+// groups, blocks: the kernel itself with its jobs dealt out to so many lanes per (value, row), in so many blocks (0 0: the launcher, which has to
+// give a lane more than one job), over both assignments of the half gates' modes to the primes and masks of all digits.
 #define SIMT_MAIN
 #include <hip/hip_runtime.h>
 
@@ -20,6 +22,8 @@ static uint32_t rnd() { rng_state = rng_state * 6364136223846793005ull + 1442695
 
 static dash_ctx ctx;
 static uint32_t n, jobs, reps, slot0;
+static bool forced = false;                     // groups and blocks were given
+static uint32_t groups = 0, blocks = 0;
 static AesKey fixed, fixed_rot;
 
 static std::vector<uint8_t> labels(const ModInfo& M, uint32_t count) {
@@ -30,8 +34,8 @@ static std::vector<uint8_t> labels(const ModInfo& M, uint32_t count) {
     return v;
 }
 
-// half: every second job the evaluator's half of a half gate, every other the known input; else casts
-static bool same(bool half) {
+// half: every second job the evaluator's half of a half gate, every other the known input, from the first on or (shift) from the second; else casts
+static bool same(bool half, uint32_t shift = 0) {
     static const uint32_t primes[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};
     // all wires of a repetition are one step apart: the widest label, of modulus 2
     const int64_t step = (int64_t)8 * n * 16, tstep = (int64_t)n * 2 * 128;
@@ -44,6 +48,7 @@ static bool same(bool half) {
         return v;
     };
     std::vector<uint8_t> mask((size_t)n), phi(2 * jobs);
+    std::vector<std::vector<uint8_t>> masks(jobs);      // of every digit of the job's prime (forced)
     GateLaunch L;
     memset(&L, 0, sizeof(L));
     L.mods = ctx.d_mods; L.layer = 9; L.njobs = jobs; L.ttab = TT;
@@ -53,7 +58,7 @@ static bool same(bool half) {
     for (uint32_t j = 0; j < jobs; j++) {
         GateJob& J = L.jobs[j];
         J.p = 2; J.q = primes[(j + (half ? 0 : 1)) % 12]; J.slot = slot0 + j;
-        J.mode = !half ? PAY_PHI : j % 2 ? PAY_SHORT : PAY_EHALF;
+        J.mode = !half ? PAY_PHI : (j + shift) % 2 ? PAY_SHORT : PAY_EHALF;
         J.elem_base = (1ull << 32) - 3; J.n_elem = n;
         J.in = LView{wires[0].data(), (int64_t)16 * n, 16u};
         const ModInfo& M = ctx.mods[J.q];
@@ -62,6 +67,11 @@ static bool same(bool half) {
         if (half) {
             for (uint32_t e = 0; e < n; e++) mask[e] %= 2;      // a digit of every prime
             J.r = mask.data();
+            if (forced) {
+                masks[j].resize(n);
+                for (uint32_t e = 0; e < n; e++) masks[j][e] = (uint8_t)(e < 2 ? (J.q - 1) * (1 - e) : rnd() % J.q);
+                J.r = masks[j].data();
+            }
             wires[1 + jobs + j] = spread(M);
             J.x0 = LView{wires[1 + jobs + j].data(), (int64_t)16 * n, 16u};
         } else {
@@ -79,6 +89,15 @@ static bool same(bool half) {
                 for (uint32_t tx = 0; tx < (uint32_t)kThreads; tx++) { DirectSink sink; garble_body<PerJobMod>(L, bx, j, tx, HostTab(), sink, r); }
     for (uint32_t j = 0; j < jobs; j++) L.jobs[j].table = got[j].data();
     bool done = false;
+    if (forced && groups) {
+        L.key = fixed_rot;
+        if (half) hipLaunchKernelGGL(k_bit_garble<true>, dim3(blocks), dim3(kBigThreads), 0, nullptr, L, groups);
+        else hipLaunchKernelGGL(k_bit_garble<false>, dim3(blocks), dim3(kBigThreads), 0, nullptr, L, groups);
+        for (uint32_t j = 0; j < jobs; j++)
+            if (got[j] != want[j]) { fprintf(stderr, "job %u (q %u, mode %u), forced: tables differ\n", j, L.jobs[j].q, L.jobs[j].mode); return false; }
+        return true;
+    }
+    if (forced && bit_groups(((uint64_t)n * 2 + kThreads - 1) / kThreads * reps, jobs) >= jobs) { fprintf(stderr, "one job per lane\n"); return false; }
     if (DASH_FN(launch_bit_garble)(&ctx, L, (int)jobs, nullptr, &done) != DASH_OK || !done) { fprintf(stderr, "not launched\n"); return false; }
     for (uint32_t j = 0; j < jobs; j++)
         if (got[j] != want[j]) { fprintf(stderr, "job %u (q %u, mode %u): tables differ\n", j, L.jobs[j].q, L.jobs[j].mode); return false; }
@@ -96,10 +115,12 @@ static bool same(bool half) {
 }
 
 int main(int argc, char** argv) {
-    if (argc != 6) return 2;
+    if (argc != 6 && argc != 8) return 2;
+    forced = argc == 8;
+    if (forced) { groups = (uint32_t)atoi(argv[6]); blocks = (uint32_t)atoi(argv[7]); }
     n = (uint32_t)atoi(argv[1]); jobs = (uint32_t)atoi(argv[2]); reps = (uint32_t)atoi(argv[3]); slot0 = (uint32_t)atoi(argv[4]);
     rng_state = (uint64_t)atoll(argv[5]);
-    if (jobs < 1 || jobs > (uint32_t)kMaxJobs || reps < 1) return 2;
+    if (jobs < 1 || jobs > (uint32_t)kMaxJobs || reps < 1 || (groups != 0) != (blocks != 0)) return 2;
     uint8_t S[256], key[16];
     make_sbox(S);
     make_ttab(S, TT);
@@ -120,7 +141,7 @@ int main(int argc, char** argv) {
         M.dtab = dtab[m].data();
     }
     ctx.d_mods = ctx.mods;
-    const bool ok = same(false) && same(true);
+    const bool ok = same(false) && same(true) && (!forced || same(true, 1));
     if (ok) printf("ok\n");
     return ok ? 0 : 1;
 }

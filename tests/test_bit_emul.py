@@ -37,3 +37,19 @@ def test_gates_on_a_bit_wire(emul, gates, jobs, reps, slot):
         for order in ({}, {"SIMT_REVERSE": "1"}):
             r = subprocess.run([exe] + [str(v) for v in (gates, jobs, reps, slot, gates + jobs)], capture_output=True, text=True, env=dict(env, **order))
             assert r.returncode == 0 and r.stdout.strip() == "ok", (order, r.stderr[-3000:])
+
+
+@pytest.mark.parametrize("gates,jobs,reps,slot,groups,blocks", [
+    (9000, 16, 1, 249, 0, 0),     # dealt out by the launcher: two jobs per lane, a lane whose slots change their upper 24 bits
+    (129, 11, 2, 250, 1, 3),      # all jobs in one lane, such slots among them and in a repetition of its own
+    (300, 16, 2, 245, 1, 1),      # a second tile, and a second round of tiles, for every wave
+    (257, 11, 1, 250, 3, 2),       # groups of four jobs, a last one of three
+    (130, 12, 1, 254, 4, 1),
+])
+def test_several_jobs_per_lane(emul, gates, jobs, reps, slot, groups, blocks):
+    """a lane's jobs share the first rounds of their hashes; both kinds of half-gate jobs with every prime, masks of all its digits"""
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:detect_stack_use_after_return=0")
+    for exe in emul:
+        for order in ({}, {"SIMT_REVERSE": "1"}) if groups else ({},):
+            r = subprocess.run([exe] + [str(v) for v in (gates, jobs, reps, slot, gates + jobs, groups, blocks)], capture_output=True, text=True, env=dict(env, **order))
+            assert r.returncode == 0 and r.stdout.strip() == "ok", (order, r.stderr[-3000:])
