@@ -143,7 +143,9 @@ int dash_weights_prepare(dash_ctx *ctx, const int32_t *w, int out_c, int K, void
  * output wires and (RELU, SCALE, SIGN, PROJ) its ciphertext tables.  Fresh zero labels come from
  * the PRG, addressed by (layer_id, slot, element).  tables / scratch: device, sizes from
  * dash_layer_sizes (may be NULL when the size is 0).  For RELU, SCALE and SIGN out_zero may be the same bundle as in_zero
- * (in place; likewise out_act and in_act of dash_eval_layer); bundles that overlap only in part are not supported. */
+ * (in place; likewise out_act and in_act of dash_eval_layer); bundles that overlap only in part are not supported.
+ * Large garbling launches raise the issue priority of their waves until they are about to end (inside the kernel; stream priorities are not
+ * touched): work on other streams beside them takes up to a tenth longer, and the garbling ends sooner. */
 int dash_garble_layer(dash_ctx *ctx, const dash_layer *layer, const dash_labels *in_zero, dash_labels *out_zero,
                       void *tables, void *scratch, void *hip_stream);
 /* Ev, one layer: from the active labels of the input wires and the tables produce the active

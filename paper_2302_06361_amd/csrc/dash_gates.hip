@@ -145,7 +145,7 @@ int DASH_FN(launch_affine)(const dash_ctx* c, AffineLaunch& L, int njobs, hipStr
 // four at a time (dash_pack_rule.h), neighbouring waves neighbouring runs (a contiguous range for each wave was 16 384 streams through 8 GB: 2.7
 // ms instead of 2.3 below).
 // Packing: a lane reads its own row and has those of up to four tiles in flight.  (Rows through LDS, a dword per lane, one tile at a time and the
-// segment looked for at every tile: 2.5 TB/s, 3.4 ms for the 5.1 GB of tables of a LeNet batch of 4; this way 2.3 ms, 3.7 TB/s.)
+// segment looked for at every tile: 2.5 TB/s, 3.4 ms for the 5.1 GB of tables of a LeNet batch of 4; this way 1.8 ms, 4.6 TB/s.)
 // Packing: 64 registers, eight waves per SIMD.  A modulus without compile-time code reads its row in pieces of four dwords (dword by dword, with so many
 // waves beside each other: 4 primes, 160 000 values, 913 us; 387 this way).
 // Unpacking: a wave brings its 64 rows through LDS, so that every access to them is a dword per lane, consecutive lanes consecutive dwords,

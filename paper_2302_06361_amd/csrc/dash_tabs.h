@@ -27,9 +27,10 @@ inline namespace DASH_RULE_NS {
 // collides, and the address still costs ONE instruction, a byte permute: byte 0 <- 4b (from the lane's
 // constant), byte 1 <- the state byte; R * 128 goes into the instruction's offset.
 //
-// Measured on the LeNet batch-16 step: BankTab garbles 3.4e10 rows/s against 2.9e10, but launches that do not
-// fill the chip get slower (64 KB to fill per block, fewer and larger blocks), so each kernel exists in both
-// forms and the launcher takes BankTab from kBankedMinLanes lanes up.
+// Measured on the LeNet batch-16 step: BankTab garbles 3.4e10 rows/s against 2.9e10, but launches that do not fill the chip get slower (64 KB to
+// fill per block, fewer and larger blocks).  So the kernels that serve launches of every size exist in both forms and take BankTab from 2^20 lanes
+// up (DASH_BANKED_MIN_LANES), the garbler's digit gates by dash_gadget_rule.h; the garbler's carry gates and gates on a mod-2 wire, which small launches
+// do not reach, have it alone.
 constexpr int kTabWords = 1024;
 constexpr int kBankTabWords = 16384;
 constexpr int kBigThreads = 1024;                               // lanes per block with BankTab
@@ -145,7 +146,7 @@ template <int P> __device__ __forceinline__ void wave_priority() {
 // on a SIMD the first was through with its share of the carry gates at 0.38 of the launch, the next ones at 0.41, 0.50, 0.60 .. 1.0, and the ones
 // that were left had ever fewer others to hide their LDS look-ups behind.  Pace gives waves that are ahead a lower priority: 3 down to a
 // quarter of the wave's share, 2 down to a sixteenth, 1 down to a 64th, so that all of them reach each of these marks before one goes
-// on beyond it, and end together (0.94 .. 1.0).  43 M rows of carry gates, 96 -> 96: 1 107 000 cycles without, 955 000 with it.
+// on beyond it, and end together (0.94 .. 1.0).  36.1 M rows of carry gates, 96 -> 96: 1 107 000 cycles without, 955 000 with it.
 struct Pace {
     uint32_t left, total;                // ticks (the same in all lanes of a wave)
     // a wave's share is the tiles first, first + step, .. below end, of so many ticks each
